@@ -227,12 +227,12 @@ def _batch_grids(case):
 
 
 def _network(ctx, seed):
-    """A network whose correction is small and raises the weights, as a trained one's does on
-    an under-weighted allocation."""
+    """A network whose correction is small and widens the primitives, which an under-weighted
+    allocation gains from, so that the full correction is taken as with a trained one."""
     mlp = gve.MLP(ctx, seed=seed)
     flat = mlp.export()
-    flat[18688:20096] *= 0.002
-    flat[20096 + 10] = 0.02
+    flat[18688:20096] *= 0.0005
+    flat[20096 + 7:20096 + 10] = 0.03
     mlp.load(flat)
     return mlp
 
