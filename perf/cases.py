@@ -182,7 +182,7 @@ def _seeds(field, n, gen):
     return torch.cat([a, b]), det, g99
 
 
-def _primitives(field, n, cover, gen, origin=(0, 0, 0), weight=1.0):
+def _primitives(field, n, cover, gen, origin=(0, 0, 0)):
     """theta float32 [11, n] (and the detail count and 99th percentile gradient)."""
     nz, ny, nx = field.shape
     M = field.numel()
@@ -195,7 +195,7 @@ def _primitives(field, n, cover, gen, origin=(0, 0, 0), weight=1.0):
     th[3:7] = q / q.norm(dim=0) * (0.8 + 0.4 * _rand(gen, n))
     th[7:10] = math.log(s) + 0.25 * torch.randn(3, n, device=DEV, generator=gen)
     vol = n / M * (2 * math.pi) ** 1.5 * th[7:10].sum(0).exp()
-    th[10] = weight * field.view(-1)[v] / vol * (0.7 + 0.6 * _rand(gen, n))
+    th[10] = field.view(-1)[v] / vol * (0.7 + 0.6 * _rand(gen, n))
     return th.contiguous(), det, g99
 
 
@@ -227,12 +227,12 @@ def _batch_grids(case):
 
 
 def _network(ctx, seed):
-    """A network whose correction is small and widens the primitives, which an under-weighted
-    allocation gains from, so that the full correction is taken as with a trained one."""
+    """A network whose correction is small and narrows the primitives, which these inputs
+    gain from, so that the full correction is taken as with a trained one."""
     mlp = gve.MLP(ctx, seed=seed)
     flat = mlp.export()
     flat[18688:20096] *= 0.0005
-    flat[20096 + 7:20096 + 10] = 0.03
+    flat[20096 + 7:20096 + 10] = -0.03
     mlp.load(flat)
     return mlp
 
@@ -277,8 +277,7 @@ def prepare(case, seed):
         opts = gve.paper_options(samples=case["samples"], ell_hi=math.log(max(shape) / 16))
         return {**state, "ctx": ctx, "opts": opts, "params": gve.PaperParams(ctx, n),
                 "start": th12.cpu().numpy()}
-    under = 0.7 if op == "warmstart" else 1.0
-    th, det, g99 = _primitives(field, n, case["cover"], gen, org, under)
+    th, det, g99 = _primitives(field, n, case["cover"], gen, org)
     state["start"] = th
     if op == "autograd":
         up = torch.randn(shape, device=DEV, generator=gen)
