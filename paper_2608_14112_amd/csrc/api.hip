@@ -1608,15 +1608,17 @@ struct gve_mlp {
 
 namespace {
 
-constexpr int kDin = 16, kDh = 128, kDout = 11;
+constexpr int kDin = gve::kMlpIn, kDh = gve::kMlpHid, kDout = gve::kMlpOut;
 constexpr int64_t kW1 = 0, kB1 = 2048, kW2 = 2176, kB2 = 18560, kW3 = 18688, kB3 = 20096;
-constexpr int64_t kMlpRows = 65536;  // rows per forward / backward chunk
+constexpr int64_t kMlpRows = 65536;  // most rows of a batch
 static_assert(kB3 + kDout == GVE_MLP_NWEIGHT, "weight layout");
 
+// Workspace of the network's calls: the weights' operand tiles, the training
+// step's buffers for `rows` rows (0: inference only), `nacc` loss sums.
 struct MlpBuf {
-  float *Xs, *Ts, *Z1, *H1, *Z2, *H2, *Y, *dY, *grad, *split;
-  size_t split_floats;
-  double *part, *acc;
+  unsigned short* wf;
+  void* work;
+  double *acc, *stat;
 };
 
 gve_status mlp_buffers(gve_ctx* ctx, int64_t rows, int64_t nacc, MlpBuf* b) {
@@ -1626,60 +1628,25 @@ gve_status mlp_buffers(gve_ctx* ctx, int64_t rows, int64_t nacc, MlpBuf* b) {
     off += (bytes + 255) & ~(size_t)255;
     return o;
   };
-  const size_t r = (size_t)rows;
-  const size_t split_floats = (size_t)((rows + 511) / 512) * kDh * kDh;
-  const size_t oXs = take(4 * r * kDin), oTs = take(4 * r * kDout), oZ1 = take(4 * r * kDh),
-               oH1 = take(4 * r * kDh), oZ2 = take(4 * r * kDh), oH2 = take(4 * r * kDh),
-               oY = take(4 * r * kDout), odY = take(4 * r * kDout), og = take(4 * GVE_MLP_NWEIGHT),
-               osp = take(4 * split_floats), opart = take(8 * 64), oacc = take(8 * (size_t)nacc);
+  const size_t owf = take(2 * (size_t)gve::kMlpFragElems),
+               owork = take(rows > 0 ? gve::mlp_step_bytes(rows) : 0),
+               oacc = take(8 * (size_t)nacc), ostat = take(8 * gve::mlp_stat_tmp_doubles());
   TRY(ensure(ctx, ctx->ws.mlp, off));
   char* base = static_cast<char*>(ctx->ws.mlp.ptr);
-  auto F32 = [&](size_t o) { return reinterpret_cast<float*>(base + o); };
-  b->Xs = F32(oXs); b->Ts = F32(oTs); b->Z1 = F32(oZ1); b->H1 = F32(oH1); b->Z2 = F32(oZ2);
-  b->H2 = F32(oH2); b->Y = F32(oY); b->dY = F32(odY); b->grad = F32(og); b->split = F32(osp);
-  b->split_floats = split_floats;
-  b->part = reinterpret_cast<double*>(base + opart);
+  b->wf = reinterpret_cast<unsigned short*>(base + owf);
+  b->work = base + owork;
   b->acc = reinterpret_cast<double*>(base + oacc);
+  b->stat = reinterpret_cast<double*>(base + ostat);
   return GVE_OK;
 }
 
-// Y = network(Xs) for `rows` standardised inputs; activations kept in b.
-gve_status mlp_fwd(gve_ctx* ctx, const gve_mlp* m, const float* Xs, int64_t rows, MlpBuf& b,
-                   float* Y) {
-  hipStream_t s = ctx->stream;
-  const int R = (int)rows;
-  TRY_HIP(ctx, gve::mlp_gemm(false, true, 1, R, kDh, kDin, Xs, kDin, m->w + kW1, kDin, b.Z1, kDh,
-                             m->w + kB1, b.H1, nullptr, 0, s));
-  TRY_HIP(ctx, gve::mlp_gemm(false, true, 1, R, kDh, kDh, b.H1, kDh, m->w + kW2, kDh, b.Z2, kDh,
-                             m->w + kB2, b.H2, nullptr, 0, s));
-  TRY_HIP(ctx, gve::mlp_gemm(false, true, 0, R, kDout, kDh, b.H2, kDh, m->w + kW3, kDh, Y, kDout,
-                             m->w + kB3, nullptr, nullptr, 0, s));
-  return GVE_OK;
-}
-
-// Gradients of the mean squared error into b.grad, given b.dY (= dL/dY).
-gve_status mlp_bwd(gve_ctx* ctx, const gve_mlp* m, const float* Xs, int64_t rows, MlpBuf& b) {
-  hipStream_t s = ctx->stream;
-  const int R = (int)rows;
-  float* g = b.grad;
-  TRY_HIP(ctx, gve::mlp_gemm(true, false, 0, kDout, kDh, R, b.dY, kDout, b.H2, kDh, g + kW3, kDh,
-                             nullptr, nullptr, b.split, b.split_floats, s));
-  TRY_HIP(ctx, gve::mlp_colsum(b.dY, R, kDout, g + kB3, s));
-  // dH2 reuses H2's buffer after dW3 has consumed it (stream order)
-  float* dH2 = b.H2;
-  TRY_HIP(ctx, gve::mlp_gemm(false, false, 0, R, kDh, kDout, b.dY, kDout, m->w + kW3, kDh, dH2, kDh,
-                             nullptr, nullptr, nullptr, 0, s));
-  TRY_HIP(ctx, gve::mlp_gelu_back(dH2, b.Z2, rows * kDh, s));
-  TRY_HIP(ctx, gve::mlp_gemm(true, false, 0, kDh, kDh, R, dH2, kDh, b.H1, kDh, g + kW2, kDh,
-                             nullptr, nullptr, b.split, b.split_floats, s));
-  TRY_HIP(ctx, gve::mlp_colsum(dH2, R, kDh, g + kB2, s));
-  float* dH1 = b.H1;
-  TRY_HIP(ctx, gve::mlp_gemm(false, false, 0, R, kDh, kDh, dH2, kDh, m->w + kW2, kDh, dH1, kDh,
-                             nullptr, nullptr, nullptr, 0, s));
-  TRY_HIP(ctx, gve::mlp_gelu_back(dH1, b.Z1, rows * kDh, s));
-  TRY_HIP(ctx, gve::mlp_gemm(true, false, 0, kDh, kDin, R, dH1, kDh, Xs, kDin, g + kW1, kDin,
-                             nullptr, nullptr, b.split, b.split_floats, s));
-  TRY_HIP(ctx, gve::mlp_colsum(dH1, R, kDh, g + kB1, s));
+// Y = network(X) for n rows, standardised first when stats are given.
+gve_status mlp_apply(gve_ctx* ctx, const gve_mlp* m, const float* X, int64_t n, const float* stats,
+                     float* Y) {
+  MlpBuf b;
+  TRY(mlp_buffers(ctx, 0, 1, &b));
+  TRY_HIP(ctx, gve::mlp_pack(m->w, b.wf, ctx->stream));
+  TRY_HIP(ctx, gve::mlp_infer(X, n, stats, m->w, b.wf, Y, ctx->stream));
   return GVE_OK;
 }
 
@@ -1781,13 +1748,7 @@ gve_status gve_mlp_forward(gve_ctx* ctx, const gve_mlp* m, const float* d_X, int
   ctx->last_error.clear();
   if (!d_X || !d_Y || n < 1) return fail(ctx, GVE_ERR_INVALID_ARGUMENT, "need d_X, d_Y and n >= 1");
   TRY(set_device(ctx));
-  MlpBuf b;
-  TRY(mlp_buffers(ctx, std::min(n, kMlpRows), 1, &b));
-  for (int64_t r0 = 0; r0 < n; r0 += kMlpRows) {
-    const int64_t rows = std::min(kMlpRows, n - r0);
-    TRY(mlp_fwd(ctx, m, d_X + r0 * kDin, rows, b, d_Y + r0 * kDout));
-  }
-  return GVE_OK;
+  return mlp_apply(ctx, m, d_X, n, nullptr, d_Y);
 }
 
 gve_status gve_mlp_loss_grad(gve_ctx* ctx, const gve_mlp* m, const float* d_X, const float* d_T,
@@ -1800,15 +1761,13 @@ gve_status gve_mlp_loss_grad(gve_ctx* ctx, const gve_mlp* m, const float* d_X, c
   MlpBuf b;
   TRY(mlp_buffers(ctx, n, 1, &b));
   hipStream_t s = ctx->stream;
-  TRY(mlp_fwd(ctx, m, d_X, n, b, b.Y));
-  const double inv = 1.0 / ((double)n * kDout);
   TRY_HIP(ctx, gve::fill_u64(reinterpret_cast<unsigned long long*>(b.acc), 1, s));
-  TRY_HIP(ctx, gve::mlp_mse_grad(b.Y, d_T, n * kDout, (float)inv, b.dY, b.part, b.acc, inv, s));
-  if (d_grad) {
-    TRY(mlp_bwd(ctx, m, d_X, n, b));
-    TRY_HIP(ctx, hipMemcpyAsync(d_grad, b.grad, sizeof(float) * GVE_MLP_NWEIGHT,
-                                hipMemcpyDeviceToDevice, s));
-  }
+  TRY_HIP(ctx, gve::mlp_pack(m->w, b.wf, s));
+  // without d_grad the gradient goes to the (then unused) Adam-free output
+  TRY(ensure(ctx, ctx->ws.feat, sizeof(float) * GVE_MLP_NWEIGHT));
+  TRY_HIP(ctx, gve::mlp_step(d_X, d_T, nullptr, (int)n, nullptr, m->w, nullptr, nullptr, b.wf,
+                             b.work, 1.0, b.acc,
+                             d_grad ? d_grad : static_cast<float*>(ctx->ws.feat.ptr), 0.0f, 1, s));
   if (h_loss) {
     TRY_HIP(ctx, hipMemcpyAsync(ctx->ws.h_pinned, b.acc, 8, hipMemcpyDeviceToHost, s));
     TRY_HIP(ctx, hipStreamSynchronize(s));
@@ -1834,8 +1793,9 @@ gve_status gve_mlp_train(gve_ctx* ctx, gve_mlp* m, const float* d_X, const float
   float* fstd = m->stats + 16;
   float* tmean = m->stats + 32;
   float* tstd = m->stats + 43;
-  TRY_HIP(ctx, gve::mlp_colstats(d_X, n, kDin, fmean, fstd, s));
-  TRY_HIP(ctx, gve::mlp_colstats(d_T, n, kDout, tmean, tstd, s));
+  TRY_HIP(ctx, gve::mlp_colstats(d_X, n, kDin, fmean, fstd, b.stat, s));
+  TRY_HIP(ctx, gve::mlp_colstats(d_T, n, kDout, tmean, tstd, b.stat, s));
+  TRY_HIP(ctx, gve::mlp_pack(m->w, b.wf, s));
   TRY_HIP(ctx, gve::fill_u64(reinterpret_cast<unsigned long long*>(b.acc), std::max(epochs, 1), s));
   // shuffle buffers: the pair ping-pong buffers of the binning are reused
   auto& ws = ctx->ws;
@@ -1855,16 +1815,9 @@ gve_status gve_mlp_train(gve_ctx* ctx, gve_mlp* m, const float* d_X, const float
     for (int64_t bi = 0; bi < nb; ++bi) {
       const int64_t r0 = bi * batch;
       const int64_t rows = std::min((int64_t)batch, n - r0);
-      TRY_HIP(ctx, gve::mlp_standardize(d_X, perm + r0, rows, kDin, fmean, fstd, b.Xs, s));
-      TRY_HIP(ctx, gve::mlp_standardize(d_T, perm + r0, rows, kDout, tmean, tstd, b.Ts, s));
-      TRY(mlp_fwd(ctx, m, b.Xs, rows, b, b.Y));
-      const double inv = 1.0 / ((double)rows * kDout);
-      TRY_HIP(ctx, gve::mlp_mse_grad(b.Y, b.Ts, rows * kDout, (float)inv, b.dY, b.part, b.acc + ep,
-                                     inv / (double)nb, s));
-      TRY(mlp_bwd(ctx, m, b.Xs, rows, b));
       m->t += 1;
-      TRY_HIP(ctx, gve::mlp_adam(m->w, m->m, m->v, b.grad, GVE_MLP_NWEIGHT, lr, 0.9f, 0.999f, 1e-8f,
-                                 m->t, s));
+      TRY_HIP(ctx, gve::mlp_step(d_X, d_T, perm + r0, (int)rows, m->stats, m->w, m->m, m->v, b.wf,
+                                 b.work, 1.0 / (double)nb, b.acc + ep, nullptr, lr, m->t, s));
     }
   }
   if (h_epoch_loss && epochs > 0) {
@@ -1922,8 +1875,7 @@ gve_status gve_warmstart(gve_ctx* ctx, const gve_mlp* m, gve_params* p, const fl
   float* Y = X + (size_t)n * kDin;
   float* base = static_cast<float*>(ctx->ws.theta_base.ptr);
   TRY(gve_features(ctx, p, d_field, g, n_detail, g99, X));
-  TRY_HIP(ctx, gve::mlp_standardize(X, nullptr, n, kDin, m->stats, m->stats + 16, X, s));
-  TRY(gve_mlp_forward(ctx, m, X, n, Y));
+  TRY(mlp_apply(ctx, m, X, n, m->stats, Y));
   TRY_HIP(ctx, hipMemcpyAsync(base, p->theta, sizeof(float) * 11 * (size_t)n,
                               hipMemcpyDeviceToDevice, s));
   double L[4] = {NAN, NAN, NAN, NAN};

@@ -368,19 +368,27 @@ hipError_t paper_backward(float* th, float* m, float* v, int64_t n, const CellGr
                           const gve_grid& fg, float* grad_out, double* loss, hipStream_t s);
 
 // ---- warm-start network (mlp.hip) --------------------------------------------
-hipError_t mlp_gemm(bool ta, bool tb, int epi, int M, int N, int K, const float* A, int lda,
-                    const float* B, int ldb, float* C, int ldc, const float* bias, float* C2,
-                    float* split_tmp, size_t split_tmp_floats, hipStream_t s);
-hipError_t mlp_gelu_back(float* dH, const float* Z, int64_t n, hipStream_t s);
-hipError_t mlp_colsum(const float* X, int rows, int cols, float* out, hipStream_t s);
-hipError_t mlp_mse_grad(const float* Y, const float* T, int64_t n, float scale, float* dY,
-                        double* part, double* acc_out, double acc_scale, hipStream_t s);
-hipError_t mlp_adam(float* w, float* m, float* v, const float* g, int64_t n, float lr, float b1,
-                    float b2, float eps, int64_t t, hipStream_t s);
+constexpr int kMlpIn = 16, kMlpHid = 128, kMlpOut = 11;
+// bfloat16 copies of the weights in matrix-core operand tiles (mlp_pack).
+constexpr int kMlpFragElems = (3 * kMlpHid * 16) + 2 * kMlpHid * kMlpHid;
+hipError_t mlp_pack(const float* w, unsigned short* wf, hipStream_t s);
+// Y [n][11] = network(X [n][16]); X standardised with stats (mean, std of the
+// inputs) when given.
+hipError_t mlp_infer(const float* X, int64_t n, const float* stats, const float* w,
+                     const unsigned short* wf, float* Y, hipStream_t s);
+// Gradient of the mean squared error over `rows` rows (perm[0 .. rows) of X and
+// T when given, standardised with stats when given) into grad_out, or with
+// grad_out == nullptr the Adam step t on w and its tiles wf.  *loss += mean
+// squared error * loss_scale.  work: mlp_step_bytes(rows).
+size_t mlp_step_bytes(int64_t rows);
+hipError_t mlp_step(const float* X, const float* T, const uint32_t* perm, int rows,
+                    const float* stats, float* w, float* m, float* v, unsigned short* wf,
+                    void* work, double loss_scale, double* loss, float* grad_out, float lr,
+                    int64_t t, hipStream_t s);
+// tmp: mlp_stat_tmp_doubles() doubles.
+size_t mlp_stat_tmp_doubles();
 hipError_t mlp_colstats(const float* X, int64_t rows, int cols, float* mean, float* stdv,
-                        hipStream_t s);
-hipError_t mlp_standardize(const float* X, const uint32_t* perm, int64_t rows, int cols,
-                           const float* mean, const float* stdv, float* out, hipStream_t s);
+                        double* tmp, hipStream_t s);
 hipError_t mlp_perm_keys(uint32_t* keys, uint32_t* vals, int64_t n, uint64_t seed, uint64_t epoch,
                          hipStream_t s);
 hipError_t mlp_sat(const float* f, const gve_grid& g, double* s1, double* s2, hipStream_t s);

@@ -1,15 +1,16 @@
 // Learned warm start: per-primitive features, a 16-128-128-11 GELU network
 // run on bfloat16 matrix cores with float32 accumulation, its training
-// (backward GEMMs, bias and GELU gradients, Adam on float32 master weights),
+// (backward products, bias and GELU gradients, Adam on float32 master weights),
 // and the warm-start application with its fallback to the plain allocation.
 //
-// GEMMs use v_mfma_f32_16x16x16_bf16: a 256-lane workgroup computes a 64x64
-// output tile (each wave 32x32 = 2x2 MFMA tiles), staging 64x16 / 16x64
-// operand tiles in LDS after rounding float32 to bfloat16 (nearest even).
-// Operand fragments: lane l holds A[l % 16][4 (l / 16) + j] and
+// Products use v_mfma_f32_16x16x16_bf16 with operands rounded from float32
+// (nearest even).  Operand tiles: lane l holds A[l % 16][4 (l / 16) + j] and
 // B[4 (l / 16) + j][l % 16]; results D[4 (l / 16) + j][l % 16], j = 0..3.
-// Large-K products (weight gradients over the batch) are split over K into
-// per-split partial tiles that a second kernel sums in a fixed order.
+// Sums over the batch (weight gradients) are split into 512-row partial sums
+// that are added in a fixed order.
+#include <algorithm>
+#include <cmath>
+
 #include "common.h"
 #include "devmath.h"
 
@@ -18,9 +19,6 @@ namespace {
 
 typedef short short4v __attribute__((ext_vector_type(4)));
 typedef float float4v __attribute__((ext_vector_type(4)));
-
-constexpr int kTile = 64;
-constexpr int kK = 16;
 
 __device__ inline unsigned short f2bf(float x) {
   uint32_t u = __float_as_uint(x);
@@ -36,191 +34,600 @@ __device__ inline float gelu_grad_f(float z) {
          z * expf(-0.5f * z * z) * 0.39894228040143268f;
 }
 
-// C (+ split offset) = op(A) op(B) (+ bias); EPI 1 also writes gelu(C) to C2.
-template <bool TA, bool TB, int EPI>
-__global__ __launch_bounds__(256) void k_gemm(int M, int N, int K, const float* __restrict__ A,
-                                              int lda, const float* __restrict__ B, int ldb,
-                                              float* __restrict__ C, int ldc,
-                                              const float* __restrict__ bias,
-                                              float* __restrict__ C2, int kchunk,
-                                              size_t split_stride) {
-  __shared__ unsigned short As[kTile][kK + 4];
-  __shared__ unsigned short Bs[kK][kTile + 4];
-  const int m0 = blockIdx.y * kTile, n0 = blockIdx.x * kTile;
-  const int kbeg = blockIdx.z * kchunk;
-  const int kend = min(K, kbeg + kchunk);
-  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-  const int wm = (w >> 1) * 32, wn = (w & 1) * 32;
-  float4v acc[2][2];
+// ---- network layout --------------------------------------------------------------
+//
+// Flat weights (float32 master copy): W1 [128][16], b1, W2 [128][128], b2,
+// W3 [11][128], b3.
+constexpr int kIn = kMlpIn, kHid = kMlpHid, kOut = kMlpOut;
+constexpr int oW1 = 0, oB1 = oW1 + kHid * kIn, oW2 = oB1 + kHid, oB2 = oW2 + kHid * kHid,
+              oW3 = oB2 + kHid, oB3 = oW3 + kOut * kHid;
+static_assert(oB3 + kOut == GVE_MLP_NWEIGHT, "weight layout");
+constexpr int kHT = kHid / 16;  // 16-wide tiles of a hidden layer
+
+// Everything the matrix cores read is kept as whole operand tiles: 64 lanes x
+// 4 bfloat16 (512 contiguous bytes), lane l holding entries
+// (4 (l / 16) + j, l % 16), j = 0..3, of a 16 x 16 block.  That is the layout
+// results come out in, and, read as [reduction index][other index], the layout
+// of both operands, so a product of two stored results over their shared rows
+// (the weight gradients, over the batch) needs neither a transpose nor LDS.
+constexpr int kFrag = 256;  // bfloat16 per tile
+
+// Weight tiles as B operands, [reduction index][output index]:
+constexpr int fW1 = 0;                          // x  -> z1 : [nt]
+constexpr int fW2 = fW1 + kHT * kFrag;          // h1 -> z2 : [nt][kt]
+constexpr int fW2t = fW2 + kHT * kHT * kFrag;   // dz2 -> dh1 : [nt][kt]
+constexpr int fW3 = fW2t + kHT * kHT * kFrag;   // h2 -> y : [kt], outputs padded to 16
+constexpr int fW3t = fW3 + kHT * kFrag;         // dy -> dh2 : [nt], reduction padded to 16
+static_assert(fW3t + kHT * kFrag == kMlpFragElems, "weight tiles");
+
+__device__ inline int frag_at(int k, int n) { return (((k & 15) >> 2) * 16 + (n & 15)) * 4 + (k & 3); }
+
+// bfloat16 copies of flat weight i in the tiles that hold it.
+__device__ inline void store_weight_tiles(int i, float w, unsigned short* __restrict__ wf) {
+  const unsigned short b = f2bf(w);
+  if (i < oB1) {
+    const int n = i / kIn, k = i % kIn;
+    wf[fW1 + (n >> 4) * kFrag + frag_at(k, n)] = b;
+  } else if (i >= oW2 && i < oB2) {
+    const int r = (i - oW2) / kHid, c = (i - oW2) % kHid;
+    wf[fW2 + ((r >> 4) * kHT + (c >> 4)) * kFrag + frag_at(c, r)] = b;
+    wf[fW2t + ((c >> 4) * kHT + (r >> 4)) * kFrag + frag_at(r, c)] = b;
+  } else if (i >= oW3 && i < oB3) {
+    const int r = (i - oW3) / kHid, c = (i - oW3) % kHid;
+    wf[fW3 + (c >> 4) * kFrag + frag_at(c, r)] = b;
+    wf[fW3t + (c >> 4) * kFrag + frag_at(r, c)] = b;
+  }
+}
+
+// Weight tiles from the float32 master copy (padding entries zero).
+__global__ __launch_bounds__(256) void k_mlp_pack(const float* __restrict__ w,
+                                                  unsigned short* __restrict__ wf) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i < GVE_MLP_NWEIGHT) store_weight_tiles(i, w[i], wf);
+  if (i < kHT * kFrag) {
+    const int l = (i % kFrag) >> 2, j = i & 3;
+    if ((l & 15) >= kOut) wf[fW3 + i] = 0;               // outputs 11 .. 15
+    if (4 * (l >> 4) + j >= kOut) wf[fW3t + i] = 0;      // reduction over them
+  }
+}
+
+__device__ inline short4v ld4(const unsigned short* p) {
+  return *reinterpret_cast<const short4v*>(p);
+}
+
+__device__ inline float4v mfma16(short4v a, short4v b, float4v c) {
+  return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, c, 0, 0, 0);
+}
+
+// Rows of the LDS activation tiles: 136 bfloat16 (272 bytes), so that the
+// sixteen rows of an operand read fall four banks apart.
+constexpr int kRowS = kHid + 8;
+constexpr int kRowX = kIn + 4;
+
+// A operand from an LDS tile: lane l reads entries (l % 16, k0 + 4 (l / 16) + j).
+__device__ inline short4v lds_a(const unsigned short* t, int stride, int lane, int k0) {
+  return ld4(t + (lane & 15) * stride + k0 + 4 * (lane >> 4));
+}
+
+// Input row `row`, feature c, standardised when stats are given.
+template <bool STD>
+__device__ inline float input_at(const float* __restrict__ X, int cols, int64_t src, int c,
+                                 const float* __restrict__ mean, const float* __restrict__ sd) {
+  const float v = X[(size_t)src * cols + c];
+  return STD ? (v - mean[c]) / sd[c] : v;
+}
+
+// ---- inference -------------------------------------------------------------------
+//
+// 64 rows per step and workgroup: wave w owns output columns 32 w .. 32 w + 31
+// of both hidden layers for all four 16-row tiles (its weight tiles stay in
+// registers over the workgroup's steps) and row tile w of the last layer; the
+// activations pass between waves through LDS, so only X and Y touch memory.
+// Bound by the exact erf of 256 activations a row (about 40 vector
+// instructions each): the products are 0.04 MFLOP a row.
+template <bool STD>
+__global__ __launch_bounds__(256) void k_mlp_infer(const float* __restrict__ X, int64_t n,
+                                                   const float* __restrict__ stats,
+                                                   const float* __restrict__ w,
+                                                   const unsigned short* __restrict__ wf,
+                                                   float* __restrict__ Y) {
+  __shared__ __attribute__((aligned(16))) unsigned short xs[64 * kRowX];
+  __shared__ __attribute__((aligned(16))) unsigned short h1[64 * kRowS], h2[64 * kRowS];
+  const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+  const int col = lane & 15, g = lane >> 4;
+  short4v w1[2], w2[2][kHT], w3[kHT];
+  float b1[2], b2[2];
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int u = 0; u < 2; ++u) {
+    const int nt = 2 * wv + u;
+    w1[u] = ld4(wf + fW1 + nt * kFrag + 4 * lane);
 #pragma unroll
-    for (int jj = 0; jj < 2; ++jj) acc[i][jj] = float4v{0.f, 0.f, 0.f, 0.f};
-  for (int k0 = kbeg; k0 < kend; k0 += kK) {
-    {
-      const int r = t >> 2, kk = (t & 3) * 4;
-      const int m = m0 + r;
+    for (int kt = 0; kt < kHT; ++kt) w2[u][kt] = ld4(wf + fW2 + (nt * kHT + kt) * kFrag + 4 * lane);
+    b1[u] = w[oB1 + 16 * nt + col];
+    b2[u] = w[oB2 + 16 * nt + col];
+  }
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int k = k0 + kk + j;
-        float v = 0.0f;
-        if (m < M && k < kend) v = TA ? A[(size_t)k * lda + m] : A[(size_t)m * lda + k];
-        As[r][kk + j] = f2bf(v);
-      }
+  for (int kt = 0; kt < kHT; ++kt) w3[kt] = ld4(wf + fW3 + kt * kFrag + 4 * lane);
+  const float b3 = col < kOut ? w[oB3 + col] : 0.0f;
+  const int64_t steps = (n + 63) / 64;
+  for (int64_t st = blockIdx.x; st < steps; st += gridDim.x) {
+    const int64_t row0 = st * 64;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int r = 16 * u + (t >> 4), c = t & 15;
+      const float v = row0 + r < n ? input_at<STD>(X, kIn, row0 + r, c, stats, stats + kIn) : 0.0f;
+      xs[r * kRowX + c] = f2bf(v);
     }
-    {
-      const int kk = t >> 4, c = (t & 15) * 4;
-      const int k = k0 + kk;
+    __syncthreads();
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int n = n0 + c + j;
-        float v = 0.0f;
-        if (n < N && k < kend) v = TB ? B[(size_t)n * ldb + k] : B[(size_t)k * ldb + n];
-        Bs[kk][c + j] = f2bf(v);
+    for (int rt = 0; rt < 4; ++rt) {
+      const short4v a = lds_a(xs + 16 * rt * kRowX, kRowX, lane, 0);
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const float4v z = mfma16(a, w1[u], float4v{0.f, 0.f, 0.f, 0.f});
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          h1[(16 * rt + 4 * g + j) * kRowS + 16 * (2 * wv + u) + col] = f2bf(gelu_f(z[j] + b1[u]));
       }
     }
     __syncthreads();
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      short4v a;
+    for (int rt = 0; rt < 4; ++rt) {
+      float4v z[2] = {float4v{0.f, 0.f, 0.f, 0.f}, float4v{0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
-      for (int j = 0; j < 4; ++j) a[j] = (short)As[wm + 16 * i + (lane & 15)][4 * (lane >> 4) + j];
-#pragma unroll
-      for (int jj = 0; jj < 2; ++jj) {
-        short4v b;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) b[j] = (short)Bs[4 * (lane >> 4) + j][wn + 16 * jj + (lane & 15)];
-        acc[i][jj] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, acc[i][jj], 0, 0, 0);
+      for (int kt = 0; kt < kHT; ++kt) {
+        const short4v a = lds_a(h1 + 16 * rt * kRowS, kRowS, lane, 16 * kt);
+        z[0] = mfma16(a, w2[0][kt], z[0]);
+        z[1] = mfma16(a, w2[1][kt], z[1]);
       }
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          h2[(16 * rt + 4 * g + j) * kRowS + 16 * (2 * wv + u) + col] =
+              f2bf(gelu_f(z[u][j] + b2[u]));
     }
     __syncthreads();
+    float4v y = float4v{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int kt = 0; kt < kHT; ++kt)
+      y = mfma16(lds_a(h2 + 16 * wv * kRowS, kRowS, lane, 16 * kt), w3[kt], y);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int64_t row = row0 + 16 * wv + 4 * g + j;
+      if (col < kOut && row < n) Y[row * kOut + col] = y[j] + b3;
+    }
+    // the next step writes xs (read before the first barrier above) and, after
+    // its own first barrier, h1: every wave is past its reads of both by then
   }
-  float* Cz = C + (size_t)blockIdx.z * split_stride;
+}
+
+// ---- training ---------------------------------------------------------------------
+//
+// One optimiser step is three launches: forward and backward of every row tile
+// (k_mlp_fb), the weight gradients and bias sums over the batch (k_mlp_wgrad),
+// and the sums over the batch's splits with Adam (k_mlp_adam).  Results that a
+// later kernel multiplies are stored as bfloat16 operand tiles, the bias
+// gradients' terms in float32.  At 4,096 rows a step takes 44 us (15 + 22 + 5);
+// with a product kernel per layer and direction, separate activation, loss and
+// standardisation passes and a bias sum of one thread per column reading global
+// memory row by row (725 us each, three a step) it took 2.46 ms in 21 launches.
+
+struct MlpTiles {
+  // [row tile][8] tiles of bfloat16 (x and dy: one per row tile)
+  unsigned short *x, *h1, *h2, *dy, *dz1, *dz2;
+  // the same blocks in float32 (float4 per lane) for the bias sums
+  float4v *dy32, *dz132, *dz232;
+  double* loss;  // [row tile] sum of (y - t)^2
+};
+
+__device__ inline void put_tile(unsigned short* tiles, int64_t tile, int lane, const float v[4]) {
+  short4v b;
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int j = 0; j < 4; ++j) b[j] = (short)f2bf(v[j]);
+  *reinterpret_cast<short4v*>(tiles + tile * kFrag + 4 * lane) = b;
+}
+
+// Sixteen rows per workgroup, so that a batch of 4,096 fills the 256 CUs; wave
+// w owns hidden columns 32 w .. 32 w + 31 and keeps their z1 and z2 in
+// registers from the forward to the backward pass.  The last layer (one
+// 16-wide tile) is wave 0's.  Latency-bound: five short products with a
+// barrier between each; the weight tiles are loaded before the first.
+template <bool STD>
+__global__ __launch_bounds__(256) void k_mlp_fb(const float* __restrict__ X,
+                                                const float* __restrict__ T,
+                                                const uint32_t* __restrict__ perm, int rows,
+                                                const float* __restrict__ stats,
+                                                const float* __restrict__ w,
+                                                const unsigned short* __restrict__ wf, float scale,
+                                                MlpTiles o) {
+  __shared__ __attribute__((aligned(16))) unsigned short xs[16 * kRowX], dys[16 * kRowX];
+  __shared__ __attribute__((aligned(16))) unsigned short hs[2][16 * kRowS];
+  __shared__ float ts[16 * kOut];
+  const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+  const int col = lane & 15, g = lane >> 4;
+  const int64_t rt = blockIdx.x;
+  const int row0 = blockIdx.x * 16;
+  // weight tiles of this wave's columns
+  short4v w1[2], w2[2][kHT], w2t[2][kHT], w3t[2];
+  float b1[2], b2[2];
 #pragma unroll
-    for (int jj = 0; jj < 2; ++jj)
+  for (int u = 0; u < 2; ++u) {
+    const int nt = 2 * wv + u;
+    w1[u] = ld4(wf + fW1 + nt * kFrag + 4 * lane);
+    w3t[u] = ld4(wf + fW3t + nt * kFrag + 4 * lane);
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int m = m0 + wm + 16 * i + 4 * (lane >> 4) + j;
-        const int n = n0 + wn + 16 * jj + (lane & 15);
-        if (m < M && n < N) {
-          float v = acc[i][jj][j];
-          if (bias) v += bias[n];
-          Cz[(size_t)m * ldc + n] = v;
-          if (EPI == 1) C2[(size_t)m * ldc + n] = gelu_f(v);
-        }
-      }
-}
-
-__global__ void k_sum_splits(const float* __restrict__ parts, int splits, int M, int N,
-                             size_t stride, float* __restrict__ out) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= (int64_t)M * N) return;
-  float s = 0.0f;
-  for (int z = 0; z < splits; ++z) s += parts[(size_t)z * stride + i];
-  out[i] = s;
-}
-
-// dZ = dH * gelu'(Z), in place on dH.
-__global__ void k_gelu_back(float* __restrict__ dH, const float* __restrict__ Z, int64_t n) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) dH[i] *= gelu_grad_f(Z[i]);
-}
-
-// Column sums of a [rows][cols] matrix (bias gradients), fixed order.
-__global__ void k_colsum(const float* __restrict__ X, int rows, int cols, float* __restrict__ out) {
-  const int c = blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= cols) return;
-  float s = 0.0f;
-  for (int r = 0; r < rows; ++r) s += X[(size_t)r * cols + c];
-  out[c] = s;
-}
-
-// dY = 2 (Y - T) / (rows * cols); per-block double partial of sum (Y - T)^2.
-__global__ __launch_bounds__(256) void k_mse_grad(const float* __restrict__ Y,
-                                                  const float* __restrict__ T, int64_t n,
-                                                  float scale, float* __restrict__ dY,
-                                                  double* __restrict__ part) {
-  __shared__ double sh[256];
-  double s = 0.0;
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
-    const float r = Y[i] - T[i];
-    s += (double)r * r;
-    if (dY) dY[i] = 2.0f * r * scale;
+    for (int kt = 0; kt < kHT; ++kt) {
+      w2[u][kt] = ld4(wf + fW2 + (nt * kHT + kt) * kFrag + 4 * lane);
+      w2t[u][kt] = ld4(wf + fW2t + (nt * kHT + kt) * kFrag + 4 * lane);
+    }
+    b1[u] = w[oB1 + 16 * nt + col];
+    b2[u] = w[oB2 + 16 * nt + col];
   }
-  sh[threadIdx.x] = s;
+  {
+    const int r = t >> 4, c = t & 15;
+    float v = 0.0f;
+    if (row0 + r < rows)
+      v = input_at<STD>(X, kIn, perm ? (int64_t)perm[row0 + r] : row0 + r, c, stats, stats + kIn);
+    xs[r * kRowX + c] = f2bf(v);
+    if (t < 16 * kOut) {
+      const int rr = t / kOut, cc = t % kOut;
+      float q = 0.0f;
+      if (row0 + rr < rows)
+        q = input_at<STD>(T, kOut, perm ? (int64_t)perm[row0 + rr] : row0 + rr, cc,
+                          stats + 2 * kIn, stats + 2 * kIn + kOut);
+      ts[t] = q;
+    }
+  }
   __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w) sh[threadIdx.x] += sh[threadIdx.x + w];
+  bool in[4];  // rows 4 g + j of the tile belong to the batch
+#pragma unroll
+  for (int j = 0; j < 4; ++j) in[j] = row0 + 4 * g + j < rows;
+  if (wv == 3) {  // x as the right operand of the first weight gradient
+    short4v b;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) b[j] = (short)xs[(4 * g + j) * kRowX + col];
+    *reinterpret_cast<short4v*>(o.x + rt * kFrag + 4 * lane) = b;
+  }
+  // forward; activations of rows past the batch are stored as zero
+  float z1[2][4], z2[2][4];
+  const short4v xa = lds_a(xs, kRowX, lane, 0);
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    const int nt = 2 * wv + u;
+    const float4v z = mfma16(xa, w1[u], float4v{0.f, 0.f, 0.f, 0.f});
+    float h[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      z1[u][j] = z[j] + b1[u];
+      const float a = gelu_f(z1[u][j]);
+      h[j] = in[j] ? a : 0.0f;
+      hs[0][(4 * g + j) * kRowS + 16 * nt + col] = f2bf(h[j]);
+    }
+    put_tile(o.h1, rt * kHT + nt, lane, h);
+  }
+  __syncthreads();
+  {
+    float4v z[2] = {float4v{0.f, 0.f, 0.f, 0.f}, float4v{0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+    for (int kt = 0; kt < kHT; ++kt) {
+      const short4v a = lds_a(hs[0], kRowS, lane, 16 * kt);
+      z[0] = mfma16(a, w2[0][kt], z[0]);
+      z[1] = mfma16(a, w2[1][kt], z[1]);
+    }
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int nt = 2 * wv + u;
+      float h[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        z2[u][j] = z[u][j] + b2[u];
+        const float a = gelu_f(z2[u][j]);
+        h[j] = in[j] ? a : 0.0f;
+        hs[1][(4 * g + j) * kRowS + 16 * nt + col] = f2bf(h[j]);
+      }
+      put_tile(o.h2, rt * kHT + nt, lane, h);
+    }
+  }
+  __syncthreads();
+  if (wv == 0) {
+    float4v y = float4v{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int kt = 0; kt < kHT; ++kt)
+      y = mfma16(lds_a(hs[1], kRowS, lane, 16 * kt), ld4(wf + fW3 + kt * kFrag + 4 * lane), y);
+    const float b3 = col < kOut ? w[oB3 + col] : 0.0f;
+    double s = 0.0;
+    float d[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      d[j] = 0.0f;
+      if (col < kOut && in[j]) {
+        const float yv = y[j] + b3;
+        const float r = yv - ts[(4 * g + j) * kOut + col];
+        s += (double)r * r;
+        d[j] = 2.0f * r * scale;
+      }
+      dys[(4 * g + j) * kRowX + col] = f2bf(d[j]);
+    }
+    put_tile(o.dy, rt, lane, d);
+    o.dy32[rt * 64 + lane] = float4v{d[0], d[1], d[2], d[3]};
+#pragma unroll
+    for (int k = 32; k >= 1; k >>= 1) s += __shfl_xor(s, k, 64);
+    if (lane == 0) o.loss[rt] = s;
+  }
+  __syncthreads();
+  // backward; hs[0] (h1, last read two barriers ago) takes dz2
+  const short4v da = lds_a(dys, kRowX, lane, 0);
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    const int nt = 2 * wv + u;
+    const float4v dh = mfma16(da, w3t[u], float4v{0.f, 0.f, 0.f, 0.f});
+    float d[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const float v = dh[j] * gelu_grad_f(z2[u][j]);
+      d[j] = in[j] ? v : 0.0f;
+      hs[0][(4 * g + j) * kRowS + 16 * nt + col] = f2bf(d[j]);
+    }
+    put_tile(o.dz2, rt * kHT + nt, lane, d);
+    o.dz232[(rt * kHT + nt) * 64 + lane] = float4v{d[0], d[1], d[2], d[3]};
+  }
+  __syncthreads();
+  float4v dh[2] = {float4v{0.f, 0.f, 0.f, 0.f}, float4v{0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+  for (int kt = 0; kt < kHT; ++kt) {
+    const short4v a = lds_a(hs[0], kRowS, lane, 16 * kt);
+    dh[0] = mfma16(a, w2t[0][kt], dh[0]);
+    dh[1] = mfma16(a, w2t[1][kt], dh[1]);
+  }
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    const int nt = 2 * wv + u;
+    float d[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const float v = dh[u][j] * gelu_grad_f(z1[u][j]);
+      d[j] = in[j] ? v : 0.0f;
+    }
+    put_tile(o.dz1, rt * kHT + nt, lane, d);
+    o.dz132[(rt * kHT + nt) * 64 + lane] = float4v{d[0], d[1], d[2], d[3]};
+  }
+}
+
+// Weight gradients over the row tiles [r0, r1) of one split (M x N tiles of
+// 16 x 16 from operand tiles a[rt][sa] and b[rt][sb]), row tiles in order.
+template <int M, int N>
+__device__ inline void wgrad_tiles(const unsigned short* __restrict__ a, int sa,
+                                   const unsigned short* __restrict__ b, int sb, int64_t r0,
+                                   int64_t r1, int lane, float4v (&acc)[M][N]) {
+#pragma unroll
+  for (int m = 0; m < M; ++m)
+#pragma unroll
+    for (int n = 0; n < N; ++n) acc[m][n] = float4v{0.f, 0.f, 0.f, 0.f};
+  constexpr int kAhead = 4;  // row tiles loaded together
+  int64_t r = r0;
+  for (; r + kAhead <= r1; r += kAhead) {
+    short4v fa[kAhead][M], fb[kAhead][N];
+#pragma unroll
+    for (int q = 0; q < kAhead; ++q) {
+#pragma unroll
+      for (int m = 0; m < M; ++m) fa[q][m] = ld4(a + ((r + q) * sa + m) * kFrag + 4 * lane);
+#pragma unroll
+      for (int n = 0; n < N; ++n) fb[q][n] = ld4(b + ((r + q) * sb + n) * kFrag + 4 * lane);
+    }
+#pragma unroll
+    for (int q = 0; q < kAhead; ++q)
+#pragma unroll
+      for (int m = 0; m < M; ++m)
+#pragma unroll
+        for (int n = 0; n < N; ++n) acc[m][n] = mfma16(fa[q][m], fb[q][n], acc[m][n]);
+  }
+  for (; r < r1; ++r)
+#pragma unroll
+    for (int m = 0; m < M; ++m)
+#pragma unroll
+      for (int n = 0; n < N; ++n)
+        acc[m][n] = mfma16(ld4(a + (r * sa + m) * kFrag + 4 * lane),
+                           ld4(b + (r * sb + n) * kFrag + 4 * lane), acc[m][n]);
+}
+
+// Bias gradient of sixteen columns: the float32 terms added row by row, in row
+// order (a running sum, so its length is the kernel's: about 3 ns a row).
+// 32 row tiles at a time are staged in LDS by all four waves, the next ones
+// while sixteen lanes of wave 0 add the current ones.
+constexpr int kBiasTiles = 32;
+__device__ inline void bias_sum(const float4v* __restrict__ v, int stride, int64_t tiles,
+                                float4v* buf, float* __restrict__ out, int nout) {
+  const int t = threadIdx.x;
+  constexpr int kPer = kBiasTiles * 64 / 256;
+  float4v q[kPer];
+  auto fetch = [&](int64_t r0) {
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+      const int64_t r = r0 + 4 * u + (t >> 6);
+      q[u] = r < tiles ? v[r * stride * 64 + (t & 63)] : float4v{0.f, 0.f, 0.f, 0.f};
+    }
+  };
+  float s = 0.0f;
+  fetch(0);
+  int b = 0;
+  for (int64_t r0 = 0; r0 < tiles; r0 += kBiasTiles, b ^= 1) {
+    float4v* cur = buf + b * kBiasTiles * 64;
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) cur[(4 * u + (t >> 6)) * 64 + (t & 63)] = q[u];
     __syncthreads();
+    if (r0 + kBiasTiles < tiles) fetch(r0 + kBiasTiles);
+    // the buffer written next was read before the barrier above
+    if (t < 16) {
+      const int lim = (int)min((int64_t)kBiasTiles, tiles - r0) * 4;
+#pragma unroll 8
+      for (int k = 0; k < lim; ++k) {  // rows 4 k .. 4 k + 3
+        const float4v x = cur[k * 16 + t];
+        s += x[0];
+        s += x[1];
+        s += x[2];
+        s += x[3];
+      }
+    }
   }
-  if (threadIdx.x == 0) part[blockIdx.x] = sh[0];
+  if (t < nout) out[t] = s;
 }
 
-__global__ void k_sum_double(const double* __restrict__ part, int np, double scale,
-                             double* __restrict__ out) {
-  if (threadIdx.x != 0) return;
-  double s = 0.0;
-  for (int i = 0; i < np; ++i) s += part[i];
-  *out += s * scale;
+constexpr int kBiasBlocks = 2 * kHT + 1;
+constexpr int kSplitBlocks = 5;  // workgroups of one split: 20 waves
+
+// Blocks 0 .. 16: bias sums.  Then five workgroups per split of `per` row
+// tiles: waves 0 .. 15 a 2 x 2 patch of W2's 8 x 8 tiles, 16 and 17 half of
+// W3's row of tiles, 18 and 19 half of W1's column.  Split z writes its
+// partial gradient to part[z] (flat weight layout).
+__global__ __launch_bounds__(256) void k_mlp_wgrad(MlpTiles o, int64_t tiles, int64_t per,
+                                                   float* __restrict__ part,
+                                                   float* __restrict__ bias) {
+  __shared__ __attribute__((aligned(16))) float4v buf[2 * kBiasTiles * 64];
+  if (blockIdx.x < kBiasBlocks) {
+    const int b = blockIdx.x;
+    if (b < kHT) bias_sum(o.dz232 + b * 64, kHT, tiles, buf, bias + kHid + 16 * b, 16);
+    else if (b < 2 * kHT) bias_sum(o.dz132 + (b - kHT) * 64, kHT, tiles, buf, bias + 16 * (b - kHT), 16);
+    else bias_sum(o.dy32, 1, tiles, buf, bias + 2 * kHid, kOut);
+    return;
+  }
+  const int z = (blockIdx.x - kBiasBlocks) / kSplitBlocks;
+  const int job = ((blockIdx.x - kBiasBlocks) % kSplitBlocks) * 4 + (threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63, col = lane & 15, g = lane >> 4;
+  const int64_t r0 = z * per, r1 = min(tiles, r0 + per);
+  float* out = part + (size_t)z * GVE_MLP_NWEIGHT;
+  if (job < 16) {
+    const int m0 = (job >> 2) * 2, n0 = (job & 3) * 2;
+    float4v acc[2][2];
+    wgrad_tiles<2, 2>(o.dz2 + m0 * kFrag, kHT, o.h1 + n0 * kFrag, kHT, r0, r1, lane, acc);
+#pragma unroll
+    for (int m = 0; m < 2; ++m)
+#pragma unroll
+      for (int n = 0; n < 2; ++n)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          out[oW2 + (16 * (m0 + m) + 4 * g + j) * kHid + 16 * (n0 + n) + col] = acc[m][n][j];
+  } else if (job < 18) {
+    const int n0 = (job - 16) * 4;
+    float4v acc[1][4];
+    wgrad_tiles<1, 4>(o.dy, 1, o.h2 + n0 * kFrag, kHT, r0, r1, lane, acc);
+#pragma unroll
+    for (int n = 0; n < 4; ++n)
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        if (4 * g + j < kOut) out[oW3 + (4 * g + j) * kHid + 16 * (n0 + n) + col] = acc[0][n][j];
+  } else {
+    const int m0 = (job - 18) * 4;
+    float4v acc[4][1];
+    wgrad_tiles<4, 1>(o.dz1 + m0 * kFrag, kHT, o.x, 1, r0, r1, lane, acc);
+#pragma unroll
+    for (int m = 0; m < 4; ++m)
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        out[oW1 + (16 * (m0 + m) + 4 * g + j) * kIn + col] = acc[m][0][j];
+  }
 }
 
-// Bias-corrected Adam on a flat float32 array.
-__global__ void k_adam_flat(float* __restrict__ w, float* __restrict__ m, float* __restrict__ v,
-                            const float* __restrict__ g, int64_t n, float lr, float b1, float b2,
-                            float eps, float ibc1, float ibc2) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const float gi = g[i];
-  const float mm = b1 * m[i] + (1.0f - b1) * gi;
-  const float vv = b2 * v[i] + (1.0f - b2) * gi * gi;
-  m[i] = mm;
-  v[i] = vv;
-  w[i] -= lr * (mm * ibc1) / (sqrtf(vv * ibc2) + eps);
+// Sum over the splits, in order, then the gradient to grad_out (when given) or
+// a bias-corrected Adam step on the float32 weights with their bfloat16 tiles.
+// Block 0 also adds the batch's loss, scaled, to *loss.
+__global__ __launch_bounds__(256) void k_mlp_adam(const float* __restrict__ part, int splits,
+                                                  const float* __restrict__ bias,
+                                                  const double* __restrict__ tile_loss,
+                                                  int64_t tiles, double loss_scale,
+                                                  double* __restrict__ loss,
+                                                  float* __restrict__ grad_out,
+                                                  float* __restrict__ w, float* __restrict__ m,
+                                                  float* __restrict__ v,
+                                                  unsigned short* __restrict__ wf, float lr,
+                                                  float b1, float b2, float eps, float ibc1,
+                                                  float ibc2) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i < GVE_MLP_NWEIGHT) {
+    float gi;
+    if (i >= oB1 && i < oW2) gi = bias[i - oB1];
+    else if (i >= oB2 && i < oW3) gi = bias[kHid + i - oB2];
+    else if (i >= oB3) gi = bias[2 * kHid + i - oB3];
+    else {
+      gi = 0.0f;
+#pragma unroll 8
+      for (int z = 0; z < splits; ++z) gi += part[(size_t)z * GVE_MLP_NWEIGHT + i];
+    }
+    if (grad_out) {
+      grad_out[i] = gi;
+    } else {
+      const float mm = b1 * m[i] + (1.0f - b1) * gi;
+      const float vv = b2 * v[i] + (1.0f - b2) * gi * gi;
+      m[i] = mm;
+      v[i] = vv;
+      const float x = w[i] - lr * (mm * ibc1) / (sqrtf(vv * ibc2) + eps);
+      w[i] = x;
+      store_weight_tiles(i, x, wf);
+    }
+  }
+  if (blockIdx.x == 0) {
+    __shared__ double sh[256];
+    double s = 0.0;
+    for (int64_t k = threadIdx.x; k < tiles; k += 256) s += tile_loss[k];
+    sh[threadIdx.x] = s;
+    __syncthreads();
+    for (int k = 128; k > 0; k >>= 1) {
+      if ((int)threadIdx.x < k) sh[threadIdx.x] += sh[threadIdx.x + k];
+      __syncthreads();
+    }
+    if (threadIdx.x == 0) *loss += sh[0] * loss_scale;
+  }
 }
 
-// Per-column mean and standard deviation (double) of a [rows][cols] matrix.
-__global__ void k_colstats(const float* __restrict__ X, int64_t rows, int cols,
-                           float* __restrict__ mean, float* __restrict__ stdv) {
+// Per-column mean and standard deviation (double) of a [rows][cols] matrix
+// (cols <= 16): each block sums its rows (whole rows per wave, so coalesced),
+// then one block adds the block sums in order.
+constexpr int kStatBlocks = 128;
+__global__ __launch_bounds__(256) void k_colstats_part(const float* __restrict__ X, int64_t rows,
+                                                       int cols, double* __restrict__ part) {
   __shared__ double s1[256], s2[256];
-  const int c = blockIdx.x;
+  const int c = threadIdx.x & 15, q = threadIdx.x >> 4;
   double a = 0.0, b = 0.0;
-  for (int64_t r = threadIdx.x; r < rows; r += 256) {
-    const double x = X[(size_t)r * cols + c];
-    a += x;
-    b += x * x;
-  }
+  if (c < cols)
+#pragma unroll 4
+    for (int64_t r = (int64_t)blockIdx.x * 16 + q; r < rows; r += kStatBlocks * 16) {
+      const double x = X[(size_t)r * cols + c];
+      a += x;
+      b += x * x;
+    }
   s1[threadIdx.x] = a;
   s2[threadIdx.x] = b;
   __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w) {
-      s1[threadIdx.x] += s1[threadIdx.x + w];
-      s2[threadIdx.x] += s2[threadIdx.x + w];
+  for (int k = 128; k >= 16; k >>= 1) {
+    if ((int)threadIdx.x < k) {
+      s1[threadIdx.x] += s1[threadIdx.x + k];
+      s2[threadIdx.x] += s2[threadIdx.x + k];
     }
     __syncthreads();
   }
-  if (threadIdx.x == 0) {
-    const double mu = s1[0] / (double)rows;
-    double var = s2[0] / (double)rows - mu * mu;
-    if (var < 0.0) var = 0.0;
-    const double sd = sqrt(var);
-    mean[c] = (float)mu;
-    stdv[c] = (float)(sd > 1e-6 ? sd : 1.0);
+  if (threadIdx.x < 16) {
+    part[(blockIdx.x * 16 + threadIdx.x) * 2] = s1[threadIdx.x];
+    part[(blockIdx.x * 16 + threadIdx.x) * 2 + 1] = s2[threadIdx.x];
   }
 }
 
-// out[r][c] = (X[perm[r]][c] - mean[c]) / std[c]   (perm may be null)
-__global__ void k_standardize(const float* __restrict__ X, const uint32_t* __restrict__ perm,
-                              int64_t rows, int cols, const float* __restrict__ mean,
-                              const float* __restrict__ stdv, float* __restrict__ out) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= rows * cols) return;
-  const int64_t r = i / cols;
-  const int c = (int)(i % cols);
-  const int64_t src = perm ? (int64_t)perm[r] : r;
-  out[i] = (X[(size_t)src * cols + c] - mean[c]) / stdv[c];
+__global__ __launch_bounds__(64) void k_colstats_final(const double* __restrict__ part, int64_t rows,
+                                                       int cols, float* __restrict__ mean,
+                                                       float* __restrict__ stdv) {
+  const int c = threadIdx.x;
+  if (c >= cols) return;
+  double a = 0.0, b = 0.0;
+#pragma unroll 16
+  for (int k = 0; k < kStatBlocks; ++k) {
+    a += part[(k * 16 + c) * 2];
+    b += part[(k * 16 + c) * 2 + 1];
+  }
+  const double mu = a / (double)rows;
+  double var = b / (double)rows - mu * mu;
+  if (var < 0.0) var = 0.0;
+  const double sd = sqrt(var);
+  mean[c] = (float)mu;
+  stdv[c] = (float)(sd > 1e-6 ? sd : 1.0);
 }
 
 // Random 32-bit keys and identity values for an epoch's permutation.
@@ -453,88 +860,100 @@ __global__ void k_apply_delta(float* __restrict__ theta, const float* __restrict
 // ---------------------------------------------------------------------------
 // Host-side helpers.
 
-hipError_t mlp_gemm(bool ta, bool tb, int epi, int M, int N, int K, const float* A, int lda,
-                    const float* B, int ldb, float* C, int ldc, const float* bias, float* C2,
-                    float* split_tmp, size_t split_tmp_floats, hipStream_t s) {
-  if (M <= 0 || N <= 0) return hipSuccess;
-  const int gx = (N + kTile - 1) / kTile, gy = (M + kTile - 1) / kTile;
-  // split long reductions (weight gradients over the batch) into K chunks
-  int kchunk = ((K + kK - 1) / kK) * kK;
-  int splits = 1;
-  if (epi == 0 && !bias && K > 1024 && split_tmp && ldc == N) {
-    kchunk = 512;
-    splits = (K + kchunk - 1) / kchunk;
-    while (splits > 1 && (size_t)splits * M * ldc > split_tmp_floats) {
-      kchunk *= 2;
-      splits = (K + kchunk - 1) / kchunk;
-    }
-  }
-  if (kchunk <= 0) kchunk = kK;
-  float* out = splits > 1 ? split_tmp : C;
-  const size_t stride = (size_t)M * ldc;
-  const dim3 grid(gx, gy, splits);
-#define GVE_GEMM(TA, TB, EPI)                                                                 \
-  hipLaunchKernelGGL((k_gemm<TA, TB, EPI>), grid, dim3(256), 0, s, M, N, K, A, lda, B, ldb,   \
-                     out, ldc, bias, C2, kchunk, stride)
-  if (epi == 1) {
-    if (!ta && !tb) GVE_GEMM(false, false, 1);
-    else if (!ta && tb) GVE_GEMM(false, true, 1);
-    else return hipErrorInvalidValue;
-  } else {
-    if (!ta && !tb) GVE_GEMM(false, false, 0);
-    else if (!ta && tb) GVE_GEMM(false, true, 0);
-    else if (ta && !tb) GVE_GEMM(true, false, 0);
-    else GVE_GEMM(true, true, 0);
-  }
-#undef GVE_GEMM
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess || splits == 1) return e;
-  const int64_t tot = (int64_t)M * N;
-  hipLaunchKernelGGL(k_sum_splits, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, s, split_tmp,
-                     splits, M, N, stride, C);
+namespace {
+
+int64_t row_tiles(int64_t rows) { return (rows + 15) / 16; }
+
+// Splits of the batch for the weight gradients: 512 rows each once a batch has
+// more than 1,024 rows, else one (fewer rows a split would only lengthen the
+// sums that follow, one split of 4,096 rows leaves the chip to 20 waves).
+int64_t split_tiles(int64_t rows) { return rows > 1024 ? 32 : std::max<int64_t>(row_tiles(rows), 1); }
+
+}  // namespace
+
+// Workspace of mlp_step for up to `rows` rows (bytes, 256-byte aligned parts).
+size_t mlp_step_bytes(int64_t rows) {
+  const size_t t = (size_t)row_tiles(rows);
+  const size_t splits = rows > 1024 ? (t + 31) / 32 : 1;
+  return t * (2 + 4 * kHT) * kFrag * 2 + t * (1 + 2 * kHT) * 1024 + t * 8 +
+         splits * GVE_MLP_NWEIGHT * 4 + 4096 + 16 * 256;
+}
+
+size_t mlp_stat_tmp_doubles() { return kStatBlocks * 16 * 2; }
+
+hipError_t mlp_pack(const float* w, unsigned short* wf, hipStream_t s) {
+  hipLaunchKernelGGL(k_mlp_pack, dim3((GVE_MLP_NWEIGHT + 255) / 256), dim3(256), 0, s, w, wf);
   return hipGetLastError();
 }
 
-hipError_t mlp_gelu_back(float* dH, const float* Z, int64_t n, hipStream_t s) {
-  hipLaunchKernelGGL(k_gelu_back, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, dH, Z, n);
+hipError_t mlp_infer(const float* X, int64_t n, const float* stats, const float* w,
+                     const unsigned short* wf, float* Y, hipStream_t s) {
+  if (n <= 0) return hipSuccess;
+  // four workgroups (of 37 KB LDS) fit a CU: 1,024 fill the chip
+  const unsigned blocks = (unsigned)std::min<int64_t>((n + 63) / 64, 1024);
+  if (stats)
+    hipLaunchKernelGGL((k_mlp_infer<true>), dim3(blocks), dim3(256), 0, s, X, n, stats, w, wf, Y);
+  else
+    hipLaunchKernelGGL((k_mlp_infer<false>), dim3(blocks), dim3(256), 0, s, X, n, stats, w, wf, Y);
   return hipGetLastError();
 }
 
-hipError_t mlp_colsum(const float* X, int rows, int cols, float* out, hipStream_t s) {
-  hipLaunchKernelGGL(k_colsum, dim3((unsigned)((cols + 127) / 128)), dim3(128), 0, s, X, rows, cols,
-                     out);
-  return hipGetLastError();
-}
-
-hipError_t mlp_mse_grad(const float* Y, const float* T, int64_t n, float scale, float* dY,
-                        double* part, double* acc_out, double acc_scale, hipStream_t s) {
-  hipLaunchKernelGGL(k_mse_grad, dim3(64), dim3(256), 0, s, Y, T, n, scale, dY, part);
+hipError_t mlp_step(const float* X, const float* T, const uint32_t* perm, int rows,
+                    const float* stats, float* w, float* m, float* v, unsigned short* wf,
+                    void* work, double loss_scale, double* loss, float* grad_out, float lr,
+                    int64_t t, hipStream_t s) {
+  const int64_t tiles = row_tiles(rows);
+  char* p = static_cast<char*>(work);
+  auto take = [&](size_t bytes) {
+    char* q = p;
+    p += (bytes + 255) & ~(size_t)255;
+    return q;
+  };
+  MlpTiles o;
+  const size_t one = (size_t)tiles * kFrag * 2, hid = one * kHT;
+  o.x = reinterpret_cast<unsigned short*>(take(one));
+  o.dy = reinterpret_cast<unsigned short*>(take(one));
+  o.h1 = reinterpret_cast<unsigned short*>(take(hid));
+  o.h2 = reinterpret_cast<unsigned short*>(take(hid));
+  o.dz1 = reinterpret_cast<unsigned short*>(take(hid));
+  o.dz2 = reinterpret_cast<unsigned short*>(take(hid));
+  o.dy32 = reinterpret_cast<float4v*>(take(2 * one));
+  o.dz132 = reinterpret_cast<float4v*>(take(2 * hid));
+  o.dz232 = reinterpret_cast<float4v*>(take(2 * hid));
+  o.loss = reinterpret_cast<double*>(take((size_t)tiles * 8));
+  const int64_t per = split_tiles(rows);
+  const int splits = (int)((tiles + per - 1) / per);
+  float* bias = reinterpret_cast<float*>(take(4096));
+  float* part = reinterpret_cast<float*>(take((size_t)splits * GVE_MLP_NWEIGHT * 4));
+  const double inv = 1.0 / ((double)rows * kOut);
+  if (stats)
+    hipLaunchKernelGGL((k_mlp_fb<true>), dim3((unsigned)tiles), dim3(256), 0, s, X, T, perm, rows,
+                       stats, w, wf, (float)inv, o);
+  else
+    hipLaunchKernelGGL((k_mlp_fb<false>), dim3((unsigned)tiles), dim3(256), 0, s, X, T, perm, rows,
+                       stats, w, wf, (float)inv, o);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_sum_double, dim3(1), dim3(64), 0, s, part, 64, acc_scale, acc_out);
-  return hipGetLastError();
-}
-
-hipError_t mlp_adam(float* w, float* m, float* v, const float* g, int64_t n, float lr, float b1,
-                    float b2, float eps, int64_t t, hipStream_t s) {
-  const float ibc1 = (float)(1.0 / (1.0 - pow((double)b1, (double)t)));
-  const float ibc2 = (float)(1.0 / (1.0 - pow((double)b2, (double)t)));
-  hipLaunchKernelGGL(k_adam_flat, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, w, m, v, g, n,
-                     lr, b1, b2, eps, ibc1, ibc2);
+  hipLaunchKernelGGL(k_mlp_wgrad, dim3((unsigned)(kBiasBlocks + kSplitBlocks * splits)), dim3(256),
+                     0, s, o, tiles, per, part, bias);
+  e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
+  const double tt = (double)std::max<int64_t>(t, 1);
+  const float ibc1 = (float)(1.0 / (1.0 - pow((double)b1, tt)));
+  const float ibc2 = (float)(1.0 / (1.0 - pow((double)b2, tt)));
+  hipLaunchKernelGGL(k_mlp_adam, dim3((GVE_MLP_NWEIGHT + 255) / 256), dim3(256), 0, s, part, splits,
+                     bias, o.loss, tiles, inv * loss_scale, loss, grad_out, w, m, v, wf, lr, b1, b2,
+                     eps, ibc1, ibc2);
   return hipGetLastError();
 }
 
 hipError_t mlp_colstats(const float* X, int64_t rows, int cols, float* mean, float* stdv,
-                        hipStream_t s) {
-  hipLaunchKernelGGL(k_colstats, dim3(cols), dim3(256), 0, s, X, rows, cols, mean, stdv);
-  return hipGetLastError();
-}
-
-hipError_t mlp_standardize(const float* X, const uint32_t* perm, int64_t rows, int cols,
-                           const float* mean, const float* stdv, float* out, hipStream_t s) {
-  const int64_t tot = rows * cols;
-  hipLaunchKernelGGL(k_standardize, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, s, X, perm,
-                     rows, cols, mean, stdv, out);
+                        double* tmp, hipStream_t s) {
+  hipLaunchKernelGGL(k_colstats_part, dim3(kStatBlocks), dim3(256), 0, s, X, rows, cols, tmp);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_colstats_final, dim3(1), dim3(64), 0, s, tmp, rows, cols, mean, stdv);
   return hipGetLastError();
 }
 
