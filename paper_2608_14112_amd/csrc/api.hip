@@ -487,12 +487,12 @@ gve_status bin(gve_ctx* ctx, const gve_params* p, const gve_grid& g, Binned* out
 
 // Launch the fused kernel over a binning (resets the queue counter first).
 gve_status fused(gve_ctx* ctx, const gve_params* p, const Binned& bn, const float* d_field,
-                 float* part, float* brick_loss, bool vjp) {
+                 float* part, float* brick_loss, int mode) {
   if (bn.sched.kind == gve::kSchedQueue)
     TRY_HIP(ctx, gve::fill_u32(bn.sched.counter, 1, ctx->stream));
   TRY_HIP(ctx, gve::launch_fused(p->rec, bn.gid, bn.start, bn.items, bn.nitems, bn.bg,
                                  ctx->opt.k, d_field, p->acc, p->n, part, bn.slot, brick_loss,
-                                 bn.sched, ctx->stream, vjp));
+                                 bn.sched, ctx->stream, mode));
   return GVE_OK;
 }
 
@@ -539,7 +539,7 @@ gve_status loss_and_sums_vol(gve_ctx* ctx, const gve_params* p, const float* d_f
   float* part = nullptr;
   TRY(partials_for(ctx, bn.capacity, &part));
   *part_out = part;
-  TRY(fused(ctx, p, bn, d_field, part, bl, false));
+  TRY(fused(ctx, p, bn, d_field, part, bl, gve::kFusedGrad));
   TRY(losses(ctx, bn, bl, d_loss_out));
   return GVE_OK;
 }
@@ -933,7 +933,8 @@ gve_status gve_vjp(gve_ctx* ctx, const gve_params* p, const float* d_upstream, g
   float* part = nullptr;
   TRY(partials_for(ctx, bn.capacity, &part));
   if (!part) TRY_HIP(ctx, gve::fill_f32(pm->acc, gve::kAccStride * p->n, 0.0f, ctx->stream));
-  TRY(fused(ctx, p, bn, d_upstream, part, static_cast<float*>(ctx->ws.brick_loss.ptr), true));
+  TRY(fused(ctx, p, bn, d_upstream, part, static_cast<float*>(ctx->ws.brick_loss.ptr),
+            gve::kFusedVjp));
   TRY_HIP(ctx, gve::launch_update(0, pm->theta, pm->m, pm->v, pm->acc, part, p->offset, nullptr,
                                   d_grad, p->n, p->t, ctx->opt, nullptr, ctx->stream));
   return GVE_OK;
@@ -1300,7 +1301,7 @@ gve_status refine_iters(gve_ctx* ctx, gve_params* p, const float* d_field, const
     float* part = nullptr;
     TRY(partials_for(ctx, bn.capacity, &part));
     if (timing) TRY_HIP(ctx, hipEventRecord(ev[1], s));
-    TRY(fused(ctx, p, bn, d_field, part, bl, false));
+    TRY(fused(ctx, p, bn, d_field, part, bl, gve::kFusedGrad));
     if (timing) TRY_HIP(ctx, hipEventRecord(ev[2], s));
     TRY(losses(ctx, bn, bl, hist + (size_t)it * vol.n));
     p->t += 1;
@@ -2120,7 +2121,7 @@ gve_status tune_pass(gve_ctx* ctx, const gve_params* p, const float* d_field, co
   float* bl = static_cast<float*>(ctx->ws.brick_loss.ptr);
   float* part = nullptr;
   TRY(partials_for(ctx, bn.capacity, &part));
-  TRY(fused(ctx, p, bn, d_field, part, bl, false));
+  TRY(fused(ctx, p, bn, d_field, part, bl, gve::kFusedGrad));
   TRY(ensure(ctx, ctx->ws.grad_tmp, sizeof(double) * (size_t)vol.n));
   TRY(losses(ctx, bn, bl, static_cast<double*>(ctx->ws.grad_tmp.ptr)));
   return GVE_OK;

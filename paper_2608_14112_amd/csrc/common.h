@@ -265,11 +265,14 @@ hipError_t launch_forward(const Record* rec, const uint32_t* pair_gid,
 // brick) pair stores its ten sums to part[pslot[j] * 10 + a], pslot[j] = the
 // emission index of sorted pair j (a primitive's emission range is
 // [offset[i], offset[i + 1])), which the update sums per primitive in order.
+// mode: loss and gradient sums, the sums for an upstream gradient in `field`
+// (no loss), or the loss alone (no sums).
+enum { kFusedGrad = 0, kFusedVjp = 1, kFusedLoss = 2 };
 hipError_t launch_fused(const Record* rec, const uint32_t* pair_gid,
                         const uint32_t* brick_start, const ItemDesc* items, int nitems,
                         BrickGeom bg, float k, const float* field, float* acc, int64_t n,
                         float* part, const uint32_t* pslot, float* brick_loss,
-                        const Schedule& sc, hipStream_t s, bool vjp = false);
+                        const Schedule& sc, hipStream_t s, int mode = kFusedGrad);
 hipError_t launch_count(const Record* rec, const uint32_t* pair_gid, const uint32_t* brick_start,
                         const ItemDesc* items, int nitems, BrickGeom bg, float k,
                         unsigned long long* counts, hipStream_t s);

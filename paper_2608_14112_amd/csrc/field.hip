@@ -119,7 +119,7 @@ __device__ inline ColumnSetup column_setup(const Record& r, float px, float py, 
   s.zmask = (s.zb >= s.za) ? (((2u << s.zb) - 1u) & ~((1u << s.za) - 1u)) : 0u;
   const float dx = px - r.mu[0];
   const float dy = py - r.mu[1];
-  s.qxy = fmaf(r.s[0], dx, r.s[1] * dy) * dx + r.s[2] * dy * dy;
+  s.qxy = fmaf(fmaf(r.s[0], dx, r.s[1] * dy), dx, r.s[2] * dy * dy);
   // w = sz t at the brick's middle: the brick offset from the centre first
   // (pz0 + BZ / 2 is exact and the same for every pair of the brick), then
   // the record's scaled slopes
@@ -265,6 +265,79 @@ __device__ inline void accumulate_brick(const Record* __restrict__ rec,
   if (jw < j1) touch_end(tc);
 }
 
+// ---- z-slices ------------------------------------------------------------------
+//
+// Where the launch has few bricks, a brick's forward pass is dealt to BZ / 8
+// waves by offset: wave w sums every pair, in list order, at offsets
+// 8 w .. 8 w + 7.  Each voxel's value is then formed from the same operations in
+// the same order as by one wave for the whole column, so results do not depend
+// on whether a brick is sliced.
+constexpr int kSlice = 8;
+
+// Forward steps of one pair at the wave's eight offsets (zc[u] = the offset
+// less BZ / 2).  Returns the active offsets (bits 0 .. 7): those at which some
+// lane is inside the support.  (All eight side by side without branches, the
+// ones outside the box compared against infinity, measured 2 % faster at 128
+// bricks and 12 % slower at 8,192.)
+__device__ inline uint32_t slice_steps(const ColumnSetup& s, float szv, float c, float thr,
+                                       uint32_t zm, const float (&zc)[kSlice],
+                                       float (&acc)[kSlice]) {
+  uint32_t active = 0u;
+#pragma unroll
+  for (int u = 0; u < kSlice; ++u) {
+    if ((zm >> u) & 1u) {
+      const float q = quad_w(s, fmaf(zc[u], szv, s.wm));
+      if (__builtin_amdgcn_ballot_w64(q > thr) != 0ull) {
+        active |= 1u << u;
+        const float G = (q > thr) ? __builtin_amdgcn_exp2f(q) : 0.0f;
+        acc[u] = fmaf(c, G, acc[u]);
+      }
+    }
+  }
+  return active;
+}
+
+// Forward accumulation of all pairs [j0, j1) of a brick at one slice.  With
+// `steps`, byte `slice` of steps[j - j0] takes the active offsets of pair j
+// (j - j0 < kStepCap): the four slices' bytes form the mask of the column.
+// The record of the next pair is loaded while the current one's steps run: a
+// brick's time is its list length times the latency of a pair, and few waves
+// share a SIMD.
+template <int BZ>
+__device__ inline void accumulate_slice(const Record* __restrict__ rec,
+                                        const uint32_t* __restrict__ pair_gid, uint32_t j0,
+                                        uint32_t j1, float px, float py, float pz0, int iz0,
+                                        int slice, float thr, float (&acc)[kSlice],
+                                        uint32_t* __restrict__ steps) {
+  if (j0 >= j1) return;
+  const int z0 = slice * kSlice;
+  float zc[kSlice];
+#pragma unroll
+  for (int u = 0; u < kSlice; ++u) zc[u] = (float)(z0 + u - BZ / 2);
+  const int lane = threadIdx.x & 63;
+  Record r = load_record(rec, __builtin_amdgcn_readfirstlane(pair_gid[j0]));
+  uint32_t next = __builtin_amdgcn_readfirstlane(pair_gid[min(j0 + 1, j1 - 1)]);
+  for (uint32_t j = j0; j < j1; ++j) {
+    const Record rn = load_record(rec, next);
+    next = __builtin_amdgcn_readfirstlane(pair_gid[min(j + 2, j1 - 1)]);
+    uint32_t active = 0u;
+    const ColumnSetup s = column_setup<BZ>(r, px, py, pz0, iz0);
+    const uint32_t zm = (s.zmask >> z0) & 0xFFu;
+    if (zm) {
+      const float szv = vreg(r.sz);
+      // the offset of the slice's part of the box nearest the vertex
+      const float wa = fmaf((float)(max(s.za, z0) - BZ / 2), szv, s.wm);
+      const float wb = fmaf((float)(min(s.zb, z0 + kSlice - 1) - BZ / 2), szv, s.wm);
+      const float wn = __builtin_amdgcn_fmed3f(wa, wb, 0.0f);
+      if (__builtin_amdgcn_ballot_w64(fmaf(-wn, wn, s.qxy) > thr) != 0ull)
+        active = slice_steps(s, szv, r.c, thr, zm, zc, acc);
+    }
+    if (steps && j - j0 < kStepCap && lane == 0)
+      reinterpret_cast<uint8_t*>(steps + (j - j0))[slice] = (uint8_t)active;
+    r = rn;
+  }
+}
+
 // ---- where a brick lies --------------------------------------------------------
 //
 // Global brick b belongs to the last volume whose first brick is <= b; b is
@@ -374,15 +447,39 @@ __global__ __launch_bounds__(BXY* BXY) void k_forward(const Record* __restrict__
   forward_brick<BXY, BZ>(rec, pair_gid, brick_start, items, nitems, b, thr, out);
 }
 
+// The same with the brick's offsets dealt to BZ / 8 waves.
+template <int BZ>
+__global__ __launch_bounds__(BZ / kSlice * 64) void k_forward_sliced(
+    const Record* __restrict__ rec, const uint32_t* __restrict__ pair_gid,
+    const uint32_t* __restrict__ brick_start, const ItemDesc* __restrict__ items, int nitems,
+    uint32_t nbricks, int xcd, float thr, float* __restrict__ out) {
+  const uint32_t b = xcd ? xcd_brick(blockIdx.x, nbricks) : blockIdx.x;
+  const int slice = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const Site st = site_of<8, BZ>(items, nitems, b, threadIdx.x & 63);
+  float acc[kSlice];
+#pragma unroll
+  for (int u = 0; u < kSlice; ++u) acc[u] = 0.0f;
+  accumulate_slice<BZ>(rec, pair_gid, brick_start[b], brick_start[b + 1], st.px, st.py, st.pz0,
+                       st.iz0, slice, thr, acc, nullptr);
+  if (st.col_in) {
+#pragma unroll
+    for (int u = 0; u < kSlice; ++u)
+      if (slice * kSlice + u < st.zrem) *st.at(out, slice * kSlice + u) = acc[u];
+  }
+}
+
 // The backward steps of one pair over the brick offsets in `run`: moments
 // of e = r G over zz.  CHECK skips offsets where no lane is inside the
 // support; without it every offset in `run` must hold some lane inside (the
 // offsets the forward pass recorded), and the steps carry no branch that
-// waits on a compare.
+// waits on a compare.  Contraction is off here and in the recurrence below
+// (fused operations are written out), so that every variant of the kernel
+// forms a pair's sums from the same operations.
 template <int BZ, bool CHECK>
 __device__ inline void backward_steps(const ColumnSetup& s, float szv, uint32_t run,
                                       const float (&res)[BZ], float thr, float& se, float& sK,
                                       float& sKK) {
+#pragma clang fp contract(off)
 #pragma unroll
   for (int g0 = 0; g0 < BZ; g0 += 8) {
     if ((run >> g0) & 0xFFu) {
@@ -394,7 +491,7 @@ __device__ inline void backward_steps(const ColumnSetup& s, float szv, uint32_t 
           if (!CHECK || __builtin_amdgcn_ballot_w64(q > thr) != 0ull) {
             const float G = (q > thr) ? __builtin_amdgcn_exp2f(q) : 0.0f;
             const float e = res[zz] * G;
-            se += e;
+            se = fmaf(res[zz], G, se);
             sK = fmaf((float)zz, e, sK);
             sKK = fmaf((float)(zz * zz), e, sKK);
           }
@@ -425,6 +522,7 @@ template <int BZ>
 __device__ inline void backward_steps_chain(const ColumnSetup& s, float szv, float sz, float C,
                                             int z0, int z1, const float (&res)[BZ], float T,
                                             float& se, float& sK, float& sKK) {
+#pragma clang fp contract(off)
   const float w0 = fmaf((float)(z0 - 1 - BZ / 2), szv, s.wm);
   const float q0 = quad_w(s, w0);
   float G = q0 > -100.0f ? __builtin_amdgcn_exp2f(q0) : 0.0f;
@@ -442,8 +540,9 @@ __device__ inline void backward_steps_chain(const ColumnSetup& s, float szv, flo
           asm volatile("");
           G *= R;
           R *= C;
-          const float e = res[zz] * (G > T ? G : 0.0f);
-          se += e;
+          const float Gs = G > T ? G : 0.0f;
+          const float e = res[zz] * Gs;
+          se = fmaf(res[zz], Gs, se);
           sK = fmaf((float)zz, e, sK);
           sKK = fmaf((float)(zz * zz), e, sKK);
         }
@@ -483,9 +582,10 @@ __device__ inline void load_column_chunk(const float* __restrict__ field, const 
   }
 }
 
-// One brick of the fused pass.  VJP = false: residual r = 2 (Vhat - V) from
-// the forward pass and the target `field`, loss share to brick_loss.
-// VJP = true: no forward pass; r is read from `field` (an upstream gradient
+// One brick of the fused pass.
+// kGrad: residual r = 2 (Vhat - V) from the forward pass and the target
+// `field`, loss share to brick_loss, ten sums.  kLoss: the same without the
+// sums.  kVjp: no forward pass; r is read from `field` (an upstream gradient
 // dl/dVhat), so the ten sums give the vector-Jacobian product
 // sum_p r(p) dVhat(p)/dtheta.
 // W > 1 (8 x 8 columns only): W waves share the brick's columns and split its
@@ -493,7 +593,11 @@ __device__ inline void load_column_chunk(const float* __restrict__ field, const 
 // in wave order through LDS (`comb`, W * BZ * 64 floats), after which every
 // wave holds the whole field of the brick.  `comb` is then each wave's block
 // of the ten-sum reduction (lds_sum10).
-template <int BXY, int BZ, bool VJP, int W>
+// SLICED (W = BZ / 8 > 1): the waves split the forward pass by offsets instead
+// (accumulate_slice) and exchange residuals; values, recorded offsets, loss
+// and each pair's sums are those of W = 1 exactly.
+constexpr int kGrad = kFusedGrad, kVjp = kFusedVjp, kLoss = kFusedLoss;
+template <int BXY, int BZ, int MODE, int W, bool SLICED>
 __device__ __attribute__((always_inline)) inline void fused_brick(const Record* __restrict__ rec,
                                    const uint32_t* __restrict__ pair_gid,
                                    const uint32_t* __restrict__ brick_start,
@@ -507,9 +611,12 @@ __device__ __attribute__((always_inline)) inline void fused_brick(const Record* 
   // `comb` holds the forward partial sums of W > 1 waves until they are
   // added, then the waves' ten-sum blocks (kSumFloats each)
   constexpr int kWaves = (BXY * BXY + 63) / 64;  // waves over the columns
+  constexpr bool VJP = MODE == kVjp;
   static_assert(W == 1 || kWaves == 1, "pairs are split only over one wave of columns");
+  static_assert(!SLICED || (W == BZ / kSlice && W > 1 && !VJP), "one wave per slice");
   const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6;
+  // uniform, so that the waves' pair indices, masks and branches stay scalar
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const Site st = site_of<BXY, BZ>(items, nitems, b, W > 1 ? (uint32_t)lane : threadIdx.x);
   const float px = st.px, py = st.py, pz0 = st.pz0;
   const int iz0 = st.iz0;
@@ -535,9 +642,37 @@ __device__ __attribute__((always_inline)) inline void fused_brick(const Record* 
       for (int u = 0; u < kLoadZ; ++u) res[z0 + u] = t[u];
       asm volatile("" ::: "memory");
     }
+  } else if (SLICED) {
+    const int slice = wave;
+    float acc[kSlice];
+#pragma unroll
+    for (int u = 0; u < kSlice; ++u) acc[u] = 0.0f;
+    accumulate_slice<BZ>(rec, pair_gid, j0, j1, px, py, pz0, iz0, slice, thr, acc,
+                         MODE == kGrad ? steps : nullptr);
+    float t[kSlice];
+    load_column_chunk<kSlice>(field, st, voff, nrec, slice * kSlice, t);
+#pragma unroll
+    for (int u = 0; u < kSlice; ++u) {
+      const int zz = slice * kSlice + u;
+      comb[zz * 64 + lane] = col_in && zz < st.zrem ? 2.0f * (acc[u] - t[u]) : 0.0f;
+    }
+    __syncthreads();
+    // every wave takes the whole column's residual; (r / 2)^2 in offset order
+    // is the loss sum of an unsliced brick (r is twice the difference, exactly)
+    float lsum = 0.0f;
+    if (MODE == kGrad || wave == 0) {
+#pragma unroll
+      for (int zz = 0; zz < BZ; ++zz) res[zz] = comb[zz * 64 + lane];
+#pragma unroll
+      for (int zz = 0; zz < BZ; ++zz) lsum = fmaf(0.5f * res[zz], 0.5f * res[zz], lsum);
+      lsum = wave_sum(lsum);
+      if (threadIdx.x == 0) brick_loss[b] = lsum;
+    }
+    // the residuals are read before `comb` takes the waves' ten-sum blocks
+    if (MODE == kGrad) __syncthreads();
   } else {
     accumulate_brick<BZ>(rec, pair_gid, j0, jw, (uint32_t)W, j1, px, py, pz0, iz0, cols, thr,
-                         res, kWaves == 1 ? steps : nullptr);
+                         res, kWaves == 1 && MODE == kGrad ? steps : nullptr);
     if (W > 1) {
       // the waves' partial sums, added in wave order
 #pragma unroll
@@ -600,6 +735,7 @@ __device__ __attribute__((always_inline)) inline void fused_brick(const Record* 
     }
   }
 
+  if (MODE == kLoss) return;
   // support test and reach of the recurrence form of the backward steps
   const float T = __builtin_amdgcn_exp2f(thr);
   const float reach = 100.0f + thr > 0.0f ? sqrtf(100.0f + thr) - sqrtf(-thr) : 0.0f;
@@ -609,7 +745,10 @@ __device__ __attribute__((always_inline)) inline void fused_brick(const Record* 
     const ColumnSetup s = column_setup<BZ>(r, px, py, pz0, iz0);
     // the steps the forward pass found active, else the box's z-range
     const bool recorded = kWaves == 1 && !VJP && j - j0 < kStepCap;
-    const uint32_t run = recorded ? __builtin_amdgcn_readfirstlane(steps[j - j0]) : s.zmask;
+    // (sliced bricks write one byte per slice: fewer than four leave the rest unset)
+    constexpr uint32_t kOffsets = BZ < 32 ? (1u << (BZ & 31)) - 1u : 0xFFFFFFFFu;
+    const uint32_t run = recorded ? __builtin_amdgcn_readfirstlane(steps[j - j0]) & kOffsets
+                                  : s.zmask;
     const bool hit = recorded ? run != 0u : column_hit<BZ>(s, r.sz, cols, thr);
     if (kWaves == 1 && !hit) {
       // a pair whose support misses every column still owns a partials slot
@@ -680,15 +819,15 @@ __device__ __attribute__((always_inline)) inline void fused_brick(const Record* 
 // Floats of the fused kernels' shared block: the larger of the W > 1 forward
 // partial sums and the waves' ten-sum blocks (the two are live one after the
 // other).
-constexpr int fused_lds_floats(int bz, bool vjp, int w, int waves) {
-  const int comb = w > 1 && !vjp ? w * bz * 64 : 0;
-  const int sums = w * waves * kSumFloats;
+constexpr int fused_lds_floats(int bz, int mode, int w, int waves, bool sliced) {
+  const int comb = sliced ? bz * 64 : (w > 1 && mode != kVjp ? w * bz * 64 : 0);
+  const int sums = mode == kLoss ? 1 : w * waves * kSumFloats;
   return comb > sums ? comb : sums;
 }
 
 // One workgroup per brick (xcd: consecutive bricks grouped per XCD); W waves
 // per brick split its pairs (fused_brick).
-template <int BXY, int BZ, bool VJP, int W>
+template <int BXY, int BZ, int MODE, int W, bool SLICED>
 __global__ __launch_bounds__(BXY* BXY* W) void k_fused(const Record* __restrict__ rec,
                                                 const uint32_t* __restrict__ pair_gid,
                                                 const uint32_t* __restrict__ brick_start,
@@ -701,17 +840,17 @@ __global__ __launch_bounds__(BXY* BXY* W) void k_fused(const Record* __restrict_
                                                 float* __restrict__ brick_loss) {
   constexpr int kWaves = (BXY * BXY + 63) / 64;
   __shared__ float red[kWaves][10];
-  __shared__ uint32_t steps[kWaves == 1 && !VJP ? kStepCap : 1];
-  __shared__ __attribute__((aligned(16))) float comb[fused_lds_floats(BZ, VJP, W, kWaves)];
+  __shared__ uint32_t steps[kWaves == 1 && MODE == kGrad ? kStepCap : 1];
+  __shared__ __attribute__((aligned(16))) float comb[fused_lds_floats(BZ, MODE, W, kWaves, SLICED)];
   const uint32_t b = xcd ? xcd_brick(blockIdx.x, nbricks) : blockIdx.x;
-  fused_brick<BXY, BZ, VJP, W>(rec, pair_gid, brick_start, items, nitems, b, thr, field, gacc, n,
-                               part, pslot, brick_loss, red, steps, comb);
+  fused_brick<BXY, BZ, MODE, W, SLICED>(rec, pair_gid, brick_start, items, nitems, b, thr, field,
+                                        gacc, n, part, pslot, brick_loss, red, steps, comb);
 }
 
 // Persistent: each workgroup takes queue positions from *counter until they
 // run out (every workgroup reaches that exit) and processes brick
 // order[position] (heaviest first).
-template <int BXY, int BZ, bool VJP, int W>
+template <int BXY, int BZ, int MODE, int W>
 __global__ __launch_bounds__(BXY* BXY* W) void k_fused_queue(const Record* __restrict__ rec,
                                                       const uint32_t* __restrict__ pair_gid,
                                                       const uint32_t* __restrict__ brick_start,
@@ -726,8 +865,8 @@ __global__ __launch_bounds__(BXY* BXY* W) void k_fused_queue(const Record* __res
                                                       float* __restrict__ brick_loss) {
   constexpr int kWaves = (BXY * BXY + 63) / 64;
   __shared__ float red[kWaves][10];
-  __shared__ uint32_t steps[kWaves == 1 && !VJP ? kStepCap : 1];
-  __shared__ __attribute__((aligned(16))) float comb[fused_lds_floats(BZ, VJP, W, kWaves)];
+  __shared__ uint32_t steps[kWaves == 1 && MODE == kGrad ? kStepCap : 1];
+  __shared__ __attribute__((aligned(16))) float comb[fused_lds_floats(BZ, MODE, W, kWaves, false)];
   __shared__ uint32_t next;
   for (;;) {
     if (threadIdx.x == 0) next = atomicAdd(counter, 1u);
@@ -735,8 +874,8 @@ __global__ __launch_bounds__(BXY* BXY* W) void k_fused_queue(const Record* __res
     const uint32_t w = __builtin_amdgcn_readfirstlane(next);
     __syncthreads();
     if (w >= nbricks) break;
-    fused_brick<BXY, BZ, VJP, W>(rec, pair_gid, brick_start, items, nitems, order[w], thr,
-                                 field, gacc, n, part, pslot, brick_loss, red, steps, comb);
+    fused_brick<BXY, BZ, MODE, W, false>(rec, pair_gid, brick_start, items, nitems, order[w], thr,
+                                         field, gacc, n, part, pslot, brick_loss, red, steps, comb);
   }
 }
 
@@ -856,6 +995,27 @@ __global__ __launch_bounds__(kRedThreads) void k_item_loss(const float* __restri
   X(8, 8, 1) X(8, 8, 2) X(8, 8, 4) X(8, 16, 1) X(8, 16, 2) X(8, 16, 4) X(8, 32, 1) X(8, 32, 2) \
   X(8, 32, 4) X(16, 16, 1)
 
+// One wave per brick leaves the chip (8,192 resident waves) idle or waiting for
+// its heaviest bricks when the launch has few: a pair costs a lone wave about
+// 1 us forward and 1 us backward, most of it latency.  Up to these brick
+// counts the offsets of the forward pass are dealt to BZ / 8 waves and the pairs
+// of the backward pass to the same waves.  Past them the chip is full and the
+// slices' repeated per-pair set-up (about 15 % more vector instructions) costs
+// more than the balance gains.  Measured, 20 supports a voxel, 8 x 8 x 32
+// bricks, unsliced -> sliced: loss and gradient 128 bricks 546 -> 265 us,
+// 1,024 829 -> 411, 3,456 1075 -> 716, 8,192 1346 -> 1091, 16,000 1936 -> 1959;
+// evaluation 128 bricks 293 -> 160 us, 3,456 556 -> 390, 8,192 660 -> 605,
+// 16,000 919 -> 1048 (whole calls, binning included).
+constexpr int64_t kSlicedForwardBricks = 10240;
+constexpr int64_t kSlicedFusedBricks = 12288;
+// The VJP has no forward pass, and each pair's sums are its own, so four waves
+// simply take every fourth pair: always with 8 x 8 x 32 bricks (128^3 558 ->
+// 243 us, 256^3 892 -> 506, 512^3 2619 -> 2229, 768^3 6383 -> 6173, whole
+// calls), with shallower ones, whose lists are shorter, up to this many (8 x 8
+// x 8: 110,592 bricks 1603 -> 1521 us, 884,736 8997 -> 9205; x 16: 131,072
+// 2759 -> 2591, 442,368 7127 -> 7173).
+constexpr int64_t kSplitVjpBricks = 131072;
+
 bool brick_shape_supported(int bxy, int bz) {
 #define GVE_CASE(XY, Z) if (bxy == XY && bz == Z) return true;
   GVE_BRICK_SHAPES(GVE_CASE)
@@ -876,7 +1036,7 @@ int fused_resident_groups(int bxy, int bz, int waves, int device) {
     return 0;
 #define GVE_CASE(XY, Z, W)                                                                    \
   if (bxy == XY && bz == Z && waves == W) {                                                   \
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_fused_queue<XY, Z, false, W>, \
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_fused_queue<XY, Z, kGrad, W>, \
                                                      XY * XY * W, 0) != hipSuccess)           \
       return 0;                                                                               \
     return per_cu * cus;                                                                      \
@@ -893,6 +1053,15 @@ hipError_t launch_forward(const Record* rec, const uint32_t* pair_gid, const uin
   if (bg.nbricks <= 0) return hipSuccess;
   const dim3 grid((unsigned)bg.nbricks);
   const int xcd = sc.kind == kSchedXcd ? 1 : 0;
+#define GVE_CASE(Z)                                                                           \
+  if (bg.Bxy == 8 && bg.Bz == Z && bg.nbricks <= kSlicedForwardBricks) {                        \
+    hipLaunchKernelGGL((k_forward_sliced<Z>), grid, dim3(Z / kSlice * 64), 0, s, rec, pair_gid, \
+                       brick_start, items, nitems, (uint32_t)bg.nbricks, xcd, thr, out);        \
+    return hipGetLastError();                                                                 \
+  }
+  GVE_CASE(16)
+  GVE_CASE(32)
+#undef GVE_CASE
 #define GVE_CASE(XY, Z)                                                                       \
   if (bg.Bxy == XY && bg.Bz == Z) {                                                           \
     hipLaunchKernelGGL((k_forward<XY, Z>), grid, dim3(XY * XY), 0, s, rec, pair_gid,            \
@@ -904,41 +1073,80 @@ hipError_t launch_forward(const Record* rec, const uint32_t* pair_gid, const uin
   return hipErrorInvalidValue;
 }
 
+namespace {
+
+// Arguments of the fused kernels.
+struct FusedArgs {
+  const Record* rec;
+  const uint32_t *pair_gid, *brick_start;
+  const ItemDesc* items;
+  int nitems;
+  uint32_t nb;
+  float thr;
+  const float* field;
+  float* acc;
+  int64_t n;
+  float* part;
+  const uint32_t* pslot;
+  float* brick_loss;
+};
+
+template <int XY, int Z, int MODE, int W, bool SLICED>
+hipError_t run_fused(const FusedArgs& a, const Schedule& sc, hipStream_t s) {
+  if (sc.kind == kSchedQueue && !SLICED) {
+    const dim3 grid((unsigned)std::min<int64_t>(sc.persistent_groups, a.nb));
+    hipLaunchKernelGGL((k_fused_queue<XY, Z, MODE, W>), grid, dim3(XY * XY * W), 0, s, a.rec,
+                       a.pair_gid, a.brick_start, a.items, a.nitems, a.nb, sc.order, sc.counter,
+                       a.thr, a.field, a.acc, a.n, a.part, a.pslot, a.brick_loss);
+  } else {
+    hipLaunchKernelGGL((k_fused<XY, Z, MODE, W, SLICED>), dim3(a.nb), dim3(XY * XY * W), 0, s,
+                       a.rec, a.pair_gid, a.brick_start, a.items, a.nitems, a.nb,
+                       sc.kind == kSchedXcd ? 1 : 0, a.thr, a.field, a.acc, a.n, a.part, a.pslot,
+                       a.brick_loss);
+  }
+  return hipGetLastError();
+}
+
+template <int XY, int Z, int W>
+hipError_t run_mode(int mode, const FusedArgs& a, const Schedule& sc, hipStream_t s) {
+  if (mode == kVjp) return run_fused<XY, Z, kVjp, W, false>(a, sc, s);
+  if (mode == kLoss) return run_fused<XY, Z, kLoss, W, false>(a, sc, s);
+  return run_fused<XY, Z, kGrad, W, false>(a, sc, s);
+}
+
+template <int Z>
+hipError_t run_sliced(int mode, const FusedArgs& a, const Schedule& sc, hipStream_t s) {
+  constexpr int W = Z / kSlice;
+  if (mode == kLoss) return run_fused<8, Z, kLoss, W, true>(a, sc, s);
+  return run_fused<8, Z, kGrad, W, true>(a, sc, s);
+}
+
+}  // namespace
+
 hipError_t launch_fused(const Record* rec, const uint32_t* pair_gid, const uint32_t* brick_start,
                         const ItemDesc* items, int nitems, BrickGeom bg, float k,
                         const float* field, float* acc, int64_t n, float* part,
                         const uint32_t* pslot, float* brick_loss, const Schedule& sc,
-                        hipStream_t s, bool vjp) {
-  const float thr = -kHalfLog2e * k * k;
+                        hipStream_t s, int mode) {
   if (bg.nbricks <= 0) return hipSuccess;
   const bool queue = sc.kind == kSchedQueue;
   if (queue && (!sc.order || !sc.counter || sc.persistent_groups <= 0)) return hipErrorInvalidValue;
-  const dim3 grid(queue ? (unsigned)std::min<int64_t>(sc.persistent_groups, bg.nbricks)
-                        : (unsigned)bg.nbricks);
-  const int xcd = sc.kind == kSchedXcd ? 1 : 0;
-  const uint32_t* order = sc.order;
-  uint32_t* counter = sc.counter;
-  const uint32_t nb = (uint32_t)bg.nbricks;
-#define GVE_CASE(XY, Z, W)                                                                    \
-  if (bg.Bxy == XY && bg.Bz == Z && bg.waves == W) {                                          \
-    if (queue && vjp)                                                                         \
-      hipLaunchKernelGGL((k_fused_queue<XY, Z, true, W>), grid, dim3(XY * XY * W), 0, s, rec,   \
-                         pair_gid, brick_start, items, nitems, nb, order, counter, thr, field,  \
-                         acc, n, part, pslot, brick_loss);                                     \
-    else if (queue)                                                                           \
-      hipLaunchKernelGGL((k_fused_queue<XY, Z, false, W>), grid, dim3(XY * XY * W), 0, s, rec,  \
-                         pair_gid, brick_start, items, nitems, nb, order, counter, thr, field,  \
-                         acc, n, part, pslot, brick_loss);                                     \
-    else if (vjp)                                                                             \
-      hipLaunchKernelGGL((k_fused<XY, Z, true, W>), grid, dim3(XY * XY * W), 0, s, rec,         \
-                         pair_gid, brick_start, items, nitems, nb, xcd, thr, field, acc, n,     \
-                         part, pslot, brick_loss);                                              \
-    else                                                                                      \
-      hipLaunchKernelGGL((k_fused<XY, Z, false, W>), grid, dim3(XY * XY * W), 0, s, rec,        \
-                         pair_gid, brick_start, items, nitems, nb, xcd, thr, field, acc, n,     \
-                         part, pslot, brick_loss);                                              \
-    return hipGetLastError();                                                                 \
+  const FusedArgs a{rec, pair_gid, brick_start, items, nitems, (uint32_t)bg.nbricks,
+                    -kHalfLog2e * k * k, field, acc, n, part, pslot, brick_loss};
+  if (bg.Bxy == 8 && bg.waves == 1 && !queue) {
+    if (mode == kVjp) {
+      if (bg.Bz == 32) return run_fused<8, 32, kVjp, 4, false>(a, sc, s);
+      if (bg.nbricks <= kSplitVjpBricks) {
+        if (bg.Bz == 8) return run_fused<8, 8, kVjp, 4, false>(a, sc, s);
+        if (bg.Bz == 16) return run_fused<8, 16, kVjp, 4, false>(a, sc, s);
+      }
+    } else if (bg.nbricks <= kSlicedFusedBricks) {
+      if (bg.Bz == 16) return run_sliced<16>(mode, a, sc, s);
+      if (bg.Bz == 32) return run_sliced<32>(mode, a, sc, s);
+    }
   }
+#define GVE_CASE(XY, Z, W) \
+  if (bg.Bxy == XY && bg.Bz == Z && bg.waves == W) return run_mode<XY, Z, W>(mode, a, sc, s);
   GVE_FUSED_SHAPES(GVE_CASE)
 #undef GVE_CASE
   return hipErrorInvalidValue;
