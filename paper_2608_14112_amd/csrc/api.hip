@@ -529,7 +529,8 @@ gve_status partials_for(gve_ctx* ctx, int64_t npairs, float** part) {
 }
 
 // Fused forward + squared error + backward into p->acc (or the partials),
-// the loss of each volume into d_loss_out[0 .. vol.n).
+// the loss of each volume into d_loss_out[0 .. vol.n).  With part_out ==
+// nullptr the loss alone: no backward pass, the accumulators stay as they are.
 gve_status loss_and_sums_vol(gve_ctx* ctx, const gve_params* p, const float* d_field, const Vol& vol,
                              double* d_loss_out, float** part_out) {
   Binned bn;
@@ -537,9 +538,11 @@ gve_status loss_and_sums_vol(gve_ctx* ctx, const gve_params* p, const float* d_f
   TRY(ensure(ctx, ctx->ws.brick_loss, sizeof(float) * (size_t)std::max<int64_t>(bn.bg.nbricks, 1)));
   float* bl = static_cast<float*>(ctx->ws.brick_loss.ptr);
   float* part = nullptr;
-  TRY(partials_for(ctx, bn.capacity, &part));
-  *part_out = part;
-  TRY(fused(ctx, p, bn, d_field, part, bl, gve::kFusedGrad));
+  // (the allocation-free path reserves the partials either way, so that what it
+  // refuses does not depend on the outputs asked for)
+  if (part_out || ctx->arena_base) TRY(partials_for(ctx, bn.capacity, &part));
+  if (part_out) *part_out = part;
+  TRY(fused(ctx, p, bn, d_field, part, bl, part_out ? gve::kFusedGrad : gve::kFusedLoss));
   TRY(losses(ctx, bn, bl, d_loss_out));
   return GVE_OK;
 }
@@ -807,15 +810,15 @@ gve_status gve_loss_grad(gve_ctx* ctx, const gve_params* p, const float* d_field
     const int64_t off[2] = {0, p->n};
     TRY(select_auto(ctx, p, d_field, Vol{&g, off, 1}, ctx->arena_base == nullptr));
   }
-  TRY_HIP(ctx, gve::fill_f32(pm->acc, gve::kAccStride * p->n, 0.0f, ctx->stream));
   double* dl = static_cast<double*>(ctx->ws.dloss.ptr);
-  float* part = nullptr;
-  TRY(loss_and_sums(ctx, p, d_field, g, dl, &part));
   if (d_grad) {
+    float* part = nullptr;
+    TRY_HIP(ctx, gve::fill_f32(pm->acc, gve::kAccStride * p->n, 0.0f, ctx->stream));
+    TRY(loss_and_sums(ctx, p, d_field, g, dl, &part));
     TRY_HIP(ctx, gve::launch_update(0, pm->theta, pm->m, pm->v, pm->acc, part, p->offset, nullptr,
                                     d_grad, p->n, p->t, ctx->opt, nullptr, ctx->stream));
   } else {
-    TRY_HIP(ctx, gve::fill_f32(pm->acc, gve::kAccStride * p->n, 0.0f, ctx->stream));
+    TRY(loss_and_sums(ctx, p, d_field, g, dl, nullptr));
   }
   if (h_loss) {
     TRY_HIP(ctx, hipMemcpyAsync(ctx->ws.h_pinned, dl, sizeof(double), hipMemcpyDeviceToHost,
@@ -1651,13 +1654,11 @@ gve_status mlp_apply(gve_ctx* ctx, const gve_mlp* m, const float* X, int64_t n, 
   return GVE_OK;
 }
 
-// Loss L of p on the field (forward + fused pass), read back to the host.
+// Loss L of p on the field (no gradient), read back to the host.
 gve_status eval_loss(gve_ctx* ctx, const gve_params* p, const float* d_field, const gve_grid& g,
                      double* out) {
   double* dl = static_cast<double*>(ctx->ws.dloss.ptr);
-  float* part = nullptr;
-  TRY(loss_and_sums(ctx, p, d_field, g, dl, &part));
-  if (!part) TRY_HIP(ctx, gve::fill_f32(const_cast<gve_params*>(p)->acc, gve::kAccStride * p->n, 0.0f, ctx->stream));
+  TRY(loss_and_sums(ctx, p, d_field, g, dl, nullptr));
   TRY_HIP(ctx, hipMemcpyAsync(ctx->ws.h_pinned, dl, sizeof(double), hipMemcpyDeviceToHost,
                               ctx->stream));
   TRY_HIP(ctx, hipStreamSynchronize(ctx->stream));
@@ -2046,14 +2047,14 @@ gve_status gve_batch_loss_grad(gve_ctx* ctx, const gve_batch* b, const float* d_
   const int ni = (int)b->grids.size();
   TRY(ensure(ctx, ctx->ws.grad_tmp, sizeof(double) * (size_t)ni));
   double* dl = static_cast<double*>(ctx->ws.grad_tmp.ptr);
-  TRY_HIP(ctx, gve::fill_f32(pm->acc, gve::kAccStride * pm->n, 0.0f, ctx->stream));
-  float* part = nullptr;
-  TRY(loss_and_sums_vol(ctx, pm, d_fields, vol_of(b), dl, &part));
   if (d_grad) {
+    float* part = nullptr;
+    TRY_HIP(ctx, gve::fill_f32(pm->acc, gve::kAccStride * pm->n, 0.0f, ctx->stream));
+    TRY(loss_and_sums_vol(ctx, pm, d_fields, vol_of(b), dl, &part));
     TRY_HIP(ctx, gve::launch_update(0, pm->theta, pm->m, pm->v, pm->acc, part, pm->offset, nullptr,
                                     d_grad, pm->n, pm->t, ctx->opt, nullptr, ctx->stream));
   } else {
-    TRY_HIP(ctx, gve::fill_f32(pm->acc, gve::kAccStride * pm->n, 0.0f, ctx->stream));
+    TRY(loss_and_sums_vol(ctx, pm, d_fields, vol_of(b), dl, nullptr));
   }
   if (h_loss) {
     TRY_HIP(ctx, hipMemcpyAsync(h_loss, dl, sizeof(double) * (size_t)ni, hipMemcpyDeviceToHost,

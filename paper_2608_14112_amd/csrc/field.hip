@@ -876,6 +876,10 @@ __global__ __launch_bounds__(BXY* BXY* W) void k_fused_queue(const Record* __res
     if (w >= nbricks) break;
     fused_brick<BXY, BZ, MODE, W, false>(rec, pair_gid, brick_start, items, nitems, order[w], thr,
                                          field, gacc, n, part, pslot, brick_loss, red, steps, comb);
+    // A loss-only brick ends in a branch on thread 0, as the loop begins with
+    // one.  Without a barrier between them the compiler joins the two, and the
+    // other lanes of the wave go round the loop and its barriers without lane 0.
+    if (MODE == kLoss) __syncthreads();
   }
 }
 

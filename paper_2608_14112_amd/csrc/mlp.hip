@@ -124,7 +124,8 @@ __device__ inline float input_at(const float* __restrict__ X, int cols, int64_t 
 // registers over the workgroup's steps) and row tile w of the last layer; the
 // activations pass between waves through LDS, so only X and Y touch memory.
 // Bound by the exact erf of 256 activations a row (about 40 vector
-// instructions each): the products are 0.04 MFLOP a row.
+// instructions each): the products are 0.04 MFLOP a row.  110,592 rows: 35 us
+// (a kernel per layer with float32 activations in memory: 223 us).
 template <bool STD>
 __global__ __launch_bounds__(256) void k_mlp_infer(const float* __restrict__ X, int64_t n,
                                                    const float* __restrict__ stats,
