@@ -1463,36 +1463,35 @@ gve_status gve_allocate(gve_ctx* ctx, const float* d_field, gve_grid g, int64_t 
   const int64_t nb = (int64_t)gve::alloc_block_count(M);
   const int64_t n_det = (int64_t)std::floor(0.55 * (double)budget + 0.5);
   const int64_t n_cov = budget - n_det;
-  // carve the allocation scratch
+  // scratch of the survey, then (once the candidates are counted) of the rest
   size_t off = 0;
   auto take = [&](size_t bytes) {
     size_t o = off;
     off += (bytes + 255) & ~(size_t)255;
     return o;
   };
-  const size_t o_counts = take(16), o_st = take(48), o_hist = take(256 * 8), o_sb = take(16),
-               o_best = take(4096 * 8), o_dot = take(sizeof(double) * gve::alloc_dot_tmp_doubles()),
-               o_less = take(4 * (nb + 1)), o_tie = take(4 * (nb + 1)), o_toff = take(4 * (nb + 1)),
-               o_take = take(4 * (nb + 1)), o_ooff = take(4 * (nb + 1)), o_det = take(8 * n_det),
-               o_cov = take(8 * n_cov), o_j6 = take(6 * sizeof(double) * (size_t)budget);
+  const size_t o_sel = take(8 * gve::alloc_select_words()), o_sb = take(16),
+               o_best = take(4096 * 8),
+               o_dot = take(sizeof(double) * gve::alloc_dot_tmp_doubles()),
+               o_det = take(8 * n_det), o_cov = take(8 * n_cov),
+               o_j6 = take(6 * sizeof(double) * (size_t)budget);
   TRY(ensure(ctx, ctx->ws.alloc, off));
   TRY(ensure(ctx, ctx->ws.voxf, sizeof(float) * (size_t)M));
-  TRY(ensure(ctx, ctx->ws.scan_tmp, gve::scan_tmp_bytes(nb + 1)));
   char* base = static_cast<char*>(ctx->ws.alloc.ptr);
   auto U64 = [&](size_t o) { return reinterpret_cast<unsigned long long*>(base + o); };
-  auto U32 = [&](size_t o) { return reinterpret_cast<uint32_t*>(base + o); };
   auto I64 = [&](size_t o) { return reinterpret_cast<int64_t*>(base + o); };
   auto F64 = [&](size_t o) { return reinterpret_cast<double*>(base + o); };
   float* g32 = static_cast<float*>(ctx->ws.voxf.ptr);
+  unsigned long long* sel = U64(o_sel);
 
   // S1a: gradient magnitude and domain counts; feasibility (Sec. V-B)
-  TRY_HIP(ctx, gve::fill_u64(U64(o_counts), 2, s));
-  TRY_HIP(ctx, gve::fill_u64(U64(o_hist), 256, s));
-  TRY_HIP(ctx, gve::alloc_grad(d_field, g, g32, U64(o_counts), s));
-  TRY_HIP(ctx, hipMemcpyAsync(ctx->ws.h_pinned, U64(o_counts), 16, hipMemcpyDeviceToHost, s));
+  TRY_HIP(ctx, gve::alloc_survey(d_field, g, seed, n_det, n_cov, g32, sel, s));
+  TRY_HIP(ctx, hipMemcpyAsync(ctx->ws.h_pinned, sel, 64, hipMemcpyDeviceToHost, s));
   TRY_HIP(ctx, hipStreamSynchronize(s));
-  const int64_t n_occ = (int64_t) static_cast<unsigned long long*>(ctx->ws.h_pinned)[0];
-  const int64_t n_el = (int64_t) static_cast<unsigned long long*>(ctx->ws.h_pinned)[1];
+  const unsigned long long* hsel = static_cast<const unsigned long long*>(ctx->ws.h_pinned);
+  const int64_t n_occ = (int64_t)hsel[gve::kSelOccupied];
+  const int64_t n_el = (int64_t)hsel[gve::kSelEligible];
+  const int64_t n_list[2] = {(int64_t)hsel[gve::kSelDet], (int64_t)hsel[gve::kSelCov]};
   gve_alloc_info inf{};
   inf.n_detail = n_det;
   inf.n_coverage = n_cov;
@@ -1506,24 +1505,50 @@ gve_status gve_allocate(gve_ctx* ctx, const float* d_field, gve_grid g, int64_t 
     return fail(ctx, GVE_ERR_BUDGET_INFEASIBLE,
                 "budget needs " + std::to_string(shortfall) + " more distinct seed voxels");
   }
-  // S1b: the two draws and the 99th percentile of |grad V| over V > 0.02
-  unsigned long long* st_det = U64(o_st);
-  unsigned long long* st_cov = st_det + 2;
-  unsigned long long* st_g99 = st_det + 4;
-  const int64_t r99 = (int64_t)std::floor(0.99 * (double)(n_occ - 1));
-  TRY_HIP(ctx, gve::alloc_set_state(st_det, 0ull, (unsigned long long)n_det, s));
-  TRY_HIP(ctx, gve::alloc_set_state(st_cov, 0ull, (unsigned long long)n_cov, s));
-  TRY_HIP(ctx, gve::alloc_set_state(st_g99, 0ull, (unsigned long long)(r99 + 1), s));
+  // S1b: the two draws and the 99th percentile of |grad V| over V > 0.02.  The
+  // lists live in the binning's pair buffers, which the weights' evaluation
+  // below needs only once the seeds are drawn.
+  if (n_list[0] >= (int64_t)0xFFFFFFF0ll || n_list[1] >= (int64_t)0xFFFFFFF0ll)
+    return fail(ctx, GVE_ERR_UNSUPPORTED, "more than 2^32 candidate seeds");
   int64_t* det = I64(o_det);
   int64_t* cov = I64(o_cov);
-  TRY_HIP(ctx, gve::alloc_select(0, d_field, g32, g, seed, st_det, U64(o_hist), U32(o_less),
-                                 U32(o_tie), U32(o_toff), U32(o_take), U32(o_ooff),
-                                 ctx->ws.scan_tmp.ptr, det, s));
-  TRY_HIP(ctx, gve::alloc_select(1, d_field, g32, g, seed, st_cov, U64(o_hist), U32(o_less),
-                                 U32(o_tie), U32(o_toff), U32(o_take), U32(o_ooff),
-                                 ctx->ws.scan_tmp.ptr, cov, s));
-  TRY_HIP(ctx, gve::alloc_select(2, d_field, g32, g, seed, st_g99, U64(o_hist), nullptr, nullptr,
-                                 nullptr, nullptr, nullptr, nullptr, nullptr, s));
+  {
+    const size_t nbw = (size_t)gve::alloc_block_count(M) + 1;
+    size_t lo = 0;
+    auto part = [&](size_t bytes) {
+      size_t o = lo;
+      lo += (bytes + 255) & ~(size_t)255;
+      return o;
+    };
+    size_t om[2], oc[2], oo[2], ok[2], ov[2], ob[2];
+    for (int y = 0; y < 2; ++y) {
+      const size_t ln = (size_t)std::max<int64_t>(n_list[y], 1);
+      om[y] = part(8 * gve::alloc_mask_words(M));
+      oc[y] = part(4 * nbw);
+      oo[y] = part(4 * nbw);
+      ok[y] = part(8 * ln);
+      ov[y] = part(8 * ln);
+      ob[y] = part(5 * 4 * (gve::alloc_block_count((int64_t)ln) + 1));
+    }
+    TRY(ensure(ctx, ctx->ws.keys[0], lo));
+    TRY(ensure(ctx, ctx->ws.scan_tmp,
+               gve::scan_tmp_bytes((int64_t)std::max(nbw, (size_t)gve::alloc_block_count(
+                                                             std::max(n_list[0], n_list[1])) +
+                                                             1))));
+    char* lb = static_cast<char*>(ctx->ws.keys[0].ptr);
+    gve::AllocLists l;
+    for (int y = 0; y < 2; ++y) {
+      l.mask[y] = reinterpret_cast<uint64_t*>(lb + om[y]);
+      l.cnt[y] = reinterpret_cast<uint32_t*>(lb + oc[y]);
+      l.off[y] = reinterpret_cast<uint32_t*>(lb + oo[y]);
+      l.key[y] = reinterpret_cast<uint64_t*>(lb + ok[y]);
+      l.vox[y] = reinterpret_cast<int64_t*>(lb + ov[y]);
+      l.blk[y] = reinterpret_cast<uint32_t*>(lb + ob[y]);
+      l.n[y] = n_list[y];
+    }
+    TRY_HIP(ctx, gve::alloc_draw(d_field, g32, g, seed, sel, l, det, cov, ctx->ws.scan_tmp.ptr, s));
+  }
+  const unsigned long long* st_g99 = sel + gve::kSelG99;
   gve_params* p = nullptr;
   TRY(gve_params_create(ctx, budget, &p));
   auto cleanup = [&](gve_status st) {

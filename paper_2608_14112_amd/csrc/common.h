@@ -313,16 +313,29 @@ hipError_t fill_f32(float* p, int64_t n, float v, hipStream_t s);
 hipError_t fill_u64(unsigned long long* p, int64_t n, hipStream_t s);
 
 // ---- allocation (alloc.hip) --------------------------------------------------
-size_t alloc_block_count(int64_t M);
-hipError_t alloc_grad(const float* f, const gve_grid& g, float* g32, unsigned long long* counts,
-                      hipStream_t s);
-hipError_t alloc_set_state(unsigned long long* st, unsigned long long prefix,
-                           unsigned long long rank, hipStream_t s);
-hipError_t alloc_select(int mode, const float* f, const float* g32, const gve_grid& g,
-                        uint64_t seed, unsigned long long* st, unsigned long long* hist,
-                        uint32_t* less_cnt, uint32_t* tie_cnt, uint32_t* tie_off,
-                        uint32_t* take_cnt, uint32_t* out_off, void* scan_tmp, int64_t* out,
-                        hipStream_t s);
+// Blocks of 4,096 voxels (or list entries), and mask words (u64) of M voxels.
+size_t alloc_block_count(int64_t n);
+size_t alloc_mask_words(int64_t M);
+size_t alloc_select_words();
+// Words of the select block the host reads after alloc_survey: occupied and
+// eligible voxels, candidates of the two draws; kSelG99 holds the percentile's
+// bits after alloc_draw.
+enum { kSelOccupied = 0, kSelEligible = 1, kSelDet = 3, kSelCov = 5, kSelG99 = 6 };
+hipError_t alloc_survey(const float* f, const gve_grid& g, uint64_t seed, int64_t n_det,
+                        int64_t n_cov, float* g32, unsigned long long* w, hipStream_t s);
+// Buffers of the draws, [0] detail and [1] coverage: masks (alloc_mask_words),
+// cnt and off (blocks + 1), key and vox (n entries), blk (5 (blocks of n + 1)).
+struct AllocLists {
+  uint64_t* mask[2];
+  uint32_t *cnt[2], *off[2];
+  uint64_t* key[2];
+  int64_t* vox[2];
+  int64_t n[2];
+  uint32_t* blk[2];
+};
+hipError_t alloc_draw(const float* f, const float* g32, const gve_grid& g, uint64_t seed,
+                      unsigned long long* w, const AllocLists& l, int64_t* det, int64_t* cov,
+                      void* scan_tmp, hipStream_t s);
 hipError_t alloc_jitter(const gve_grid& g, const int64_t* det, const int64_t* cov, int64_t n_det,
                         int64_t n, uint64_t seed, float* theta, hipStream_t s);
 hipError_t alloc_spacing(const float* theta, int64_t n, int64_t first, int64_t ng, double* best,
