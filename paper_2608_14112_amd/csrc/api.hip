@@ -653,7 +653,7 @@ gve_status gve_destroy(gve_ctx* ctx) {
                     &ws.grad_tmp, &ws.alloc, &ws.voxf, &ws.partials, &ws.mlp,
                     &ws.sat, &ws.feat, &ws.theta_base, &ws.items, &ws.order_keys[0],
                     &ws.order_keys[1], &ws.order_vals[0], &ws.order_vals[1], &ws.queue,
-                    &ws.p_cls, &ws.p_pts, &ws.p_acc, &ws.p_coef, &ws.p_keys[0], &ws.p_keys[1],
+                    &ws.p_cls, &ws.p_pts, &ws.p_acc, &ws.p_sorted, &ws.p_hits, &ws.p_keys[0], &ws.p_keys[1],
                     &ws.p_idx[0], &ws.p_idx[1], &ws.p_start, &ws.p_loss, &ws.dense, &ws.snap,
                     &ws.box_off, &ws.owner, &ws.slot_gid};
   static_assert(sizeof(all) / sizeof(all[0]) * sizeof(Scratch) + sizeof(void*) ==
@@ -1609,7 +1609,7 @@ gve_status gve_get_stats(const gve_ctx* ctx, gve_stats* out) {
                                &w.mlp, &w.sat, &w.feat, &w.theta_base, &w.items,
                                &w.order_keys[0], &w.order_keys[1], &w.order_vals[0],
                                &w.order_vals[1], &w.queue, &w.p_cls, &w.p_pts, &w.p_acc,
-                               &w.p_coef, &w.p_keys[0], &w.p_keys[1], &w.p_idx[0], &w.p_idx[1],
+                               &w.p_sorted, &w.p_hits, &w.p_keys[0], &w.p_keys[1], &w.p_idx[0], &w.p_idx[1],
                                &w.p_start, &w.p_loss, &w.dense, &w.snap};
   static_assert(sizeof(all) / sizeof(all[0]) * sizeof(gve::Scratch) + sizeof(void*) ==
                     sizeof(gve::Workspace),
@@ -2366,65 +2366,95 @@ gve_status check_paper(const gve_ctx* ctx, const gve_paper* p) {
   return GVE_OK;
 }
 
-// Bucket np points into the cell grid: sorted point indices and cell ranges.
+// Points in cell order and the cells' ranges.
+struct PBuckets {
+  const float4* p4 = nullptr;
+  const uint32_t* start = nullptr;
+};
+
+// Bucket `batch` sets of np points (consecutive in pts): one launch when a
+// workgroup holds a set, else (batch 1) cell keys, radix sort, ranges, gather.
 gve_status paper_bucket(gve_ctx* ctx, const float* pts, int64_t np, const gve::CellGrid& cg,
-                        const uint32_t** sorted, const uint32_t** start) {
+                        int batch, PBuckets* out) {
   auto& ws = ctx->ws;
+  hipStream_t s = ctx->stream;
   const int64_t ncells = (int64_t)cg.ncx * cg.ncy * cg.ncz;
   if (ncells >= ((int64_t)1 << 31)) return fail(ctx, GVE_ERR_UNSUPPORTED, "too many cells");
+  const size_t sets = (size_t)batch;
+  TRY(ensure(ctx, ws.p_sorted, sizeof(float4) * sets * (size_t)std::max<int64_t>(np, 1)));
+  TRY(ensure(ctx, ws.p_start, sizeof(uint32_t) * sets * (size_t)(ncells + 1)));
+  float4* p4 = static_cast<float4*>(ws.p_sorted.ptr);
+  uint32_t* st = static_cast<uint32_t*>(ws.p_start.ptr);
+  out->p4 = p4;
+  out->start = st;
+  if (gve::paper_bucket_fits(np, ncells)) {
+    TRY_HIP(ctx, gve::paper_bucket(pts, (int)np, cg, bits_for(ncells), batch, p4, st, s));
+    return GVE_OK;
+  }
   const size_t pb = sizeof(uint32_t) * (size_t)std::max<int64_t>(np, 1);
   for (int b = 0; b < 2; ++b) {
     TRY(ensure(ctx, ws.p_keys[b], pb));
     TRY(ensure(ctx, ws.p_idx[b], pb));
   }
-  TRY(ensure(ctx, ws.p_start, sizeof(uint32_t) * (size_t)(ncells + 1)));
   TRY(ensure(ctx, ws.sort_hist, gve::sort_hist_bytes(np)));
   uint32_t* keys[2] = {static_cast<uint32_t*>(ws.p_keys[0].ptr), static_cast<uint32_t*>(ws.p_keys[1].ptr)};
   uint32_t* idx[2] = {static_cast<uint32_t*>(ws.p_idx[0].ptr), static_cast<uint32_t*>(ws.p_idx[1].ptr)};
-  TRY_HIP(ctx, gve::paper_cell_keys(pts, np, cg, keys[0], idx[0], ctx->stream));
+  TRY_HIP(ctx, gve::paper_cell_keys(pts, np, cg, keys[0], idx[0], s));
   int which = 0;
-  TRY_HIP(ctx, gve::radix_sort_pairs(keys, idx, np, bits_for(ncells), ws.sort_hist.ptr, &which,
-                                     ctx->stream));
-  uint32_t* st = static_cast<uint32_t*>(ws.p_start.ptr);
-  TRY_HIP(ctx, gve::launch_ranges(keys[which], np, ncells, st, ctx->stream));
-  *sorted = idx[which];
-  *start = st;
+  TRY_HIP(ctx, gve::radix_sort_pairs(keys, idx, np, bits_for(ncells), ws.sort_hist.ptr, &which, s));
+  TRY_HIP(ctx, gve::launch_ranges(keys[which], np, ncells, st, s));
+  TRY_HIP(ctx, gve::paper_gather(pts, np, idx[which], p4, s));
   return GVE_OK;
 }
 
-// Sums w a G and w G at np points (the first S get the numerator).
-gve_status paper_accumulate(gve_ctx* ctx, const gve_paper* p, const gve::CellGrid& cg, float k,
-                            const float* pts, int64_t np, int64_t S, const uint32_t** sorted,
-                            const uint32_t** start, double** num, double** den) {
-  TRY(paper_bucket(ctx, pts, np, cg, sorted, start));
-  TRY(ensure(ctx, ctx->ws.p_acc, sizeof(double) * 2 * (size_t)std::max<int64_t>(np, 1)));
-  double* acc = static_cast<double*>(ctx->ws.p_acc.ptr);
-  TRY_HIP(ctx, gve::paper_zero(acc, 2 * np, ctx->stream));
-  *num = acc;
-  *den = acc + np;
-  TRY_HIP(ctx, gve::paper_forward(p->theta, p->n, cg, k, S, pts, *sorted, *start, *num, *den,
-                                  ctx->stream));
+// Iterations sampled and bucketed together: their points and cell ranges stay
+// within 64 MB, and at most 32 (a batch's launches are then far cheaper than
+// its iterations).  One when a workgroup cannot hold an iteration's points.
+int paper_batch(int64_t S, const gve::CellGrid& cg, int32_t iters) {
+  const int64_t ncells = (int64_t)cg.ncx * cg.ncy * cg.ncz;
+  if (!gve::paper_bucket_fits(2 * S, ncells)) return 1;
+  const int64_t bytes = S * (28 + 32) + 4 * (ncells + 1);
+  return (int)std::max<int64_t>(1, std::min<int64_t>({32, iters, ((int64_t)64 << 20) / bytes}));
+}
+
+// The two accumulator sets (num, den of np points each) and the hit lists.
+gve_status paper_accumulators(gve_ctx* ctx, int64_t np, int sets, double** acc) {
+  const int64_t n = 2 * std::max<int64_t>(np, 1);
+  TRY(ensure(ctx, ctx->ws.p_acc, sizeof(double) * (size_t)(n * sets)));
+  *acc = static_cast<double*>(ctx->ws.p_acc.ptr);
+  TRY_HIP(ctx, gve::paper_zero(*acc, n * sets, ctx->stream));
   return GVE_OK;
 }
 
-// One objective evaluation at 2S points (samples then partners): losses to
-// loss[0..5], gradient (mode 0) or Adam step (mode 1, step t).
+gve_status paper_hits(gve_ctx* ctx, int64_t n, uint32_t** hits) {
+  TRY(ensure(ctx, ctx->ws.p_hits, sizeof(uint32_t) * (size_t)(1 + gve::kPaperHits) * (size_t)n));
+  *hits = static_cast<uint32_t*>(ctx->ws.p_hits.ptr);
+  return GVE_OK;
+}
+
+// One objective evaluation at 2S bucketed points (samples then partners) with
+// zeroed accumulators acc [4S]: terms added to loss [kPaperSlots][6], gradient
+// (mode 0) or Adam step (mode 1, step t); zeroes `clear` [4S] when given.
 gve_status paper_pass(gve_ctx* ctx, gve_paper* p, const float* d_field, const gve_grid& g,
-                      const gve_paper_options& o, float lam_sm, const float* pts,
-                      const float* vals, int64_t S, int mode, float* d_grad, double* loss) {
+                      const gve_paper_options& o, float lam_sm, const PBuckets& bk,
+                      const float* vals, int64_t S, double* acc, uint32_t* hits, int mode,
+                      float* d_grad, double* loss, double* clear) {
   const gve::CellGrid cg = gve::make_cells(g, o.cell);
-  const uint32_t *sorted = nullptr, *start = nullptr;
-  double *num = nullptr, *den = nullptr;
-  TRY_HIP(ctx, gve::paper_zero(loss, 6, ctx->stream));
-  TRY(paper_accumulate(ctx, p, cg, o.k, pts, 2 * S, S, &sorted, &start, &num, &den));
-  TRY(ensure(ctx, ctx->ws.p_coef, sizeof(float) * 4 * (size_t)S));
-  float* coefA = static_cast<float*>(ctx->ws.p_coef.ptr);
-  float* coefB = coefA + 2 * S;
-  TRY_HIP(ctx, gve::paper_coef(S, o, lam_sm, num, den, vals, coefA, coefB, loss, ctx->stream));
-  TRY_HIP(ctx, gve::paper_backward(p->theta, p->m, p->v, p->n, cg, o, mode, p->t, S, pts, sorted,
-                                   start, coefA, coefB, d_field, g, d_grad, loss + 3,
-                                   ctx->stream));
+  double *num = acc, *den = acc + 2 * S;
+  TRY_HIP(ctx, gve::paper_forward(p->theta, p->n, cg, o.k, S, bk.p4, bk.start, num, den, hits,
+                                  ctx->stream));
+  TRY_HIP(ctx, gve::paper_backward(p->theta, p->m, p->v, p->n, cg, o, lam_sm, mode, p->t, S, bk.p4,
+                                   bk.start, hits, num, den, vals, d_field, g, d_grad, loss, clear,
+                                   clear ? 4 * S : 0, ctx->stream));
   return GVE_OK;
+}
+
+// Six terms from the slots, in slot order.
+void paper_terms(const double* slots, double terms[6]) {
+  for (int a = 0; a < 6; ++a) {
+    terms[a] = 0.0;
+    for (int k = 0; k < gve::kPaperSlots; ++k) terms[a] += slots[6 * k + a];
+  }
 }
 
 double paper_total(const gve_paper_options& o, float lam_sm, const double* parts) {
@@ -2466,10 +2496,10 @@ void paper_class_split(const gve_paper_options& o, uint64_t n_hi_vox, uint64_t n
   *n_mid = n_mid_vox ? (int)std::floor((double)o.frac_mid * S + 0.5) : 0;
 }
 
-gve_status paper_points(gve_ctx* ctx, int64_t S, float** pts, float** vals) {
-  TRY(ensure(ctx, ctx->ws.p_pts, sizeof(float) * 7 * (size_t)S));
+gve_status paper_points(gve_ctx* ctx, int64_t S, int batch, float** pts, float** vals) {
+  TRY(ensure(ctx, ctx->ws.p_pts, sizeof(float) * 7 * (size_t)S * (size_t)batch));
   *pts = static_cast<float*>(ctx->ws.p_pts.ptr);
-  *vals = *pts + 6 * S;
+  *vals = *pts + 6 * S * batch;
   return GVE_OK;
 }
 
@@ -2597,7 +2627,7 @@ gve_status gve_paper_sample(gve_ctx* ctx, const float* d_field, gve_grid g,
   int n_hi, n_mid;
   paper_class_split(*o, nh, nm, &n_hi, &n_mid);
   TRY_HIP(ctx, gve::paper_sample(d_field, g, oh, om, o->samples, n_hi, n_mid, seed, (uint64_t)iter,
-                                 o->v_hi, o->v_occ, d_pts, d_vals, ctx->stream));
+                                 1, o->v_hi, o->v_occ, d_pts, d_vals, ctx->stream));
   return GVE_OK;
 }
 
@@ -2609,10 +2639,14 @@ gve_status gve_paper_eval(gve_ctx* ctx, const gve_paper* p, gve_grid g, const gv
     return fail(ctx, GVE_ERR_INVALID_ARGUMENT, "need points, 1 <= npts < 2^31 and an output");
   TRY(validate_grid(ctx, g));
   TRY(set_device(ctx));
-  const uint32_t *sorted = nullptr, *start = nullptr;
-  double *num = nullptr, *den = nullptr;
-  TRY(paper_accumulate(ctx, p, gve::make_cells(g, o->cell), o->k, d_pts, npts, npts, &sorted,
-                       &start, &num, &den));
+  const gve::CellGrid cg = gve::make_cells(g, o->cell);
+  PBuckets bk;
+  double* num = nullptr;
+  TRY(paper_bucket(ctx, d_pts, npts, cg, 1, &bk));
+  TRY(paper_accumulators(ctx, npts, 1, &num));
+  double* den = num + npts;
+  TRY_HIP(ctx, gve::paper_forward(p->theta, p->n, cg, o->k, npts, bk.p4, bk.start, num, den,
+                                  nullptr, ctx->stream));
   TRY_HIP(ctx, gve::paper_density(num, den, npts, o->rho0, d_vt, d_density, ctx->stream));
   return GVE_OK;
 }
@@ -2627,12 +2661,25 @@ gve_status gve_paper_loss_grad(gve_ctx* ctx, gve_paper* p, const float* d_field,
     return fail(ctx, GVE_ERR_INVALID_ARGUMENT, "field, points, values, gradient and samples required");
   TRY(validate_grid(ctx, g));
   TRY(set_device(ctx));
-  TRY(ensure(ctx, ctx->ws.p_loss, sizeof(double) * 8));
+  constexpr int kTerms = 6 * gve::kPaperSlots;
+  static_assert(kTerms * sizeof(double) <= 512, "pinned staging size");
+  TRY(ensure(ctx, ctx->ws.p_loss, sizeof(double) * kTerms));
   double* loss = static_cast<double*>(ctx->ws.p_loss.ptr);
-  TRY(paper_pass(ctx, p, d_field, g, *o, lam_sm, d_pts, d_vals, samples, 0, d_grad, loss));
-  double* hp = static_cast<double*>(ctx->ws.h_pinned);
-  TRY_HIP(ctx, hipMemcpyAsync(hp, loss, sizeof(double) * 6, hipMemcpyDeviceToHost, ctx->stream));
+  TRY_HIP(ctx, gve::paper_zero(loss, kTerms, ctx->stream));
+  PBuckets bk;
+  double* acc = nullptr;
+  uint32_t* hits = nullptr;
+  TRY(paper_bucket(ctx, d_pts, 2 * samples, gve::make_cells(g, o->cell), 1, &bk));
+  TRY(paper_accumulators(ctx, 2 * samples, 1, &acc));
+  TRY(paper_hits(ctx, p->n, &hits));
+  TRY(paper_pass(ctx, p, d_field, g, *o, lam_sm, bk, d_vals, samples, acc, hits, 0, d_grad, loss,
+                 nullptr));
+  double* slots = static_cast<double*>(ctx->ws.h_pinned);
+  TRY_HIP(ctx, hipMemcpyAsync(slots, loss, sizeof(double) * kTerms, hipMemcpyDeviceToHost,
+                              ctx->stream));
   TRY_HIP(ctx, hipStreamSynchronize(ctx->stream));
+  double hp[6];
+  paper_terms(slots, hp);
   if (h_parts) std::copy(hp, hp + 6, h_parts);
   if (h_loss) *h_loss = paper_total(*o, lam_sm, hp);
   return GVE_OK;
@@ -2654,27 +2701,48 @@ gve_status gve_paper_refine(gve_ctx* ctx, gve_paper* p, const float* d_field, gv
   int n_hi, n_mid;
   paper_class_split(*o, nh, nm, &n_hi, &n_mid);
   const int64_t S = o->samples;
-  TRY(ensure(ctx, ctx->ws.p_loss, sizeof(double) * 6 * (size_t)iters));
+  constexpr int kTerms = 6 * gve::kPaperSlots;
+  TRY(ensure(ctx, ctx->ws.p_loss, sizeof(double) * kTerms * (size_t)iters));
   double* loss = static_cast<double*>(ctx->ws.p_loss.ptr);
+  TRY_HIP(ctx, gve::paper_zero(loss, (int64_t)kTerms * iters, ctx->stream));
+  const gve::CellGrid cg = gve::make_cells(g, o->cell);
+  const int64_t ncells = (int64_t)cg.ncx * cg.ncy * cg.ncz;
+  const int batch = paper_batch(S, cg, iters);
   float *pts = nullptr, *vals = nullptr;
-  TRY(paper_points(ctx, S, &pts, &vals));
+  double* acc = nullptr;
+  uint32_t* hits = nullptr;
+  TRY(paper_points(ctx, S, batch, &pts, &vals));
+  TRY(paper_accumulators(ctx, 2 * S, 2, &acc));
+  TRY(paper_hits(ctx, p->n, &hits));
   std::vector<float> lam((size_t)iters);
+  PBuckets bk;
   for (int32_t i = 0; i < iters; ++i) {
     const int32_t it = first_iter + i;
     const double f = schedule_len > 1 ? (double)std::min(it, schedule_len - 1) / (schedule_len - 1)
                                       : 0.0;
     lam[i] = (float)(o->lam_sm_start + (o->lam_sm_end - o->lam_sm_start) * f);
-    TRY_HIP(ctx, gve::paper_sample(d_field, g, oh, om, (int)S, n_hi, n_mid, seed, (uint64_t)it,
-                                   o->v_hi, o->v_occ, pts, vals, ctx->stream));
+    const int j = i % batch;
+    if (j == 0) {
+      const int nb = std::min(batch, iters - i);
+      TRY_HIP(ctx, gve::paper_sample(d_field, g, oh, om, (int)S, n_hi, n_mid, seed, (uint64_t)it,
+                                     nb, o->v_hi, o->v_occ, pts, vals, ctx->stream));
+      TRY(paper_bucket(ctx, pts, 2 * S, cg, nb, &bk));
+    }
+    const PBuckets bj{bk.p4 + 2 * S * j, bk.start + (ncells + 1) * j};
     p->t += 1;
-    TRY(paper_pass(ctx, p, d_field, g, *o, lam[i], pts, vals, S, 1, nullptr, loss + 6 * i));
+    // the accumulators alternate: the backward pass of one iteration zeroes the
+    // other set for the next
+    TRY(paper_pass(ctx, p, d_field, g, *o, lam[i], bj, vals + S * j, S, acc + 4 * S * (i & 1),
+                   hits, 1, nullptr, loss + (int64_t)kTerms * i, acc + 4 * S * ((i + 1) & 1)));
   }
-  std::vector<double> h((size_t)6 * iters);
+  std::vector<double> h((size_t)kTerms * iters);
   TRY_HIP(ctx, hipMemcpyAsync(h.data(), loss, sizeof(double) * h.size(), hipMemcpyDeviceToHost,
                               ctx->stream));
   TRY_HIP(ctx, hipStreamSynchronize(ctx->stream));
   for (int32_t i = 0; i < iters; ++i) {
-    const double L = paper_total(*o, lam[i], &h[6 * (size_t)i]);
+    double terms[6];
+    paper_terms(&h[(size_t)kTerms * i], terms);
+    const double L = paper_total(*o, lam[i], terms);
     if (h_loss) h_loss[i] = L;
     if (!std::isfinite(L)) return fail(ctx, GVE_ERR_NUMERIC, "objective is not finite");
   }

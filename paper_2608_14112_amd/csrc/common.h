@@ -106,8 +106,9 @@ struct Workspace {
   Scratch order_keys[2], order_vals[2];  // heaviest-first brick order (queue schedule)
   Scratch queue;                 // uint32 work counter of the persistent launch
   // the paper's training loop: class block counts / offsets, sample points,
-  // their float64 accumulators, gradient coefficients, cell sort, losses
-  Scratch p_cls, p_pts, p_acc, p_coef, p_keys[2], p_idx[2], p_start, p_loss;
+  // their float64 accumulators (two sets), points in cell order, cell sort,
+  // losses, the points each primitive reached
+  Scratch p_cls, p_pts, p_acc, p_sorted, p_keys[2], p_idx[2], p_start, p_loss, p_hits;
   Scratch dense;                 // float [M] residual of the dense reference path
   Scratch snap;                  // float [3][11][n] parameters and Adam moments (refinement
                                  // restart point) + counters
@@ -362,26 +363,39 @@ CellGrid make_cells(const gve_grid& g, float h);
 int64_t paper_class_blocks(int64_t M);
 hipError_t paper_class_counts(const float* f, int64_t M, float v_hi, float v_occ, uint32_t* cnt_hi,
                               uint32_t* cnt_mid, hipStream_t s);
+// Points and values of `batch` iterations from `it` on, one iteration's points
+// [2S][3] and values [S] after another's.
 hipError_t paper_sample(const float* f, const gve_grid& g, const uint32_t* off_hi,
                         const uint32_t* off_mid, int S, int n_hi, int n_mid, uint64_t seed,
-                        uint64_t it, float v_hi, float v_occ, float* pts, float* vals,
+                        uint64_t it, int batch, float v_hi, float v_occ, float* pts, float* vals,
+                        hipStream_t s);
+// Points in cell order (x, y, z, index) and the cells' ranges start [ncells + 1]
+// for `batch` iterations of np points each, if a workgroup can hold them.
+bool paper_bucket_fits(int64_t np, int64_t ncells);
+hipError_t paper_bucket(const float* pts, int np, const CellGrid& cg, int bits, int batch,
+                        float4* p4, uint32_t* start, hipStream_t s);
+hipError_t paper_gather(const float* pts, int64_t np, const uint32_t* sorted, float4* p4,
                         hipStream_t s);
 hipError_t paper_cell_keys(const float* pts, int64_t np, const CellGrid& cg, uint32_t* keys,
                            uint32_t* idx, hipStream_t s);
 hipError_t paper_zero(double* p, int64_t n, hipStream_t s);
+// hits (optional): [1 + kPaperHits][n], the number of points each primitive
+// reached and the positions of the first kPaperHits.
+constexpr int kPaperHits = 8;
 hipError_t paper_forward(const float* th, int64_t n, const CellGrid& cg, float k, int64_t S,
-                         const float* pts, const uint32_t* sorted, const uint32_t* start,
-                         double* num, double* den, hipStream_t s);
+                         const float4* p4, const uint32_t* start, double* num, double* den,
+                         uint32_t* hits, hipStream_t s);
 hipError_t paper_density(const double* num, const double* den, int64_t np, float rho0, float* vt,
                          float* dn, hipStream_t s);
-hipError_t paper_coef(int64_t S, const gve_paper_options& o, float lam_sm, const double* num,
-                      const double* den, const float* vals, float* coefA, float* coefB,
-                      double* loss, hipStream_t s);
+// Adds the objective's six terms to loss [kPaperSlots][6] and zeroes
+// clear [nclear].
+constexpr int kPaperSlots = 8;
 hipError_t paper_backward(float* th, float* m, float* v, int64_t n, const CellGrid& cg,
-                          const gve_paper_options& o, int mode, int64_t t, int64_t S,
-                          const float* pts, const uint32_t* sorted, const uint32_t* start,
-                          const float* coefA, const float* coefB, const float* field,
-                          const gve_grid& fg, float* grad_out, double* loss, hipStream_t s);
+                          const gve_paper_options& o, float lam_sm, int mode, int64_t t, int64_t S,
+                          const float4* p4, const uint32_t* start, const uint32_t* hits,
+                          const double* num, const double* den, const float* vals,
+                          const float* field, const gve_grid& fg, float* grad_out, double* loss,
+                          double* clear, int64_t nclear, hipStream_t s);
 
 // ---- warm-start network (mlp.hip) --------------------------------------------
 constexpr int kMlpIn = 16, kMlpHid = 128, kMlpOut = 11;

@@ -15,15 +15,19 @@
 //   k_psample      : one wave per sample: class member j = floor(u n_class)
 //                    found through the block prefix sums and a ballot rank
 //                    inside the block, jitter, partner, trilinear value;
-//   k_pcell_keys   : cell of every point;
+//   k_pbucket      : the points of an iteration in cell order (one workgroup
+//                    per iteration; more points take k_pcell_keys, the radix
+//                    sort and k_pgather);
 //   k_pfwd         : per primitive, sum_i w a G and sum_i w G into the points'
-//                    float64 accumulators (atomics);
-//   k_pcoef        : per sample, Vt, the loss terms, and the coefficients of
+//                    float64 accumulators (atomics), and the points it reached;
+//   k_pbwd         : per primitive, the gradient from those points (no atomics:
+//                    each primitive owns its sums), with the coefficients of
 //                    d(w a G) and d(w G) in dL/dtheta (quotient rule; the
-//                    density floor passes no gradient);
-//   k_pbwd         : per primitive, the gradient from its points (no atomics:
-//                    each primitive owns its sums), the regularisers, and
-//                    either the gradient (test hook) or the Adam step.
+//                    density floor passes no gradient) formed where they are
+//                    used; the regularisers; either the gradient (test hook) or
+//                    the Adam step; and the objective's terms.
+// Sampling and bucketing depend on no parameter, so refinement does them for
+// many iterations at once: an iteration is two launches.
 #include <algorithm>
 #include <cmath>
 
@@ -198,22 +202,27 @@ __device__ inline bool in_class(float x, int cls, float v_hi, float v_occ) {
 struct SampleCfg {
   gve_grid g;
   int64_t M, nblocks;
-  int S, n_hi, n_mid;
+  int S, n_hi, n_mid, batch;
   uint64_t seed, it;
   float v_hi, v_occ;
 };
 
-// One wave per sample.  Points are stored as [2S][3]: sample s at row s, its
-// smoothness partner at row S + s.
+// One wave per sample of `batch` consecutive iterations.  An iteration's points
+// are stored as [2S][3] (sample s at row s, its smoothness partner at row
+// S + s) and its S values follow in `vals`.
 __global__ __launch_bounds__(kThreads) void k_psample(const float* __restrict__ f,
                                                       const uint32_t* __restrict__ off_hi,
                                                       const uint32_t* __restrict__ off_mid,
                                                       SampleCfg c, float* __restrict__ pts,
                                                       float* __restrict__ vals) {
-  const int s = (int)(((int64_t)blockIdx.x * kThreads + threadIdx.x) >> 6);
+  const int64_t wv = ((int64_t)blockIdx.x * kThreads + threadIdx.x) >> 6;
   const int lane = threadIdx.x & 63;
-  if (s >= c.S) return;
-  const uint64_t idx = c.it * (uint64_t)c.S + (uint64_t)s;
+  if (wv >= (int64_t)c.S * c.batch) return;
+  const int s = (int)(wv % c.S);
+  const int64_t bi = wv / c.S;
+  pts += bi * 6 * c.S;
+  vals += bi * c.S;
+  const uint64_t idx = (c.it + (uint64_t)bi) * (uint64_t)c.S + (uint64_t)s;
   const double u = uniform01(c.seed, kStreamPick, idx);
   int64_t vox;
   if (s < c.n_hi + c.n_mid) {
@@ -222,11 +231,16 @@ __global__ __launch_bounds__(kThreads) void k_psample(const float* __restrict__ 
     const uint64_t total = off[c.nblocks];
     uint64_t j = (uint64_t)floor(u * (double)total);
     if (j >= total) j = total - 1;
-    // block b: the last with off[b] <= j
-    int64_t lo = 0, hi = c.nblocks - 1;
-    while (lo < hi) {
-      const int64_t mid = (lo + hi + 1) >> 1;
-      if ((uint64_t)off[mid] <= j) lo = mid; else hi = mid - 1;
+    // block b: the last with off[b] <= j (off[lo] <= j throughout), the range
+    // cut to a 64th by one probe per lane
+    int64_t lo = 0, len = c.nblocks;
+    while (len > 1) {
+      const int64_t step = (len + 63) / 64, p = lane * step;
+      const uint64_t le =
+          __builtin_amdgcn_ballot_w64(p < len && (uint64_t)off[lo + p] <= j);
+      const int64_t last = 63 - __builtin_clzll(le);
+      lo += last * step;
+      len = min(step, len - last * step);
     }
     const uint32_t r = (uint32_t)(j - off[lo]);
     // rank inside the block: lane L holds voxels 4L .. 4L+3 (ascending)
@@ -294,6 +308,135 @@ __global__ __launch_bounds__(kThreads) void k_pcell_keys(const float* __restrict
   idx[j] = (uint32_t)j;
 }
 
+// Points in cell order as (x, y, z, index): what the primitives' passes read.
+__global__ __launch_bounds__(kThreads) void k_pgather(const float* __restrict__ pts, int64_t np,
+                                                      const uint32_t* __restrict__ sorted,
+                                                      float4* __restrict__ p4) {
+  const int64_t j = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+  if (j >= np) return;
+  const uint32_t i = sorted[j];
+  p4[j] = make_float4(pts[3 * (size_t)i], pts[3 * (size_t)i + 1], pts[3 * (size_t)i + 2],
+                      __uint_as_float(i));
+}
+
+// The same for one iteration's points in one workgroup: a stable radix sort of
+// the cell keys in LDS (8 bits a pass; a wave ranks its own PER * 64 items in
+// index order by ballots, so the rounds need no barrier), the points written in
+// cell order and the cells' ranges found by binary search.  A dozen short
+// launches otherwise; here the launch covers a whole batch of iterations, one
+// workgroup each.
+constexpr int kBucketThreads = 1024;
+constexpr int kBucketWaves = kBucketThreads / 64;
+template <int PER>
+__global__ __launch_bounds__(kBucketThreads) void k_pbucket(const float* __restrict__ pts, int np,
+                                                            CellGrid cg, int bits,
+                                                            float4* __restrict__ p4,
+                                                            uint32_t* __restrict__ start) {
+  constexpr int kCap = PER * kBucketThreads;
+  __shared__ uint32_t keys[kCap];
+  __shared__ uint16_t ids[kCap];
+  __shared__ uint32_t cnt[kBucketWaves][256];
+  __shared__ uint32_t wsum[4];
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  const int ncells = cg.ncx * cg.ncy * cg.ncz;
+  pts += (size_t)blockIdx.x * 3 * np;
+  p4 += (size_t)blockIdx.x * np;
+  start += (size_t)blockIdx.x * (ncells + 1);
+  uint32_t key[PER];
+  uint32_t id[PER];
+#pragma unroll
+  for (int r = 0; r < PER; ++r) {
+    const int i = (wave * PER + r) * 64 + lane;
+    id[r] = (uint32_t)i;
+    key[r] = 0xFFFFFFFFu;  // past the points: after every cell
+    if (i < np) {
+      const int cx = cell_coord(pts[3 * i + 0], cg.x0, cg.h, cg.ncx);
+      const int cy = cell_coord(pts[3 * i + 1], cg.y0, cg.h, cg.ncy);
+      const int cz = cell_coord(pts[3 * i + 2], cg.z0, cg.h, cg.ncz);
+      key[r] = (uint32_t)(cx + cg.ncx * (cy + cg.ncy * cz));
+    }
+  }
+  for (int shift = 0; shift < bits; shift += 8) {
+    if (shift > 0) {
+#pragma unroll
+      for (int r = 0; r < PER; ++r) {
+        const int i = (wave * PER + r) * 64 + lane;
+        key[r] = keys[i];
+        id[r] = ids[i];
+      }
+    }
+    volatile uint32_t* mine = cnt[wave];
+    for (int d = lane; d < 256; d += 64) mine[d] = 0;
+    uint32_t rank[PER];
+#pragma unroll
+    for (int r = 0; r < PER; ++r) {
+      const uint32_t d = (key[r] >> shift) & 255u;
+      uint64_t same = ~0ull;
+#pragma unroll
+      for (int bit = 0; bit < 8; ++bit) {
+        const bool on = (d >> bit) & 1u;
+        const uint64_t b = __builtin_amdgcn_ballot_w64(on);
+        same &= on ? b : ~b;
+      }
+      // a wave's LDS operations complete in order: every lane reads the count
+      // before the group's first lane raises it
+      const uint32_t base = mine[d];
+      const uint32_t below = (uint32_t)__popcll(same & ((1ull << lane) - 1ull));
+      rank[r] = base + below;
+      if (below == 0) mine[d] = base + (uint32_t)__popcll(same);
+    }
+    __syncthreads();
+    // digit bases (threads 0 .. 255, one digit each) and each wave's start
+    uint32_t total = 0;
+    if (t < 256)
+      for (int w = 0; w < kBucketWaves; ++w) total += cnt[w][t];
+    uint32_t inc = total;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const uint32_t y = __shfl_up(inc, d, 64);
+      if (lane >= d) inc += y;
+    }
+    if (t < 256 && lane == 63) wsum[wave] = inc;
+    __syncthreads();
+    if (t < 256) {
+      uint32_t run = inc - total;
+      for (int w = 0; w < wave; ++w) run += wsum[w];
+      for (int w = 0; w < kBucketWaves; ++w) {
+        const uint32_t c = cnt[w][t];
+        cnt[w][t] = run;
+        run += c;
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < PER; ++r) {
+      const uint32_t pos = cnt[wave][(key[r] >> shift) & 255u] + rank[r];
+      keys[pos] = key[r];
+      ids[pos] = (uint16_t)id[r];
+    }
+    __syncthreads();
+  }
+  if (bits <= 0) {  // one cell
+    for (int j = t; j < np; j += kBucketThreads) {
+      keys[j] = 0u;
+      ids[j] = (uint16_t)j;
+    }
+    __syncthreads();
+  }
+  for (int j = t; j < np; j += kBucketThreads) {
+    const int i = ids[j];
+    p4[j] = make_float4(pts[3 * i], pts[3 * i + 1], pts[3 * i + 2], __uint_as_float((uint32_t)i));
+  }
+  for (int c = t; c <= ncells; c += kBucketThreads) {
+    int lo = 0, hi = np;
+    while (lo < hi) {
+      const int mid = (lo + hi) >> 1;
+      if (keys[mid] < (uint32_t)c) lo = mid + 1; else hi = mid;
+    }
+    start[c] = (uint32_t)lo;
+  }
+}
+
 // ---- forward / backward over the cells a primitive's box overlaps -------------------
 
 struct PairCfg {
@@ -302,9 +445,12 @@ struct PairCfg {
   int64_t S;  // points [0, S) are samples (get the numerator), [S, np) partners
 };
 
+// fn(j, point, d, G) for every point (position j in cell order) inside the
+// support.  The cells of one row (fixed y and z) are consecutive, so a row is
+// one range of points: two range reads and its points, instead of two reads
+// per cell and an index to chase per point.
 template <typename F>
-__device__ inline void for_points(const PGeom& g, const PairCfg& c, const float* __restrict__ pts,
-                                  const uint32_t* __restrict__ sorted,
+__device__ inline void for_points(const PGeom& g, const PairCfg& c, const float4* __restrict__ p4,
                                   const uint32_t* __restrict__ start, F&& fn) {
   const int x0 = cell_coord(g.mu[0] - g.half[0], c.cg.x0, c.cg.h, c.cg.ncx);
   const int x1 = cell_coord(g.mu[0] + g.half[0], c.cg.x0, c.cg.h, c.cg.ncx);
@@ -313,122 +459,155 @@ __device__ inline void for_points(const PGeom& g, const PairCfg& c, const float*
   const int z0 = cell_coord(g.mu[2] - g.half[2], c.cg.z0, c.cg.h, c.cg.ncz);
   const int z1 = cell_coord(g.mu[2] + g.half[2], c.cg.z0, c.cg.h, c.cg.ncz);
   for (int cz = z0; cz <= z1; ++cz)
-    for (int cy = y0; cy <= y1; ++cy)
-      for (int cx = x0; cx <= x1; ++cx) {
-        const uint32_t cell = (uint32_t)(cx + c.cg.ncx * (cy + c.cg.ncy * cz));
-        const uint32_t e = start[cell + 1];
-        for (uint32_t j = start[cell]; j < e; ++j) {
-          const uint32_t pi = sorted[j];
-          const float dx = pts[3 * pi + 0] - g.mu[0];
-          const float dy = pts[3 * pi + 1] - g.mu[1];
-          const float dz = pts[3 * pi + 2] - g.mu[2];
-          const float m2 = mahal2(g, dx, dy, dz);
-          if (m2 < c.k2) fn(pi, dx, dy, dz, expf(-0.5f * m2));
-        }
+    for (int cy = y0; cy <= y1; ++cy) {
+      const uint32_t row = (uint32_t)(c.cg.ncx * (cy + c.cg.ncy * cz));
+      const uint32_t e = start[row + x1 + 1];
+      for (uint32_t j = start[row + x0]; j < e; ++j) {
+        const float4 q = p4[j];
+        const float dx = q.x - g.mu[0];
+        const float dy = q.y - g.mu[1];
+        const float dz = q.z - g.mu[2];
+        const float m2 = mahal2(g, dx, dy, dz);
+        if (m2 < c.k2) fn(j, __float_as_uint(q.w), dx, dy, dz, expf(-0.5f * m2));
       }
+    }
 }
+
+// Points a primitive reached, kept for the backward pass: their number, and the
+// positions of the first kHits ([kHits][n]).  A primitive with more searches
+// again.
+constexpr int kHits = kPaperHits;
 
 __global__ __launch_bounds__(kThreads) void k_pfwd(const float* __restrict__ th, int64_t n,
                                                    PairCfg c, float k,
-                                                   const float* __restrict__ pts,
-                                                   const uint32_t* __restrict__ sorted,
+                                                   const float4* __restrict__ p4,
                                                    const uint32_t* __restrict__ start,
                                                    double* __restrict__ num,
-                                                   double* __restrict__ den) {
+                                                   double* __restrict__ den,
+                                                   uint32_t* __restrict__ hits) {
   const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
   if (i >= n) return;
   const PGeom g = pgeom(th, n, i, k);
-  for_points(g, c, pts, sorted, start, [&](uint32_t pi, float, float, float, float G) {
+  uint32_t nh = 0;
+  for_points(g, c, p4, start, [&](uint32_t j, uint32_t pi, float, float, float, float G) {
     const float wg = g.w * G;
     atomicAdd(&den[pi], (double)wg);
     if ((int64_t)pi < c.S) atomicAdd(&num[pi], (double)(wg * g.a));
+    if (hits && nh < (uint32_t)kHits) hits[n + nh * n + i] = j;
+    ++nh;
   });
+  if (hits) hits[i] = nh;
 }
 
 struct CoefCfg {
   int64_t S;
   double rho0, lam_rho, lam_sm, v_occ;
+  const double *num, *den;
+  const float* vals;
 };
 
-// coefA: coefficient of d(w a G) (samples only); coefB: of d(w G).
-// loss[0..2] += L_val, L_rho, L_sm.
-__global__ __launch_bounds__(kThreads) void k_pcoef(CoefCfg c, const double* __restrict__ num,
-                                                    const double* __restrict__ den,
-                                                    const float* __restrict__ vals,
-                                                    float* __restrict__ coefA,
-                                                    float* __restrict__ coefB,
-                                                    double* __restrict__ loss,
-                                                    float* __restrict__ vt_out) {
-  const int64_t s = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-  double lv = 0.0, lr = 0.0, ls = 0.0;
-  if (s < c.S) {
-    const double d1 = den[s], d2 = den[c.S + s];
-    const double D = fmax(d1, c.rho0);
-    const double vt = num[s] / D;
-    const double val = (double)vals[s];
-    const bool occ = val > c.v_occ;
-    const double u = occ ? 2.0 * (vt - val) : 0.0;
-    const double v = (occ ? 2.0 * c.lam_rho * (d1 - 1.0) : 0.0) + 2.0 * c.lam_sm * (d1 - d2);
-    coefA[s] = (float)(u / D);
-    coefB[s] = (float)(v - (d1 > c.rho0 ? u * vt / D : 0.0));
-    coefA[c.S + s] = 0.0f;
-    coefB[c.S + s] = (float)(-2.0 * c.lam_sm * (d1 - d2));
-    if (occ) {
-      lv = (vt - val) * (vt - val);
-      lr = (d1 - 1.0) * (d1 - 1.0);
-    }
-    ls = (d1 - d2) * (d1 - d2);
-    if (vt_out) vt_out[s] = (float)vt;
+// Coefficients of d(w a G) (samples only) and of d(w G) at point pi.
+__device__ inline void coef_at(const CoefCfg& c, int64_t pi, float& cA, float& cB) {
+  const int64_t s = pi < c.S ? pi : pi - c.S;
+  const double d1 = c.den[s], d2 = c.den[c.S + s];
+  if (pi >= c.S) {
+    cA = 0.0f;
+    cB = (float)(-2.0 * c.lam_sm * (d1 - d2));
+    return;
   }
-  block_add3(lv, lr, ls, loss);
+  const double D = fmax(d1, c.rho0);
+  const double vt = c.num[s] / D;
+  const double val = (double)c.vals[s];
+  const bool occ = val > c.v_occ;
+  const double u = occ ? 2.0 * (vt - val) : 0.0;
+  const double v = (occ ? 2.0 * c.lam_rho * (d1 - 1.0) : 0.0) + 2.0 * c.lam_sm * (d1 - d2);
+  cA = (float)(u / D);
+  cB = (float)(v - (d1 > c.rho0 ? u * vt / D : 0.0));
 }
 
 struct BwdCfg {
   float k, lam_anc, lam_aniso, lam_cap, log_aniso, ell_lo, ell_hi;
   float lr, b1, b2, eps, inv_bc1, inv_bc2;
-  int mode;  // 0: write the gradient; 1: Adam step
+  int mode;        // 0: write the gradient; 1: Adam step
+  double* clear;   // the accumulators of the next iteration, zeroed here
+  int64_t nclear;
 };
 
+// Gradient, regularisers and step of every primitive; the objective's terms
+// into loss[slot][6] (slot = block mod kPaperSlots, so that the blocks' atomics
+// do not queue on one address).  Bound by the parameters and moments it reads
+// and writes (288 bytes a primitive) and by the latency of the eight volume
+// reads of the anchor.
 __global__ __launch_bounds__(kThreads) void k_pbwd(float* __restrict__ th, float* __restrict__ m,
                                                    float* __restrict__ v, int64_t n, PairCfg c,
-                                                   BwdCfg b, const float* __restrict__ pts,
-                                                   const uint32_t* __restrict__ sorted,
+                                                   BwdCfg b, CoefCfg cc,
+                                                   const float4* __restrict__ p4,
                                                    const uint32_t* __restrict__ start,
-                                                   const float* __restrict__ coefA,
-                                                   const float* __restrict__ coefB,
+                                                   const uint32_t* __restrict__ hits,
                                                    const float* __restrict__ field, gve_grid fg,
                                                    float* __restrict__ grad_out,
                                                    double* __restrict__ loss) {
   const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+  loss += (blockIdx.x % kPaperSlots) * 6;
+  // the next iteration's accumulators, and the samples' own terms
+  const int64_t stride = (int64_t)gridDim.x * kThreads;
+  for (int64_t j = i; j < b.nclear; j += stride) b.clear[j] = 0.0;
+  double lv = 0.0, lr = 0.0, ls = 0.0;
+  for (int64_t s = i; s < cc.S; s += stride) {
+    const double d1 = cc.den[s], d2 = cc.den[cc.S + s];
+    const double vt = cc.num[s] / fmax(d1, cc.rho0);
+    const double val = (double)cc.vals[s];
+    if (val > cc.v_occ) {
+      lv += (vt - val) * (vt - val);
+      lr += (d1 - 1.0) * (d1 - 1.0);
+    }
+    ls += (d1 - d2) * (d1 - d2);
+  }
   double la = 0.0, lan = 0.0, lc = 0.0;
   if (i < n) {
-    const PGeom g = pgeom(th, n, i, b.k);
-    float sgd[3] = {0.f, 0.f, 0.f}, D[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    float dA = 0.f, dB = 0.f;
-    for_points(g, c, pts, sorted, start, [&](uint32_t pi, float dx, float dy, float dz, float G) {
-      const float cA = coefA[pi], cB = coefB[pi];
-      const float e = fmaf(cA, g.a, cB);  // coefficient of d(w G)
-      const float gc = e * g.w * G;
-      sgd[0] = fmaf(gc, dx, sgd[0]);
-      sgd[1] = fmaf(gc, dy, sgd[1]);
-      sgd[2] = fmaf(gc, dz, sgd[2]);
-      D[0] = fmaf(gc * dx, dx, D[0]);
-      D[1] = fmaf(gc * dx, dy, D[1]);
-      D[2] = fmaf(gc * dx, dz, D[2]);
-      D[3] = fmaf(gc * dy, dy, D[3]);
-      D[4] = fmaf(gc * dy, dz, D[4]);
-      D[5] = fmaf(gc * dz, dz, D[5]);
-      dA = fmaf(cA * g.w, G, dA);
-      dB = fmaf(e, G, dB);
-    });
     float t[12], gr[12];
 #pragma unroll
     for (int a = 0; a < 12; ++a) t[a] = th[a * n + i];
+    const double aref = trilinear(field, fg, (double)t[0], (double)t[1], (double)t[2]);
+    float sgd[3] = {0.f, 0.f, 0.f}, D[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    float dA = 0.f, dB = 0.f;
+    const float w = 1.0f / (1.0f + expf(-t[11]));
+    const uint32_t nh = hits[i];
+    if (nh > 0) {
+      const PGeom g = pgeom(th, n, i, b.k);
+      auto add = [&](uint32_t, uint32_t pi, float dx, float dy, float dz, float G) {
+        float cA, cB;
+        coef_at(cc, (int64_t)pi, cA, cB);
+        const float e = fmaf(cA, g.a, cB);  // coefficient of d(w G)
+        const float gc = e * g.w * G;
+        sgd[0] = fmaf(gc, dx, sgd[0]);
+        sgd[1] = fmaf(gc, dy, sgd[1]);
+        sgd[2] = fmaf(gc, dz, sgd[2]);
+        D[0] = fmaf(gc * dx, dx, D[0]);
+        D[1] = fmaf(gc * dx, dy, D[1]);
+        D[2] = fmaf(gc * dx, dz, D[2]);
+        D[3] = fmaf(gc * dy, dy, D[3]);
+        D[4] = fmaf(gc * dy, dz, D[4]);
+        D[5] = fmaf(gc * dz, dz, D[5]);
+        dA = fmaf(cA * g.w, G, dA);
+        dB = fmaf(e, G, dB);
+      };
+      if (nh <= (uint32_t)kHits) {
+        for (uint32_t h = 0; h < nh; ++h) {
+          const float4 q = p4[hits[n + h * n + i]];
+          const float dx = q.x - g.mu[0];
+          const float dy = q.y - g.mu[1];
+          const float dz = q.z - g.mu[2];
+          add(0u, __float_as_uint(q.w), dx, dy, dz, expf(-0.5f * mahal2(g, dx, dy, dz)));
+        }
+      } else {
+        for_points(g, c, p4, start, add);
+      }
+    }
     geometry_grad(&t[3], &t[7], sgd, D, gr);
     gr[10] = dA;
-    gr[11] = dB * g.w * (1.0f - g.w);
+    gr[11] = dB * w * (1.0f - w);
     // regularisers
-    const double aref = trilinear(field, fg, (double)t[0], (double)t[1], (double)t[2]);
     const double da = (double)t[10] - aref;
     gr[10] += (float)(2.0 * b.lam_anc * da);
     la = da * da;
@@ -471,7 +650,9 @@ __global__ __launch_bounds__(kThreads) void k_pbwd(float* __restrict__ th, float
       }
     }
   }
-  block_add3(la, lan, lc, loss);
+  block_add3(lv, lr, ls, loss);
+  __syncthreads();
+  block_add3(la, lan, lc, loss + 3);
 }
 
 __global__ __launch_bounds__(kThreads) void k_pfill_d(double* __restrict__ p, int64_t n) {
@@ -520,7 +701,7 @@ hipError_t paper_class_counts(const float* f, int64_t M, float v_hi, float v_occ
 
 hipError_t paper_sample(const float* f, const gve_grid& g, const uint32_t* off_hi,
                         const uint32_t* off_mid, int S, int n_hi, int n_mid, uint64_t seed,
-                        uint64_t it, float v_hi, float v_occ, float* pts, float* vals,
+                        uint64_t it, int batch, float v_hi, float v_occ, float* pts, float* vals,
                         hipStream_t s) {
   SampleCfg c;
   c.g = g;
@@ -529,12 +710,35 @@ hipError_t paper_sample(const float* f, const gve_grid& g, const uint32_t* off_h
   c.S = S;
   c.n_hi = n_hi;
   c.n_mid = n_mid;
+  c.batch = batch;
   c.seed = seed;
   c.it = it;
   c.v_hi = v_hi;
   c.v_occ = v_occ;
-  hipLaunchKernelGGL(k_psample, dim3(blocks_for((int64_t)S * 64)), dim3(kThreads), 0, s, f, off_hi,
-                     off_mid, c, pts, vals);
+  hipLaunchKernelGGL(k_psample, dim3(blocks_for((int64_t)S * 64 * batch)), dim3(kThreads), 0, s, f,
+                     off_hi, off_mid, c, pts, vals);
+  return hipGetLastError();
+}
+
+// A workgroup's LDS holds 16,384 points (114 KB); the positions are 16 bits.
+bool paper_bucket_fits(int64_t np, int64_t ncells) {
+  return np <= 16 * kBucketThreads && ncells < ((int64_t)1 << 24);
+}
+
+hipError_t paper_bucket(const float* pts, int np, const CellGrid& cg, int bits, int batch,
+                        float4* p4, uint32_t* start, hipStream_t s) {
+  if (np <= 8 * kBucketThreads)
+    hipLaunchKernelGGL((k_pbucket<8>), dim3((unsigned)batch), dim3(kBucketThreads), 0, s, pts, np,
+                       cg, bits, p4, start);
+  else
+    hipLaunchKernelGGL((k_pbucket<16>), dim3((unsigned)batch), dim3(kBucketThreads), 0, s, pts, np,
+                       cg, bits, p4, start);
+  return hipGetLastError();
+}
+
+hipError_t paper_gather(const float* pts, int64_t np, const uint32_t* sorted, float4* p4,
+                        hipStream_t s) {
+  hipLaunchKernelGGL(k_pgather, dim3(blocks_for(np)), dim3(kThreads), 0, s, pts, np, sorted, p4);
   return hipGetLastError();
 }
 
@@ -553,14 +757,14 @@ hipError_t paper_zero(double* p, int64_t n, hipStream_t s) {
 }
 
 hipError_t paper_forward(const float* th, int64_t n, const CellGrid& cg, float k, int64_t S,
-                         const float* pts, const uint32_t* sorted, const uint32_t* start,
-                         double* num, double* den, hipStream_t s) {
+                         const float4* p4, const uint32_t* start, double* num, double* den,
+                         uint32_t* hits, hipStream_t s) {
   PairCfg c;
   c.cg = cg;
   c.k2 = k * k;
   c.S = S;
-  hipLaunchKernelGGL(k_pfwd, dim3(blocks_for(n)), dim3(kThreads), 0, s, th, n, c, k, pts, sorted,
-                     start, num, den);
+  hipLaunchKernelGGL(k_pfwd, dim3(blocks_for(n)), dim3(kThreads), 0, s, th, n, c, k, p4, start, num,
+                     den, hits);
   return hipGetLastError();
 }
 
@@ -571,30 +775,28 @@ hipError_t paper_density(const double* num, const double* den, int64_t np, float
   return hipGetLastError();
 }
 
-hipError_t paper_coef(int64_t S, const gve_paper_options& o, float lam_sm, const double* num,
-                      const double* den, const float* vals, float* coefA, float* coefB,
-                      double* loss, hipStream_t s) {
-  CoefCfg c;
-  c.S = S;
-  c.rho0 = o.rho0;
-  c.lam_rho = o.lam_rho;
-  c.lam_sm = lam_sm;
-  c.v_occ = o.v_occ;
-  hipLaunchKernelGGL(k_pcoef, dim3(blocks_for(S)), dim3(kThreads), 0, s, c, num, den, vals, coefA,
-                     coefB, loss, (float*)nullptr);
-  return hipGetLastError();
-}
-
 hipError_t paper_backward(float* th, float* m, float* v, int64_t n, const CellGrid& cg,
-                          const gve_paper_options& o, int mode, int64_t t, int64_t S,
-                          const float* pts, const uint32_t* sorted, const uint32_t* start,
-                          const float* coefA, const float* coefB, const float* field,
-                          const gve_grid& fg, float* grad_out, double* loss, hipStream_t s) {
+                          const gve_paper_options& o, float lam_sm, int mode, int64_t t, int64_t S,
+                          const float4* p4, const uint32_t* start, const uint32_t* hits,
+                          const double* num, const double* den, const float* vals,
+                          const float* field, const gve_grid& fg, float* grad_out, double* loss,
+                          double* clear, int64_t nclear, hipStream_t s) {
   PairCfg c;
   c.cg = cg;
   c.k2 = o.k * o.k;
   c.S = S;
+  CoefCfg cc;
+  cc.S = S;
+  cc.rho0 = o.rho0;
+  cc.lam_rho = o.lam_rho;
+  cc.lam_sm = lam_sm;
+  cc.v_occ = o.v_occ;
+  cc.num = num;
+  cc.den = den;
+  cc.vals = vals;
   BwdCfg b;
+  b.clear = clear;
+  b.nclear = nclear;
   b.k = o.k;
   b.lam_anc = o.lam_anc;
   b.lam_aniso = o.lam_aniso;
@@ -610,8 +812,8 @@ hipError_t paper_backward(float* th, float* m, float* v, int64_t n, const CellGr
   b.inv_bc1 = (float)(1.0 / (1.0 - std::pow((double)o.beta1, tt)));
   b.inv_bc2 = (float)(1.0 / (1.0 - std::pow((double)o.beta2, tt)));
   b.mode = mode;
-  hipLaunchKernelGGL(k_pbwd, dim3(blocks_for(n)), dim3(kThreads), 0, s, th, m, v, n, c, b, pts,
-                     sorted, start, coefA, coefB, field, fg, grad_out, loss);
+  hipLaunchKernelGGL(k_pbwd, dim3(blocks_for(n)), dim3(kThreads), 0, s, th, m, v, n, c, b, cc, p4,
+                     start, hits, field, fg, grad_out, loss);
   return hipGetLastError();
 }
 
