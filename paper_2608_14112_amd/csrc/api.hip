@@ -653,7 +653,8 @@ gve_status gve_destroy(gve_ctx* ctx) {
                     &ws.grad_tmp, &ws.alloc, &ws.voxf, &ws.partials, &ws.mlp,
                     &ws.sat, &ws.feat, &ws.theta_base, &ws.items, &ws.order_keys[0],
                     &ws.order_keys[1], &ws.order_vals[0], &ws.order_vals[1], &ws.queue,
-                    &ws.p_cls, &ws.p_pts, &ws.p_acc, &ws.p_sorted, &ws.p_hits, &ws.p_keys[0], &ws.p_keys[1],
+                    &ws.p_cls, &ws.p_pts, &ws.p_acc, &ws.p_sorted, &ws.p_hits, &ws.p_coef,
+                    &ws.p_corner, &ws.p_keys[0], &ws.p_keys[1],
                     &ws.p_idx[0], &ws.p_idx[1], &ws.p_start, &ws.p_loss, &ws.dense, &ws.snap,
                     &ws.box_off, &ws.owner, &ws.slot_gid};
   static_assert(sizeof(all) / sizeof(all[0]) * sizeof(Scratch) + sizeof(void*) ==
@@ -1609,7 +1610,7 @@ gve_status gve_get_stats(const gve_ctx* ctx, gve_stats* out) {
                                &w.mlp, &w.sat, &w.feat, &w.theta_base, &w.items,
                                &w.order_keys[0], &w.order_keys[1], &w.order_vals[0],
                                &w.order_vals[1], &w.queue, &w.p_cls, &w.p_pts, &w.p_acc,
-                               &w.p_sorted, &w.p_hits, &w.p_keys[0], &w.p_keys[1], &w.p_idx[0], &w.p_idx[1],
+                               &w.p_sorted, &w.p_hits, &w.p_coef, &w.p_corner, &w.p_keys[0], &w.p_keys[1], &w.p_idx[0], &w.p_idx[1],
                                &w.p_start, &w.p_loss, &w.dense, &w.snap};
   static_assert(sizeof(all) / sizeof(all[0]) * sizeof(gve::Scratch) + sizeof(void*) ==
                     sizeof(gve::Workspace),
@@ -2417,35 +2418,38 @@ int paper_batch(int64_t S, const gve::CellGrid& cg, int32_t iters) {
   return (int)std::max<int64_t>(1, std::min<int64_t>({32, iters, ((int64_t)64 << 20) / bytes}));
 }
 
-// The two accumulator sets (num, den of np points each) and the hit lists.
-gve_status paper_accumulators(gve_ctx* ctx, int64_t np, int sets, double** acc) {
+// Zeroed accumulators (num, then den, of np points).
+gve_status paper_accumulators(gve_ctx* ctx, int64_t np, double** acc) {
   const int64_t n = 2 * std::max<int64_t>(np, 1);
-  TRY(ensure(ctx, ctx->ws.p_acc, sizeof(double) * (size_t)(n * sets)));
+  TRY(ensure(ctx, ctx->ws.p_acc, sizeof(double) * (size_t)n));
   *acc = static_cast<double*>(ctx->ws.p_acc.ptr);
-  TRY_HIP(ctx, gve::paper_zero(*acc, n * sets, ctx->stream));
+  TRY_HIP(ctx, gve::paper_zero(*acc, n, ctx->stream));
   return GVE_OK;
 }
 
 gve_status paper_hits(gve_ctx* ctx, int64_t n, uint32_t** hits) {
-  TRY(ensure(ctx, ctx->ws.p_hits, sizeof(uint32_t) * (size_t)(1 + gve::kPaperHits) * (size_t)n));
+  TRY(ensure(ctx, ctx->ws.p_hits, sizeof(uint32_t) * gve::paper_hit_words(n)));
   *hits = static_cast<uint32_t*>(ctx->ws.p_hits.ptr);
   return GVE_OK;
 }
 
 // One objective evaluation at 2S bucketed points (samples then partners) with
-// zeroed accumulators acc [4S]: terms added to loss [kPaperSlots][6], gradient
-// (mode 0) or Adam step (mode 1, step t); zeroes `clear` [4S] when given.
+// zeroed accumulators acc [4S], which are zero again afterwards: terms added to
+// loss [kPaperSlots][6], gradient (mode 0) or Adam step (mode 1, step t).
 gve_status paper_pass(gve_ctx* ctx, gve_paper* p, const float* d_field, const gve_grid& g,
                       const gve_paper_options& o, float lam_sm, const PBuckets& bk,
-                      const float* vals, int64_t S, double* acc, uint32_t* hits, int mode,
-                      float* d_grad, double* loss, double* clear) {
+                      const float* vals, int64_t S, double* acc, uint32_t* hits, float* corner,
+                      int mode, float* d_grad, double* loss) {
   const gve::CellGrid cg = gve::make_cells(g, o.cell);
   double *num = acc, *den = acc + 2 * S;
+  TRY(ensure(ctx, ctx->ws.p_coef, sizeof(float2) * 2 * (size_t)S));
+  float2* coef = static_cast<float2*>(ctx->ws.p_coef.ptr);
   TRY_HIP(ctx, gve::paper_forward(p->theta, p->n, cg, o.k, S, bk.p4, bk.start, num, den, hits,
                                   ctx->stream));
-  TRY_HIP(ctx, gve::paper_backward(p->theta, p->m, p->v, p->n, cg, o, lam_sm, mode, p->t, S, bk.p4,
-                                   bk.start, hits, num, den, vals, d_field, g, d_grad, loss, clear,
-                                   clear ? 4 * S : 0, ctx->stream));
+  TRY_HIP(ctx, gve::paper_coef(S, o, lam_sm, bk.p4, num, den, vals, coef, loss, ctx->stream));
+  TRY_HIP(ctx, gve::paper_backward(p->theta, p->m, p->v, p->n, cg, o, mode, p->t, bk.p4, bk.start,
+                                   coef, hits, d_field, g, corner, d_grad, loss, acc, 4 * S,
+                                   ctx->stream));
   return GVE_OK;
 }
 
@@ -2643,7 +2647,7 @@ gve_status gve_paper_eval(gve_ctx* ctx, const gve_paper* p, gve_grid g, const gv
   PBuckets bk;
   double* num = nullptr;
   TRY(paper_bucket(ctx, d_pts, npts, cg, 1, &bk));
-  TRY(paper_accumulators(ctx, npts, 1, &num));
+  TRY(paper_accumulators(ctx, npts, &num));
   double* den = num + npts;
   TRY_HIP(ctx, gve::paper_forward(p->theta, p->n, cg, o->k, npts, bk.p4, bk.start, num, den,
                                   nullptr, ctx->stream));
@@ -2670,10 +2674,10 @@ gve_status gve_paper_loss_grad(gve_ctx* ctx, gve_paper* p, const float* d_field,
   double* acc = nullptr;
   uint32_t* hits = nullptr;
   TRY(paper_bucket(ctx, d_pts, 2 * samples, gve::make_cells(g, o->cell), 1, &bk));
-  TRY(paper_accumulators(ctx, 2 * samples, 1, &acc));
+  TRY(paper_accumulators(ctx, 2 * samples, &acc));
   TRY(paper_hits(ctx, p->n, &hits));
-  TRY(paper_pass(ctx, p, d_field, g, *o, lam_sm, bk, d_vals, samples, acc, hits, 0, d_grad, loss,
-                 nullptr));
+  TRY(paper_pass(ctx, p, d_field, g, *o, lam_sm, bk, d_vals, samples, acc, hits, nullptr, 0,
+                 d_grad, loss));
   double* slots = static_cast<double*>(ctx->ws.h_pinned);
   TRY_HIP(ctx, hipMemcpyAsync(slots, loss, sizeof(double) * kTerms, hipMemcpyDeviceToHost,
                               ctx->stream));
@@ -2712,8 +2716,11 @@ gve_status gve_paper_refine(gve_ctx* ctx, gve_paper* p, const float* d_field, gv
   double* acc = nullptr;
   uint32_t* hits = nullptr;
   TRY(paper_points(ctx, S, batch, &pts, &vals));
-  TRY(paper_accumulators(ctx, 2 * S, 2, &acc));
+  TRY(paper_accumulators(ctx, 2 * S, &acc));
   TRY(paper_hits(ctx, p->n, &hits));
+  TRY(ensure(ctx, ctx->ws.p_corner, sizeof(float) * 9 * (size_t)p->n));
+  float* corner = static_cast<float*>(ctx->ws.p_corner.ptr);
+  TRY_HIP(ctx, gve::paper_corner_reset(corner, p->n, ctx->stream));
   std::vector<float> lam((size_t)iters);
   PBuckets bk;
   for (int32_t i = 0; i < iters; ++i) {
@@ -2730,10 +2737,8 @@ gve_status gve_paper_refine(gve_ctx* ctx, gve_paper* p, const float* d_field, gv
     }
     const PBuckets bj{bk.p4 + 2 * S * j, bk.start + (ncells + 1) * j};
     p->t += 1;
-    // the accumulators alternate: the backward pass of one iteration zeroes the
-    // other set for the next
-    TRY(paper_pass(ctx, p, d_field, g, *o, lam[i], bj, vals + S * j, S, acc + 4 * S * (i & 1),
-                   hits, 1, nullptr, loss + (int64_t)kTerms * i, acc + 4 * S * ((i + 1) & 1)));
+    TRY(paper_pass(ctx, p, d_field, g, *o, lam[i], bj, vals + S * j, S, acc, hits, corner, 1,
+                   nullptr, loss + (int64_t)kTerms * i));
   }
   std::vector<double> h((size_t)kTerms * iters);
   TRY_HIP(ctx, hipMemcpyAsync(h.data(), loss, sizeof(double) * h.size(), hipMemcpyDeviceToHost,

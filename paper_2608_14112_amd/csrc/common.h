@@ -106,9 +106,10 @@ struct Workspace {
   Scratch order_keys[2], order_vals[2];  // heaviest-first brick order (queue schedule)
   Scratch queue;                 // uint32 work counter of the persistent launch
   // the paper's training loop: class block counts / offsets, sample points,
-  // their float64 accumulators (two sets), points in cell order, cell sort,
-  // losses, the points each primitive reached
-  Scratch p_cls, p_pts, p_acc, p_sorted, p_keys[2], p_idx[2], p_start, p_loss, p_hits;
+  // their float64 accumulators, points in cell order, cell sort, losses, the
+  // points each primitive reached, gradient coefficients, volume values around
+  // the centres
+  Scratch p_cls, p_pts, p_acc, p_sorted, p_keys[2], p_idx[2], p_start, p_loss, p_hits, p_coef, p_corner;
   Scratch dense;                 // float [M] residual of the dense reference path
   Scratch snap;                  // float [3][11][n] parameters and Adam moments (refinement
                                  // restart point) + counters
@@ -379,23 +380,29 @@ hipError_t paper_gather(const float* pts, int64_t np, const uint32_t* sorted, fl
 hipError_t paper_cell_keys(const float* pts, int64_t np, const CellGrid& cg, uint32_t* keys,
                            uint32_t* idx, hipStream_t s);
 hipError_t paper_zero(double* p, int64_t n, hipStream_t s);
-// hits (optional): [1 + kPaperHits][n], the number of points each primitive
-// reached and the positions of the first kPaperHits.
+// hits (optional): the points each primitive reached (paper_hit_words(n) words;
+// 64 consecutive primitives share room for 64 kPaperHits).
 constexpr int kPaperHits = 8;
+size_t paper_hit_words(int64_t n);
 hipError_t paper_forward(const float* th, int64_t n, const CellGrid& cg, float k, int64_t S,
                          const float4* p4, const uint32_t* start, double* num, double* den,
                          uint32_t* hits, hipStream_t s);
 hipError_t paper_density(const double* num, const double* den, int64_t np, float rho0, float* vt,
                          float* dn, hipStream_t s);
-// Adds the objective's six terms to loss [kPaperSlots][6] and zeroes
-// clear [nclear].
+// The objective's six terms are added to loss [kPaperSlots][6]: the first three
+// by paper_coef (coef: one pair per position of the cell order), the others by
+// paper_backward, which also zeroes clear [nclear].  corner (optional): [9][n],
+// marked by paper_corner_reset before the first iteration that uses it.
 constexpr int kPaperSlots = 8;
+hipError_t paper_coef(int64_t S, const gve_paper_options& o, float lam_sm, const float4* p4,
+                      const double* num, const double* den, const float* vals, float2* coef,
+                      double* loss, hipStream_t s);
+hipError_t paper_corner_reset(float* corner, int64_t n, hipStream_t s);
 hipError_t paper_backward(float* th, float* m, float* v, int64_t n, const CellGrid& cg,
-                          const gve_paper_options& o, float lam_sm, int mode, int64_t t, int64_t S,
-                          const float4* p4, const uint32_t* start, const uint32_t* hits,
-                          const double* num, const double* den, const float* vals,
-                          const float* field, const gve_grid& fg, float* grad_out, double* loss,
-                          double* clear, int64_t nclear, hipStream_t s);
+                          const gve_paper_options& o, int mode, int64_t t, const float4* p4,
+                          const uint32_t* start, const float2* coef, const uint32_t* hits,
+                          const float* field, const gve_grid& fg, float* corner, float* grad_out,
+                          double* loss, double* clear, int64_t nclear, hipStream_t s);
 
 // ---- warm-start network (mlp.hip) --------------------------------------------
 constexpr int kMlpIn = 16, kMlpHid = 128, kMlpOut = 11;

@@ -20,14 +20,14 @@
 //                    sort and k_pgather);
 //   k_pfwd         : per primitive, sum_i w a G and sum_i w G into the points'
 //                    float64 accumulators (atomics), and the points it reached;
+//   k_pcoef        : per point, the coefficients of d(w a G) and d(w G) in
+//                    dL/dtheta (quotient rule; the density floor passes no
+//                    gradient), and the samples' terms of the objective;
 //   k_pbwd         : per primitive, the gradient from those points (no atomics:
-//                    each primitive owns its sums), with the coefficients of
-//                    d(w a G) and d(w G) in dL/dtheta (quotient rule; the
-//                    density floor passes no gradient) formed where they are
-//                    used; the regularisers; either the gradient (test hook) or
-//                    the Adam step; and the objective's terms.
+//                    each primitive owns its sums), the regularisers with their
+//                    terms, and either the gradient (test hook) or the Adam step.
 // Sampling and bucketing depend on no parameter, so refinement does them for
-// many iterations at once: an iteration is two launches.
+// many iterations at once: an iteration is three launches.
 #include <algorithm>
 #include <cmath>
 
@@ -104,40 +104,61 @@ __device__ inline int cell_coord(float x, float org, float h, int nc) {
   return c >= (float)nc ? nc - 1 : (int)c;
 }
 
-// Trilinear interpolation of the float32 volume at a world point (clamped).
-__device__ inline double trilinear(const float* __restrict__ f, const gve_grid& g, double px,
-                                   double py, double pz) {
-  const double p[3] = {px - (double)g.x0, py - (double)g.y0, pz - (double)g.z0};
-  const int64_t dim[3] = {g.nx, g.ny, g.nz};
+// Trilinear interpolation of the float32 volume at a world point (clamped):
+// the cell's lower corner, the fractions in it, and the weighted sum of its
+// eight corners (x fastest).
+struct TriCell {
   int64_t lo[3];
   double fr[3];
+};
+
+__device__ inline TriCell tri_cell(const gve_grid& g, double px, double py, double pz) {
+  const double p[3] = {px - (double)g.x0, py - (double)g.y0, pz - (double)g.z0};
+  const int64_t dim[3] = {g.nx, g.ny, g.nz};
+  TriCell t;
 #pragma unroll
   for (int j = 0; j < 3; ++j) {
     double x = fmin(fmax(p[j], 0.0), (double)(dim[j] - 1));
     if (dim[j] > 1) {
       int64_t i0 = (int64_t)floor(x);
       if (i0 > dim[j] - 2) i0 = dim[j] - 2;
-      lo[j] = i0;
-      fr[j] = x - (double)i0;
+      t.lo[j] = i0;
+      t.fr[j] = x - (double)i0;
     } else {
-      lo[j] = 0;
-      fr[j] = 0.0;
+      t.lo[j] = 0;
+      t.fr[j] = 0.0;
     }
   }
+  return t;
+}
+
+__device__ inline void tri_corners(const float* __restrict__ f, const gve_grid& g,
+                                   const TriCell& t, float v[8]) {
+  const int64_t sx = t.lo[0] + 1 < g.nx ? 1 : 0, sy = t.lo[1] + 1 < g.ny ? g.nx : 0,
+                sz = t.lo[2] + 1 < g.nz ? g.nx * g.ny : 0;
+  const float* p = f + (t.lo[0] + g.nx * (t.lo[1] + g.ny * t.lo[2]));
+#pragma unroll
+  for (int c = 0; c < 8; ++c)
+    v[c] = p[(c & 1 ? sx : 0) + (c & 2 ? sy : 0) + (c & 4 ? sz : 0)];
+}
+
+__device__ inline double tri_sum(const TriCell& t, const float v[8]) {
   double acc = 0.0;
 #pragma unroll
-  for (int dz = 0; dz < 2; ++dz)
-#pragma unroll
-    for (int dy = 0; dy < 2; ++dy)
-#pragma unroll
-      for (int dx = 0; dx < 2; ++dx) {
-        const int64_t ix = min(lo[0] + dx, dim[0] - 1), iy = min(lo[1] + dy, dim[1] - 1),
-                      iz = min(lo[2] + dz, dim[2] - 1);
-        const double wgt = (dx ? fr[0] : 1.0 - fr[0]) * (dy ? fr[1] : 1.0 - fr[1]) *
-                           (dz ? fr[2] : 1.0 - fr[2]);
-        acc += wgt * (double)f[ix + g.nx * (iy + g.ny * iz)];
-      }
+  for (int c = 0; c < 8; ++c) {
+    const double wgt = (c & 1 ? t.fr[0] : 1.0 - t.fr[0]) * (c & 2 ? t.fr[1] : 1.0 - t.fr[1]) *
+                       (c & 4 ? t.fr[2] : 1.0 - t.fr[2]);
+    acc += wgt * (double)v[c];
+  }
   return acc;
+}
+
+__device__ inline double trilinear(const float* __restrict__ f, const gve_grid& g, double px,
+                                   double py, double pz) {
+  const TriCell t = tri_cell(g, px, py, pz);
+  float v[8];
+  tri_corners(f, g, t, v);
+  return tri_sum(t, v);
 }
 
 template <typename T>
@@ -445,58 +466,199 @@ struct PairCfg {
   int64_t S;  // points [0, S) are samples (get the numerator), [S, np) partners
 };
 
-// fn(j, point, d, G) for every point (position j in cell order) inside the
-// support.  The cells of one row (fixed y and z) are consecutive, so a row is
-// one range of points: two range reads and its points, instead of two reads
-// per cell and an index to chase per point.
+// Cells a primitive's box overlaps.  The cells of one row (fixed y and z) are
+// consecutive, so a row is one range of points.
+struct BoxCells {
+  int x0, x1, y0, y1, z0, z1;
+};
+
+__device__ inline BoxCells box_cells(const PGeom& g, const CellGrid& cg) {
+  BoxCells b;
+  b.x0 = cell_coord(g.mu[0] - g.half[0], cg.x0, cg.h, cg.ncx);
+  b.x1 = cell_coord(g.mu[0] + g.half[0], cg.x0, cg.h, cg.ncx);
+  b.y0 = cell_coord(g.mu[1] - g.half[1], cg.y0, cg.h, cg.ncy);
+  b.y1 = cell_coord(g.mu[1] + g.half[1], cg.y0, cg.h, cg.ncy);
+  b.z0 = cell_coord(g.mu[2] - g.half[2], cg.z0, cg.h, cg.ncz);
+  b.z1 = cell_coord(g.mu[2] + g.half[2], cg.z0, cg.h, cg.ncz);
+  return b;
+}
+
+// fn(j, d, G) for every point (position j in cell order) inside the support.
 template <typename F>
 __device__ inline void for_points(const PGeom& g, const PairCfg& c, const float4* __restrict__ p4,
                                   const uint32_t* __restrict__ start, F&& fn) {
-  const int x0 = cell_coord(g.mu[0] - g.half[0], c.cg.x0, c.cg.h, c.cg.ncx);
-  const int x1 = cell_coord(g.mu[0] + g.half[0], c.cg.x0, c.cg.h, c.cg.ncx);
-  const int y0 = cell_coord(g.mu[1] - g.half[1], c.cg.y0, c.cg.h, c.cg.ncy);
-  const int y1 = cell_coord(g.mu[1] + g.half[1], c.cg.y0, c.cg.h, c.cg.ncy);
-  const int z0 = cell_coord(g.mu[2] - g.half[2], c.cg.z0, c.cg.h, c.cg.ncz);
-  const int z1 = cell_coord(g.mu[2] + g.half[2], c.cg.z0, c.cg.h, c.cg.ncz);
-  for (int cz = z0; cz <= z1; ++cz)
-    for (int cy = y0; cy <= y1; ++cy) {
+  const BoxCells b = box_cells(g, c.cg);
+  for (int cz = b.z0; cz <= b.z1; ++cz)
+    for (int cy = b.y0; cy <= b.y1; ++cy) {
       const uint32_t row = (uint32_t)(c.cg.ncx * (cy + c.cg.ncy * cz));
-      const uint32_t e = start[row + x1 + 1];
-      for (uint32_t j = start[row + x0]; j < e; ++j) {
+      const uint32_t e = start[row + b.x1 + 1];
+      for (uint32_t j = start[row + b.x0]; j < e; ++j) {
         const float4 q = p4[j];
         const float dx = q.x - g.mu[0];
         const float dy = q.y - g.mu[1];
         const float dz = q.z - g.mu[2];
         const float m2 = mahal2(g, dx, dy, dz);
-        if (m2 < c.k2) fn(j, __float_as_uint(q.w), dx, dy, dz, expf(-0.5f * m2));
+        if (m2 < c.k2) fn(j, dx, dy, dz, expf(-0.5f * m2));
       }
     }
 }
 
-// Points a primitive reached, kept for the backward pass: their number, and the
-// positions of the first kHits ([kHits][n]).  A primitive with more searches
-// again.
-constexpr int kHits = kPaperHits;
+// Forward pass, one wave per 64 primitives.  The rows of a primitive's box hold
+// a handful of points each, unevenly: with a lane per primitive a wave takes as
+// many steps as its busiest lane (some fifty, nine of them useful on average).
+// So the lanes only collect their candidate points, four a lane and round, into
+// a list in LDS that is then tested 64 at a time.
+//
+// Points a primitive reached are kept for the backward pass: the wave's lists,
+// primitive after primitive, in its 64 kPaperHits entries of hit_list, and
+// hit_range [n] = first entry << 16 | number.  A wave that reached more keeps
+// none (kAllPoints): the backward pass then searches again.
+constexpr int kWavePrims = 64;
+constexpr int kCandidates = 512;
+constexpr int kWaveHits = kWavePrims * kPaperHits;
+constexpr uint32_t kAllPoints = 0xFFFFu;
 
-__global__ __launch_bounds__(kThreads) void k_pfwd(const float* __restrict__ th, int64_t n,
-                                                   PairCfg c, float k,
-                                                   const float4* __restrict__ p4,
-                                                   const uint32_t* __restrict__ start,
-                                                   double* __restrict__ num,
-                                                   double* __restrict__ den,
-                                                   uint32_t* __restrict__ hits) {
-  const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-  if (i >= n) return;
-  const PGeom g = pgeom(th, n, i, k);
-  uint32_t nh = 0;
-  for_points(g, c, p4, start, [&](uint32_t j, uint32_t pi, float, float, float, float G) {
-    const float wg = g.w * G;
-    atomicAdd(&den[pi], (double)wg);
-    if ((int64_t)pi < c.S) atomicAdd(&num[pi], (double)(wg * g.a));
-    if (hits && nh < (uint32_t)kHits) hits[n + nh * n + i] = j;
-    ++nh;
-  });
-  if (hits) hits[i] = nh;
+__global__ __launch_bounds__(kWavePrims) void k_pfwd(const float* __restrict__ th, int64_t n,
+                                                     PairCfg c, float k,
+                                                     const float4* __restrict__ p4,
+                                                     const uint32_t* __restrict__ start,
+                                                     double* __restrict__ num,
+                                                     double* __restrict__ den,
+                                                     uint32_t* __restrict__ hit_range,
+                                                     uint32_t* __restrict__ hit_list) {
+  __shared__ float geo[11][kWavePrims];      // mu, P, a, w of the wave's primitives
+  __shared__ uint32_t cand[kCandidates];     // candidate points
+  __shared__ uint8_t cand_of[kCandidates];   // and their primitives
+  __shared__ uint32_t hit[kWaveHits];
+  __shared__ uint8_t hit_of[kWaveHits];
+  __shared__ uint32_t nhit[kWavePrims];
+  const int lane = threadIdx.x;
+  const int64_t i = (int64_t)blockIdx.x * kWavePrims + lane;
+  const uint64_t below = (1ull << lane) - 1ull;
+  BoxCells b{0, 0, 0, -1, 0, 0};
+  if (i < n) {
+    const PGeom g = pgeom(th, n, i, k);
+    b = box_cells(g, c.cg);
+#pragma unroll
+    for (int a = 0; a < 3; ++a) geo[a][lane] = g.mu[a];
+#pragma unroll
+    for (int a = 0; a < 6; ++a) geo[3 + a][lane] = g.P[a];
+    geo[9][lane] = g.a;
+    geo[10][lane] = g.w;
+  }
+  nhit[lane] = 0;
+  uint32_t listed = 0, kept = 0;  // candidates waiting, points kept (uniform)
+  int cy = b.y0 - 1, cz = b.z0;   // row walked last
+  uint32_t j = 0, e = 0;
+  bool rows = i < n;
+  for (;;) {
+    // each lane with no points left moves on to its next row
+    if (rows && j >= e) {
+      if (++cy > b.y1) {
+        cy = b.y0;
+        if (++cz > b.z1) rows = false;
+      }
+      if (rows) {
+        const uint32_t row = (uint32_t)(c.cg.ncx * (cy + c.cg.ncy * cz));
+        j = start[row + b.x0];
+        e = start[row + b.x1 + 1];
+      }
+    }
+    // up to four points of every lane join the list, lane after lane
+    const uint32_t m = rows ? min(e - j, 4u) : 0u;
+    uint32_t inc = m;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const uint32_t y = __shfl_up(inc, d, 64);
+      if (lane >= d) inc += y;
+    }
+    const uint32_t at = listed + inc - m;
+    for (uint32_t q = 0; q < m; ++q) {
+      cand[at + q] = j + q;
+      cand_of[at + q] = (uint8_t)lane;
+    }
+    j += m;
+    listed += __shfl(inc, 63, 64);
+    const bool more = __builtin_amdgcn_ballot_w64(rows) != 0ull;
+    // room for one more round of 4 x 64
+    if (more && listed <= kCandidates - 4 * kWavePrims) continue;
+    __syncthreads();
+    for (uint32_t t0 = 0; t0 < listed; t0 += 64) {
+      const uint32_t t = t0 + lane;
+      bool in = false;
+      uint32_t o = 0, cj = 0, pi = 0;
+      float m2 = 0.0f;
+      if (t < listed) {
+        o = cand_of[t];
+        cj = cand[t];
+        const float4 q = p4[cj];
+        PGeom g;
+#pragma unroll
+        for (int a = 0; a < 6; ++a) g.P[a] = geo[3 + a][o];
+        m2 = mahal2(g, q.x - geo[0][o], q.y - geo[1][o], q.z - geo[2][o]);
+        in = m2 < c.k2;
+        pi = __float_as_uint(q.w);
+      }
+      if (in) {
+        const float wg = geo[10][o] * expf(-0.5f * m2);
+        atomicAdd(&den[pi], (double)wg);
+        if ((int64_t)pi < c.S) atomicAdd(&num[pi], (double)(wg * geo[9][o]));
+      }
+      if (hit_range) {
+        const uint64_t hm = __builtin_amdgcn_ballot_w64(in);
+        const uint32_t pos = kept + (uint32_t)__popcll(hm & below);
+        if (in && pos < (uint32_t)kWaveHits) {
+          hit[pos] = cj;
+          hit_of[pos] = (uint8_t)o;
+          atomicAdd(&nhit[o], 1u);
+        }
+        kept += (uint32_t)__popcll(hm);
+      }
+    }
+    listed = 0;
+    __syncthreads();
+    if (!more) break;
+  }
+  if (!hit_range) return;
+  uint32_t* out = hit_list + (size_t)blockIdx.x * kWaveHits;
+  if (kept > (uint32_t)kWaveHits) {
+    if (i < n) hit_range[i] = kAllPoints;
+    return;
+  }
+  // entries grouped by primitive, in order: first entry of each primitive, then
+  // an entry's place among its primitive's (entries of one primitive in a
+  // step are ranked by lane)
+  const uint32_t mine = nhit[lane];
+  uint32_t inc = mine;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const uint32_t y = __shfl_up(inc, d, 64);
+    if (lane >= d) inc += y;
+  }
+  __syncthreads();
+  nhit[lane] = inc - mine;
+  if (i < n) hit_range[i] = ((inc - mine) << 16) | mine;
+  __syncthreads();
+  for (uint32_t t0 = 0; t0 < kept; t0 += 64) {
+    const uint32_t t = t0 + lane;
+    const bool live = t < kept;
+    const uint32_t o = live ? hit_of[t] : 255u;
+    uint64_t left = __builtin_amdgcn_ballot_w64(live);
+    uint32_t pos = 0;
+    while (left) {
+      const int l = __builtin_ctzll(left);
+      const uint32_t ol = __shfl(o, l, 64);
+      const uint64_t same = __builtin_amdgcn_ballot_w64(o == ol);
+      if (o == ol) {
+        const uint32_t base = nhit[ol];
+        pos = base + (uint32_t)__popcll(same & below);
+        // read by every lane of the group before its first lane raises it
+        if ((same & below) == 0ull) nhit[ol] = base + (uint32_t)__popcll(same);
+      }
+      left &= ~same;
+    }
+    if (live) out[pos] = hit[t];
+  }
 }
 
 struct CoefCfg {
@@ -506,23 +668,39 @@ struct CoefCfg {
   const float* vals;
 };
 
-// Coefficients of d(w a G) (samples only) and of d(w G) at point pi.
-__device__ inline void coef_at(const CoefCfg& c, int64_t pi, float& cA, float& cB) {
-  const int64_t s = pi < c.S ? pi : pi - c.S;
-  const double d1 = c.den[s], d2 = c.den[c.S + s];
-  if (pi >= c.S) {
-    cA = 0.0f;
-    cB = (float)(-2.0 * c.lam_sm * (d1 - d2));
-    return;
+// Coefficients of d(w a G) (samples only) and of d(w G) of the point at each
+// position of the cell order, and the samples' terms of the objective.
+__global__ __launch_bounds__(kThreads) void k_pcoef(CoefCfg c, const float4* __restrict__ p4,
+                                                    float2* __restrict__ coef,
+                                                    double* __restrict__ loss) {
+  const int64_t j = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+  double lv = 0.0, lr = 0.0, ls = 0.0;
+  if (j < 2 * c.S) {
+    const int64_t pi = (int64_t)__float_as_uint(p4[j].w);
+    const int64_t s = pi < c.S ? pi : pi - c.S;
+    const double d1 = c.den[s], d2 = c.den[c.S + s];
+    float2 o;
+    if (pi >= c.S) {
+      o.x = 0.0f;
+      o.y = (float)(-2.0 * c.lam_sm * (d1 - d2));
+    } else {
+      const double D = fmax(d1, c.rho0);
+      const double vt = c.num[s] / D;
+      const double val = (double)c.vals[s];
+      const bool occ = val > c.v_occ;
+      const double u = occ ? 2.0 * (vt - val) : 0.0;
+      const double v = (occ ? 2.0 * c.lam_rho * (d1 - 1.0) : 0.0) + 2.0 * c.lam_sm * (d1 - d2);
+      o.x = (float)(u / D);
+      o.y = (float)(v - (d1 > c.rho0 ? u * vt / D : 0.0));
+      if (occ) {
+        lv = (vt - val) * (vt - val);
+        lr = (d1 - 1.0) * (d1 - 1.0);
+      }
+      ls = (d1 - d2) * (d1 - d2);
+    }
+    coef[j] = o;
   }
-  const double D = fmax(d1, c.rho0);
-  const double vt = c.num[s] / D;
-  const double val = (double)c.vals[s];
-  const bool occ = val > c.v_occ;
-  const double u = occ ? 2.0 * (vt - val) : 0.0;
-  const double v = (occ ? 2.0 * c.lam_rho * (d1 - 1.0) : 0.0) + 2.0 * c.lam_sm * (d1 - d2);
-  cA = (float)(u / D);
-  cB = (float)(v - (d1 > c.rho0 ? u * vt / D : 0.0));
+  block_add3(lv, lr, ls, loss + (blockIdx.x % kPaperSlots) * 6);
 }
 
 struct BwdCfg {
@@ -533,51 +711,61 @@ struct BwdCfg {
   int64_t nclear;
 };
 
-// Gradient, regularisers and step of every primitive; the objective's terms
-// into loss[slot][6] (slot = block mod kPaperSlots, so that the blocks' atomics
-// do not queue on one address).  Bound by the parameters and moments it reads
-// and writes (288 bytes a primitive) and by the latency of the eight volume
-// reads of the anchor.
+// Gradient, regularisers and step of every primitive, and their terms of the
+// objective into loss[slot][3 ..] (slot = block mod kPaperSlots, so that the
+// blocks' atomics do not queue on one address).  With `corner`, the eight volume
+// values around a centre are kept from iteration to iteration of one call
+// ([9][n]: the cell's first voxel, then its corners): a centre moves by about the
+// learning rate, so it rarely leaves its cell, and the eight values are read
+// side by side instead of from four lines all over the volume (at 400,000
+// primitives some 200 MB an iteration).  Bound by the parameters and moments it
+// reads and writes (288 bytes a primitive).
 __global__ __launch_bounds__(kThreads) void k_pbwd(float* __restrict__ th, float* __restrict__ m,
                                                    float* __restrict__ v, int64_t n, PairCfg c,
-                                                   BwdCfg b, CoefCfg cc,
-                                                   const float4* __restrict__ p4,
+                                                   BwdCfg b, const float4* __restrict__ p4,
                                                    const uint32_t* __restrict__ start,
-                                                   const uint32_t* __restrict__ hits,
+                                                   const float2* __restrict__ coef,
+                                                   const uint32_t* __restrict__ hit_range,
+                                                   const uint32_t* __restrict__ hit_list,
                                                    const float* __restrict__ field, gve_grid fg,
+                                                   float* __restrict__ corner,
                                                    float* __restrict__ grad_out,
                                                    double* __restrict__ loss) {
   const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-  loss += (blockIdx.x % kPaperSlots) * 6;
-  // the next iteration's accumulators, and the samples' own terms
+  // the next iteration's accumulators
   const int64_t stride = (int64_t)gridDim.x * kThreads;
   for (int64_t j = i; j < b.nclear; j += stride) b.clear[j] = 0.0;
-  double lv = 0.0, lr = 0.0, ls = 0.0;
-  for (int64_t s = i; s < cc.S; s += stride) {
-    const double d1 = cc.den[s], d2 = cc.den[cc.S + s];
-    const double vt = cc.num[s] / fmax(d1, cc.rho0);
-    const double val = (double)cc.vals[s];
-    if (val > cc.v_occ) {
-      lv += (vt - val) * (vt - val);
-      lr += (d1 - 1.0) * (d1 - 1.0);
-    }
-    ls += (d1 - d2) * (d1 - d2);
-  }
   double la = 0.0, lan = 0.0, lc = 0.0;
   if (i < n) {
+    const uint32_t hr = hit_range[i];
+    const uint32_t nh = hr & 0xFFFFu;
     float t[12], gr[12];
 #pragma unroll
     for (int a = 0; a < 12; ++a) t[a] = th[a * n + i];
-    const double aref = trilinear(field, fg, (double)t[0], (double)t[1], (double)t[2]);
+    const TriCell tc = tri_cell(fg, (double)t[0], (double)t[1], (double)t[2]);
+    float cv[8];
+    if (corner) {
+      const uint32_t at = (uint32_t)(tc.lo[0] + fg.nx * (tc.lo[1] + fg.ny * tc.lo[2]));
+#pragma unroll
+      for (int q = 0; q < 8; ++q) cv[q] = corner[(1 + q) * n + i];
+      if (__float_as_uint(corner[i]) != at) {
+        tri_corners(field, fg, tc, cv);
+        corner[i] = __uint_as_float(at);
+#pragma unroll
+        for (int q = 0; q < 8; ++q) corner[(1 + q) * n + i] = cv[q];
+      }
+    } else {
+      tri_corners(field, fg, tc, cv);
+    }
+    const double aref = tri_sum(tc, cv);
     float sgd[3] = {0.f, 0.f, 0.f}, D[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     float dA = 0.f, dB = 0.f;
     const float w = 1.0f / (1.0f + expf(-t[11]));
-    const uint32_t nh = hits[i];
     if (nh > 0) {
       const PGeom g = pgeom(th, n, i, b.k);
-      auto add = [&](uint32_t, uint32_t pi, float dx, float dy, float dz, float G) {
-        float cA, cB;
-        coef_at(cc, (int64_t)pi, cA, cB);
+      auto add = [&](uint32_t j, float dx, float dy, float dz, float G) {
+        const float2 cj = coef[j];
+        const float cA = cj.x, cB = cj.y;
         const float e = fmaf(cA, g.a, cB);  // coefficient of d(w G)
         const float gc = e * g.w * G;
         sgd[0] = fmaf(gc, dx, sgd[0]);
@@ -592,13 +780,15 @@ __global__ __launch_bounds__(kThreads) void k_pbwd(float* __restrict__ th, float
         dA = fmaf(cA * g.w, G, dA);
         dB = fmaf(e, G, dB);
       };
-      if (nh <= (uint32_t)kHits) {
+      if (nh != kAllPoints) {
+        const uint32_t* mine = hit_list + (size_t)(i / kWavePrims) * kWaveHits + (hr >> 16);
         for (uint32_t h = 0; h < nh; ++h) {
-          const float4 q = p4[hits[n + h * n + i]];
+          const uint32_t j = mine[h];
+          const float4 q = p4[j];
           const float dx = q.x - g.mu[0];
           const float dy = q.y - g.mu[1];
           const float dz = q.z - g.mu[2];
-          add(0u, __float_as_uint(q.w), dx, dy, dz, expf(-0.5f * mahal2(g, dx, dy, dz)));
+          add(j, dx, dy, dz, expf(-0.5f * mahal2(g, dx, dy, dz)));
         }
       } else {
         for_points(g, c, p4, start, add);
@@ -650,9 +840,14 @@ __global__ __launch_bounds__(kThreads) void k_pbwd(float* __restrict__ th, float
       }
     }
   }
-  block_add3(lv, lr, ls, loss);
-  __syncthreads();
-  block_add3(la, lan, lc, loss + 3);
+  block_add3(la, lan, lc, loss + (blockIdx.x % kPaperSlots) * 6 + 3);
+}
+
+// Marks every primitive's corner values as not read yet (no cell starts at
+// voxel 2^32 - 1: volumes have fewer voxels).
+__global__ __launch_bounds__(kThreads) void k_pcorner_reset(float* __restrict__ corner, int64_t n) {
+  const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+  if (i < n) corner[i] = __uint_as_float(0xFFFFFFFFu);
 }
 
 __global__ __launch_bounds__(kThreads) void k_pfill_d(double* __restrict__ p, int64_t n) {
@@ -756,6 +951,10 @@ hipError_t paper_zero(double* p, int64_t n, hipStream_t s) {
   return hipGetLastError();
 }
 
+size_t paper_hit_words(int64_t n) {
+  return (size_t)n + (size_t)((n + kWavePrims - 1) / kWavePrims) * kWaveHits;
+}
+
 hipError_t paper_forward(const float* th, int64_t n, const CellGrid& cg, float k, int64_t S,
                          const float4* p4, const uint32_t* start, double* num, double* den,
                          uint32_t* hits, hipStream_t s) {
@@ -763,8 +962,9 @@ hipError_t paper_forward(const float* th, int64_t n, const CellGrid& cg, float k
   c.cg = cg;
   c.k2 = k * k;
   c.S = S;
-  hipLaunchKernelGGL(k_pfwd, dim3(blocks_for(n)), dim3(kThreads), 0, s, th, n, c, k, p4, start, num,
-                     den, hits);
+  hipLaunchKernelGGL(k_pfwd, dim3((unsigned)((n + kWavePrims - 1) / kWavePrims)),
+                     dim3(kWavePrims), 0, s, th, n, c, k, p4, start, num, den, hits,
+                     hits ? hits + n : nullptr);
   return hipGetLastError();
 }
 
@@ -775,16 +975,9 @@ hipError_t paper_density(const double* num, const double* den, int64_t np, float
   return hipGetLastError();
 }
 
-hipError_t paper_backward(float* th, float* m, float* v, int64_t n, const CellGrid& cg,
-                          const gve_paper_options& o, float lam_sm, int mode, int64_t t, int64_t S,
-                          const float4* p4, const uint32_t* start, const uint32_t* hits,
-                          const double* num, const double* den, const float* vals,
-                          const float* field, const gve_grid& fg, float* grad_out, double* loss,
-                          double* clear, int64_t nclear, hipStream_t s) {
-  PairCfg c;
-  c.cg = cg;
-  c.k2 = o.k * o.k;
-  c.S = S;
+hipError_t paper_coef(int64_t S, const gve_paper_options& o, float lam_sm, const float4* p4,
+                      const double* num, const double* den, const float* vals, float2* coef,
+                      double* loss, hipStream_t s) {
   CoefCfg cc;
   cc.S = S;
   cc.rho0 = o.rho0;
@@ -794,6 +987,24 @@ hipError_t paper_backward(float* th, float* m, float* v, int64_t n, const CellGr
   cc.num = num;
   cc.den = den;
   cc.vals = vals;
+  hipLaunchKernelGGL(k_pcoef, dim3(blocks_for(2 * S)), dim3(kThreads), 0, s, cc, p4, coef, loss);
+  return hipGetLastError();
+}
+
+hipError_t paper_corner_reset(float* corner, int64_t n, hipStream_t s) {
+  hipLaunchKernelGGL(k_pcorner_reset, dim3(blocks_for(n)), dim3(kThreads), 0, s, corner, n);
+  return hipGetLastError();
+}
+
+hipError_t paper_backward(float* th, float* m, float* v, int64_t n, const CellGrid& cg,
+                          const gve_paper_options& o, int mode, int64_t t, const float4* p4,
+                          const uint32_t* start, const float2* coef, const uint32_t* hits,
+                          const float* field, const gve_grid& fg, float* corner, float* grad_out,
+                          double* loss, double* clear, int64_t nclear, hipStream_t s) {
+  PairCfg c;
+  c.cg = cg;
+  c.k2 = o.k * o.k;
+  c.S = 0;  // the coefficients already tell samples from partners
   BwdCfg b;
   b.clear = clear;
   b.nclear = nclear;
@@ -812,8 +1023,8 @@ hipError_t paper_backward(float* th, float* m, float* v, int64_t n, const CellGr
   b.inv_bc1 = (float)(1.0 / (1.0 - std::pow((double)o.beta1, tt)));
   b.inv_bc2 = (float)(1.0 / (1.0 - std::pow((double)o.beta2, tt)));
   b.mode = mode;
-  hipLaunchKernelGGL(k_pbwd, dim3(blocks_for(n)), dim3(kThreads), 0, s, th, m, v, n, c, b, cc, p4,
-                     start, hits, field, fg, grad_out, loss);
+  hipLaunchKernelGGL(k_pbwd, dim3(blocks_for(n)), dim3(kThreads), 0, s, th, m, v, n, c, b,
+                     p4, start, coef, hits, hits + n, field, fg, corner, grad_out, loss);
   return hipGetLastError();
 }
 
