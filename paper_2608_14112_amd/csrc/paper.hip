@@ -518,6 +518,19 @@ constexpr int kCandidates = 512;
 constexpr int kWaveHits = kWavePrims * kPaperHits;
 constexpr uint32_t kAllPoints = 0xFFFFu;
 
+// Inclusive prefix sum over a wave by data-parallel moves (no LDS traffic): four
+// shifts within the rows of sixteen lanes, then the rows' totals.
+__device__ inline uint32_t wave_scan(uint32_t v) {
+  int x = (int)v;
+  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);  // row_shr:1
+  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);  // row_shr:2
+  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);  // row_shr:4
+  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);  // row_shr:8
+  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);  // row_bcast:15
+  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);  // row_bcast:31
+  return (uint32_t)x;
+}
+
 __global__ __launch_bounds__(kWavePrims) void k_pfwd(const float* __restrict__ th, int64_t n,
                                                      PairCfg c, float k,
                                                      const float4* __restrict__ p4,
@@ -526,7 +539,6 @@ __global__ __launch_bounds__(kWavePrims) void k_pfwd(const float* __restrict__ t
                                                      double* __restrict__ den,
                                                      uint32_t* __restrict__ hit_range,
                                                      uint32_t* __restrict__ hit_list) {
-  __shared__ float geo[11][kWavePrims];      // mu, P, a, w of the wave's primitives
   __shared__ uint32_t cand[kCandidates];     // candidate points
   __shared__ uint8_t cand_of[kCandidates];   // and their primitives
   __shared__ uint32_t hit[kWaveHits];
@@ -535,74 +547,50 @@ __global__ __launch_bounds__(kWavePrims) void k_pfwd(const float* __restrict__ t
   const int lane = threadIdx.x;
   const int64_t i = (int64_t)blockIdx.x * kWavePrims + lane;
   const uint64_t below = (1ull << lane) - 1ull;
+  PGeom g{};
   BoxCells b{0, 0, 0, -1, 0, 0};
   if (i < n) {
-    const PGeom g = pgeom(th, n, i, k);
+    g = pgeom(th, n, i, k);
     b = box_cells(g, c.cg);
-#pragma unroll
-    for (int a = 0; a < 3; ++a) geo[a][lane] = g.mu[a];
-#pragma unroll
-    for (int a = 0; a < 6; ++a) geo[3 + a][lane] = g.P[a];
-    geo[9][lane] = g.a;
-    geo[10][lane] = g.w;
   }
   nhit[lane] = 0;
   uint32_t listed = 0, kept = 0;  // candidates waiting, points kept (uniform)
   int cy = b.y0 - 1, cz = b.z0;   // row walked last
-  uint32_t j = 0, e = 0;
   bool rows = i < n;
-  for (;;) {
-    // each lane with no points left moves on to its next row
-    if (rows && j >= e) {
-      if (++cy > b.y1) {
-        cy = b.y0;
-        if (++cz > b.z1) rows = false;
-      }
-      if (rows) {
-        const uint32_t row = (uint32_t)(c.cg.ncx * (cy + c.cg.ncy * cz));
-        j = start[row + b.x0];
-        e = start[row + b.x1 + 1];
-      }
-    }
-    // up to four points of every lane join the list, lane after lane
-    const uint32_t m = rows ? min(e - j, 4u) : 0u;
-    uint32_t inc = m;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-      const uint32_t y = __shfl_up(inc, d, 64);
-      if (lane >= d) inc += y;
-    }
-    const uint32_t at = listed + inc - m;
-    for (uint32_t q = 0; q < m; ++q) {
-      cand[at + q] = j + q;
-      cand_of[at + q] = (uint8_t)lane;
-    }
-    j += m;
-    listed += __shfl(inc, 63, 64);
-    const bool more = __builtin_amdgcn_ballot_w64(rows) != 0ull;
-    // room for one more round of 4 x 64
-    if (more && listed <= kCandidates - 4 * kWavePrims) continue;
+  // tests the listed candidates, 64 at a time; the next ones' points are loaded
+  // meanwhile
+  auto flush = [&]() {
     __syncthreads();
+    uint32_t on = 0, cn = 0;
+    float4 qn = make_float4(0.f, 0.f, 0.f, 0.f);
+    if ((uint32_t)lane < listed) {
+      on = cand_of[lane];
+      cn = cand[lane];
+      qn = p4[cn];
+    }
     for (uint32_t t0 = 0; t0 < listed; t0 += 64) {
-      const uint32_t t = t0 + lane;
-      bool in = false;
-      uint32_t o = 0, cj = 0, pi = 0;
-      float m2 = 0.0f;
-      if (t < listed) {
-        o = cand_of[t];
-        cj = cand[t];
-        const float4 q = p4[cj];
-        PGeom g;
-#pragma unroll
-        for (int a = 0; a < 6; ++a) g.P[a] = geo[3 + a][o];
-        m2 = mahal2(g, q.x - geo[0][o], q.y - geo[1][o], q.z - geo[2][o]);
-        in = m2 < c.k2;
-        pi = __float_as_uint(q.w);
+      const bool live = t0 + lane < listed;
+      const uint32_t o = on, cj = cn;
+      const float4 q = qn;
+      if (t0 + 64 + lane < listed) {
+        on = cand_of[t0 + 64 + lane];
+        cn = cand[t0 + 64 + lane];
+        qn = p4[cn];
       }
+      // the primitive's geometry, from the lane that holds it
+      PGeom go;
+#pragma unroll
+      for (int a = 0; a < 6; ++a) go.P[a] = __shfl(g.P[a], (int)o, 64);
+      const float m2 = mahal2(go, q.x - __shfl(g.mu[0], (int)o, 64),
+                              q.y - __shfl(g.mu[1], (int)o, 64),
+                              q.z - __shfl(g.mu[2], (int)o, 64));
+      const float ow = __shfl(g.w, (int)o, 64), oa = __shfl(g.a, (int)o, 64);
+      const uint32_t pi = __float_as_uint(q.w);
+      const bool in = live && m2 < c.k2;
       if (in) {
-        const float wg = geo[10][o] * expf(-0.5f * m2);
+        const float wg = ow * expf(-0.5f * m2);
         atomicAdd(&den[pi], (double)wg);
-        if ((int64_t)pi < c.S) atomicAdd(&num[pi], (double)(wg * geo[9][o]));
+        if ((int64_t)pi < c.S) atomicAdd(&num[pi], (double)(wg * oa));
       }
       if (hit_range) {
         const uint64_t hm = __builtin_amdgcn_ballot_w64(in);
@@ -617,8 +605,45 @@ __global__ __launch_bounds__(kWavePrims) void k_pfwd(const float* __restrict__ t
     }
     listed = 0;
     __syncthreads();
-    if (!more) break;
+  };
+  while (__builtin_amdgcn_ballot_w64(rows) != 0ull) {
+    // the lane's next rows, their ranges loaded together
+    constexpr int kRows = 4;
+    uint32_t j[kRows], e[kRows];
+#pragma unroll
+    for (int r = 0; r < kRows; ++r) {
+      j[r] = e[r] = 0;
+      if (rows && ++cy > b.y1) {
+        cy = b.y0;
+        if (++cz > b.z1) rows = false;
+      }
+      if (rows) {
+        const uint32_t row = (uint32_t)(c.cg.ncx * (cy + c.cg.ncy * cz));
+        j[r] = start[row + b.x0];
+        e[r] = start[row + b.x1 + 1];
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < kRows; ++r) {
+      // up to four points of every lane join the list, lane after lane
+      while (__builtin_amdgcn_ballot_w64(j[r] < e[r]) != 0ull) {
+        const uint32_t m = min(e[r] - j[r], 4u);
+        const uint32_t inc = wave_scan(m);
+        const uint32_t at = listed + inc - m;
+#pragma unroll
+        for (uint32_t q = 0; q < 4; ++q)
+          if (q < m) {
+            cand[at + q] = j[r] + q;
+            cand_of[at + q] = (uint8_t)lane;
+          }
+        j[r] += m;
+        listed += (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
+        // room for one more round of 4 x 64
+        if (listed > kCandidates - 4 * kWavePrims) flush();
+      }
+    }
   }
+  flush();
   if (!hit_range) return;
   uint32_t* out = hit_list + (size_t)blockIdx.x * kWaveHits;
   if (kept > (uint32_t)kWaveHits) {
@@ -629,12 +654,7 @@ __global__ __launch_bounds__(kWavePrims) void k_pfwd(const float* __restrict__ t
   // an entry's place among its primitive's (entries of one primitive in a
   // step are ranked by lane)
   const uint32_t mine = nhit[lane];
-  uint32_t inc = mine;
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    const uint32_t y = __shfl_up(inc, d, 64);
-    if (lane >= d) inc += y;
-  }
+  const uint32_t inc = wave_scan(mine);
   __syncthreads();
   nhit[lane] = inc - mine;
   if (i < n) hit_range[i] = ((inc - mine) << 16) | mine;
