@@ -560,36 +560,100 @@ __global__ __launch_bounds__(kThreads) void k_list_write(ListArgs a,
     if ((takem >> j) & 1u) a.out[y][pos++] = a.vox[y][base + j];
 }
 
-// S1c: nearest-neighbour squared distance for subsample s (block per s).
-__global__ __launch_bounds__(kThreads) void k_nn(const float* __restrict__ mx,
-                                                 const float* __restrict__ my,
-                                                 const float* __restrict__ mz, int64_t ng,
-                                                 int64_t stride, double* __restrict__ best) {
+// S1c: nearest-neighbour squared distances of eight subsamples of a group per
+// block (blockIdx.y: group), so that a pass over the group's centres, which come
+// from L2, serves eight.  The distance is exact to a rounding in double, but
+// formed only for the centres that a float estimate does not rule out: float
+// differences of float centres and their squares are off by less than 4e-7
+// relative, well inside the allowance of 1e-5.  262,144 seeds: one subsample a
+// block in double 800 us, with the float estimate 673, eight a block 264.
+struct NnArgs {
+  const float *mx, *my, *mz;  // [n] centres
+  int64_t first[2], ng[2], stride[2], m[2];
+  double* best[2];
+};
+
+constexpr int kNnPer = 8;
+__global__ __launch_bounds__(kThreads) void k_nn(NnArgs a) {
 #pragma clang fp contract(off)
-  __shared__ double sh[kThreads];
-  const int64_t i = (int64_t)blockIdx.x * stride;
-  const double xi = mx[i], yi = my[i], zi = mz[i];
-  double b = INFINITY;
-  for (int64_t j = threadIdx.x; j < ng; j += kThreads) {
-    if (j == i) continue;
-    const double dx = (double)mx[j] - xi, dy = (double)my[j] - yi, dz = (double)mz[j] - zi;
-    const double xx = dx * dx, yy = dy * dy, zz = dz * dz;
-    const double d2 = (xx + yy) + zz;
-    b = fmin(b, d2);
+  __shared__ double sh[kNnPer][kThreads / 64];
+  const int y = blockIdx.y;
+  const int64_t q0 = (int64_t)blockIdx.x * kNnPer;
+  if (q0 >= a.m[y]) return;
+  const float* __restrict__ mx = a.mx + a.first[y];
+  const float* __restrict__ my = a.my + a.first[y];
+  const float* __restrict__ mz = a.mz + a.first[y];
+  const int64_t ng = a.ng[y];
+  float xf[kNnPer], yf[kNnPer], zf[kNnPer], lim[kNnPer];
+  double b[kNnPer];
+#pragma unroll
+  for (int q = 0; q < kNnPer; ++q) {
+    const int64_t i = min(q0 + q, a.m[y] - 1) * a.stride[y];
+    xf[q] = mx[i];
+    yf[q] = my[i];
+    zf[q] = mz[i];
+    // the group is in voxel order: seeds near in the list give a bound that few
+    // others stay below
+    const int64_t j = i - 32 + (int)(threadIdx.x & 63);
+    b[q] = INFINITY;
+    if (j >= 0 && j < ng && j != i) {
+      const double dx = (double)mx[j] - (double)xf[q], dy = (double)my[j] - (double)yf[q],
+                   dz = (double)mz[j] - (double)zf[q];
+      const double xx = dx * dx, yy = dy * dy, zz = dz * dz;
+      b[q] = (xx + yy) + zz;
+    }
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) b[q] = fmin(b[q], __shfl_xor(b[q], d, 64));
+    lim[q] = (float)b[q] * 1.00001f + 1e-30f;
   }
-  sh[threadIdx.x] = b;
+  // the next centre is loaded while one is tested (past the end: the last
+  // again, a distance already counted)
+  const uint32_t last = (uint32_t)ng - 1u;
+  uint32_t j = min((uint32_t)threadIdx.x, last);
+  float px = mx[j], py = my[j], pz = mz[j];
+  for (uint32_t j0 = 0; j0 <= last; j0 += kThreads) {
+    const uint32_t jn = min(j0 + kThreads + threadIdx.x, last);
+    const float nx = mx[jn], ny = my[jn], nz = mz[jn];
+#pragma unroll
+    for (int q = 0; q < kNnPer; ++q) {
+      const float ex = px - xf[q], ey = py - yf[q], ez = pz - zf[q];
+      const float e2 = ex * ex + ey * ey + ez * ez;
+      if (!(e2 > lim[q])) {
+        if ((int64_t)j == min(q0 + q, a.m[y] - 1) * a.stride[y]) continue;  // the subsample itself
+        const double dx = (double)px - (double)xf[q], dy = (double)py - (double)yf[q],
+                     dz = (double)pz - (double)zf[q];
+        const double xx = dx * dx, yy = dy * dy, zz = dz * dz;
+        const double d2 = (xx + yy) + zz;
+        b[q] = fmin(b[q], d2);
+        lim[q] = (float)b[q] * 1.00001f + 1e-30f;
+      }
+    }
+    j = jn;
+    px = nx;
+    py = ny;
+    pz = nz;
+  }
+#pragma unroll
+  for (int q = 0; q < kNnPer; ++q) {
+    double v = b[q];
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) v = fmin(v, __shfl_xor(v, d, 64));
+    if ((threadIdx.x & 63) == 0) sh[q][threadIdx.x >> 6] = v;
+  }
   __syncthreads();
-  for (int w = kThreads / 2; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w) sh[threadIdx.x] = fmin(sh[threadIdx.x], sh[threadIdx.x + w]);
-    __syncthreads();
+  if (threadIdx.x < kNnPer && q0 + threadIdx.x < a.m[y]) {
+    double v = sh[threadIdx.x][0];
+    for (int w = 1; w < kThreads / 64; ++w) v = fmin(v, sh[threadIdx.x][w]);
+    a.best[y][q0 + threadIdx.x] = v;
   }
-  if (threadIdx.x == 0) best[blockIdx.x] = sh[0];
 }
 
-// Lower median of m <= 4096 values -> sqrt, by bitonic sort in LDS.
-__global__ __launch_bounds__(1024) void k_median(const double* __restrict__ best, int m,
-                                                 double* __restrict__ out) {
+// Lower median of m <= 4096 values -> sqrt, by bitonic sort in LDS (one block
+// per group); 1 for a group of fewer than two seeds.
+__global__ __launch_bounds__(1024) void k_median(NnArgs a, double* __restrict__ out) {
   __shared__ double v[4096];
+  const double* __restrict__ best = a.best[blockIdx.x];
+  const int m = (int)a.m[blockIdx.x];
   for (int i = threadIdx.x; i < 4096; i += 1024) v[i] = (i < m) ? best[i] : INFINITY;
   __syncthreads();
   for (int size = 2; size <= 4096; size <<= 1)
@@ -598,13 +662,13 @@ __global__ __launch_bounds__(1024) void k_median(const double* __restrict__ best
         const int j = i ^ stride;
         if (j > i) {
           const bool up = (i & size) == 0;
-          const double a = v[i], b = v[j];
-          if ((a > b) == up) { v[i] = b; v[j] = a; }
+          const double p = v[i], q = v[j];
+          if ((p > q) == up) { v[i] = q; v[j] = p; }
         }
       }
       __syncthreads();
     }
-  if (threadIdx.x == 0) *out = (m >= 1) ? sqrt(v[(m - 1) / 2]) : 1.0;
+  if (threadIdx.x == 0) out[blockIdx.x] = (m >= 1) ? sqrt(v[(m - 1) / 2]) : 1.0;
 }
 
 __device__ inline void quat_from_R(const double R[3][3], double q[4]) {
@@ -656,7 +720,8 @@ __global__ __launch_bounds__(256) void k_tensor(const float* __restrict__ f, Dim
   if (i >= n) return;  // wave-uniform
   const int64_t vox = i < n_det ? det[i] : cov[i - n_det];
   const int64_t ii = vox % d.nx, jj = (vox / d.nx) % d.ny, kk = vox / (d.nx * d.ny);
-  wave_structure_tensor(f, d, ii, jj, kk, J6 + 6 * i);
+  __shared__ float box[4][kTensorBox];
+  wave_structure_tensor(f, d, ii, jj, kk, box[threadIdx.x >> 6], J6 + 6 * i);
 }
 
 __global__ __launch_bounds__(128) void k_assemble(AssembleArgs a) {
@@ -937,20 +1002,28 @@ hipError_t alloc_draw(const float* f, const float* g32, const gve_grid& g, uint6
   return hipGetLastError();
 }
 
-hipError_t alloc_spacing(const float* theta, int64_t n, int64_t first, int64_t ng, double* best,
+// Both groups' spacing: seeds [0, n_det) and [n_det, n); best: 2 x 4096.
+hipError_t alloc_spacing(const float* theta, int64_t n, int64_t n_det, double* best,
                          double* s_base, hipStream_t s) {
-  if (ng < 2) {
+  NnArgs a{};
+  a.mx = theta;
+  a.my = theta + n;
+  a.mz = theta + 2 * n;
+  for (int y = 0; y < 2; ++y) {
+    a.first[y] = y == 0 ? 0 : n_det;
+    a.ng[y] = y == 0 ? n_det : n - n_det;
+    a.stride[y] = std::max<int64_t>((a.ng[y] + 4095) / 4096, 1);
     // a single seed has no neighbour: unit spacing
-    hipLaunchKernelGGL(k_median, dim3(1), dim3(1024), 0, s, best, 0, s_base);
-    return hipGetLastError();
+    a.m[y] = a.ng[y] < 2 ? 0 : (a.ng[y] + a.stride[y] - 1) / a.stride[y];
+    a.best[y] = best + 4096 * y;
   }
-  const int64_t stride = (ng + 4095) / 4096;
-  const int64_t m = (ng + stride - 1) / stride;
-  hipLaunchKernelGGL(k_nn, dim3((unsigned)m), dim3(kThreads), 0, s, theta + 0 * n + first,
-                     theta + 1 * n + first, theta + 2 * n + first, ng, stride, best);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_median, dim3(1), dim3(1024), 0, s, best, (int)m, s_base);
+  const unsigned blocks = (unsigned)((std::max(a.m[0], a.m[1]) + kNnPer - 1) / kNnPer);
+  if (blocks > 0) {
+    hipLaunchKernelGGL(k_nn, dim3(blocks, 2), dim3(kThreads), 0, s, a);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL(k_median, dim3(2), dim3(1024), 0, s, a, s_base);
   return hipGetLastError();
 }
 

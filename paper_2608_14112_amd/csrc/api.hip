@@ -1472,7 +1472,7 @@ gve_status gve_allocate(gve_ctx* ctx, const float* d_field, gve_grid g, int64_t 
     return o;
   };
   const size_t o_sel = take(8 * gve::alloc_select_words()), o_sb = take(16),
-               o_best = take(4096 * 8),
+               o_best = take(2 * 4096 * 8),
                o_dot = take(sizeof(double) * gve::alloc_dot_tmp_doubles()),
                o_det = take(8 * n_det), o_cov = take(8 * n_cov),
                o_j6 = take(6 * sizeof(double) * (size_t)budget);
@@ -1565,8 +1565,7 @@ gve_status gve_allocate(gve_ctx* ctx, const float* d_field, gve_grid g, int64_t 
   TRY_A(gve::alloc_jitter(g, det, cov, n_det, budget, seed, p->theta, s));
   // S1c: group spacing
   double* sb = F64(o_sb);
-  TRY_A(gve::alloc_spacing(p->theta, budget, 0, n_det, F64(o_best), sb, s));
-  TRY_A(gve::alloc_spacing(p->theta, budget, n_det, n_cov, F64(o_best), sb + 1, s));
+  TRY_A(gve::alloc_spacing(p->theta, budget, n_det, F64(o_best), sb, s));
   // S1d/S1e: frames, scales, values
   TRY_A(gve::alloc_assemble(d_field, g32, g, det, cov, n_det, budget, sb, st_g99, seed, p->theta,
                             F64(o_j6), s));

@@ -340,7 +340,7 @@ hipError_t alloc_draw(const float* f, const float* g32, const gve_grid& g, uint6
                       void* scan_tmp, hipStream_t s);
 hipError_t alloc_jitter(const gve_grid& g, const int64_t* det, const int64_t* cov, int64_t n_det,
                         int64_t n, uint64_t seed, float* theta, hipStream_t s);
-hipError_t alloc_spacing(const float* theta, int64_t n, int64_t first, int64_t ng, double* best,
+hipError_t alloc_spacing(const float* theta, int64_t n, int64_t n_det, double* best,
                          double* s_base, hipStream_t s);
 // J6: 6 n doubles of workspace (the seeds' structure tensors).
 hipError_t alloc_assemble(const float* f, const float* g32, const gve_grid& g, const int64_t* det,

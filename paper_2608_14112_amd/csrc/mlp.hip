@@ -735,7 +735,9 @@ __global__ __launch_bounds__(256) void k_feat_tensor(const float* __restrict__ f
   if (i >= n) return;  // wave-uniform
   int64_t c[3];
   centre_voxel(theta, n, i, g, c);
-  wave_structure_tensor(f, Dims{g.nx, g.ny, g.nz}, c[0], c[1], c[2], J6 + 6 * i);
+  __shared__ float box[4][kTensorBox];
+  wave_structure_tensor(f, Dims{g.nx, g.ny, g.nz}, c[0], c[1], c[2], box[threadIdx.x >> 6],
+                        J6 + 6 * i);
 }
 
 __global__ __launch_bounds__(128) void k_features(FeatArgs a) {
