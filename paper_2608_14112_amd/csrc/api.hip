@@ -127,11 +127,13 @@ gve_status ensure(gve_ctx* ctx, Scratch& s, size_t bytes) {
 
 // Small device block: [0] loss (double), [2] clamp count and [3] non-finite
 // parameter count (u64, cumulative), [4 .. 6] work counters of the counting
-// pass, [16 ..] loss-reduction partials, then kTotalSlots pair-total counters
-// and the degenerate-quaternion counter (u64).  Zeroed when first allocated.
+// pass, [16 ..] loss-reduction partials, then three sets of kTotalSlots
+// pair-total counters and the degenerate-quaternion counter (u64): the general
+// binning's, and two that direct binnings use in turn.  Zeroed when first
+// allocated.
 gve_status ensure_dloss(gve_ctx* ctx) {
   if (ctx->ws.dloss.ptr) return GVE_OK;
-  const size_t nd = 16 + gve::loss_reduce_tmp_doubles() + gve::kTotalSlots + 1;
+  const size_t nd = 16 + gve::loss_reduce_tmp_doubles() + 3 * (gve::kTotalSlots + 1);
   TRY(ensure(ctx, ctx->ws.dloss, sizeof(double) * nd));
   TRY_HIP(ctx, gve::fill_u64(static_cast<unsigned long long*>(ctx->ws.dloss.ptr), (int64_t)nd,
                              ctx->stream));
@@ -141,6 +143,27 @@ gve_status ensure_dloss(gve_ctx* ctx) {
 unsigned long long* pair_total_slots(gve_ctx* ctx) {
   return reinterpret_cast<unsigned long long*>(ctx->ws.dloss.ptr) + 16 +
          gve::loss_reduce_tmp_doubles();
+}
+
+unsigned long long* direct_slots(gve_ctx* ctx, int set) {
+  return pair_total_slots(ctx) + (gve::kTotalSlots + 1) * (1 + set);
+}
+
+// Pair and degenerate-quaternion counts of a direct binning whose counts are
+// still on the device (waits for it).
+gve_status resolve_counts(gve_ctx* ctx) {
+  if (ctx->pending_set < 0) return GVE_OK;
+  TRY_HIP(ctx, hipMemcpyAsync(ctx->ws.h_pinned, direct_slots(ctx, ctx->pending_set),
+                              sizeof(unsigned long long) * (gve::kTotalSlots + 1),
+                              hipMemcpyDeviceToHost, ctx->stream));
+  TRY_HIP(ctx, hipStreamSynchronize(ctx->stream));
+  const unsigned long long* h = static_cast<const unsigned long long*>(ctx->ws.h_pinned);
+  int64_t pairs = 0;
+  for (int j = 0; j < gve::kTotalSlots; ++j) pairs += (int64_t)h[j];
+  ctx->stats.n_overlaps = pairs;
+  ctx->stats.n_degenerate_q = (int64_t)h[gve::kTotalSlots];
+  ctx->pending_set = -1;
+  return GVE_OK;
 }
 
 gve_status validate_options(const gve_ctx* ctx, const gve_options& o) {
@@ -222,7 +245,7 @@ struct Binned {
   gve::Schedule sched;
   const uint32_t* gid = nullptr;   // primitive of each sorted pair
   const uint32_t* slot = nullptr;  // its emission index (deterministic sums), else null
-  const uint32_t* start = nullptr;
+  gve::BrickLists lists{};         // each brick's range of the pair list
   const uint32_t* sorted_keys = nullptr;  // brick key of each sorted pair
   int64_t npairs = 0;      // pairs (-1: counted on the device only)
   int64_t capacity = 0;    // pairs the buffers hold (>= npairs)
@@ -276,6 +299,48 @@ bool same_items(const std::vector<gve::ItemDesc>& a, const std::vector<gve::Item
          (a.empty() || std::memcmp(a.data(), b.data(), sizeof(gve::ItemDesc) * a.size()) == 0);
 }
 
+bool stream_capturing(const gve_ctx* ctx) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(ctx->stream, &st) != hipSuccess) {
+    (void)hipGetLastError();
+    return true;
+  }
+  return st != hipStreamCaptureStatusNone;
+}
+
+// Direct binning tests every (brick, primitive) pair of a volume: taken up to
+// this many tests over the set (also the length of its list: 128 MB at most)
+// and this many primitives in a volume (a brick's workgroup walks them 2,048 at
+// a time).  An evaluation, general binning -> direct: 64^3 x 2,048 (2^18 tests)
+// 133 -> 73 us, 64^3 x 16,384 (2^23) 217 -> 144, 128^3 x 16,384 (2^25) 162 ->
+// 119; 2^26 tests 165 -> 152 and its refinement iterations 223 -> 231, 2^27
+// 175 -> 227.  64 bricks x 32,768 primitives 314 -> 284, x 65,536 530 -> 541.
+constexpr int64_t kDirectTests = (int64_t)1 << 25;
+constexpr int64_t kDirectPrims = 32768;
+
+// Whether the set (with the current brick shape) is binned directly.  Not with
+// reproducible sums or the queue schedule, which need the general binning's
+// emission order and sorted ranges, nor in the allocation-free path, whose
+// scratch the lists would not fit, nor while the stream is being captured (a
+// binning there is refused: the general one waits for the device).
+bool bins_directly(const gve_ctx* ctx, const Vol& vol) {
+  if (ctx->opt.deterministic != 0 || sched_of(ctx) == GVE_SCHED_QUEUE || ctx->arena_base)
+    return false;
+  const int64_t bxy = brick_xy(ctx), bz = brick_z(ctx);
+  double tests = 0.0;
+  for (int i = 0; i < vol.n; ++i) {
+    const gve_grid& g = vol.grids[i];
+    const int64_t nbx = (g.nx + bxy - 1) / bxy, nby = (g.ny + bxy - 1) / bxy,
+                  nbz = (g.nz + bz - 1) / bz, np = vol.prim_off[i + 1] - vol.prim_off[i];
+    if (nbx > gve::kDirectAxis || nby > gve::kDirectAxis || nbz > gve::kDirectAxis ||
+        np > kDirectPrims)
+      return false;
+    tests += (double)nbx * (double)nby * (double)nbz * (double)np;
+    if (tests > (double)kDirectTests) return false;
+  }
+  return !stream_capturing(ctx);
+}
+
 // Flags of the asynchronous binning in the small device block: [7] fits
 // (u32) and sticky (u32), [8] the largest box pair total and [9] the largest
 // kept pair total seen (u64).
@@ -288,6 +353,61 @@ unsigned long long* need_slot(gve_ctx* ctx) {
 }
 unsigned long long* need_pairs_slot(gve_ctx* ctx) {
   return static_cast<unsigned long long*>(ctx->ws.dloss.ptr) + 9;
+}
+
+void binned_stats(gve_ctx* ctx, int64_t n, const gve::BrickGeom& bg) {
+  ctx->stats.n_primitives = n;
+  ctx->stats.n_bricks = bg.nbricks;
+  ctx->stats.bin_brick = bg.Bxy;
+  ctx->stats.bin_brick_z = bg.Bz;
+  ctx->stats.bin_schedule = sched_of(ctx);
+  ctx->stats.bin_waves = bg.waves;
+}
+
+// prep -> direct binning: no host read, no sort; the pair count stays on the
+// device until it is asked for.
+gve_status bin_direct(gve_ctx* ctx, const gve_params* p, const Vol& vol, const gve::BrickGeom& bg,
+                      Binned* out) {
+  auto& ws = ctx->ws;
+  hipStream_t s = ctx->stream;
+  const int64_t n = p->n;
+  const gve::ItemDesc* items = static_cast<const gve::ItemDesc*>(ws.items.ptr);
+  int64_t tests = 0;
+  for (int i = 0; i < vol.n; ++i) {
+    const gve::ItemDesc& d = ctx->items_host[(size_t)i];
+    tests += (int64_t)d.nbx * d.nby * d.nbz * (vol.prim_off[i + 1] - vol.prim_off[i]);
+  }
+  TRY(ensure_dloss(ctx));
+  // at least 1 MB, so that a growing small workload seldom reallocates
+  TRY(ensure(ctx, ws.vals[0], std::max<size_t>(sizeof(uint32_t) * (size_t)tests, (size_t)1 << 20)));
+  TRY(ensure(ctx, ws.brick_start, 2 * sizeof(uint32_t) * (size_t)(bg.nbricks + 1)));
+  TRY(ensure(ctx, ws.brick_box, sizeof(uint64_t) * (size_t)n));
+  uint32_t* list = static_cast<uint32_t*>(ws.vals[0].ptr);
+  uint32_t* start = static_cast<uint32_t*>(ws.brick_start.ptr);
+  uint32_t* end = start + bg.nbricks + 1;
+  uint64_t* box = static_cast<uint64_t*>(ws.brick_box.ptr);
+  unsigned long long* total = direct_slots(ctx, ctx->direct_set);
+  TRY_HIP(ctx, gve::launch_prep(p->theta, n, items, vol.n, ctx->opt.k, bg, p->rec, p->count, total,
+                                s, box));
+  TRY_HIP(ctx, gve::launch_bin_direct(p->rec, n, box, items, vol.n, bg, ctx->opt.k, list, start,
+                                      end, total, direct_slots(ctx, ctx->direct_set ^ 1), s));
+  ctx->pending_set = ctx->direct_set;
+  ctx->direct_set ^= 1;
+  out->sched = gve::Schedule();
+  out->sched.kind = sched_of(ctx);
+  out->bg = bg;
+  out->items = items;
+  out->nitems = vol.n;
+  out->gid = list;
+  out->slot = nullptr;
+  out->lists = gve::BrickLists{start, end};
+  out->sorted_keys = nullptr;
+  out->npairs = -1;
+  out->capacity = tests;
+  out->box_total = -1;
+  out->fits = nullptr;
+  binned_stats(ctx, n, bg);
+  return GVE_OK;
 }
 
 // prep -> scan -> cull -> scan -> emit -> radix sort -> brick ranges (->
@@ -313,6 +433,7 @@ gve_status bin_vol(gve_ctx* ctx, const gve_params* p, const Vol& vol, Binned* ou
   TRY(upload_items(ctx, vol, bg.Bxy, bg.Bz, &bg.nbricks));
   if (bg.nbricks >= ((int64_t)1 << 31))
     return fail(ctx, GVE_ERR_UNSUPPORTED, "too many bricks for 32-bit brick keys");
+  if (!ec && bins_directly(ctx, vol)) return bin_direct(ctx, p, vol, bg, out);
   // capacity sized for these volumes and this brick shape only
   if (async && (ctx->box_cap <= 0 || !same_items(ctx->pair_cap_items, ctx->items_host)))
     async = false;
@@ -439,17 +560,13 @@ gve_status bin_vol(gve_ctx* ctx, const gve_params* p, const Vol& vol, Binned* ou
     out->slot = vals[which];
     out->gid = g;
   }
-  out->start = start;
+  out->lists = gve::BrickLists{start, start + 1};
   out->sorted_keys = keys[which];
   out->npairs = async ? -1 : (int64_t)T;
   out->capacity = (int64_t)T;
   out->fits = fits;
-  ctx->stats.n_primitives = n;
-  ctx->stats.n_bricks = bg.nbricks;
-  ctx->stats.bin_brick = bg.Bxy;
-  ctx->stats.bin_brick_z = bg.Bz;
-  ctx->stats.bin_schedule = sched_of(ctx);
-  ctx->stats.bin_waves = bg.waves;
+  binned_stats(ctx, n, bg);
+  ctx->pending_set = -1;
   if (!async) ctx->stats.n_overlaps = (int64_t)T;
   return GVE_OK;
 }
@@ -490,7 +607,7 @@ gve_status fused(gve_ctx* ctx, const gve_params* p, const Binned& bn, const floa
                  float* part, float* brick_loss, int mode) {
   if (bn.sched.kind == gve::kSchedQueue)
     TRY_HIP(ctx, gve::fill_u32(bn.sched.counter, 1, ctx->stream));
-  TRY_HIP(ctx, gve::launch_fused(p->rec, bn.gid, bn.start, bn.items, bn.nitems, bn.bg,
+  TRY_HIP(ctx, gve::launch_fused(p->rec, bn.gid, bn.lists, bn.items, bn.nitems, bn.bg,
                                  ctx->opt.k, d_field, p->acc, p->n, part, bn.slot, brick_loss,
                                  bn.sched, ctx->stream, mode));
   return GVE_OK;
@@ -656,7 +773,7 @@ gve_status gve_destroy(gve_ctx* ctx) {
                     &ws.p_cls, &ws.p_pts, &ws.p_acc, &ws.p_sorted, &ws.p_hits, &ws.p_coef,
                     &ws.p_corner, &ws.p_keys[0], &ws.p_keys[1],
                     &ws.p_idx[0], &ws.p_idx[1], &ws.p_start, &ws.p_loss, &ws.dense, &ws.snap,
-                    &ws.box_off, &ws.owner, &ws.slot_gid};
+                    &ws.box_off, &ws.owner, &ws.slot_gid, &ws.brick_box};
   static_assert(sizeof(all) / sizeof(all[0]) * sizeof(Scratch) + sizeof(void*) ==
                     sizeof(gve::Workspace),
                 "every scratch buffer of the workspace is freed");
@@ -793,7 +910,7 @@ gve_status gve_evaluate(gve_ctx* ctx, const gve_params* p, gve_grid g, float* d_
   TRY(set_device(ctx));
   Binned bn;
   TRY(bin(ctx, p, g, &bn));
-  TRY_HIP(ctx, gve::launch_forward(p->rec, bn.gid, bn.start, bn.items, bn.nitems, bn.bg,
+  TRY_HIP(ctx, gve::launch_forward(p->rec, bn.gid, bn.lists, bn.items, bn.nitems, bn.bg,
                                    ctx->opt.k, d_out, bn.sched, ctx->stream));
   return GVE_OK;
 }
@@ -1202,7 +1319,7 @@ gve_status gve_count_pairs(gve_ctx* ctx, const gve_params* p, gve_grid g, int64_
   TRY(bin(ctx, p, g, &bn));
   unsigned long long* cnt = reinterpret_cast<unsigned long long*>(ctx->ws.dloss.ptr) + 4;
   TRY_HIP(ctx, gve::fill_u64(cnt, 3, ctx->stream));
-  TRY_HIP(ctx, gve::launch_count(p->rec, bn.gid, bn.start, bn.items, bn.nitems, bn.bg, ctx->opt.k,
+  TRY_HIP(ctx, gve::launch_count(p->rec, bn.gid, bn.lists, bn.items, bn.nitems, bn.bg, ctx->opt.k,
                                  cnt, ctx->stream));
   TRY_HIP(ctx, hipMemcpyAsync(ctx->ws.h_pinned, cnt, 24, hipMemcpyDeviceToHost, ctx->stream));
   TRY_HIP(ctx, hipStreamSynchronize(ctx->stream));
@@ -1242,7 +1359,7 @@ gve_status gve_bin_pairs(gve_ctx* ctx, const gve_params* p, gve_grid g, uint32_t
       TRY_HIP(ctx, hipMemcpyAsync(d_vals, bn.slot ? bn.slot : bn.gid, sizeof(uint32_t) * T,
                                   hipMemcpyDeviceToDevice, s));
     }
-    TRY_HIP(ctx, hipMemcpyAsync(d_brick_start, bn.start,
+    TRY_HIP(ctx, hipMemcpyAsync(d_brick_start, bn.lists.start,
                                 sizeof(uint32_t) * (size_t)(bn.bg.nbricks + 1),
                                 hipMemcpyDeviceToDevice, s));
   }
@@ -1391,7 +1508,9 @@ gve_status refine_vol(gve_ctx* ctx, gve_params* p, const float* d_field, const V
     }
   }
   hipStream_t s = ctx->stream;
-  const int32_t first_async = std::min<int32_t>(1, iters);
+  // a directly binned set has no buffer to overflow: no restart points
+  const bool direct = bins_directly(ctx, vol);
+  const int32_t first_async = direct ? iters : std::min<int32_t>(1, iters);
   TRY(refine_iters(ctx, p, d_field, vol, 0, first_async, hist, timing, false));
   for (int32_t c0 = first_async; c0 < iters; c0 += kCheckEvery) {
     const int32_t c1 = std::min(iters, c0 + kCheckEvery);
@@ -1414,7 +1533,7 @@ gve_status refine_vol(gve_ctx* ctx, gve_params* p, const float* d_field, const V
       TRY(refine_iters(ctx, p, d_field, vol, c0, c1, hist, timing, false));
     }
   }
-  if (iters > 0) {
+  if (iters > 0 && !direct) {
     // pair and degenerate-quaternion counts of the last (asynchronous) binning
     unsigned char* hp = static_cast<unsigned char*>(ctx->ws.h_pinned);
     TRY_HIP(ctx, hipMemcpyAsync(hp, p->offset + p->n, sizeof(uint32_t), hipMemcpyDeviceToHost, s));
@@ -1573,7 +1692,7 @@ gve_status gve_allocate(gve_ctx* ctx, const float* d_field, gve_grid g, int64_t 
   Binned bn;
   st = bin(ctx, p, g, &bn);
   if (st != GVE_OK) return cleanup(st);
-  TRY_A(gve::launch_forward(p->rec, bn.gid, bn.start, bn.items, bn.nitems, bn.bg, ctx->opt.k, g32,
+  TRY_A(gve::launch_forward(p->rec, bn.gid, bn.lists, bn.items, bn.nitems, bn.bg, ctx->opt.k, g32,
                             bn.sched, s));
   TRY_A(gve::alloc_weights(g32, d_field, M, p->theta + 10 * budget, budget, F64(o_dot), s));
 #undef TRY_A
@@ -1600,6 +1719,10 @@ gve_status gve_allocate(gve_ctx* ctx, const float* d_field, gve_grid g, int64_t 
 
 gve_status gve_get_stats(const gve_ctx* ctx, gve_stats* out) {
   if (!ctx || !out) return GVE_ERR_INVALID_ARGUMENT;
+  if (ctx->pending_set >= 0 && !stream_capturing(ctx)) {
+    TRY(set_device(ctx));
+    TRY(resolve_counts(const_cast<gve_ctx*>(ctx)));
+  }
   *out = ctx->stats;
   const gve::Workspace& w = ctx->ws;
   const gve::Scratch* all[] = {&w.keys[0], &w.keys[1], &w.vals[0], &w.vals[1], &w.brick_start,
@@ -1610,7 +1733,7 @@ gve_status gve_get_stats(const gve_ctx* ctx, gve_stats* out) {
                                &w.order_keys[0], &w.order_keys[1], &w.order_vals[0],
                                &w.order_vals[1], &w.queue, &w.p_cls, &w.p_pts, &w.p_acc,
                                &w.p_sorted, &w.p_hits, &w.p_coef, &w.p_corner, &w.p_keys[0], &w.p_keys[1], &w.p_idx[0], &w.p_idx[1],
-                               &w.p_start, &w.p_loss, &w.dense, &w.snap};
+                               &w.p_start, &w.p_loss, &w.dense, &w.snap, &w.brick_box};
   static_assert(sizeof(all) / sizeof(all[0]) * sizeof(gve::Scratch) + sizeof(void*) ==
                     sizeof(gve::Workspace),
                 "every scratch buffer of the workspace is counted");
@@ -2056,7 +2179,7 @@ gve_status gve_batch_evaluate(gve_ctx* ctx, const gve_batch* b, float* d_out) {
   TRY(set_device(ctx));
   Binned bn;
   TRY(bin_vol(ctx, b->params, vol_of(b), &bn));
-  TRY_HIP(ctx, gve::launch_forward(b->params->rec, bn.gid, bn.start, bn.items, bn.nitems, bn.bg,
+  TRY_HIP(ctx, gve::launch_forward(b->params->rec, bn.gid, bn.lists, bn.items, bn.nitems, bn.bg,
                                    ctx->opt.k, d_out, bn.sched, ctx->stream));
   return GVE_OK;
 }
@@ -2111,7 +2234,7 @@ gve_status gve_batch_count_pairs(gve_ctx* ctx, const gve_batch* b, int64_t* h_in
   TRY(bin_vol(ctx, b->params, vol_of(b), &bn));
   unsigned long long* cnt = reinterpret_cast<unsigned long long*>(ctx->ws.dloss.ptr) + 4;
   TRY_HIP(ctx, gve::fill_u64(cnt, 3, ctx->stream));
-  TRY_HIP(ctx, gve::launch_count(b->params->rec, bn.gid, bn.start, bn.items, bn.nitems, bn.bg,
+  TRY_HIP(ctx, gve::launch_count(b->params->rec, bn.gid, bn.lists, bn.items, bn.nitems, bn.bg,
                                  ctx->opt.k, cnt, ctx->stream));
   TRY_HIP(ctx, hipMemcpyAsync(ctx->ws.h_pinned, cnt, 24, hipMemcpyDeviceToHost, ctx->stream));
   TRY_HIP(ctx, hipStreamSynchronize(ctx->stream));
@@ -2294,6 +2417,7 @@ gve_status gve_autotune(gve_ctx* ctx, const gve_params* p, const float* d_field,
   {
     Binned bn;
     TRY(bin_vol(ctx, P, vol, &bn));
+    TRY(resolve_counts(ctx));
   }
   const double cover = (double)ctx->stats.n_overlaps * 512.0 / (double)M;
   const std::array<int, 4> key = {vol.n, bucket((double)M, 1.0), bucket((double)P->n, 1.0),

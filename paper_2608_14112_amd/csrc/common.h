@@ -73,7 +73,7 @@ struct ItemDesc {
   int32_t nbx, nby, nbz;           // bricks per axis
   uint32_t brick0;                 // first global brick id
   uint32_t prim0;                  // first primitive
-  uint32_t pad;
+  uint32_t list0;                  // bricks x primitives of the volumes before (direct binning)
 };
 static_assert(sizeof(ItemDesc) == 80, "ItemDesc layout");
 
@@ -111,6 +111,7 @@ struct Workspace {
   // the centres
   Scratch p_cls, p_pts, p_acc, p_sorted, p_keys[2], p_idx[2], p_start, p_loss, p_hits, p_coef, p_corner;
   Scratch dense;                 // float [M] residual of the dense reference path
+  Scratch brick_box;             // uint64 [n] packed brick boxes (direct binning)
   Scratch snap;                  // float [3][11][n] parameters and Adam moments (refinement
                                  // restart point) + counters
   void* h_pinned = nullptr;      // pinned host staging (512 bytes)
@@ -146,6 +147,10 @@ struct gve_ctx {
   // descriptors and brick shape they were sized for.
   int64_t box_cap = 0, pair_cap = 0;
   std::vector<gve::ItemDesc> pair_cap_items;
+  // Direct binning: which of the two sets of pair-total slots the next one uses,
+  // and the set of the last one while its counts have not been read
+  // (gve_get_stats), else -1.
+  int direct_set = 0, pending_set = -1;
 };
 
 struct gve_params {
@@ -180,6 +185,11 @@ hipError_t scan_exclusive_u32(const uint32_t* in, uint32_t* out, int64_t n, void
 size_t sort_hist_bytes(int64_t n);
 hipError_t radix_sort_pairs(uint32_t* keys[2], uint32_t* vals[2], int64_t n, int bits,
                             void* hist, int* which, hipStream_t s, const uint32_t* dn = nullptr);
+
+// Pairs of brick b: list positions [start[b], end[b]).
+struct BrickLists {
+  const uint32_t *start, *end;
+};
 
 // Bricks are Bxy x Bxy x Bz voxels: a workgroup's lanes own the Bxy^2 voxel
 // columns, each lane Bz voxels of its column.
@@ -218,9 +228,22 @@ struct Schedule {
 // queueing on one; the host sums the slots.  total[kTotalSlots] counts the
 // primitives whose quaternion has |q| < 1e-12 (taken as the identity).
 constexpr int kTotalSlots = 32;
+// With brick_box (direct binning) also the bricks of each primitive's box,
+// packed (see launch_bin_direct), and no pair total.
 hipError_t launch_prep(const float* theta, int64_t n, const ItemDesc* items, int nitems, float k,
                        BrickGeom bg, Record* rec, uint32_t* count, unsigned long long* total,
-                       hipStream_t s);
+                       hipStream_t s, uint64_t* brick_box = nullptr);
+// Direct binning of a small set: a workgroup per brick tests every primitive of
+// its volume and writes those that launch_cull would keep, in increasing index,
+// to list[b's slot ..] (a slot holds the volume's primitive count), with their
+// range in start[b], end[b]; the number of pairs is added to
+// total[b % kTotalSlots] and next [kTotalSlots + 1] is zeroed (the slots of the
+// binning after this one).  Bricks per axis <= kDirectAxis.
+constexpr int64_t kDirectAxis = 1023;
+hipError_t launch_bin_direct(const Record* rec, int64_t n, const uint64_t* brick_box,
+                             const ItemDesc* items, int nitems, BrickGeom bg, float k,
+                             uint32_t* list, uint32_t* start, uint32_t* end,
+                             unsigned long long* total, unsigned long long* next, hipStream_t s);
 // Culling: box_off = exclusive scan of prep's box brick counts; the keys of
 // the box bricks a separating plane does not part from the support m^2 < k^2
 // go to kept[box_off[i] ..] and their number to count[i].
@@ -261,7 +284,7 @@ bool brick_waves_supported(int bxy, int bz, int waves);
 // Workgroups of the fused kernel that fit on the device at once.
 int fused_resident_groups(int bxy, int bz, int waves, int device);
 hipError_t launch_forward(const Record* rec, const uint32_t* pair_gid,
-                          const uint32_t* brick_start, const ItemDesc* items, int nitems,
+                          BrickLists lists, const ItemDesc* items, int nitems,
                           BrickGeom bg, float k, float* out, const Schedule& sc, hipStream_t s);
 // part == nullptr: float atomics into acc [n][kAccStride].  Otherwise each (primitive,
 // brick) pair stores its ten sums to part[pslot[j] * 10 + a], pslot[j] = the
@@ -271,11 +294,11 @@ hipError_t launch_forward(const Record* rec, const uint32_t* pair_gid,
 // (no loss), or the loss alone (no sums).
 enum { kFusedGrad = 0, kFusedVjp = 1, kFusedLoss = 2 };
 hipError_t launch_fused(const Record* rec, const uint32_t* pair_gid,
-                        const uint32_t* brick_start, const ItemDesc* items, int nitems,
+                        BrickLists lists, const ItemDesc* items, int nitems,
                         BrickGeom bg, float k, const float* field, float* acc, int64_t n,
                         float* part, const uint32_t* pslot, float* brick_loss,
                         const Schedule& sc, hipStream_t s, int mode = kFusedGrad);
-hipError_t launch_count(const Record* rec, const uint32_t* pair_gid, const uint32_t* brick_start,
+hipError_t launch_count(const Record* rec, const uint32_t* pair_gid, BrickLists lists,
                         const ItemDesc* items, int nitems, BrickGeom bg, float k,
                         unsigned long long* counts, hipStream_t s);
 // Sum of brick_loss in double into *out; part holds loss_reduce_tmp_doubles().

@@ -419,14 +419,15 @@ __device__ inline uint32_t xcd_brick(uint32_t w, uint32_t nb) {
 template <int BXY, int BZ>
 __device__ __attribute__((always_inline)) inline void forward_brick(const Record* __restrict__ rec,
                                      const uint32_t* __restrict__ pair_gid,
-                                     const uint32_t* __restrict__ brick_start,
+                                     BrickLists lists,
                                      const ItemDesc* __restrict__ items, int nitems, uint32_t b,
                                      float thr, float* __restrict__ out) {
   const Site st = site_of<BXY, BZ>(items, nitems, b);
   float acc[BZ];
 #pragma unroll
   for (int zz = 0; zz < BZ; ++zz) acc[zz] = 0.0f;
-  accumulate_brick<BZ>(rec, pair_gid, brick_start[b], brick_start[b], 1u, brick_start[b + 1],
+  const uint32_t j0 = lists.start[b];
+  accumulate_brick<BZ>(rec, pair_gid, j0, j0, 1u, lists.end[b],
                        st.px, st.py, st.pz0, st.iz0, __builtin_amdgcn_ballot_w64(st.col_in), thr,
                        acc, nullptr);
   if (st.col_in) {
@@ -439,19 +440,19 @@ __device__ __attribute__((always_inline)) inline void forward_brick(const Record
 template <int BXY, int BZ>
 __global__ __launch_bounds__(BXY* BXY) void k_forward(const Record* __restrict__ rec,
                                                   const uint32_t* __restrict__ pair_gid,
-                                                  const uint32_t* __restrict__ brick_start,
+                                                  BrickLists lists,
                                                   const ItemDesc* __restrict__ items, int nitems,
                                                   uint32_t nbricks, int xcd, float thr,
                                                   float* __restrict__ out) {
   const uint32_t b = xcd ? xcd_brick(blockIdx.x, nbricks) : blockIdx.x;
-  forward_brick<BXY, BZ>(rec, pair_gid, brick_start, items, nitems, b, thr, out);
+  forward_brick<BXY, BZ>(rec, pair_gid, lists, items, nitems, b, thr, out);
 }
 
 // The same with the brick's offsets dealt to BZ / 8 waves.
 template <int BZ>
 __global__ __launch_bounds__(BZ / kSlice * 64) void k_forward_sliced(
     const Record* __restrict__ rec, const uint32_t* __restrict__ pair_gid,
-    const uint32_t* __restrict__ brick_start, const ItemDesc* __restrict__ items, int nitems,
+    BrickLists lists, const ItemDesc* __restrict__ items, int nitems,
     uint32_t nbricks, int xcd, float thr, float* __restrict__ out) {
   const uint32_t b = xcd ? xcd_brick(blockIdx.x, nbricks) : blockIdx.x;
   const int slice = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -459,7 +460,7 @@ __global__ __launch_bounds__(BZ / kSlice * 64) void k_forward_sliced(
   float acc[kSlice];
 #pragma unroll
   for (int u = 0; u < kSlice; ++u) acc[u] = 0.0f;
-  accumulate_slice<BZ>(rec, pair_gid, brick_start[b], brick_start[b + 1], st.px, st.py, st.pz0,
+  accumulate_slice<BZ>(rec, pair_gid, lists.start[b], lists.end[b], st.px, st.py, st.pz0,
                        st.iz0, slice, thr, acc, nullptr);
   if (st.col_in) {
 #pragma unroll
@@ -600,7 +601,7 @@ constexpr int kGrad = kFusedGrad, kVjp = kFusedVjp, kLoss = kFusedLoss;
 template <int BXY, int BZ, int MODE, int W, bool SLICED>
 __device__ __attribute__((always_inline)) inline void fused_brick(const Record* __restrict__ rec,
                                    const uint32_t* __restrict__ pair_gid,
-                                   const uint32_t* __restrict__ brick_start,
+                                   BrickLists lists,
                                    const ItemDesc* __restrict__ items, int nitems, uint32_t b,
                                    float thr, const float* __restrict__ field,
                                    float* __restrict__ gacc, int64_t n, float* __restrict__ part,
@@ -622,7 +623,7 @@ __device__ __attribute__((always_inline)) inline void fused_brick(const Record* 
   const int iz0 = st.iz0;
   const bool col_in = st.col_in;
   const uint64_t cols = __builtin_amdgcn_ballot_w64(col_in);
-  const uint32_t j0 = brick_start[b], j1 = brick_start[b + 1];
+  const uint32_t j0 = lists.start[b], j1 = lists.end[b];
   const uint32_t jw = j0 + (W > 1 ? (uint32_t)wave : 0u);  // this wave's first pair
   // target reads: lanes outside the volume read past the record count (0);
   // an inside lane's offset is below one plane and below 2^29 bytes
@@ -830,7 +831,7 @@ constexpr int fused_lds_floats(int bz, int mode, int w, int waves, bool sliced) 
 template <int BXY, int BZ, int MODE, int W, bool SLICED>
 __global__ __launch_bounds__(BXY* BXY* W) void k_fused(const Record* __restrict__ rec,
                                                 const uint32_t* __restrict__ pair_gid,
-                                                const uint32_t* __restrict__ brick_start,
+                                                BrickLists lists,
                                                 const ItemDesc* __restrict__ items, int nitems,
                                                 uint32_t nbricks, int xcd, float thr,
                                                 const float* __restrict__ field,
@@ -843,7 +844,7 @@ __global__ __launch_bounds__(BXY* BXY* W) void k_fused(const Record* __restrict_
   __shared__ uint32_t steps[kWaves == 1 && MODE == kGrad ? kStepCap : 1];
   __shared__ __attribute__((aligned(16))) float comb[fused_lds_floats(BZ, MODE, W, kWaves, SLICED)];
   const uint32_t b = xcd ? xcd_brick(blockIdx.x, nbricks) : blockIdx.x;
-  fused_brick<BXY, BZ, MODE, W, SLICED>(rec, pair_gid, brick_start, items, nitems, b, thr, field,
+  fused_brick<BXY, BZ, MODE, W, SLICED>(rec, pair_gid, lists, items, nitems, b, thr, field,
                                         gacc, n, part, pslot, brick_loss, red, steps, comb);
 }
 
@@ -853,7 +854,7 @@ __global__ __launch_bounds__(BXY* BXY* W) void k_fused(const Record* __restrict_
 template <int BXY, int BZ, int MODE, int W>
 __global__ __launch_bounds__(BXY* BXY* W) void k_fused_queue(const Record* __restrict__ rec,
                                                       const uint32_t* __restrict__ pair_gid,
-                                                      const uint32_t* __restrict__ brick_start,
+                                                      BrickLists lists,
                                                       const ItemDesc* __restrict__ items,
                                                       int nitems, uint32_t nbricks,
                                                       const uint32_t* __restrict__ order,
@@ -874,7 +875,7 @@ __global__ __launch_bounds__(BXY* BXY* W) void k_fused_queue(const Record* __res
     const uint32_t w = __builtin_amdgcn_readfirstlane(next);
     __syncthreads();
     if (w >= nbricks) break;
-    fused_brick<BXY, BZ, MODE, W, false>(rec, pair_gid, brick_start, items, nitems, order[w], thr,
+    fused_brick<BXY, BZ, MODE, W, false>(rec, pair_gid, lists, items, nitems, order[w], thr,
                                          field, gacc, n, part, pslot, brick_loss, red, steps, comb);
     // A loss-only brick ends in a branch on thread 0, as the loop begins with
     // one.  Without a barrier between them the compiler joins the two, and the
@@ -891,7 +892,7 @@ __global__ __launch_bounds__(BXY* BXY* W) void k_fused_queue(const Record* __res
 template <int BXY, int BZ>
 __global__ __launch_bounds__(BXY* BXY) void k_count(const Record* __restrict__ rec,
                                                 const uint32_t* __restrict__ pair_gid,
-                                                const uint32_t* __restrict__ brick_start,
+                                                BrickLists lists,
                                                 const ItemDesc* __restrict__ items, int nitems,
                                                 float thr,
                                                 unsigned long long* __restrict__ counts) {
@@ -902,7 +903,7 @@ __global__ __launch_bounds__(BXY* BXY) void k_count(const Record* __restrict__ r
   const uint64_t cols = __builtin_amdgcn_ballot_w64(st.col_in);
   const int wave = threadIdx.x >> 6;
   unsigned long long nin = 0, ncand = 0, npair = 0;
-  for (uint32_t j = brick_start[b]; j < brick_start[b + 1]; ++j) {
+  for (uint32_t j = lists.start[b]; j < lists.end[b]; ++j) {
     const Record r = load_record(rec, __builtin_amdgcn_readfirstlane(pair_gid[j]));
     const ColumnSetup s = column_setup<BZ>(r, st.px, st.py, st.pz0, st.iz0);
     uint32_t active = 0u;
@@ -969,6 +970,23 @@ __global__ __launch_bounds__(kRedThreads) void k_loss_final(const double* __rest
   if (threadIdx.x == 0) out[0] = sh[0];
 }
 
+
+// The whole sum in one workgroup, for few bricks: one launch instead of two.
+constexpr int kOneThreads = 1024;
+constexpr int64_t kOneBricks = 8192;
+__global__ __launch_bounds__(kOneThreads) void k_loss_one(const float* __restrict__ x, int64_t n,
+                                                          double* __restrict__ out) {
+  __shared__ double sh[kOneThreads];
+  double s = 0.0;
+  for (int64_t i = threadIdx.x; i < n; i += kOneThreads) s += (double)x[i];
+  sh[threadIdx.x] = s;
+  __syncthreads();
+  for (int w = kOneThreads / 2; w > 0; w >>= 1) {
+    if ((int)threadIdx.x < w) sh[threadIdx.x] += sh[threadIdx.x + w];
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) out[0] = sh[0];
+}
 
 // Per-volume loss: one workgroup per volume sums its bricks' losses in double
 // (fixed order, so deterministic).
@@ -1050,7 +1068,7 @@ int fused_resident_groups(int bxy, int bz, int waves, int device) {
   return 0;
 }
 
-hipError_t launch_forward(const Record* rec, const uint32_t* pair_gid, const uint32_t* brick_start,
+hipError_t launch_forward(const Record* rec, const uint32_t* pair_gid, BrickLists lists,
                           const ItemDesc* items, int nitems, BrickGeom bg, float k, float* out,
                           const Schedule& sc, hipStream_t s) {
   const float thr = -kHalfLog2e * k * k;
@@ -1060,7 +1078,7 @@ hipError_t launch_forward(const Record* rec, const uint32_t* pair_gid, const uin
 #define GVE_CASE(Z)                                                                           \
   if (bg.Bxy == 8 && bg.Bz == Z && bg.nbricks <= kSlicedForwardBricks) {                        \
     hipLaunchKernelGGL((k_forward_sliced<Z>), grid, dim3(Z / kSlice * 64), 0, s, rec, pair_gid, \
-                       brick_start, items, nitems, (uint32_t)bg.nbricks, xcd, thr, out);        \
+                       lists, items, nitems, (uint32_t)bg.nbricks, xcd, thr, out);              \
     return hipGetLastError();                                                                 \
   }
   GVE_CASE(16)
@@ -1069,7 +1087,7 @@ hipError_t launch_forward(const Record* rec, const uint32_t* pair_gid, const uin
 #define GVE_CASE(XY, Z)                                                                       \
   if (bg.Bxy == XY && bg.Bz == Z) {                                                           \
     hipLaunchKernelGGL((k_forward<XY, Z>), grid, dim3(XY * XY), 0, s, rec, pair_gid,            \
-                       brick_start, items, nitems, (uint32_t)bg.nbricks, xcd, thr, out);        \
+                       lists, items, nitems, (uint32_t)bg.nbricks, xcd, thr, out);              \
     return hipGetLastError();                                                                 \
   }
   GVE_BRICK_SHAPES(GVE_CASE)
@@ -1082,7 +1100,8 @@ namespace {
 // Arguments of the fused kernels.
 struct FusedArgs {
   const Record* rec;
-  const uint32_t *pair_gid, *brick_start;
+  const uint32_t* pair_gid;
+  BrickLists lists;
   const ItemDesc* items;
   int nitems;
   uint32_t nb;
@@ -1100,11 +1119,11 @@ hipError_t run_fused(const FusedArgs& a, const Schedule& sc, hipStream_t s) {
   if (sc.kind == kSchedQueue && !SLICED) {
     const dim3 grid((unsigned)std::min<int64_t>(sc.persistent_groups, a.nb));
     hipLaunchKernelGGL((k_fused_queue<XY, Z, MODE, W>), grid, dim3(XY * XY * W), 0, s, a.rec,
-                       a.pair_gid, a.brick_start, a.items, a.nitems, a.nb, sc.order, sc.counter,
+                       a.pair_gid, a.lists, a.items, a.nitems, a.nb, sc.order, sc.counter,
                        a.thr, a.field, a.acc, a.n, a.part, a.pslot, a.brick_loss);
   } else {
     hipLaunchKernelGGL((k_fused<XY, Z, MODE, W, SLICED>), dim3(a.nb), dim3(XY * XY * W), 0, s,
-                       a.rec, a.pair_gid, a.brick_start, a.items, a.nitems, a.nb,
+                       a.rec, a.pair_gid, a.lists, a.items, a.nitems, a.nb,
                        sc.kind == kSchedXcd ? 1 : 0, a.thr, a.field, a.acc, a.n, a.part, a.pslot,
                        a.brick_loss);
   }
@@ -1127,7 +1146,7 @@ hipError_t run_sliced(int mode, const FusedArgs& a, const Schedule& sc, hipStrea
 
 }  // namespace
 
-hipError_t launch_fused(const Record* rec, const uint32_t* pair_gid, const uint32_t* brick_start,
+hipError_t launch_fused(const Record* rec, const uint32_t* pair_gid, BrickLists lists,
                         const ItemDesc* items, int nitems, BrickGeom bg, float k,
                         const float* field, float* acc, int64_t n, float* part,
                         const uint32_t* pslot, float* brick_loss, const Schedule& sc,
@@ -1135,7 +1154,7 @@ hipError_t launch_fused(const Record* rec, const uint32_t* pair_gid, const uint3
   if (bg.nbricks <= 0) return hipSuccess;
   const bool queue = sc.kind == kSchedQueue;
   if (queue && (!sc.order || !sc.counter || sc.persistent_groups <= 0)) return hipErrorInvalidValue;
-  const FusedArgs a{rec, pair_gid, brick_start, items, nitems, (uint32_t)bg.nbricks,
+  const FusedArgs a{rec, pair_gid, lists, items, nitems, (uint32_t)bg.nbricks,
                     -kHalfLog2e * k * k, field, acc, n, part, pslot, brick_loss};
   if (bg.Bxy == 8 && bg.waves == 1 && !queue) {
     if (mode == kVjp) {
@@ -1156,7 +1175,7 @@ hipError_t launch_fused(const Record* rec, const uint32_t* pair_gid, const uint3
   return hipErrorInvalidValue;
 }
 
-hipError_t launch_count(const Record* rec, const uint32_t* pair_gid, const uint32_t* brick_start,
+hipError_t launch_count(const Record* rec, const uint32_t* pair_gid, BrickLists lists,
                         const ItemDesc* items, int nitems, BrickGeom bg, float k,
                         unsigned long long* counts, hipStream_t s) {
   const float thr = -kHalfLog2e * k * k;
@@ -1164,7 +1183,7 @@ hipError_t launch_count(const Record* rec, const uint32_t* pair_gid, const uint3
   const dim3 grid((unsigned)bg.nbricks);
 #define GVE_CASE(XY, Z)                                                                       \
   if (bg.Bxy == XY && bg.Bz == Z) {                                                           \
-    hipLaunchKernelGGL((k_count<XY, Z>), grid, dim3(XY * XY), 0, s, rec, pair_gid, brick_start, \
+    hipLaunchKernelGGL((k_count<XY, Z>), grid, dim3(XY * XY), 0, s, rec, pair_gid, lists,       \
                        items, nitems, thr, counts);                                             \
     return hipGetLastError();                                                                 \
   }
@@ -1177,6 +1196,10 @@ size_t loss_reduce_tmp_doubles() { return kRedBlocks; }
 
 hipError_t launch_loss_reduce(const float* brick_loss, int64_t nbricks, double* part, double* out,
                               hipStream_t s) {
+  if (nbricks <= kOneBricks) {
+    hipLaunchKernelGGL(k_loss_one, dim3(1), dim3(kOneThreads), 0, s, brick_loss, nbricks, out);
+    return hipGetLastError();
+  }
   hipLaunchKernelGGL(k_loss_partial, dim3(kRedBlocks), dim3(kRedThreads), 0, s, brick_loss,
                      nbricks, part);
   hipError_t e = hipGetLastError();
