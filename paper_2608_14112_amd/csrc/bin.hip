@@ -13,6 +13,7 @@
 //   emit   : the (brick, primitive) pairs at the scanned offsets;
 //   ranges : first pair of every brick in the brick-sorted list (binary search).
 #include "common.h"
+#include "devmath.h"
 
 namespace gve {
 namespace {
@@ -178,23 +179,7 @@ __global__ __launch_bounds__(kThreads) void k_prep(const float* __restrict__ the
 
 // ---- culling of bricks that miss the support -----------------------------
 //
-// A brick that meets a primitive's k-sigma box can still miss its ellipsoid
-// m^2 < k^2 (the corners of a rotated ellipsoid's box).  Let C be the brick's
-// part of the box (voxel centres), c its centre, h its half extents,
-// d = c - mu and n = P d, the ellipsoid's normal direction at c.  Along n the
-// ellipsoid m <= K reaches at most n.mu + K sqrt(n^T Sigma n) = n.mu + K sqrt(d^T P d),
-// and C reaches down to n.c - sum_j |n_j| h_j, so the plane normal to n parts
-// them when
-//     d^T P d - sum_j |n_j| h_j > K sqrt(d^T P d).
-// With K = k (1 + 1e-3) every voxel of C then has m^2 > 1.002 k^2, well
-// clear of where float32 rounding could decide the cut either way, and a
-// relative allowance of 1e-5 covers the rounding of the test itself.  In the
-// record's scaled units (Q = -(log2 e / 2) m^2, the xy part qxy = s0 dx^2 +
-// s1 dx dy + s2 dy^2, the z part -(sz t)^2 with t = dz - gx dx - gy dy) the
-// scaled normal (log2 e / 2) P d is
-//     (-(s0 dx + s1 dy / 2) - sz^2 t gx, -(s1 dx / 2 + s2 dy) - sz^2 t gy, sz^2 t)
-// and (log2 e / 2) d^T P d = sz^2 t^2 - qxy.  The test is conservative: a brick
-// it keeps may still miss (the brick kernels test every column anyway).
+// support_meets_box on the brick's part of the primitive's box.
 // (ox, oy, oz): the volume's origin minus the primitive's centre (float).
 __device__ inline bool brick_meets_support(const Record& r, const BoxXY& box, float ox, float oy,
                                            float oz, BrickGeom bg, uint32_t bx, uint32_t by,
@@ -210,19 +195,7 @@ __device__ inline bool brick_meets_support(const Record& r, const BoxXY& box, fl
   const float dz = fmaf(0.5f, (float)(za + zb), oz);
   const float hx = 0.5f * (float)(xb - xa), hy = 0.5f * (float)(yb - ya),
               hz = 0.5f * (float)(zb - za);
-  // fused operations are written out: both binnings keep the same bricks
-  const float t = dz - fmaf(r.gx, dx, r.gy * dy);
-  const float sz2 = r.sz * r.sz, h1 = 0.5f * r.s[1];
-  const float nz = sz2 * t, ax = r.s[0] * dx, cy = r.s[2] * dy;
-  const float qxy = fmaf(dy, cy, dx * fmaf(r.s[1], dy, ax));
-  const float nx = fmaf(-r.gx, nz, -fmaf(h1, dy, ax));
-  const float ny = fmaf(-r.gy, nz, -fmaf(h1, dx, cy));
-  const float mm = fmaf(t, nz, -qxy);
-  const float side = fmaf(hz, fabsf(nz), fmaf(hx, fabsf(nx), hy * fabsf(ny)));
-  // the hardware square root (within 1 ulp) is ample against the 1e-3 margin
-  const float reach = (1.0f + 1e-3f) * k * sqrtf(kHalfLog2e);
-  // NaN anywhere keeps the brick
-  return !(mm - side > fmaf(reach, __builtin_amdgcn_sqrtf(mm), 1e-5f * (mm + side)));
+  return support_meets_box(r, dx, dy, dz, hx, hy, hz, (1.0f + 1e-3f) * k * sqrtf(kHalfLog2e));
 }
 
 // j / d for j < 2^21 through a float reciprocal: (j + 1/2) / d lies at least

@@ -253,4 +253,39 @@ static __device__ inline void jacobi3(double A[3][3], double V[3][3]) {
 }
 
 
+// Whether a box of voxels that meets a primitive's k-sigma box can meet its
+// ellipsoid m^2 < k^2 (the corners of a rotated ellipsoid's box do not).  Let C
+// be the box (voxel centres), c its centre, h its half extents,
+// d = c - mu and n = P d, the ellipsoid's normal direction at c.  Along n the
+// ellipsoid m <= K reaches at most n.mu + K sqrt(n^T Sigma n) = n.mu + K sqrt(d^T P d),
+// and C reaches down to n.c - sum_j |n_j| h_j, so the plane normal to n parts
+// them when
+//     d^T P d - sum_j |n_j| h_j > K sqrt(d^T P d).
+// With K = k (1 + 1e-3) every voxel of C then has m^2 > 1.002 k^2, well
+// clear of where float32 rounding could decide the cut either way, and a
+// relative allowance of 1e-5 covers the rounding of the test itself.  In the
+// record's scaled units (Q = -(log2 e / 2) m^2, the xy part qxy = s0 dx^2 +
+// s1 dx dy + s2 dy^2, the z part -(sz t)^2 with t = dz - gx dx - gy dy) the
+// scaled normal (log2 e / 2) P d is
+//     (-(s0 dx + s1 dy / 2) - sz^2 t gx, -(s1 dx / 2 + s2 dy) - sz^2 t gy, sz^2 t)
+// and (log2 e / 2) d^T P d = sz^2 t^2 - qxy.  The test is conservative: a box
+// it keeps may still miss (the brick kernels test every column anyway).  Fused
+// operations are written out, so that every kernel keeps the same boxes.
+// reach = k (1 + 1e-3) sqrt(log2 e / 2).
+__device__ inline bool support_meets_box(const Record& r, float dx, float dy, float dz, float hx,
+                                         float hy, float hz, float reach) {
+#pragma clang fp contract(off)
+  const float t = dz - fmaf(r.gx, dx, r.gy * dy);
+  const float sz2 = r.sz * r.sz, h1 = 0.5f * r.s[1];
+  const float nz = sz2 * t, ax = r.s[0] * dx, cy = r.s[2] * dy;
+  const float qxy = fmaf(dy, cy, dx * fmaf(r.s[1], dy, ax));
+  const float nx = fmaf(-r.gx, nz, -fmaf(h1, dy, ax));
+  const float ny = fmaf(-r.gy, nz, -fmaf(h1, dx, cy));
+  const float mm = fmaf(t, nz, -qxy);
+  const float side = fmaf(hz, fabsf(nz), fmaf(hx, fabsf(nx), hy * fabsf(ny)));
+  // the hardware square root (within 1 ulp) is ample against the 1e-3 margin;
+  // NaN anywhere keeps the box
+  return !(mm - side > fmaf(reach, __builtin_amdgcn_sqrtf(mm), 1e-5f * (mm + side)));
+}
+
 }  // namespace gve

@@ -30,6 +30,7 @@
 #include <algorithm>
 
 #include "common.h"
+#include "devmath.h"
 
 namespace gve {
 namespace {
@@ -265,79 +266,6 @@ __device__ inline void accumulate_brick(const Record* __restrict__ rec,
   if (jw < j1) touch_end(tc);
 }
 
-// ---- z-slices ------------------------------------------------------------------
-//
-// Where the launch has few bricks, a brick's forward pass is dealt to BZ / 8
-// waves by offset: wave w sums every pair, in list order, at offsets
-// 8 w .. 8 w + 7.  Each voxel's value is then formed from the same operations in
-// the same order as by one wave for the whole column, so results do not depend
-// on whether a brick is sliced.
-constexpr int kSlice = 8;
-
-// Forward steps of one pair at the wave's eight offsets (zc[u] = the offset
-// less BZ / 2).  Returns the active offsets (bits 0 .. 7): those at which some
-// lane is inside the support.  (All eight side by side without branches, the
-// ones outside the box compared against infinity, measured 2 % faster at 128
-// bricks and 12 % slower at 8,192.)
-__device__ inline uint32_t slice_steps(const ColumnSetup& s, float szv, float c, float thr,
-                                       uint32_t zm, const float (&zc)[kSlice],
-                                       float (&acc)[kSlice]) {
-  uint32_t active = 0u;
-#pragma unroll
-  for (int u = 0; u < kSlice; ++u) {
-    if ((zm >> u) & 1u) {
-      const float q = quad_w(s, fmaf(zc[u], szv, s.wm));
-      if (__builtin_amdgcn_ballot_w64(q > thr) != 0ull) {
-        active |= 1u << u;
-        const float G = (q > thr) ? __builtin_amdgcn_exp2f(q) : 0.0f;
-        acc[u] = fmaf(c, G, acc[u]);
-      }
-    }
-  }
-  return active;
-}
-
-// Forward accumulation of all pairs [j0, j1) of a brick at one slice.  With
-// `steps`, byte `slice` of steps[j - j0] takes the active offsets of pair j
-// (j - j0 < kStepCap): the four slices' bytes form the mask of the column.
-// The record of the next pair is loaded while the current one's steps run: a
-// brick's time is its list length times the latency of a pair, and few waves
-// share a SIMD.
-template <int BZ>
-__device__ inline void accumulate_slice(const Record* __restrict__ rec,
-                                        const uint32_t* __restrict__ pair_gid, uint32_t j0,
-                                        uint32_t j1, float px, float py, float pz0, int iz0,
-                                        int slice, float thr, float (&acc)[kSlice],
-                                        uint32_t* __restrict__ steps) {
-  if (j0 >= j1) return;
-  const int z0 = slice * kSlice;
-  float zc[kSlice];
-#pragma unroll
-  for (int u = 0; u < kSlice; ++u) zc[u] = (float)(z0 + u - BZ / 2);
-  const int lane = threadIdx.x & 63;
-  Record r = load_record(rec, __builtin_amdgcn_readfirstlane(pair_gid[j0]));
-  uint32_t next = __builtin_amdgcn_readfirstlane(pair_gid[min(j0 + 1, j1 - 1)]);
-  for (uint32_t j = j0; j < j1; ++j) {
-    const Record rn = load_record(rec, next);
-    next = __builtin_amdgcn_readfirstlane(pair_gid[min(j + 2, j1 - 1)]);
-    uint32_t active = 0u;
-    const ColumnSetup s = column_setup<BZ>(r, px, py, pz0, iz0);
-    const uint32_t zm = (s.zmask >> z0) & 0xFFu;
-    if (zm) {
-      const float szv = vreg(r.sz);
-      // the offset of the slice's part of the box nearest the vertex
-      const float wa = fmaf((float)(max(s.za, z0) - BZ / 2), szv, s.wm);
-      const float wb = fmaf((float)(min(s.zb, z0 + kSlice - 1) - BZ / 2), szv, s.wm);
-      const float wn = __builtin_amdgcn_fmed3f(wa, wb, 0.0f);
-      if (__builtin_amdgcn_ballot_w64(fmaf(-wn, wn, s.qxy) > thr) != 0ull)
-        active = slice_steps(s, szv, r.c, thr, zm, zc, acc);
-    }
-    if (steps && j - j0 < kStepCap && lane == 0)
-      reinterpret_cast<uint8_t*>(steps + (j - j0))[slice] = (uint8_t)active;
-    r = rn;
-  }
-}
-
 // ---- where a brick lies --------------------------------------------------------
 //
 // Global brick b belongs to the last volume whose first brick is <= b; b is
@@ -416,6 +344,125 @@ __device__ inline uint32_t xcd_brick(uint32_t w, uint32_t nb) {
   return ((k / kXcdChunk) * 8u + x) * kXcdChunk + k % kXcdChunk;
 }
 
+// ---- z-slices ------------------------------------------------------------------
+//
+// Where the launch has few bricks, a brick's forward pass is dealt to BZ / SL
+// waves by offset: wave w sums its pairs, in list order, at offsets
+// SL w .. SL w + SL - 1.  Each voxel's value is then formed from the same
+// operations in the same order as by one wave for the whole column, so results
+// do not depend on whether a brick is sliced.
+
+// Forward steps of one pair at the wave's offsets (zc[u] = the offset less
+// BZ / 2).  Returns the active offsets (bits 0 .. SL - 1): those at which some
+// lane is inside the support.  (All side by side without branches, the ones
+// outside the box compared against infinity, measured 2 % faster at 128 bricks
+// and 12 % slower at 8,192.)
+template <int SL>
+__device__ inline uint32_t slice_steps(const ColumnSetup& s, float szv, float c, float thr,
+                                       uint32_t zm, const float (&zc)[SL], float (&acc)[SL]) {
+  uint32_t active = 0u;
+#pragma unroll
+  for (int u = 0; u < SL; ++u) {
+    if ((zm >> u) & 1u) {
+      const float q = quad_w(s, fmaf(zc[u], szv, s.wm));
+      if (__builtin_amdgcn_ballot_w64(q > thr) != 0ull) {
+        active |= 1u << u;
+        const float G = (q > thr) ? __builtin_amdgcn_exp2f(q) : 0.0f;
+        acc[u] = fmaf(c, G, acc[u]);
+      }
+    }
+  }
+  return active;
+}
+
+// The pairs of a brick that reach one slice, in list order: each lane tests one
+// of 64 pairs (z-range, then the separating plane), and the kept ones are taken
+// from the ballot, so a pair that misses the slice costs its wave a 64th of a
+// test in place of the set-up of its columns.
+template <int BZ, int SL>
+struct SlicePairs {
+  const Record* __restrict__ rec;
+  const uint32_t* __restrict__ pair_gid;
+  uint32_t j1;         // end of the brick's pairs
+  float x0, y0, pz0;   // the brick's corner
+  int iz0, z0;         // its first z (volume index), the slice's first offset
+  float reach;         // (1 + 1e-3) sqrt(-thr)
+  uint32_t base;       // first pair of the block of 64
+  uint32_t gid;        // the lane's pair of the block
+  uint64_t left;       // kept pairs of the block not yet taken
+
+  __device__ void block(uint32_t b) {
+    base = b;
+    const uint32_t j = b + (threadIdx.x & 63);
+    gid = pair_gid[min(j, j1 - 1)];
+    const Record r = rec[gid];
+    const int za = max(r.zlo - iz0, z0), zb = min(r.zhi - iz0, z0 + SL - 1);
+    const bool keep =
+        j < j1 && za <= zb &&
+        support_meets_box(r, (x0 - r.mu[0]) + 3.5f, (y0 - r.mu[1]) + 3.5f,
+                          fmaf(0.5f, (float)(za + zb), pz0 - r.mu[2]), 3.5f, 3.5f,
+                          0.5f * (float)(zb - za), reach);
+    left = __builtin_amdgcn_ballot_w64(keep);
+  }
+  // List position of the next pair (its id to g), j1 after the last.
+  __device__ uint32_t next(uint32_t& g) {
+    while (left == 0ull) {
+      if (j1 - base <= 64u) return j1;
+      block(base + 64u);
+    }
+    const int p = (int)__builtin_ctzll(left);
+    left &= left - 1ull;
+    g = (uint32_t)__builtin_amdgcn_readlane((int)gid, p);
+    return base + (uint32_t)p;
+  }
+};
+
+// Forward accumulation of a brick's pairs [j0, j1) at one slice.  With `steps`
+// (zeroed before), the slice's bits of steps[j - j0] take the active offsets of
+// pair j (j - j0 < kStepCap).  The
+// record of the next pair is loaded while the current one's steps run: a
+// brick's time is its list length times the latency of a pair, and few waves
+// share a SIMD.
+template <int BZ, int SL>
+__device__ inline void accumulate_slice(const Record* __restrict__ rec,
+                                        const uint32_t* __restrict__ pair_gid, uint32_t j0,
+                                        uint32_t j1, const Site& st, int slice, float thr,
+                                        float (&acc)[SL], uint32_t* __restrict__ steps) {
+  if (j0 >= j1) return;
+  const int z0 = slice * SL;
+  float zc[SL];
+#pragma unroll
+  for (int u = 0; u < SL; ++u) zc[u] = (float)(z0 + u - BZ / 2);
+  const int lane = threadIdx.x & 63;
+  SlicePairs<BZ, SL> sp{rec, pair_gid, j1, st.px - (float)(lane & 7),
+                        st.py - (float)(lane >> 3), st.pz0, st.iz0, z0,
+                        (1.0f + 1e-3f) * sqrtf(-thr)};
+  sp.block(j0);
+  uint32_t g = 0;
+  uint32_t j = sp.next(g);
+  if (j >= j1) return;
+  Record r = load_record(rec, g);
+  for (;;) {
+    const uint32_t jn = sp.next(g);
+    const Record rn = load_record(rec, g);
+    uint32_t active = 0u;
+    const ColumnSetup s = column_setup<BZ>(r, st.px, st.py, st.pz0, st.iz0);
+    const uint32_t zm = (s.zmask >> z0) & ((1u << SL) - 1u);
+    const float szv = vreg(r.sz);
+    // the offset of the slice's part of the box nearest the vertex
+    const float wa = fmaf((float)(max(s.za, z0) - BZ / 2), szv, s.wm);
+    const float wb = fmaf((float)(min(s.zb, z0 + SL - 1) - BZ / 2), szv, s.wm);
+    const float wn = __builtin_amdgcn_fmed3f(wa, wb, 0.0f);
+    if (__builtin_amdgcn_ballot_w64(fmaf(-wn, wn, s.qxy) > thr) != 0ull)
+      active = slice_steps<SL>(s, szv, r.c, thr, zm, zc, acc);
+    if (steps && active != 0u && j - j0 < kStepCap && lane == 0)
+      atomicOr(&steps[j - j0], active << z0);
+    if (jn >= j1) break;
+    j = jn;
+    r = rn;
+  }
+}
+
 template <int BXY, int BZ>
 __device__ __attribute__((always_inline)) inline void forward_brick(const Record* __restrict__ rec,
                                      const uint32_t* __restrict__ pair_gid,
@@ -448,24 +495,23 @@ __global__ __launch_bounds__(BXY* BXY) void k_forward(const Record* __restrict__
   forward_brick<BXY, BZ>(rec, pair_gid, lists, items, nitems, b, thr, out);
 }
 
-// The same with the brick's offsets dealt to BZ / 8 waves.
-template <int BZ>
-__global__ __launch_bounds__(BZ / kSlice * 64) void k_forward_sliced(
+// The same with the brick's offsets dealt to BZ / SL waves.
+template <int BZ, int SL>
+__global__ __launch_bounds__(BZ / SL * 64) void k_forward_sliced(
     const Record* __restrict__ rec, const uint32_t* __restrict__ pair_gid,
     BrickLists lists, const ItemDesc* __restrict__ items, int nitems,
     uint32_t nbricks, int xcd, float thr, float* __restrict__ out) {
   const uint32_t b = xcd ? xcd_brick(blockIdx.x, nbricks) : blockIdx.x;
   const int slice = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const Site st = site_of<8, BZ>(items, nitems, b, threadIdx.x & 63);
-  float acc[kSlice];
+  float acc[SL];
 #pragma unroll
-  for (int u = 0; u < kSlice; ++u) acc[u] = 0.0f;
-  accumulate_slice<BZ>(rec, pair_gid, lists.start[b], lists.end[b], st.px, st.py, st.pz0,
-                       st.iz0, slice, thr, acc, nullptr);
+  for (int u = 0; u < SL; ++u) acc[u] = 0.0f;
+  accumulate_slice<BZ, SL>(rec, pair_gid, lists.start[b], lists.end[b], st, slice, thr, acc, nullptr);
   if (st.col_in) {
 #pragma unroll
-    for (int u = 0; u < kSlice; ++u)
-      if (slice * kSlice + u < st.zrem) *st.at(out, slice * kSlice + u) = acc[u];
+    for (int u = 0; u < SL; ++u)
+      if (slice * SL + u < st.zrem) *st.at(out, slice * SL + u) = acc[u];
   }
 }
 
@@ -594,7 +640,7 @@ __device__ inline void load_column_chunk(const float* __restrict__ field, const 
 // in wave order through LDS (`comb`, W * BZ * 64 floats), after which every
 // wave holds the whole field of the brick.  `comb` is then each wave's block
 // of the ten-sum reduction (lds_sum10).
-// SLICED (W = BZ / 8 > 1): the waves split the forward pass by offsets instead
+// SLICED (W > 1): the waves split the forward pass by offsets instead
 // (accumulate_slice) and exchange residuals; values, recorded offsets, loss
 // and each pair's sums are those of W = 1 exactly.
 constexpr int kGrad = kFusedGrad, kVjp = kFusedVjp, kLoss = kFusedLoss;
@@ -614,7 +660,7 @@ __device__ __attribute__((always_inline)) inline void fused_brick(const Record* 
   constexpr int kWaves = (BXY * BXY + 63) / 64;  // waves over the columns
   constexpr bool VJP = MODE == kVjp;
   static_assert(W == 1 || kWaves == 1, "pairs are split only over one wave of columns");
-  static_assert(!SLICED || (W == BZ / kSlice && W > 1 && !VJP), "one wave per slice");
+  static_assert(!SLICED || (BZ % W == 0 && W > 1 && !VJP), "one wave per slice");
   const int lane = threadIdx.x & 63;
   // uniform, so that the waves' pair indices, masks and branches stay scalar
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -644,17 +690,22 @@ __device__ __attribute__((always_inline)) inline void fused_brick(const Record* 
       asm volatile("" ::: "memory");
     }
   } else if (SLICED) {
+    constexpr int SL = SLICED ? BZ / W : 1;
     const int slice = wave;
-    float acc[kSlice];
+    if (MODE == kGrad) {
+      for (uint32_t i = threadIdx.x; i < min(j1 - j0, kStepCap); i += 64 * W) steps[i] = 0u;
+      __syncthreads();
+    }
+    float acc[SL];
 #pragma unroll
-    for (int u = 0; u < kSlice; ++u) acc[u] = 0.0f;
-    accumulate_slice<BZ>(rec, pair_gid, j0, j1, px, py, pz0, iz0, slice, thr, acc,
+    for (int u = 0; u < SL; ++u) acc[u] = 0.0f;
+    accumulate_slice<BZ, SL>(rec, pair_gid, j0, j1, st, slice, thr, acc,
                          MODE == kGrad ? steps : nullptr);
-    float t[kSlice];
-    load_column_chunk<kSlice>(field, st, voff, nrec, slice * kSlice, t);
+    float t[SL];
+    load_column_chunk<SL>(field, st, voff, nrec, slice * SL, t);
 #pragma unroll
-    for (int u = 0; u < kSlice; ++u) {
-      const int zz = slice * kSlice + u;
+    for (int u = 0; u < SL; ++u) {
+      const int zz = slice * SL + u;
       comb[zz * 64 + lane] = col_in && zz < st.zrem ? 2.0f * (acc[u] - t[u]) : 0.0f;
     }
     __syncthreads();
@@ -746,10 +797,7 @@ __device__ __attribute__((always_inline)) inline void fused_brick(const Record* 
     const ColumnSetup s = column_setup<BZ>(r, px, py, pz0, iz0);
     // the steps the forward pass found active, else the box's z-range
     const bool recorded = kWaves == 1 && !VJP && j - j0 < kStepCap;
-    // (sliced bricks write one byte per slice: fewer than four leave the rest unset)
-    constexpr uint32_t kOffsets = BZ < 32 ? (1u << (BZ & 31)) - 1u : 0xFFFFFFFFu;
-    const uint32_t run = recorded ? __builtin_amdgcn_readfirstlane(steps[j - j0]) & kOffsets
-                                  : s.zmask;
+    const uint32_t run = recorded ? __builtin_amdgcn_readfirstlane(steps[j - j0]) : s.zmask;
     const bool hit = recorded ? run != 0u : column_hit<BZ>(s, r.sz, cols, thr);
     if (kWaves == 1 && !hit) {
       // a pair whose support misses every column still owns a partials slot
@@ -1019,23 +1067,36 @@ __global__ __launch_bounds__(kRedThreads) void k_item_loss(const float* __restri
 
 // One wave per brick leaves the chip (8,192 resident waves) idle or waiting for
 // its heaviest bricks when the launch has few: a pair costs a lone wave about
-// 1 us forward and 1 us backward, most of it latency.  Up to these brick
-// counts the offsets of the forward pass are dealt to BZ / 8 waves and the pairs
-// of the backward pass to the same waves.  Past them the chip is full and the
-// slices' repeated per-pair set-up (about 15 % more vector instructions) costs
-// more than the balance gains.  Measured, 20 supports a voxel, 8 x 8 x 32
-// bricks, unsliced -> sliced: loss and gradient 128 bricks 546 -> 265 us,
-// 1,024 829 -> 411, 3,456 1075 -> 716, 8,192 1346 -> 1091, 16,000 1936 -> 1959;
-// evaluation 128 bricks 293 -> 160 us, 3,456 556 -> 390, 8,192 660 -> 605,
-// 16,000 919 -> 1048 (whole calls, binning included).
+// 1 us forward and 1 us backward, most of it instructions waiting for each
+// other.  Up to the counts below the offsets of the forward pass are dealt to
+// several waves and the pairs of the backward pass to the same waves.  Past
+// them the chip is full, and the slices' repeated per-pair set-up and the waves
+// that wait at the slices' end cost more than the balance gains.
+//
+// Evaluation, by slabs of eight offsets (bricks x BZ / 8): slices of 2, 4 and 8
+// measured 50, 56 and 69 us at 512 slabs (64^3 x 2,048, 8 x 8 x 8 bricks; one
+// wave 73), 84, 72 and 80 at 1,728 (96^3, 8 x 8 x 32), 147, 116 and 118 at
+// 4,096, 314, 248 and 225 at 13,824.  8 x 8 x 32 bricks, one wave -> slices of 8
+// (tests of 64 pairs at a time included): 256^3 x 131,072, 8,192 bricks, 660 ->
+// 372 us; 320^3, 16,000 461 -> 512, 27,648 672 -> 764, 65,536 1290 -> 1550.
+constexpr int64_t kSlabs2 = 1024, kSlabs4 = 4096;
 constexpr int64_t kSlicedForwardBricks = 10240;
+// Loss and gradient, refinement iterations of the same sets, 8 x 8 x 32 bricks
+// dealt to 16, 8 and 4 waves: 128 bricks 85, 93, 128 us; 432 144, 120, 145;
+// 1,024 285, 204, 205; 3,456 634, 408, 363; 8,192 1496, 881, 745 (one wave
+// 1,346); 16,000 uniformly filled 1,038 by 4, 903 by one.  8 x 8 x 16 to 8, 4
+// and 2: 256 bricks 73, 95, 138; 864 133, 133, 165; 2,048 262, 234, 253; 6,912
+// 504, 400, 380.  8 x 8 x 8 to 4 and 1: 512 bricks 79, 160; 1,728 145, 195;
+// 4,096 307, 298.
 constexpr int64_t kSlicedFusedBricks = 12288;
-// The VJP has no forward pass, and each pair's sums are its own, so four waves
-// simply take every fourth pair: always with 8 x 8 x 32 bricks (128^3 558 ->
-// 243 us, 256^3 892 -> 506, 512^3 2619 -> 2229, 768^3 6383 -> 6173, whole
-// calls), with shallower ones, whose lists are shorter, up to this many (8 x 8
-// x 8: 110,592 bricks 1603 -> 1521 us, 884,736 8997 -> 9205; x 16: 131,072
-// 2759 -> 2591, 442,368 7127 -> 7173).
+// The VJP has no forward pass, and each pair's sums are its own, so several
+// waves simply take every W-th pair.  16, 8 and 4 waves: 8 x 8 x 32, 128 bricks
+// 47, 58, 81 us; 432 67, 73, 94; 1,024 111, 111, 126; 3,456 253, 240, 235; 8 x 8
+// x 8, 512 bricks 42, 45, 51; 1,728 88, 85, 85.  Four waves against one: always
+// with 8 x 8 x 32 bricks (128^3 558 -> 243 us, 256^3 892 -> 506, 512^3 2619 ->
+// 2229, 768^3 6383 -> 6173, whole calls), with shallower ones, whose lists are
+// shorter, up to this many (8 x 8 x 8: 110,592 bricks 1603 -> 1521 us, 884,736
+// 8997 -> 9205; x 16: 131,072 2759 -> 2591, 442,368 7127 -> 7173).
 constexpr int64_t kSplitVjpBricks = 131072;
 
 bool brick_shape_supported(int bxy, int bz) {
@@ -1075,14 +1136,19 @@ hipError_t launch_forward(const Record* rec, const uint32_t* pair_gid, BrickList
   if (bg.nbricks <= 0) return hipSuccess;
   const dim3 grid((unsigned)bg.nbricks);
   const int xcd = sc.kind == kSchedXcd ? 1 : 0;
-#define GVE_CASE(Z)                                                                           \
-  if (bg.Bxy == 8 && bg.Bz == Z && bg.nbricks <= kSlicedForwardBricks) {                        \
-    hipLaunchKernelGGL((k_forward_sliced<Z>), grid, dim3(Z / kSlice * 64), 0, s, rec, pair_gid, \
+#define GVE_CASE(Z, SL, LIMIT)                                                                  \
+  if (bg.Bxy == 8 && bg.Bz == Z && bg.nbricks <= (LIMIT)) {                                     \
+    hipLaunchKernelGGL((k_forward_sliced<Z, SL>), grid, dim3(Z / SL * 64), 0, s, rec, pair_gid, \
                        lists, items, nitems, (uint32_t)bg.nbricks, xcd, thr, out);              \
-    return hipGetLastError();                                                                 \
+    return hipGetLastError();                                                                   \
   }
-  GVE_CASE(16)
-  GVE_CASE(32)
+  GVE_CASE(8, 2, kSlabs2)
+  GVE_CASE(16, 2, kSlabs2 / 2)
+  GVE_CASE(8, 4, kSlabs4 / 2)
+  GVE_CASE(16, 4, kSlabs4 / 2)
+  GVE_CASE(32, 4, kSlabs4 / 4)
+  GVE_CASE(16, 8, kSlicedForwardBricks)
+  GVE_CASE(32, 8, kSlicedForwardBricks)
 #undef GVE_CASE
 #define GVE_CASE(XY, Z)                                                                       \
   if (bg.Bxy == XY && bg.Bz == Z) {                                                           \
@@ -1137,9 +1203,8 @@ hipError_t run_mode(int mode, const FusedArgs& a, const Schedule& sc, hipStream_
   return run_fused<XY, Z, kGrad, W, false>(a, sc, s);
 }
 
-template <int Z>
+template <int Z, int W>
 hipError_t run_sliced(int mode, const FusedArgs& a, const Schedule& sc, hipStream_t s) {
-  constexpr int W = Z / kSlice;
   if (mode == kLoss) return run_fused<8, Z, kLoss, W, true>(a, sc, s);
   return run_fused<8, Z, kGrad, W, true>(a, sc, s);
 }
@@ -1158,15 +1223,34 @@ hipError_t launch_fused(const Record* rec, const uint32_t* pair_gid, BrickLists 
                     -kHalfLog2e * k * k, field, acc, n, part, pslot, brick_loss};
   if (bg.Bxy == 8 && bg.waves == 1 && !queue) {
     if (mode == kVjp) {
-      if (bg.Bz == 32) return run_fused<8, 32, kVjp, 4, false>(a, sc, s);
-      if (bg.nbricks <= kSplitVjpBricks) {
-        if (bg.Bz == 8) return run_fused<8, 8, kVjp, 4, false>(a, sc, s);
-        if (bg.Bz == 16) return run_fused<8, 16, kVjp, 4, false>(a, sc, s);
-      }
-    } else if (bg.nbricks <= kSlicedFusedBricks) {
-      if (bg.Bz == 16) return run_sliced<16>(mode, a, sc, s);
-      if (bg.Bz == 32) return run_sliced<32>(mode, a, sc, s);
+#define GVE_VJP(Z, W, LIMIT) \
+  if (bg.Bz == Z && bg.nbricks <= (LIMIT)) return run_fused<8, Z, kVjp, W, false>(a, sc, s);
+      GVE_VJP(8, 16, 1024) GVE_VJP(16, 16, 1024) GVE_VJP(32, 16, 1024)
+      GVE_VJP(8, 8, 2048) GVE_VJP(16, 8, 2048) GVE_VJP(32, 8, 2048)
+      GVE_VJP(8, 4, kSplitVjpBricks) GVE_VJP(16, 4, kSplitVjpBricks)
+      GVE_VJP(32, 4, bg.nbricks)
+#undef GVE_VJP
+    } else {
+#define GVE_SLICED(Z, W, LIMIT) \
+  if (bg.Bz == Z && bg.nbricks <= (LIMIT)) return run_sliced<Z, W>(mode, a, sc, s);
+      GVE_SLICED(8, 4, 2048)
+      GVE_SLICED(16, 8, 768) GVE_SLICED(16, 4, 3072) GVE_SLICED(16, 2, kSlicedFusedBricks)
+      GVE_SLICED(32, 16, 256) GVE_SLICED(32, 8, 1024) GVE_SLICED(32, 4, kSlicedFusedBricks)
+#undef GVE_SLICED
     }
+  }
+  // Four waves that split a brick's pairs become 8 or 16 in small launches: 8 x 8
+  // x 8, 64 bricks 50 -> 38 -> 35 us, 512 63 -> 49 -> 52, 1,728 106 -> 102, 4,096
+  // 235 -> 236; 8 x 8 x 16, 256 82 -> 56 -> 49, 864 100 -> 86 -> 120, 2,048 182 ->
+  // 176; 8 x 8 x 32, 432 130 -> 94, 1,024 170 -> 178.
+  if (bg.Bxy == 8 && bg.waves == 4 && !queue && mode != kVjp) {
+#define GVE_SPLIT(Z, W, LIMIT)                                              \
+  if (bg.Bz == Z && bg.nbricks <= (LIMIT))                                  \
+    return mode == kLoss ? run_fused<8, Z, kLoss, W, false>(a, sc, s)       \
+                         : run_fused<8, Z, kGrad, W, false>(a, sc, s);
+    GVE_SPLIT(8, 16, 128) GVE_SPLIT(16, 16, 512)
+    GVE_SPLIT(8, 8, 2048) GVE_SPLIT(16, 8, 2048) GVE_SPLIT(32, 8, 768)
+#undef GVE_SPLIT
   }
 #define GVE_CASE(XY, Z, W) \
   if (bg.Bxy == XY && bg.Bz == Z && bg.waves == W) return run_mode<XY, Z, W>(mode, a, sc, s);
