@@ -1987,14 +1987,9 @@ gve_status gve_features(gve_ctx* ctx, const gve_params* p, const float* d_field,
   TRY(validate_grid(ctx, g));
   TRY(set_device(ctx));
   const int64_t M = g.nx * g.ny * g.nz;
-  // summed-area tables of V and V^2, then the primitives' structure tensors
-  TRY(ensure(ctx, ctx->ws.sat, sizeof(double) * (2 * (size_t)M + 6 * (size_t)p->n)));
-  double* s1 = static_cast<double*>(ctx->ws.sat.ptr);
-  double* s2 = s1 + M;
-  double* J6 = s2 + M;
-  TRY_HIP(ctx, gve::mlp_sat(d_field, g, s1, s2, ctx->stream));
-  TRY_HIP(ctx, gve::mlp_features(d_field, p->theta, p->n, n_detail, g, g99, ctx->opt.k, s1, s2, J6,
-                                 d_X, ctx->stream));
+  TRY(ensure(ctx, ctx->ws.sat, sizeof(double) * gve::mlp_feature_doubles(M, p->n)));
+  TRY_HIP(ctx, gve::mlp_features(d_field, p->theta, p->n, n_detail, g, g99, ctx->opt.k,
+                                 static_cast<double*>(ctx->ws.sat.ptr), d_X, ctx->stream));
   return GVE_OK;
 }
 

@@ -451,11 +451,11 @@ hipError_t mlp_colstats(const float* X, int64_t rows, int cols, float* mean, flo
                         double* tmp, hipStream_t s);
 hipError_t mlp_perm_keys(uint32_t* keys, uint32_t* vals, int64_t n, uint64_t seed, uint64_t epoch,
                          hipStream_t s);
-hipError_t mlp_sat(const float* f, const gve_grid& g, double* s1, double* s2, hipStream_t s);
-// J6: 6 n doubles of workspace (the structure tensors at the centres).
+// work: mlp_feature_doubles(voxels, n) doubles.
+size_t mlp_feature_doubles(int64_t M, int64_t n);
 hipError_t mlp_features(const float* f, const float* theta, int64_t n, int64_t n_detail,
-                        const gve_grid& g, double g99, float k, const double* s1, const double* s2,
-                        double* J6, float* X, hipStream_t s);
+                        const gve_grid& g, double g99, float k, double* work, float* X,
+                        hipStream_t s);
 hipError_t mlp_targets(const float* ta, const float* tr, int64_t n, float* T, hipStream_t s);
 hipError_t mlp_apply_delta(float* theta, const float* base, const float* Y, int64_t n,
                            const float* tmean, const float* tstd, float alpha, hipStream_t s);

@@ -642,41 +642,68 @@ __global__ void k_perm_keys(uint32_t* __restrict__ keys, uint32_t* __restrict__ 
 
 // ---- features --------------------------------------------------------------
 
-// Inclusive prefix sums of V and V^2 along x (one workgroup per (y, z) line).
+// Mean and variance of V over a primitive's box come from prefix sums of V and
+// V^2, in one of two forms.  Block tables: within each block of 64 x 8 x 8 voxels
+// the sums from the block's corner, which one wave forms in one pass over the
+// volume without a carry from other blocks (20 bytes a voxel); a box adds up to
+// eight entries of each block it touches, a lane per block.  Summed-area tables
+// of the whole volume: three passes (84 bytes a voxel), then eight entries a box.
+// The blocks that the set's boxes touch are counted on the device, and the
+// kernels of the form not taken return at once.  Features, tables -> blocks:
+// 64^3 x 2,048 of scales 1.5 - 4 106 -> 85 us; 256^3 x 65,536, 2 - 6 599 -> 311, 8
+// - 12 589 -> 457; 384^3 x 110,592, 1 - 3 1,530 -> 646; 256^3 x 20,000, 20 - 30
+// (about 2.5 touched blocks per voxel) 468 -> 430: tables past 2.  The block
+// tables take 257 us at 384^3, 4.4 TB/s: the rate of a copy.
+constexpr int kSatX = 64, kSatY = 8, kSatZ = 8;
+constexpr uint64_t kBlocksPerVoxel = 2;
+constexpr int64_t kSatLines = 8192;           // workgroups of the x pass
+constexpr int64_t kSatBlocks = 1 << 20;       // and of the block tables
+
+__device__ inline bool takes_blocks(const unsigned long long* __restrict__ touched, int64_t M) {
+  return *touched <= kBlocksPerVoxel * (uint64_t)M;
+}
+
+// Inclusive prefix sums of V and V^2 along x, a (y, z) line at a time.
 __global__ __launch_bounds__(256) void k_sat_x(const float* __restrict__ f, int64_t nx,
+                                               int64_t lines,
+                                               const unsigned long long* __restrict__ touched,
                                                double* __restrict__ s1, double* __restrict__ s2) {
+  if (takes_blocks(touched, nx * lines)) return;
   __shared__ double c1[256], c2[256];
-  const size_t base = (size_t)blockIdx.x * nx;
-  double carry1 = 0.0, carry2 = 0.0;
-  for (int64_t x0 = 0; x0 < nx; x0 += 256) {
-    const int64_t x = x0 + threadIdx.x;
-    const double v = x < nx ? (double)f[base + x] : 0.0;
-    c1[threadIdx.x] = v;
-    c2[threadIdx.x] = v * v;
-    __syncthreads();
-    for (int d = 1; d < 256; d <<= 1) {
-      const double a = threadIdx.x >= (unsigned)d ? c1[threadIdx.x - d] : 0.0;
-      const double b = threadIdx.x >= (unsigned)d ? c2[threadIdx.x - d] : 0.0;
+  for (int64_t line = blockIdx.x; line < lines; line += gridDim.x) {
+    const size_t base = (size_t)line * nx;
+    double carry1 = 0.0, carry2 = 0.0;
+    for (int64_t x0 = 0; x0 < nx; x0 += 256) {
+      const int64_t x = x0 + threadIdx.x;
+      const double v = x < nx ? (double)f[base + x] : 0.0;
+      c1[threadIdx.x] = v;
+      c2[threadIdx.x] = v * v;
       __syncthreads();
-      c1[threadIdx.x] += a;
-      c2[threadIdx.x] += b;
+      for (int d = 1; d < 256; d <<= 1) {
+        const double a = threadIdx.x >= (unsigned)d ? c1[threadIdx.x - d] : 0.0;
+        const double b = threadIdx.x >= (unsigned)d ? c2[threadIdx.x - d] : 0.0;
+        __syncthreads();
+        c1[threadIdx.x] += a;
+        c2[threadIdx.x] += b;
+        __syncthreads();
+      }
+      if (x < nx) {
+        s1[base + x] = carry1 + c1[threadIdx.x];
+        s2[base + x] = carry2 + c2[threadIdx.x];
+      }
+      carry1 += c1[255];
+      carry2 += c2[255];
       __syncthreads();
     }
-    if (x < nx) {
-      s1[base + x] = carry1 + c1[threadIdx.x];
-      s2[base + x] = carry2 + c2[threadIdx.x];
-    }
-    carry1 += c1[255];
-    carry2 += c2[255];
-    __syncthreads();
   }
 }
 
 // Running sums along an axis with element stride `stride` (line = thread).
 __global__ void k_sat_axis(double* __restrict__ s1, double* __restrict__ s2, int64_t nlines,
-                           int64_t inner, int64_t len, int64_t stride) {
+                           int64_t inner, int64_t len, int64_t stride,
+                           const unsigned long long* __restrict__ touched) {
   const int64_t l = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (l >= nlines) return;
+  if (l >= nlines || takes_blocks(touched, nlines * len)) return;
   const size_t base = (size_t)(l / inner) * (size_t)(inner * len) + (size_t)(l % inner);
   double a = 0.0, b = 0.0;
   for (int64_t k = 0; k < len; ++k) {
@@ -702,16 +729,25 @@ __device__ inline double box_sum(const double* __restrict__ S, int64_t nx, int64
          sat_at(S, nx, ny, xb, ya - 1, za - 1) - sat_at(S, nx, ny, xa - 1, ya - 1, za - 1);
 }
 
+// A primitive's k-sigma box, voxel indices within the volume; empty if some
+// hi < lo.
+struct FeatBox {
+  int lo[3], hi[3];
+};
+static_assert(sizeof(FeatBox) == 3 * sizeof(double), "a box takes three doubles of the workspace");
+
 struct FeatArgs {
   const float* f;
   const float* theta;
   int64_t n, n_detail;
   gve_grid g;
   double g99;
-  float k;
   const double* s1;
   const double* s2;
   const double* J6;  // [n][6] structure tensors at the centres (k_feat_tensor)
+  const FeatBox* box;
+  const double* mom;  // [n][2] sums of V and V^2 over the boxes (k_box_sums)
+  const unsigned long long* touched;
   float* X;  // [n][16]
 };
 
@@ -738,6 +774,158 @@ __global__ __launch_bounds__(256) void k_feat_tensor(const float* __restrict__ f
   __shared__ float box[4][kTensorBox];
   wave_structure_tensor(f, Dims{g.nx, g.ny, g.nz}, c[0], c[1], c[2], box[threadIdx.x >> 6],
                         J6 + 6 * i);
+}
+
+// The boxes, and the blocks they touch added to *touched.
+__global__ __launch_bounds__(256) void k_feat_box(const float* __restrict__ theta, int64_t n,
+                                                  gve_grid g, float k, FeatBox* __restrict__ box,
+                                                  unsigned long long* __restrict__ touched) {
+  __shared__ unsigned long long tot[4];
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  unsigned long long t = 0;
+  if (i < n) {
+    const double mu[3] = {theta[0 * n + i], theta[1 * n + i], theta[2 * n + i]};
+    const int64_t org[3] = {g.x0, g.y0, g.z0};
+    const int64_t dim[3] = {g.nx, g.ny, g.nz};
+    double qw = theta[3 * n + i], qx = theta[4 * n + i], qy = theta[5 * n + i],
+           qz = theta[6 * n + i];
+    const double qn = sqrt(qw * qw + qx * qx + qy * qy + qz * qz);
+    if (qn >= 1e-12) { qw /= qn; qx /= qn; qy /= qn; qz /= qn; } else { qw = 1; qx = qy = qz = 0; }
+    const double R[3][3] = {{1 - 2 * (qy * qy + qz * qz), 2 * (qx * qy - qw * qz), 2 * (qx * qz + qw * qy)},
+                            {2 * (qx * qy + qw * qz), 1 - 2 * (qx * qx + qz * qz), 2 * (qy * qz - qw * qx)},
+                            {2 * (qx * qz - qw * qy), 2 * (qy * qz + qw * qx), 1 - 2 * (qx * qx + qy * qy)}};
+    const double s2v[3] = {exp(2.0 * (double)theta[7 * n + i]), exp(2.0 * (double)theta[8 * n + i]),
+                           exp(2.0 * (double)theta[9 * n + i])};
+    int64_t lo[3], hi[3];
+    bool empty = false;
+    for (int ax = 0; ax < 3; ++ax) {
+      const double sd = R[ax][0] * R[ax][0] * s2v[0] + R[ax][1] * R[ax][1] * s2v[1] +
+                        R[ax][2] * R[ax][2] * s2v[2];
+      const double h = (double)k * sqrt(sd);
+      double lf = ceil(mu[ax] - h - (double)org[ax]), hf = floor(mu[ax] + h - (double)org[ax]);
+      lf = fmax(lf, 0.0);
+      hf = fmin(hf, (double)(dim[ax] - 1));
+      if (lf > hf) empty = true;
+      lo[ax] = (int64_t)lf;
+      hi[ax] = (int64_t)hf;
+    }
+    FeatBox b;
+    for (int ax = 0; ax < 3; ++ax) {
+      b.lo[ax] = empty ? 1 : (int)lo[ax];
+      b.hi[ax] = empty ? 0 : (int)hi[ax];
+    }
+    box[i] = b;
+    if (!empty)
+      t = (unsigned long long)((hi[0] / kSatX - lo[0] / kSatX + 1) *
+                               (hi[1] / kSatY - lo[1] / kSatY + 1) *
+                               (hi[2] / kSatZ - lo[2] / kSatZ + 1));
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) t += __shfl_xor(t, o, 64);
+  if ((threadIdx.x & 63) == 0) tot[threadIdx.x >> 6] = t;
+  __syncthreads();
+  if (threadIdx.x == 0) atomicAdd(touched, tot[0] + tot[1] + tot[2] + tot[3]);
+}
+
+// x + (x of the lane DPP names), in the lanes of the rows of MASK.
+template <int CTRL, int MASK>
+__device__ inline double dpp_plus(double x) {
+  const uint64_t b = __double_as_longlong(x);
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, CTRL, MASK, 0xF, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), CTRL, MASK, 0xF, false);
+  return x + __longlong_as_double(((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo);
+}
+
+// Inclusive prefix sum over the lanes of a wave.
+__device__ inline double wave_prefix(double x) {
+  x = dpp_plus<0x111, 0xF>(x);  // row_shr:1, 2, 4, 8
+  x = dpp_plus<0x112, 0xF>(x);
+  x = dpp_plus<0x114, 0xF>(x);
+  x = dpp_plus<0x118, 0xF>(x);
+  x = dpp_plus<0x142, 0xA>(x);  // row_bcast:15 into rows 1 and 3
+  x = dpp_plus<0x143, 0xC>(x);  // row_bcast:31 into rows 2 and 3
+  return x;
+}
+
+// One wave per block of 64 x 8 x 8 voxels: its prefix sums, row after row, the
+// rows of the plane before held in registers.
+__global__ __launch_bounds__(64) void k_sat_blocks(const float* __restrict__ f, gve_grid g,
+                                                   const unsigned long long* __restrict__ touched,
+                                                   int64_t nbx, int64_t nby, int64_t nblocks,
+                                                   double2* __restrict__ T) {
+  if (!takes_blocks(touched, g.nx * g.ny * g.nz)) return;
+  const int lane = threadIdx.x;
+  for (int64_t b = blockIdx.x; b < nblocks; b += gridDim.x) {
+    const int64_t x = (b % nbx) * kSatX + lane;
+    const int64_t y0 = (b / nbx) % nby * kSatY, z0 = b / (nbx * nby) * kSatZ;
+    const bool in = x < g.nx;
+    double2 below[kSatY];
+#pragma unroll
+    for (int u = 0; u < kSatY; ++u) below[u] = make_double2(0.0, 0.0);
+    for (int w = 0; w < kSatZ && z0 + w < g.nz; ++w) {
+      const size_t o = (size_t)(in ? x : 0) + (size_t)g.nx * ((size_t)y0 + (size_t)g.ny * (size_t)(z0 + w));
+      float v[kSatY];
+#pragma unroll
+      for (int u = 0; u < kSatY; ++u)
+        v[u] = in && y0 + u < g.ny ? f[o + (size_t)g.nx * u] : 0.0f;
+      double a = 0.0, c = 0.0;
+#pragma unroll
+      for (int u = 0; u < kSatY; ++u) {
+        const double d = (double)v[u];
+        a += wave_prefix(d);
+        c += wave_prefix(d * d);
+        below[u].x += a;
+        below[u].y += c;
+        if (in && y0 + u < g.ny) T[o + (size_t)g.nx * u] = below[u];
+      }
+    }
+  }
+}
+
+// Sums of V and V^2 over the boxes, one wave per primitive, a lane per block
+// that the box touches; added in a fixed order.
+__global__ __launch_bounds__(256) void k_box_sums(const double2* __restrict__ T, int64_t n,
+                                                  gve_grid g, const FeatBox* __restrict__ box,
+                                                  const unsigned long long* __restrict__ touched,
+                                                  double* __restrict__ mom) {
+  if (!takes_blocks(touched, g.nx * g.ny * g.nz)) return;
+  const int64_t i = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (i >= n) return;  // wave-uniform
+  const FeatBox b = box[i];
+  if (b.hi[0] < b.lo[0]) return;  // empty: its sums are not read
+  const int bx0 = b.lo[0] / kSatX, by0 = b.lo[1] / kSatY, bz0 = b.lo[2] / kSatZ;
+  const uint32_t cx = b.hi[0] / kSatX - bx0 + 1, cy = b.hi[1] / kSatY - by0 + 1,
+                 cz = b.hi[2] / kSatZ - bz0 + 1;
+  double t1 = 0.0, t2 = 0.0;
+  for (uint32_t j = threadIdx.x & 63; j < cx * cy * cz; j += 64) {
+    const uint32_t q = j / cx;
+    const int x0 = (bx0 + (int)(j - q * cx)) * kSatX, y0 = (by0 + (int)(q % cy)) * kSatY,
+              z0 = (bz0 + (int)(q / cy)) * kSatZ;
+    const int xa = max(b.lo[0], x0), xb = min(b.hi[0], x0 + kSatX - 1);
+    const int ya = max(b.lo[1], y0), yb = min(b.hi[1], y0 + kSatY - 1);
+    const int za = max(b.lo[2], z0), zb = min(b.hi[2], z0 + kSatZ - 1);
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+      // a lower face on the block's own face adds nothing
+      if (((c & 1) && xa == x0) || ((c & 2) && ya == y0) || ((c & 4) && za == z0)) continue;
+      const size_t o = (size_t)((c & 1) ? xa - 1 : xb) +
+                       (size_t)g.nx * ((size_t)((c & 2) ? ya - 1 : yb) +
+                                       (size_t)g.ny * (size_t)((c & 4) ? za - 1 : zb));
+      const double2 v = T[o];
+      const bool minus = __builtin_popcount(c) & 1;
+      t1 += minus ? -v.x : v.x;
+      t2 += minus ? -v.y : v.y;
+    }
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    t1 += __shfl_xor(t1, o, 64);
+    t2 += __shfl_xor(t2, o, 64);
+  }
+  if ((threadIdx.x & 63) == 0) {
+    mom[2 * i] = t1;
+    mom[2 * i + 1] = t2;
+  }
 }
 
 __global__ __launch_bounds__(128) void k_features(FeatArgs a) {
@@ -783,33 +971,21 @@ __global__ __launch_bounds__(128) void k_features(FeatArgs a) {
     for (int q = 0; q < 3; ++q) out[3 + 3 * r + q] = (float)E[r][q];
   const int64_t vox = c[0] + d.nx * (c[1] + d.ny * c[2]);
   out[12] = a.g99 > 0.0 ? (float)((double)grad_mag32(a.f, d, vox) / a.g99) : 0.0f;
-  // mean and variance of V over the k-sigma box (summed-area tables)
-  double qw = a.theta[3 * n + i], qx = a.theta[4 * n + i], qy = a.theta[5 * n + i],
-         qz = a.theta[6 * n + i];
-  const double qn = sqrt(qw * qw + qx * qx + qy * qy + qz * qz);
-  if (qn >= 1e-12) { qw /= qn; qx /= qn; qy /= qn; qz /= qn; } else { qw = 1; qx = qy = qz = 0; }
-  const double R[3][3] = {{1 - 2 * (qy * qy + qz * qz), 2 * (qx * qy - qw * qz), 2 * (qx * qz + qw * qy)},
-                          {2 * (qx * qy + qw * qz), 1 - 2 * (qx * qx + qz * qz), 2 * (qy * qz - qw * qx)},
-                          {2 * (qx * qz - qw * qy), 2 * (qy * qz + qw * qx), 1 - 2 * (qx * qx + qy * qy)}};
-  const double s2v[3] = {exp(2.0 * (double)a.theta[7 * n + i]), exp(2.0 * (double)a.theta[8 * n + i]),
-                         exp(2.0 * (double)a.theta[9 * n + i])};
-  int64_t lo[3], hi[3];
-  bool empty = false;
-  for (int ax = 0; ax < 3; ++ax) {
-    const double sd = R[ax][0] * R[ax][0] * s2v[0] + R[ax][1] * R[ax][1] * s2v[1] +
-                      R[ax][2] * R[ax][2] * s2v[2];
-    const double h = (double)a.k * sqrt(sd);
-    double lf = ceil(mu[ax] - h - (double)org[ax]), hf = floor(mu[ax] + h - (double)org[ax]);
-    lf = fmax(lf, 0.0);
-    hf = fmin(hf, (double)(dim[ax] - 1));
-    if (lf > hf) empty = true;
-    lo[ax] = (int64_t)lf;
-    hi[ax] = (int64_t)hf;
-  }
+  // mean and variance of V over the k-sigma box
+  const FeatBox b = a.box[i];
+  const bool empty = b.hi[0] < b.lo[0] || b.hi[1] < b.lo[1] || b.hi[2] < b.lo[2];
   if (!empty) {
-    const double cnt = (double)((hi[0] - lo[0] + 1) * (hi[1] - lo[1] + 1) * (hi[2] - lo[2] + 1));
-    const double m1 = box_sum(a.s1, d.nx, d.ny, lo[0], hi[0], lo[1], hi[1], lo[2], hi[2]) / cnt;
-    const double m2 = box_sum(a.s2, d.nx, d.ny, lo[0], hi[0], lo[1], hi[1], lo[2], hi[2]) / cnt;
+    const double cnt = (double)((int64_t)(b.hi[0] - b.lo[0] + 1) * (b.hi[1] - b.lo[1] + 1) *
+                                (b.hi[2] - b.lo[2] + 1));
+    double t1, t2;
+    if (takes_blocks(a.touched, dim[0] * dim[1] * dim[2])) {
+      t1 = a.mom[2 * i];
+      t2 = a.mom[2 * i + 1];
+    } else {
+      t1 = box_sum(a.s1, d.nx, d.ny, b.lo[0], b.hi[0], b.lo[1], b.hi[1], b.lo[2], b.hi[2]);
+      t2 = box_sum(a.s2, d.nx, d.ny, b.lo[0], b.hi[0], b.lo[1], b.hi[1], b.lo[2], b.hi[2]);
+    }
+    const double m1 = t1 / cnt, m2 = t2 / cnt;
     out[13] = (float)m1;
     out[14] = (float)fmax(m2 - m1 * m1, 0.0);
   } else {
@@ -967,31 +1143,53 @@ hipError_t mlp_perm_keys(uint32_t* keys, uint32_t* vals, int64_t n, uint64_t see
   return hipGetLastError();
 }
 
-hipError_t mlp_sat(const float* f, const gve_grid& g, double* s1, double* s2, hipStream_t s) {
+size_t mlp_feature_doubles(int64_t M, int64_t n) { return 2 * (size_t)M + 11 * (size_t)n + 1; }
+
+hipError_t mlp_features(const float* f, const float* theta, int64_t n, int64_t n_detail,
+                        const gve_grid& g, double g99, float k, double* work, float* X,
+                        hipStream_t s) {
+  const int64_t M = g.nx * g.ny * g.nz;
+  double *s1 = work, *s2 = s1 + M, *J6 = s2 + M, *mom = J6 + 6 * n;
+  FeatBox* box = reinterpret_cast<FeatBox*>(mom + 2 * n);
+  unsigned long long* touched = reinterpret_cast<unsigned long long*>(mom + 5 * n);
+  hipError_t e = fill_u64(touched, 1, s);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_feat_box, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, theta, n, g, k,
+                     box, touched);
+  e = hipGetLastError();
+  if (e != hipSuccess) return e;
   const int64_t lines = g.ny * g.nz;
-  hipLaunchKernelGGL(k_sat_x, dim3((unsigned)lines), dim3(256), 0, s, f, g.nx, s1, s2);
-  hipError_t e = hipGetLastError();
+  hipLaunchKernelGGL(k_sat_x, dim3((unsigned)std::min<int64_t>(lines, kSatLines)), dim3(256), 0, s,
+                     f, g.nx, lines, touched, s1, s2);
+  e = hipGetLastError();
   if (e != hipSuccess) return e;
   // along y: lines (x, z), inner = nx, len = ny, stride nx
   const int64_t ly = g.nx * g.nz;
   hipLaunchKernelGGL(k_sat_axis, dim3((unsigned)((ly + 255) / 256)), dim3(256), 0, s, s1, s2, ly,
-                     g.nx, g.ny, g.nx);
+                     g.nx, g.ny, g.nx, touched);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   // along z: lines (x, y), inner = nx * ny, len = nz, stride nx * ny
   const int64_t lz = g.nx * g.ny;
   hipLaunchKernelGGL(k_sat_axis, dim3((unsigned)((lz + 255) / 256)), dim3(256), 0, s, s1, s2, lz,
-                     g.nx * g.ny, g.nz, g.nx * g.ny);
-  return hipGetLastError();
-}
-
-hipError_t mlp_features(const float* f, const float* theta, int64_t n, int64_t n_detail,
-                        const gve_grid& g, double g99, float k, const double* s1, const double* s2,
-                        double* J6, float* X, hipStream_t s) {
-  FeatArgs a{f, theta, n, n_detail, g, g99, k, s1, s2, J6, X};
+                     g.nx * g.ny, g.nz, g.nx * g.ny, touched);
+  e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  double2* T = reinterpret_cast<double2*>(work);
+  const int64_t nbx = (g.nx + kSatX - 1) / kSatX, nby = (g.ny + kSatY - 1) / kSatY,
+                nblocks = nbx * nby * ((g.nz + kSatZ - 1) / kSatZ);
+  hipLaunchKernelGGL(k_sat_blocks, dim3((unsigned)std::min<int64_t>(nblocks, kSatBlocks)), dim3(64),
+                     0, s, f, g, touched, nbx, nby, nblocks, T);
+  e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_box_sums, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, s, T, n, g, box, touched,
+                     mom);
+  e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  FeatArgs a{f, theta, n, n_detail, g, g99, s1, s2, J6, box, mom, touched, X};
   hipLaunchKernelGGL(k_feat_tensor, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, s, f, theta, n, g,
                      J6);
-  hipError_t e = hipGetLastError();
+  e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_features, dim3((unsigned)((n + 127) / 128)), dim3(128), 0, s, a);
   return hipGetLastError();
