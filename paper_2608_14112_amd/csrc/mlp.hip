@@ -433,10 +433,12 @@ __device__ inline void wgrad_tiles(const unsigned short* __restrict__ a, int sa,
 }
 
 // Bias gradient of sixteen columns: the float32 terms added row by row, in row
-// order (a running sum, so its length is the kernel's: about 3 ns a row).
+// order (a running sum, so its length is the kernel's: about 3 ns a row; with the reads of LDS
+// ahead of the additions 19.3 us at 4,096 rows, 21.4 without).
 // 32 row tiles at a time are staged in LDS by all four waves, the next ones
 // while sixteen lanes of wave 0 add the current ones.
 constexpr int kBiasTiles = 32;
+constexpr int kBiasAhead = 8;
 __device__ inline void bias_sum(const float4v* __restrict__ v, int stride, int64_t tiles,
                                 float4v* buf, float* __restrict__ out, int nout) {
   const int t = threadIdx.x;
@@ -460,14 +462,43 @@ __device__ inline void bias_sum(const float4v* __restrict__ v, int stride, int64
     if (r0 + kBiasTiles < tiles) fetch(r0 + kBiasTiles);
     // the buffer written next was read before the barrier above
     if (t < 16) {
+      // rows 4 k .. 4 k + 3 at a time; the next eight reads of LDS are issued
+      // before the current eight are added
       const int lim = (int)min((int64_t)kBiasTiles, tiles - r0) * 4;
-#pragma unroll 8
-      for (int k = 0; k < lim; ++k) {  // rows 4 k .. 4 k + 3
-        const float4v x = cur[k * 16 + t];
-        s += x[0];
-        s += x[1];
-        s += x[2];
-        s += x[3];
+      const float4v* p = cur + t;
+      float4v x[kBiasAhead], y[kBiasAhead];
+      auto read = [&](float4v(&d)[kBiasAhead], int k) {
+#pragma unroll
+        for (int u = 0; u < kBiasAhead; ++u) d[u] = p[(k + u) * 16];
+      };
+      auto add = [&](const float4v(&d)[kBiasAhead]) {
+#pragma unroll
+        for (int u = 0; u < kBiasAhead; ++u) {
+          s += d[u][0];
+          s += d[u][1];
+          s += d[u][2];
+          s += d[u][3];
+        }
+      };
+      int k = 0;
+      if (lim == 4 * kBiasTiles) {
+        read(x, 0);
+#pragma unroll
+        for (; k < 4 * kBiasTiles; k += 2 * kBiasAhead) {
+          read(y, k + kBiasAhead);
+          __builtin_amdgcn_sched_barrier(0);
+          add(x);
+          if (k + 2 * kBiasAhead < 4 * kBiasTiles) read(x, k + 2 * kBiasAhead);
+          __builtin_amdgcn_sched_barrier(0);
+          add(y);
+        }
+      }
+      for (; k < lim; ++k) {
+        const float4v z = p[k * 16];
+        s += z[0];
+        s += z[1];
+        s += z[2];
+        s += z[3];
       }
     }
   }
