@@ -793,18 +793,16 @@ __global__ __launch_bounds__(256) void k_jitter(Dims d, int64_t x0, int64_t y0, 
 }
 
 // Dot products <U, V> and <U, U> in double (two-level, deterministic).
-constexpr int kDotBlocks = 1024;
-__global__ __launch_bounds__(kThreads) void k_dot_partial(const float* __restrict__ u,
-                                                          const float* __restrict__ v, int64_t M,
-                                                          double* __restrict__ part) {
+constexpr int kDotBlocks = 256;
+__global__ __launch_bounds__(kThreads) void k_dot_partial(const double2* __restrict__ in,
+                                                          int64_t n, double* __restrict__ part) {
   __shared__ double s1[kThreads], s2[kThreads];
-  const int64_t per = (M + gridDim.x - 1) / gridDim.x;
-  const int64_t a = (int64_t)blockIdx.x * per, e = min(M, a + per);
+  const int64_t per = (n + gridDim.x - 1) / gridDim.x;
+  const int64_t a = (int64_t)blockIdx.x * per, e = min(n, a + per);
   double uv = 0.0, uu = 0.0;
   for (int64_t i = a + threadIdx.x; i < e; i += kThreads) {
-    const double x = u[i], y = v[i];
-    uv += x * y;
-    uu += x * x;
+    uv += in[i].x;
+    uu += in[i].y;
   }
   s1[threadIdx.x] = uv;
   s2[threadIdx.x] = uu;
@@ -1065,9 +1063,10 @@ hipError_t alloc_assemble(const float* f, const float* g32, const gve_grid& g, c
 
 size_t alloc_dot_tmp_doubles() { return 2 * kDotBlocks + 8; }
 
-hipError_t alloc_weights(const float* U, const float* f, int64_t M, float* c_row, int64_t n,
-                         double* tmp, hipStream_t s) {
-  hipLaunchKernelGGL(k_dot_partial, dim3(kDotBlocks), dim3(kThreads), 0, s, U, f, M, tmp + 8);
+hipError_t alloc_weights(const double* part, int64_t pairs, float* c_row, int64_t n, double* tmp,
+                         hipStream_t s) {
+  hipLaunchKernelGGL(k_dot_partial, dim3(kDotBlocks), dim3(kThreads), 0, s,
+                     reinterpret_cast<const double2*>(part), pairs, tmp + 8);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_kappa, dim3(1), dim3(kThreads), 0, s, tmp + 8, kDotBlocks, tmp);

@@ -1688,13 +1688,17 @@ gve_status gve_allocate(gve_ctx* ctx, const float* d_field, gve_grid g, int64_t 
   // S1d/S1e: frames, scales, values
   TRY_A(gve::alloc_assemble(d_field, g32, g, det, cov, n_det, budget, sb, st_g99, seed, p->theta,
                             F64(o_j6), s));
-  // weights: U = sum a_i G_i on the grid (g32's buffer is free now), kappa
+  // weights: kappa from the sums of V U and U^2, U = sum a_i G_i on the grid
   Binned bn;
   st = bin(ctx, p, g, &bn);
   if (st != GVE_OK) return cleanup(st);
-  TRY_A(gve::launch_forward(p->rec, bn.gid, bn.lists, bn.items, bn.nitems, bn.bg, ctx->opt.k, g32,
-                            bn.sched, s));
-  TRY_A(gve::alloc_weights(g32, d_field, M, p->theta + 10 * budget, budget, F64(o_dot), s));
+  st = ensure(ctx, ctx->ws.brick_loss, 2 * sizeof(double) * (size_t)gve::forward_dot_pairs(bn.bg));
+  if (st != GVE_OK) return cleanup(st);
+  double* dots = static_cast<double*>(ctx->ws.brick_loss.ptr);
+  int64_t pairs = 0;
+  TRY_A(gve::launch_forward_dot(p->rec, bn.gid, bn.lists, bn.items, bn.nitems, bn.bg, ctx->opt.k,
+                                d_field, dots, &pairs, bn.sched, s));
+  TRY_A(gve::alloc_weights(dots, pairs, p->theta + 10 * budget, budget, F64(o_dot), s));
 #undef TRY_A
   // report
   double* hp = static_cast<double*>(ctx->ws.h_pinned);

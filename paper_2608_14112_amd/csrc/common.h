@@ -286,6 +286,13 @@ int fused_resident_groups(int bxy, int bz, int waves, int device);
 hipError_t launch_forward(const Record* rec, const uint32_t* pair_gid,
                           BrickLists lists, const ItemDesc* items, int nitems,
                           BrickGeom bg, float k, float* out, const Schedule& sc, hipStream_t s);
+// The sums of V Vhat and Vhat^2 over each wave's voxels in place of the field:
+// *pairs (at most forward_dot_pairs) pairs of doubles in part.
+int64_t forward_dot_pairs(BrickGeom bg);
+hipError_t launch_forward_dot(const Record* rec, const uint32_t* pair_gid, BrickLists lists,
+                              const ItemDesc* items, int nitems, BrickGeom bg, float k,
+                              const float* field, double* part, int64_t* pairs, const Schedule& sc,
+                              hipStream_t s);
 // part == nullptr: float atomics into acc [n][kAccStride].  Otherwise each (primitive,
 // brick) pair stores its ten sums to part[pslot[j] * 10 + a], pslot[j] = the
 // emission index of sorted pair j (a primitive's emission range is
@@ -371,8 +378,9 @@ hipError_t alloc_assemble(const float* f, const float* g32, const gve_grid& g, c
                           const unsigned long long* g99_state, uint64_t seed, float* theta,
                           double* J6, hipStream_t s);
 size_t alloc_dot_tmp_doubles();
-hipError_t alloc_weights(const float* U, const float* f, int64_t M, float* c_row, int64_t n,
-                         double* tmp, hipStream_t s);
+// c_row *= kappa = sum V U / sum U^2, of `pairs` pairs of partial sums.
+hipError_t alloc_weights(const double* part, int64_t pairs, float* c_row, int64_t n, double* tmp,
+                         hipStream_t s);
 size_t normalize_tmp_floats();
 hipError_t normalize_field(float* f, int64_t M, float* tmp, hipStream_t s);
 

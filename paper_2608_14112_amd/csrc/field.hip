@@ -463,12 +463,88 @@ __device__ inline void accumulate_slice(const Record* __restrict__ rec,
   }
 }
 
-template <int BXY, int BZ>
+// Target values of the lane's column at brick offsets z0 .. z0 + NZ - 1
+// (0 outside the volume), read as raw buffer loads: each z-plane's brick corner
+// is a uniform resource base and the lane's byte offset the one per-lane
+// operand, so the NZ loads share one offset register and are issued together
+// (one wait per chunk rather than per voxel).  A lane whose column lies outside
+// the volume passes an offset past the record count and reads 0.
+constexpr int kLoadZ = 8;
+// Fourth word of a gfx9-family buffer resource: 32-bit data format, no
+// swizzle, no index stride (the offset is a plain byte offset).
+constexpr int kBufferWord3 = 0x00020000;
+
+__device__ inline float plane_load(const float* __restrict__ buf, const Site& st, int zz,
+                                   uint32_t voff, int nrec) {
+  const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
+      (void*)(buf + st.org + st.plane * (size_t)zz), (short)0, nrec, kBufferWord3);
+  return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, (int)voff, 0, 0));
+}
+
+template <int NZ>
+__device__ inline void load_column_chunk(const float* __restrict__ field, const Site& st,
+                                         uint32_t voff, int nrec, int z0, float (&t)[NZ]) {
+  if (z0 + NZ <= st.zrem) {
+#pragma unroll
+    for (int u = 0; u < NZ; ++u) t[u] = plane_load(field, st, z0 + u, voff, nrec);
+  } else {
+#pragma unroll
+    for (int u = 0; u < NZ; ++u)
+      t[u] = z0 + u < st.zrem ? plane_load(field, st, z0 + u, voff, nrec) : 0.0f;
+  }
+}
+
+// Where a wave's voxel values go: to `out`, or with DOT into this wave's pair of
+// sums (V Vhat, Vhat^2) over its voxels against the target `field`, in double
+// (the allocation needs nothing else of the field, which then is neither
+// written nor read back: an allocation of 262,144 in 512^3 5.08 -> 4.82 ms).
+struct FieldOut {
+  float* out;
+  const float* field;
+  double2* part;
+};
+
+template <int NZ, bool DOT>
+__device__ inline void column_out(const float (&acc)[NZ], const Site& st, int z0, const FieldOut& o,
+                                  size_t slot) {
+  if constexpr (DOT) {
+    const uint32_t voff = st.col_in ? st.lbytes : 0x80000000u;
+    const int nrec = (int)std::min(st.plane * 4, (size_t)0x7FFFFFFF);
+    constexpr int kChunk = NZ < kLoadZ ? NZ : kLoadZ;
+    double uv = 0.0, uu = 0.0;
+#pragma unroll
+    for (int c = 0; c < NZ; c += kChunk) {
+      float t[kChunk];
+      load_column_chunk<kChunk>(o.field, st, voff, nrec, z0 + c, t);
+#pragma unroll
+      for (int u = 0; u < kChunk; ++u) {
+        // columns and offsets outside the volume count for nothing
+        const double x = st.col_in && z0 + c + u < st.zrem ? (double)acc[c + u] : 0.0;
+        uv = fma(x, (double)t[u], uv);
+        uu = fma(x, x, uu);
+      }
+      // one chunk of loads and conversions at a time: within 64 registers
+      asm volatile("" : "+v"(uv), "+v"(uu)::"memory");
+    }
+#pragma unroll
+    for (int m = 32; m > 0; m >>= 1) {
+      uv += __shfl_xor(uv, m, 64);
+      uu += __shfl_xor(uu, m, 64);
+    }
+    if ((threadIdx.x & 63) == 0) o.part[slot] = make_double2(uv, uu);
+  } else if (st.col_in) {
+#pragma unroll
+    for (int u = 0; u < NZ; ++u)
+      if (z0 + u < st.zrem) *st.at(o.out, z0 + u) = acc[u];
+  }
+}
+
+template <int BXY, int BZ, bool DOT>
 __device__ __attribute__((always_inline)) inline void forward_brick(const Record* __restrict__ rec,
                                      const uint32_t* __restrict__ pair_gid,
                                      BrickLists lists,
                                      const ItemDesc* __restrict__ items, int nitems, uint32_t b,
-                                     float thr, float* __restrict__ out) {
+                                     float thr, const FieldOut& out) {
   const Site st = site_of<BXY, BZ>(items, nitems, b);
   float acc[BZ];
 #pragma unroll
@@ -477,30 +553,27 @@ __device__ __attribute__((always_inline)) inline void forward_brick(const Record
   accumulate_brick<BZ>(rec, pair_gid, j0, j0, 1u, lists.end[b],
                        st.px, st.py, st.pz0, st.iz0, __builtin_amdgcn_ballot_w64(st.col_in), thr,
                        acc, nullptr);
-  if (st.col_in) {
-#pragma unroll
-    for (int zz = 0; zz < BZ; ++zz)
-      if (zz < st.zrem) *st.at(out, zz) = acc[zz];
-  }
+  constexpr int kWaves = (BXY * BXY + 63) / 64;
+  column_out<BZ, DOT>(acc, st, 0, out, (size_t)b * kWaves + (threadIdx.x >> 6));
 }
 
-template <int BXY, int BZ>
+template <int BXY, int BZ, bool DOT>
 __global__ __launch_bounds__(BXY* BXY) void k_forward(const Record* __restrict__ rec,
                                                   const uint32_t* __restrict__ pair_gid,
                                                   BrickLists lists,
                                                   const ItemDesc* __restrict__ items, int nitems,
                                                   uint32_t nbricks, int xcd, float thr,
-                                                  float* __restrict__ out) {
+                                                  FieldOut out) {
   const uint32_t b = xcd ? xcd_brick(blockIdx.x, nbricks) : blockIdx.x;
-  forward_brick<BXY, BZ>(rec, pair_gid, lists, items, nitems, b, thr, out);
+  forward_brick<BXY, BZ, DOT>(rec, pair_gid, lists, items, nitems, b, thr, out);
 }
 
 // The same with the brick's offsets dealt to BZ / SL waves.
-template <int BZ, int SL>
+template <int BZ, int SL, bool DOT>
 __global__ __launch_bounds__(BZ / SL * 64) void k_forward_sliced(
     const Record* __restrict__ rec, const uint32_t* __restrict__ pair_gid,
     BrickLists lists, const ItemDesc* __restrict__ items, int nitems,
-    uint32_t nbricks, int xcd, float thr, float* __restrict__ out) {
+    uint32_t nbricks, int xcd, float thr, FieldOut out) {
   const uint32_t b = xcd ? xcd_brick(blockIdx.x, nbricks) : blockIdx.x;
   const int slice = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const Site st = site_of<8, BZ>(items, nitems, b, threadIdx.x & 63);
@@ -508,11 +581,7 @@ __global__ __launch_bounds__(BZ / SL * 64) void k_forward_sliced(
 #pragma unroll
   for (int u = 0; u < SL; ++u) acc[u] = 0.0f;
   accumulate_slice<BZ, SL>(rec, pair_gid, lists.start[b], lists.end[b], st, slice, thr, acc, nullptr);
-  if (st.col_in) {
-#pragma unroll
-    for (int u = 0; u < SL; ++u)
-      if (slice * SL + u < st.zrem) *st.at(out, slice * SL + u) = acc[u];
-  }
+  column_out<SL, DOT>(acc, st, slice * SL, out, (size_t)b * (BZ / SL) + slice);
 }
 
 // The backward steps of one pair over the brick offsets in `run`: moments
@@ -595,37 +664,6 @@ __device__ inline void backward_steps_chain(const ColumnSetup& s, float szv, flo
         }
       }
     }
-  }
-}
-
-// Target values of the lane's column at brick offsets z0 .. z0 + NZ - 1
-// (0 outside the volume), read as raw buffer loads: each z-plane's brick corner
-// is a uniform resource base and the lane's byte offset the one per-lane
-// operand, so the NZ loads share one offset register and are issued together
-// (one wait per chunk rather than per voxel).  A lane whose column lies outside
-// the volume passes an offset past the record count and reads 0.
-constexpr int kLoadZ = 8;
-// Fourth word of a gfx9-family buffer resource: 32-bit data format, no
-// swizzle, no index stride (the offset is a plain byte offset).
-constexpr int kBufferWord3 = 0x00020000;
-
-__device__ inline float plane_load(const float* __restrict__ buf, const Site& st, int zz,
-                                   uint32_t voff, int nrec) {
-  const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
-      (void*)(buf + st.org + st.plane * (size_t)zz), (short)0, nrec, kBufferWord3);
-  return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, (int)voff, 0, 0));
-}
-
-template <int NZ>
-__device__ inline void load_column_chunk(const float* __restrict__ field, const Site& st,
-                                         uint32_t voff, int nrec, int z0, float (&t)[NZ]) {
-  if (z0 + NZ <= st.zrem) {
-#pragma unroll
-    for (int u = 0; u < NZ; ++u) t[u] = plane_load(field, st, z0 + u, voff, nrec);
-  } else {
-#pragma unroll
-    for (int u = 0; u < NZ; ++u)
-      t[u] = z0 + u < st.zrem ? plane_load(field, st, z0 + u, voff, nrec) : 0.0f;
   }
 }
 
@@ -1129,17 +1167,22 @@ int fused_resident_groups(int bxy, int bz, int waves, int device) {
   return 0;
 }
 
-hipError_t launch_forward(const Record* rec, const uint32_t* pair_gid, BrickLists lists,
-                          const ItemDesc* items, int nitems, BrickGeom bg, float k, float* out,
-                          const Schedule& sc, hipStream_t s) {
+namespace {
+// *waves: the waves of the launch (with DOT, the pairs of sums it writes).
+template <bool DOT>
+hipError_t run_forward(const Record* rec, const uint32_t* pair_gid, BrickLists lists,
+                       const ItemDesc* items, int nitems, BrickGeom bg, float k, FieldOut out,
+                       const Schedule& sc, hipStream_t s, int64_t* waves) {
   const float thr = -kHalfLog2e * k * k;
+  *waves = 0;
   if (bg.nbricks <= 0) return hipSuccess;
   const dim3 grid((unsigned)bg.nbricks);
   const int xcd = sc.kind == kSchedXcd ? 1 : 0;
 #define GVE_CASE(Z, SL, LIMIT)                                                                  \
   if (bg.Bxy == 8 && bg.Bz == Z && bg.nbricks <= (LIMIT)) {                                     \
-    hipLaunchKernelGGL((k_forward_sliced<Z, SL>), grid, dim3(Z / SL * 64), 0, s, rec, pair_gid, \
-                       lists, items, nitems, (uint32_t)bg.nbricks, xcd, thr, out);              \
+    *waves = bg.nbricks * (Z / SL);                                                             \
+    hipLaunchKernelGGL((k_forward_sliced<Z, SL, DOT>), grid, dim3(Z / SL * 64), 0, s, rec,      \
+                       pair_gid, lists, items, nitems, (uint32_t)bg.nbricks, xcd, thr, out);    \
     return hipGetLastError();                                                                   \
   }
   GVE_CASE(8, 2, kSlabs2)
@@ -1152,13 +1195,37 @@ hipError_t launch_forward(const Record* rec, const uint32_t* pair_gid, BrickList
 #undef GVE_CASE
 #define GVE_CASE(XY, Z)                                                                       \
   if (bg.Bxy == XY && bg.Bz == Z) {                                                           \
-    hipLaunchKernelGGL((k_forward<XY, Z>), grid, dim3(XY * XY), 0, s, rec, pair_gid,            \
+    *waves = bg.nbricks * ((XY * XY + 63) / 64);                                              \
+    hipLaunchKernelGGL((k_forward<XY, Z, DOT>), grid, dim3(XY * XY), 0, s, rec, pair_gid,       \
                        lists, items, nitems, (uint32_t)bg.nbricks, xcd, thr, out);              \
     return hipGetLastError();                                                                 \
   }
   GVE_BRICK_SHAPES(GVE_CASE)
 #undef GVE_CASE
   return hipErrorInvalidValue;
+}
+}  // namespace
+
+hipError_t launch_forward(const Record* rec, const uint32_t* pair_gid, BrickLists lists,
+                          const ItemDesc* items, int nitems, BrickGeom bg, float k, float* out,
+                          const Schedule& sc, hipStream_t s) {
+  int64_t waves;
+  return run_forward<false>(rec, pair_gid, lists, items, nitems, bg, k,
+                            FieldOut{out, nullptr, nullptr}, sc, s, &waves);
+}
+
+// A wave per 64 columns, up to 16 where bricks are sliced.
+int64_t forward_dot_pairs(BrickGeom bg) {
+  return bg.nbricks * ((bg.Bxy * bg.Bxy + 63) / 64) +
+         15 * std::min<int64_t>(bg.nbricks, kSlicedForwardBricks);
+}
+
+hipError_t launch_forward_dot(const Record* rec, const uint32_t* pair_gid, BrickLists lists,
+                              const ItemDesc* items, int nitems, BrickGeom bg, float k,
+                              const float* field, double* part, int64_t* pairs, const Schedule& sc,
+                              hipStream_t s) {
+  return run_forward<true>(rec, pair_gid, lists, items, nitems, bg, k,
+                           FieldOut{nullptr, field, reinterpret_cast<double2*>(part)}, sc, s, pairs);
 }
 
 namespace {
