@@ -28,10 +28,13 @@
  *    passes and must keep it alive until the stream has executed the work.
  *  - Work is queued on the context's stream.  Calls that write host memory
  *    (h_ outputs) synchronise that stream before returning.  The others queue
- *    their kernels asynchronously, but each binning of the primitives (every
- *    evaluation, loss and gradient) waits for two small device-to-host reads
- *    on the stream (the totals of box and kept (primitive, brick) pairs, from
- *    which the pair buffers are sized), and a call whose grids or brick shape
+ *    their kernels asynchronously, but a binning of the primitives (every
+ *    evaluation, loss and gradient) of a large set waits for two small
+ *    device-to-host reads on the stream (the totals of box and kept (primitive,
+ *    brick) pairs, from which the pair buffers are sized); so does any set with
+ *    options.deterministic or the queue schedule.  Smaller sets (at most 32,768
+ *    primitives a volume, 16,384 bricks and 2^25 (primitive, brick)
+ *    combinations) are binned without a read.  A call whose grids or brick shape
  *    differ from the previous call's also waits for the upload of its volume
  *    descriptors.  Refinement (gve_refine, gve_batch_refine) waits so only in
  *    its first iteration: later iterations bin into buffers of the first
@@ -218,7 +221,7 @@ gve_status gve_evaluate(gve_ctx* ctx, const gve_params* p, gve_grid g, float* d_
  * Loss and gradient (Sec. III-F value term, as a plain squared norm over
  * every voxel of g).  L = sum_p (Vhat(p) - V(p))^2 with V = d_field [nz][ny][nx]
  * float32.  Writes dL/dtheta as [11][n] float32 into d_grad (caller-owned;
- * may be NULL to skip) with the truncation indicator held fixed, and L into
+ * may be NULL to skip: then only the loss is computed) with the truncation indicator held fixed, and L into
  * *h_loss if h_loss is not NULL (synchronises).  With options.deterministic
  * the gradient is bitwise reproducible; with float atomics its last bits
  * depend on execution order.
@@ -605,7 +608,9 @@ gve_status gve_warmstart(gve_ctx* ctx, const gve_mlp* m, gve_params* p, const fl
                          gve_grid g, int64_t n_detail, double g99, int32_t* applied,
                          double* h_losses);
 
-/* Counters of the last call (see gve_stats). */
+/* Counters of the last call (see gve_stats).  Waits for the context's stream if
+ * the last binning's pair counts are still on the device; while that stream is
+ * being captured they stay those of the last read. */
 gve_status gve_get_stats(const gve_ctx* ctx, gve_stats* out);
 
 /* Static description of a status code; never NULL. */

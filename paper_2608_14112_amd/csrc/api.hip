@@ -315,7 +315,10 @@ bool stream_capturing(const gve_ctx* ctx) {
 // 133 -> 73 us, 64^3 x 16,384 (2^23) 217 -> 144, 128^3 x 16,384 (2^25) 162 ->
 // 119; 2^26 tests 165 -> 152 and its refinement iterations 223 -> 231, 2^27
 // 175 -> 227.  64 bricks x 32,768 primitives 314 -> 284, x 65,536 530 -> 541.
+// A workgroup per brick also has to be launched, however few the primitives:
+// 8,192 bricks x 16 108 -> 55 us, 32,768 x 64 113 -> 118, 65,536 x 16 267 -> 358.
 constexpr int64_t kDirectTests = (int64_t)1 << 25;
+constexpr int64_t kDirectBricks = 16384;
 constexpr int64_t kDirectPrims = 32768;
 
 // Whether the set (with the current brick shape) is binned directly.  Not with
@@ -328,6 +331,7 @@ bool bins_directly(const gve_ctx* ctx, const Vol& vol) {
     return false;
   const int64_t bxy = brick_xy(ctx), bz = brick_z(ctx);
   double tests = 0.0;
+  int64_t bricks = 0;
   for (int i = 0; i < vol.n; ++i) {
     const gve_grid& g = vol.grids[i];
     const int64_t nbx = (g.nx + bxy - 1) / bxy, nby = (g.ny + bxy - 1) / bxy,
@@ -335,8 +339,9 @@ bool bins_directly(const gve_ctx* ctx, const Vol& vol) {
     if (nbx > gve::kDirectAxis || nby > gve::kDirectAxis || nbz > gve::kDirectAxis ||
         np > kDirectPrims)
       return false;
+    bricks += nbx * nby * nbz;
     tests += (double)nbx * (double)nby * (double)nbz * (double)np;
-    if (tests > (double)kDirectTests) return false;
+    if (tests > (double)kDirectTests || bricks > kDirectBricks) return false;
   }
   return !stream_capturing(ctx);
 }

@@ -701,7 +701,7 @@ __device__ __attribute__((always_inline)) inline void fused_brick(const Record* 
   static_assert(!SLICED || (BZ % W == 0 && W > 1 && !VJP), "one wave per slice");
   const int lane = threadIdx.x & 63;
   // uniform, so that the waves' pair indices, masks and branches stay scalar
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wave = W * kWaves > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0;
   const Site st = site_of<BXY, BZ>(items, nitems, b, W > 1 ? (uint32_t)lane : threadIdx.x);
   const float px = st.px, py = st.py, pz0 = st.pz0;
   const int iz0 = st.iz0;

@@ -21,7 +21,8 @@ def _lib():
 
 # (grid, primitives, scales): runs of 64 and passes of 2,048 primitives, each
 # one short, whole and one over; a single voxel column; the largest directly
-# binned volume (32,768 primitives) and the first that is not; ragged extents
+# binned volume (32,768 primitives) and the first that is not, the most bricks
+# (16,384 of 8 x 8 x 8) and one more; ragged extents
 CASES = [((1, 1, 9), 1, (0.5, 2.0)),
          ((16, 16, 16), 63, (1.0, 3.0)),
          ((17, 9, 33), 64, (1.0, 6.0)),
@@ -30,7 +31,9 @@ CASES = [((1, 1, 9), 1, (0.5, 2.0)),
          ((64, 64, 64), 2048, (1.5, 4.0)),
          ((61, 45, 37), 2049, (0.5, 8.0)),
          ((40, 24, 41), 32768, (0.5, 3.0)),
-         ((40, 24, 41), 32769, (0.5, 3.0))]
+         ((40, 24, 41), 32769, (0.5, 3.0)),
+         ((256, 256, 128), 300, (0.5, 6.0)),
+         ((8, 8, 131073), 300, (0.5, 6.0))]
 
 
 def _params(n, dims, seed, scales):
