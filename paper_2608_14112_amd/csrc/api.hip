@@ -438,7 +438,13 @@ gve_status bin_vol(gve_ctx* ctx, const gve_params* p, const Vol& vol, Binned* ou
   TRY(upload_items(ctx, vol, bg.Bxy, bg.Bz, &bg.nbricks));
   if (bg.nbricks >= ((int64_t)1 << 31))
     return fail(ctx, GVE_ERR_UNSUPPORTED, "too many bricks for 32-bit brick keys");
-  if (!ec && bins_directly(ctx, vol)) return bin_direct(ctx, p, vol, bg, out);
+  if (!ec && bins_directly(ctx, vol)) {
+    const gve_status st = bin_direct(ctx, p, vol, bg, out);
+    // the general binning's buffers hold the pairs only, not every combination
+    if (st != GVE_ERR_OUT_OF_MEMORY) return st;
+    (void)hipGetLastError();
+    ctx->last_error.clear();
+  }
   // capacity sized for these volumes and this brick shape only
   if (async && (ctx->box_cap <= 0 || !same_items(ctx->pair_cap_items, ctx->items_host)))
     async = false;
