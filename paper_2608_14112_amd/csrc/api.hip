@@ -1591,7 +1591,6 @@ gve_status gve_allocate(gve_ctx* ctx, const float* d_field, gve_grid g, int64_t 
   TRY(set_device(ctx));
   hipStream_t s = ctx->stream;
   const int64_t M = g.nx * g.ny * g.nz;
-  const int64_t nb = (int64_t)gve::alloc_block_count(M);
   const int64_t n_det = (int64_t)std::floor(0.55 * (double)budget + 0.5);
   const int64_t n_cov = budget - n_det;
   // scratch of the survey, then (once the candidates are counted) of the rest

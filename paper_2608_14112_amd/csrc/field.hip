@@ -1249,17 +1249,19 @@ struct FusedArgs {
 
 template <int XY, int Z, int MODE, int W, bool SLICED>
 hipError_t run_fused(const FusedArgs& a, const Schedule& sc, hipStream_t s) {
-  if (sc.kind == kSchedQueue && !SLICED) {
-    const dim3 grid((unsigned)std::min<int64_t>(sc.persistent_groups, a.nb));
-    hipLaunchKernelGGL((k_fused_queue<XY, Z, MODE, W>), grid, dim3(XY * XY * W), 0, s, a.rec,
-                       a.pair_gid, a.lists, a.items, a.nitems, a.nb, sc.order, sc.counter,
-                       a.thr, a.field, a.acc, a.n, a.part, a.pslot, a.brick_loss);
-  } else {
-    hipLaunchKernelGGL((k_fused<XY, Z, MODE, W, SLICED>), dim3(a.nb), dim3(XY * XY * W), 0, s,
-                       a.rec, a.pair_gid, a.lists, a.items, a.nitems, a.nb,
-                       sc.kind == kSchedXcd ? 1 : 0, a.thr, a.field, a.acc, a.n, a.part, a.pslot,
-                       a.brick_loss);
+  // the queue takes bricks with the waves that the caller asked for (1, 2 or 4)
+  if constexpr (!SLICED && W <= 4) {
+    if (sc.kind == kSchedQueue) {
+      const dim3 grid((unsigned)std::min<int64_t>(sc.persistent_groups, a.nb));
+      hipLaunchKernelGGL((k_fused_queue<XY, Z, MODE, W>), grid, dim3(XY * XY * W), 0, s, a.rec,
+                         a.pair_gid, a.lists, a.items, a.nitems, a.nb, sc.order, sc.counter,
+                         a.thr, a.field, a.acc, a.n, a.part, a.pslot, a.brick_loss);
+      return hipGetLastError();
+    }
   }
+  hipLaunchKernelGGL((k_fused<XY, Z, MODE, W, SLICED>), dim3(a.nb), dim3(XY * XY * W), 0, s, a.rec,
+                     a.pair_gid, a.lists, a.items, a.nitems, a.nb, sc.kind == kSchedXcd ? 1 : 0,
+                     a.thr, a.field, a.acc, a.n, a.part, a.pslot, a.brick_loss);
   return hipGetLastError();
 }
 
