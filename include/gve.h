@@ -110,7 +110,10 @@ typedef struct gve_grid {
  * 8 x 8 columns: the waves share the brick's columns and split its
  * (primitive, brick) pairs, which puts more waves to work when a workload has
  * few bricks; the field's summation order then depends on it, within float32
- * rounding).  Evaluation alone always uses one.
+ * rounding: one sum, two or eight partial sums a voxel).  Launches of few
+ * bricks run more waves than this, with the same sums in the same order, so
+ * that results do not depend on the launch.  Evaluation alone always sums as
+ * with one.
  */
 enum { GVE_SCHED_INDEX = 0, GVE_SCHED_XCD = 1, GVE_SCHED_QUEUE = 2 };
 typedef struct gve_options {
@@ -164,7 +167,8 @@ typedef struct gve_stats {
   /* Primitives whose quaternion had |q| < 1e-12 at the last binning; they
    * are evaluated with the identity rotation. */
   int64_t n_degenerate_q;
-  /* Waves per brick of the last binning's fused kernel (brick_waves). */
+  /* brick_waves of the last binning (what fixes the summation order; a launch
+   * of few bricks runs more waves). */
   int64_t bin_waves;
 } gve_stats;
 

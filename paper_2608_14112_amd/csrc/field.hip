@@ -238,10 +238,26 @@ __device__ inline void touch_end(Touch& t) {
   asm volatile("" ::"v"(t.sink));
 }
 
+// One pair's forward steps into acc.  With `steps`, the active offsets of pair
+// j go to steps[j - jb] (jb = the brick's first pair) for j - jb < kStepCap.
+template <int BZ>
+__device__ __attribute__((always_inline)) inline void accumulate_pair(
+    const Record* __restrict__ rec, const uint32_t* __restrict__ pair_gid, uint32_t jb, uint32_t j,
+    float px, float py, float pz0, int iz0, uint64_t cols, float thr, float (&acc)[BZ],
+    uint32_t* __restrict__ steps) {
+  const uint32_t gid = __builtin_amdgcn_readfirstlane(pair_gid[j]);
+  const Record r = load_record(rec, gid);
+  const ColumnSetup s = column_setup<BZ>(r, px, py, pz0, iz0);
+  const float szv = vreg(r.sz);
+  uint32_t active = 0u;
+  if (column_hit<BZ>(s, szv, cols, thr)) {
+    active = forward_steps<BZ>(s, szv, r.c, thr, acc);
+  }
+  if (steps && j - jb < kStepCap && (threadIdx.x & 63) == 0) steps[j - jb] = active;
+}
+
 // Forward accumulation of the wave's pairs of one brick: jw, jw + stride, ...
-// (< j1; stride > 1 when several waves split a brick's pairs).  With
-// `steps`, the active offsets of pair j go to steps[j - jb] (jb = the
-// brick's first pair) for j - jb < kStepCap.
+// (< j1; stride > 1 when several waves split a brick's pairs).
 template <int BZ>
 __device__ inline void accumulate_brick(const Record* __restrict__ rec,
                                         const uint32_t* __restrict__ pair_gid, uint32_t jb,
@@ -253,15 +269,27 @@ __device__ inline void accumulate_brick(const Record* __restrict__ rec,
   uint32_t k = 0;
   for (uint32_t j = jw; j < j1; j += stride, ++k) {
     if ((k & 63u) == 0u) touch_block(rec, pair_gid, jw, stride, k, j1, tc);
-    const uint32_t gid = __builtin_amdgcn_readfirstlane(pair_gid[j]);
-    const Record r = load_record(rec, gid);
-    const ColumnSetup s = column_setup<BZ>(r, px, py, pz0, iz0);
-    const float szv = vreg(r.sz);
-    uint32_t active = 0u;
-    if (column_hit<BZ>(s, szv, cols, thr)) {
-      active = forward_steps<BZ>(s, szv, r.c, thr, acc);
-    }
-    if (steps && j - jb < kStepCap && (threadIdx.x & 63) == 0) steps[j - jb] = active;
+    accumulate_pair<BZ>(rec, pair_gid, jb, j, px, py, pz0, iz0, cols, thr, acc, steps);
+  }
+  if (jw < j1) touch_end(tc);
+}
+
+// The same with the pairs summed by turns into acc and odd.
+template <int BZ>
+__device__ inline void accumulate_two(const Record* __restrict__ rec,
+                                      const uint32_t* __restrict__ pair_gid, uint32_t jb,
+                                      uint32_t jw, uint32_t stride, uint32_t j1, float px, float py,
+                                      float pz0, int iz0, uint64_t cols, float thr,
+                                      float (&acc)[BZ], float (&odd)[BZ],
+                                      uint32_t* __restrict__ steps) {
+  Touch tc;
+  if (jw < j1) touch_begin(pair_gid, jw, stride, j1, tc);
+  uint32_t k = 0;
+  for (uint32_t j = jw; j < j1; j += 2 * stride, k += 2) {
+    if ((k & 63u) == 0u) touch_block(rec, pair_gid, jw, stride, k, j1, tc);
+    accumulate_pair<BZ>(rec, pair_gid, jb, j, px, py, pz0, iz0, cols, thr, acc, steps);
+    if (j + stride >= j1) break;
+    accumulate_pair<BZ>(rec, pair_gid, jb, j + stride, px, py, pz0, iz0, cols, thr, odd, steps);
   }
   if (jw < j1) touch_end(tc);
 }
@@ -350,7 +378,8 @@ __device__ inline uint32_t xcd_brick(uint32_t w, uint32_t nb) {
 // waves by offset: wave w sums its pairs, in list order, at offsets
 // SL w .. SL w + SL - 1.  Each voxel's value is then formed from the same
 // operations in the same order as by one wave for the whole column, so results
-// do not depend on whether a brick is sliced.
+// do not depend on whether a brick is sliced.  Where a brick's pairs
+// form P partial sums (fused_brick), each sum may be sliced so too.
 
 // Forward steps of one pair at the wave's offsets (zc[u] = the offset less
 // BZ / 2).  Returns the active offsets (bits 0 .. SL - 1): those at which some
@@ -375,11 +404,11 @@ __device__ inline uint32_t slice_steps(const ColumnSetup& s, float szv, float c,
   return active;
 }
 
-// The pairs of a brick that reach one slice, in list order: each lane tests one
-// of 64 pairs (z-range, then the separating plane), and the kept ones are taken
+// Every STRIDE-th pair of a brick that reaches one slice, in list order: each
+// lane tests one of 64 such pairs (z-range, then the separating plane), and the kept ones are taken
 // from the ballot, so a pair that misses the slice costs its wave a 64th of a
 // test in place of the set-up of its columns.
-template <int BZ, int SL>
+template <int BZ, int SL, int STRIDE>
 struct SlicePairs {
   const Record* __restrict__ rec;
   const uint32_t* __restrict__ pair_gid;
@@ -393,7 +422,7 @@ struct SlicePairs {
 
   __device__ void block(uint32_t b) {
     base = b;
-    const uint32_t j = b + (threadIdx.x & 63);
+    const uint32_t j = b + STRIDE * (threadIdx.x & 63);
     gid = pair_gid[min(j, j1 - 1)];
     const Record r = rec[gid];
     const int za = max(r.zlo - iz0, z0), zb = min(r.zhi - iz0, z0 + SL - 1);
@@ -407,37 +436,38 @@ struct SlicePairs {
   // List position of the next pair (its id to g), j1 after the last.
   __device__ uint32_t next(uint32_t& g) {
     while (left == 0ull) {
-      if (j1 - base <= 64u) return j1;
-      block(base + 64u);
+      if (j1 - base <= STRIDE * 64u) return j1;
+      block(base + STRIDE * 64u);
     }
     const int p = (int)__builtin_ctzll(left);
     left &= left - 1ull;
     g = (uint32_t)__builtin_amdgcn_readlane((int)gid, p);
-    return base + (uint32_t)p;
+    return base + STRIDE * (uint32_t)p;
   }
 };
 
-// Forward accumulation of a brick's pairs [j0, j1) at one slice.  With `steps`
-// (zeroed before), the slice's bits of steps[j - j0] take the active offsets of
-// pair j (j - j0 < kStepCap).  The
-// record of the next pair is loaded while the current one's steps run: a
+// Forward accumulation of a brick's pairs jw, jw + STRIDE, ... (< j1) at one
+// slice.  With `steps` (zeroed before), the slice's bits of steps[j - jb] (jb =
+// the brick's first pair) take the active offsets of pair j (j - jb <
+// kStepCap).  The record of the next pair is loaded while the current one's steps run: a
 // brick's time is its list length times the latency of a pair, and few waves
 // share a SIMD.
-template <int BZ, int SL>
+template <int BZ, int SL, int STRIDE>
 __device__ inline void accumulate_slice(const Record* __restrict__ rec,
-                                        const uint32_t* __restrict__ pair_gid, uint32_t j0,
-                                        uint32_t j1, const Site& st, int slice, float thr,
-                                        float (&acc)[SL], uint32_t* __restrict__ steps) {
-  if (j0 >= j1) return;
+                                        const uint32_t* __restrict__ pair_gid, uint32_t jb,
+                                        uint32_t jw, uint32_t j1, const Site& st, int slice,
+                                        float thr, float (&acc)[SL],
+                                        uint32_t* __restrict__ steps) {
+  if (jw >= j1) return;
   const int z0 = slice * SL;
   float zc[SL];
 #pragma unroll
   for (int u = 0; u < SL; ++u) zc[u] = (float)(z0 + u - BZ / 2);
   const int lane = threadIdx.x & 63;
-  SlicePairs<BZ, SL> sp{rec, pair_gid, j1, st.px - (float)(lane & 7),
+  SlicePairs<BZ, SL, STRIDE> sp{rec, pair_gid, j1, st.px - (float)(lane & 7),
                         st.py - (float)(lane >> 3), st.pz0, st.iz0, z0,
                         (1.0f + 1e-3f) * sqrtf(-thr)};
-  sp.block(j0);
+  sp.block(jw);
   uint32_t g = 0;
   uint32_t j = sp.next(g);
   if (j >= j1) return;
@@ -455,8 +485,8 @@ __device__ inline void accumulate_slice(const Record* __restrict__ rec,
     const float wn = __builtin_amdgcn_fmed3f(wa, wb, 0.0f);
     if (__builtin_amdgcn_ballot_w64(fmaf(-wn, wn, s.qxy) > thr) != 0ull)
       active = slice_steps<SL>(s, szv, r.c, thr, zm, zc, acc);
-    if (steps && active != 0u && j - j0 < kStepCap && lane == 0)
-      atomicOr(&steps[j - j0], active << z0);
+    if (steps && active != 0u && j - jb < kStepCap && lane == 0)
+      atomicOr(&steps[j - jb], active << z0);
     if (jn >= j1) break;
     j = jn;
     r = rn;
@@ -580,7 +610,8 @@ __global__ __launch_bounds__(BZ / SL * 64) void k_forward_sliced(
   float acc[SL];
 #pragma unroll
   for (int u = 0; u < SL; ++u) acc[u] = 0.0f;
-  accumulate_slice<BZ, SL>(rec, pair_gid, lists.start[b], lists.end[b], st, slice, thr, acc, nullptr);
+  const uint32_t j0 = lists.start[b];
+  accumulate_slice<BZ, SL, 1>(rec, pair_gid, j0, j0, lists.end[b], st, slice, thr, acc, nullptr);
   column_out<SL, DOT>(acc, st, slice * SL, out, (size_t)b * (BZ / SL) + slice);
 }
 
@@ -673,16 +704,25 @@ __device__ inline void backward_steps_chain(const ColumnSetup& s, float szv, flo
 // sums.  kVjp: no forward pass; r is read from `field` (an upstream gradient
 // dl/dVhat), so the ten sums give the vector-Jacobian product
 // sum_p r(p) dVhat(p)/dtheta.
-// W > 1 (8 x 8 columns only): W waves share the brick's columns and split its
-// pairs (wave w takes pairs w, w + W, ...); the forward partial sums are added
-// in wave order through LDS (`comb`, W * BZ * 64 floats), after which every
-// wave holds the whole field of the brick.  `comb` is then each wave's block
-// of the ten-sum reduction (lds_sum10).
-// SLICED (W > 1): the waves split the forward pass by offsets instead
-// (accumulate_slice) and exchange residuals; values, recorded offsets, loss
-// and each pair's sums are those of W = 1 exactly.
+// W > 1 (8 x 8 columns only): W waves share the brick's columns.  In the
+// backward pass wave w takes pairs w, w + W, ..., whose sums are its own.  The
+// forward pass forms P partial sums of a voxel, the k-th over pairs k, k + P,
+// ... (kShares of the caller's wave count; 1 where one wave was asked for), and
+// adds them in a fixed tree.  P alone fixes a voxel's operations and their
+// order, so values, recorded offsets, loss and each pair's sums depend on P and
+// not on W, which the launch's size chooses:
+//   W <= P     wave w forms sum w, or with P = 2 W sums w and w + W by turns;
+//              they are added through LDS (`comb`, W * BZ * 64 floats), after
+//              which every wave holds the whole field of the brick;
+//   P = 1      W slices of the offsets (accumulate_slice); the waves exchange
+//              residuals;
+//   otherwise  wave w forms sum w % P at slice w / P of W / P.
+// `comb` is then each wave's block of the ten-sum reduction (lds_sum10).
+// Four waves form eight sums, so that eight can share them in small launches
+// without slices (sixteen: with two), each of which repeats a pair's set-up.
+constexpr int shares_of(int waves) { return waves == 4 ? 8 : waves; }
 constexpr int kGrad = kFusedGrad, kVjp = kFusedVjp, kLoss = kFusedLoss;
-template <int BXY, int BZ, int MODE, int W, bool SLICED>
+template <int BXY, int BZ, int MODE, int W, int P>
 __device__ __attribute__((always_inline)) inline void fused_brick(const Record* __restrict__ rec,
                                    const uint32_t* __restrict__ pair_gid,
                                    BrickLists lists,
@@ -698,7 +738,11 @@ __device__ __attribute__((always_inline)) inline void fused_brick(const Record* 
   constexpr int kWaves = (BXY * BXY + 63) / 64;  // waves over the columns
   constexpr bool VJP = MODE == kVjp;
   static_assert(W == 1 || kWaves == 1, "pairs are split only over one wave of columns");
-  static_assert(!SLICED || (BZ % W == 0 && W > 1 && !VJP), "one wave per slice");
+  constexpr int NS = W > P ? W / P : 1;   // slices
+  constexpr int SLOTS = W > P ? P : W;    // partial sums that meet in LDS
+  constexpr bool SLICED = P == 1 && W > 1 && !VJP;
+  constexpr int SL = BZ / NS;
+  static_assert(W * (P / SLOTS) == P * NS && P / SLOTS <= 2 && BZ % NS == 0, "sums and slices");
   const int lane = threadIdx.x & 63;
   // uniform, so that the waves' pair indices, masks and branches stay scalar
   const int wave = W * kWaves > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0;
@@ -718,7 +762,7 @@ __device__ __attribute__((always_inline)) inline void fused_brick(const Record* 
   float res[BZ];
 #pragma unroll
   for (int zz = 0; zz < BZ; ++zz) res[zz] = 0.0f;
-  if (VJP) {
+  if constexpr (VJP) {
 #pragma unroll
     for (int z0 = 0; z0 < BZ; z0 += kLoadZ) {
       float t[kLoadZ];
@@ -727,8 +771,7 @@ __device__ __attribute__((always_inline)) inline void fused_brick(const Record* 
       for (int u = 0; u < kLoadZ; ++u) res[z0 + u] = t[u];
       asm volatile("" ::: "memory");
     }
-  } else if (SLICED) {
-    constexpr int SL = SLICED ? BZ / W : 1;
+  } else if constexpr (SLICED) {
     const int slice = wave;
     if (MODE == kGrad) {
       for (uint32_t i = threadIdx.x; i < min(j1 - j0, kStepCap); i += 64 * W) steps[i] = 0u;
@@ -737,8 +780,8 @@ __device__ __attribute__((always_inline)) inline void fused_brick(const Record* 
     float acc[SL];
 #pragma unroll
     for (int u = 0; u < SL; ++u) acc[u] = 0.0f;
-    accumulate_slice<BZ, SL>(rec, pair_gid, j0, j1, st, slice, thr, acc,
-                         MODE == kGrad ? steps : nullptr);
+    accumulate_slice<BZ, SL, 1>(rec, pair_gid, j0, j0, j1, st, slice, thr, acc,
+                                MODE == kGrad ? steps : nullptr);
     float t[SL];
     load_column_chunk<SL>(field, st, voff, nrec, slice * SL, t);
 #pragma unroll
@@ -761,24 +804,55 @@ __device__ __attribute__((always_inline)) inline void fused_brick(const Record* 
     // the residuals are read before `comb` takes the waves' ten-sum blocks
     if (MODE == kGrad) __syncthreads();
   } else {
-    accumulate_brick<BZ>(rec, pair_gid, j0, jw, (uint32_t)W, j1, px, py, pz0, iz0, cols, thr,
-                         res, kWaves == 1 && MODE == kGrad ? steps : nullptr);
-    if (W > 1) {
-      // the waves' partial sums, added in wave order
+    if constexpr (NS > 1) {
+      const int share = wave % P, slice = wave / P;
+      if (MODE == kGrad) {
+        for (uint32_t i = threadIdx.x; i < min(j1 - j0, kStepCap); i += 64 * W) steps[i] = 0u;
+        __syncthreads();
+      }
+      float acc[SL];
 #pragma unroll
-      for (int zz = 0; zz < BZ; ++zz) comb[(wave * BZ + zz) * 64 + lane] = res[zz];
+      for (int u = 0; u < SL; ++u) acc[u] = 0.0f;
+      accumulate_slice<BZ, SL, P>(rec, pair_gid, j0, j0 + (uint32_t)share, j1, st, slice, thr, acc,
+                                  MODE == kGrad ? steps : nullptr);
+#pragma unroll
+      for (int u = 0; u < SL; ++u) comb[(share * BZ + slice * SL + u) * 64 + lane] = acc[u];
+    } else if constexpr (P > W) {
+      static_assert(P == 2 * W, "two sums a wave");
+      float odd[BZ];
+#pragma unroll
+      for (int zz = 0; zz < BZ; ++zz) odd[zz] = 0.0f;
+      accumulate_two<BZ>(rec, pair_gid, j0, jw, (uint32_t)W, j1, px, py, pz0, iz0, cols, thr, res,
+                         odd, MODE == kGrad ? steps : nullptr);
+#pragma unroll
+      for (int zz = 0; zz < BZ; ++zz) comb[(wave * BZ + zz) * 64 + lane] = res[zz] + odd[zz];
+    } else {
+      accumulate_brick<BZ>(rec, pair_gid, j0, jw, (uint32_t)W, j1, px, py, pz0, iz0, cols, thr,
+                           res, kWaves == 1 && MODE == kGrad ? steps : nullptr);
+      if (W > 1) {
+#pragma unroll
+        for (int zz = 0; zz < BZ; ++zz) comb[(wave * BZ + zz) * 64 + lane] = res[zz];
+      }
+    }
+    if (W > 1) {
+      // the partial sums c: (c0 + c4) and so on (by the wave itself where it
+      // formed both), then in pairs
       __syncthreads();
 #pragma unroll
       for (int z0 = 0; z0 < BZ; z0 += 8) {
 #pragma unroll
         for (int zz = z0; zz < z0 + 8; ++zz) {
-          float t = 0.0f;
+          float c[SLOTS];
 #pragma unroll
-          for (int w = 0; w < W; ++w) t += comb[(w * BZ + zz) * 64 + lane];
-          res[zz] = t;
+          for (int w = 0; w < SLOTS; ++w) c[w] = comb[(w * BZ + zz) * 64 + lane];
+          if constexpr (SLOTS == 8) {
+#pragma unroll
+            for (int w = 0; w < 4; ++w) c[w] += c[w + 4];
+          }
+          res[zz] = SLOTS < 4 ? c[0] + c[SLOTS - 1] : (c[0] + c[1]) + (c[2 % SLOTS] + c[3 % SLOTS]);
         }
         // eight offsets at a time: the next reads wait for these sums, so
-        // the loads in flight stay within 8 W registers
+        // the loads in flight stay within 8 SLOTS registers
 #pragma unroll
         for (int zz = z0; zz < z0 + 8; ++zz) asm volatile("" ::"v"(res[zz]) : "memory");
       }
@@ -903,18 +977,18 @@ __device__ __attribute__((always_inline)) inline void fused_brick(const Record* 
   }
 }
 
-// Floats of the fused kernels' shared block: the larger of the W > 1 forward
-// partial sums and the waves' ten-sum blocks (the two are live one after the
+// Floats of the fused kernels' shared block: the larger of the forward partial
+// sums (W > 1) and the waves' ten-sum blocks (the two are live one after the
 // other).
-constexpr int fused_lds_floats(int bz, int mode, int w, int waves, bool sliced) {
-  const int comb = sliced ? bz * 64 : (w > 1 && mode != kVjp ? w * bz * 64 : 0);
+constexpr int fused_lds_floats(int bz, int mode, int w, int waves, int p) {
+  const int comb = w > 1 && mode != kVjp ? (p < w ? p : w) * bz * 64 : 0;
   const int sums = mode == kLoss ? 1 : w * waves * kSumFloats;
   return comb > sums ? comb : sums;
 }
 
-// One workgroup per brick (xcd: consecutive bricks grouped per XCD); W waves
-// per brick split its pairs (fused_brick).
-template <int BXY, int BZ, int MODE, int W, bool SLICED>
+// One workgroup per brick (xcd: consecutive bricks grouped per XCD) of W waves
+// and P partial sums (fused_brick).
+template <int BXY, int BZ, int MODE, int W, int P>
 __global__ __launch_bounds__(BXY* BXY* W) void k_fused(const Record* __restrict__ rec,
                                                 const uint32_t* __restrict__ pair_gid,
                                                 BrickLists lists,
@@ -928,10 +1002,10 @@ __global__ __launch_bounds__(BXY* BXY* W) void k_fused(const Record* __restrict_
   constexpr int kWaves = (BXY * BXY + 63) / 64;
   __shared__ float red[kWaves][10];
   __shared__ uint32_t steps[kWaves == 1 && MODE == kGrad ? kStepCap : 1];
-  __shared__ __attribute__((aligned(16))) float comb[fused_lds_floats(BZ, MODE, W, kWaves, SLICED)];
+  __shared__ __attribute__((aligned(16))) float comb[fused_lds_floats(BZ, MODE, W, kWaves, P)];
   const uint32_t b = xcd ? xcd_brick(blockIdx.x, nbricks) : blockIdx.x;
-  fused_brick<BXY, BZ, MODE, W, SLICED>(rec, pair_gid, lists, items, nitems, b, thr, field,
-                                        gacc, n, part, pslot, brick_loss, red, steps, comb);
+  fused_brick<BXY, BZ, MODE, W, P>(rec, pair_gid, lists, items, nitems, b, thr, field,
+                                   gacc, n, part, pslot, brick_loss, red, steps, comb);
 }
 
 // Persistent: each workgroup takes queue positions from *counter until they
@@ -953,7 +1027,7 @@ __global__ __launch_bounds__(BXY* BXY* W) void k_fused_queue(const Record* __res
   constexpr int kWaves = (BXY * BXY + 63) / 64;
   __shared__ float red[kWaves][10];
   __shared__ uint32_t steps[kWaves == 1 && MODE == kGrad ? kStepCap : 1];
-  __shared__ __attribute__((aligned(16))) float comb[fused_lds_floats(BZ, MODE, W, kWaves, false)];
+  __shared__ __attribute__((aligned(16))) float comb[fused_lds_floats(BZ, MODE, W, kWaves, shares_of(W))];
   __shared__ uint32_t next;
   for (;;) {
     if (threadIdx.x == 0) next = atomicAdd(counter, 1u);
@@ -961,8 +1035,9 @@ __global__ __launch_bounds__(BXY* BXY* W) void k_fused_queue(const Record* __res
     const uint32_t w = __builtin_amdgcn_readfirstlane(next);
     __syncthreads();
     if (w >= nbricks) break;
-    fused_brick<BXY, BZ, MODE, W, false>(rec, pair_gid, lists, items, nitems, order[w], thr,
-                                         field, gacc, n, part, pslot, brick_loss, red, steps, comb);
+    fused_brick<BXY, BZ, MODE, W, shares_of(W)>(rec, pair_gid, lists, items, nitems, order[w], thr,
+                                                field, gacc, n, part, pslot, brick_loss, red,
+                                                steps, comb);
     // A loss-only brick ends in a branch on thread 0, as the loop begins with
     // one.  Without a barrier between them the compiler joins the two, and the
     // other lanes of the wave go round the loop and its barriers without lane 0.
@@ -1247,10 +1322,10 @@ struct FusedArgs {
   float* brick_loss;
 };
 
-template <int XY, int Z, int MODE, int W, bool SLICED>
+template <int XY, int Z, int MODE, int W, int P>
 hipError_t run_fused(const FusedArgs& a, const Schedule& sc, hipStream_t s) {
   // the queue takes bricks with the waves that the caller asked for (1, 2 or 4)
-  if constexpr (!SLICED && W <= 4) {
+  if constexpr (P == shares_of(W) && W <= 4) {
     if (sc.kind == kSchedQueue) {
       const dim3 grid((unsigned)std::min<int64_t>(sc.persistent_groups, a.nb));
       hipLaunchKernelGGL((k_fused_queue<XY, Z, MODE, W>), grid, dim3(XY * XY * W), 0, s, a.rec,
@@ -1259,7 +1334,7 @@ hipError_t run_fused(const FusedArgs& a, const Schedule& sc, hipStream_t s) {
       return hipGetLastError();
     }
   }
-  hipLaunchKernelGGL((k_fused<XY, Z, MODE, W, SLICED>), dim3(a.nb), dim3(XY * XY * W), 0, s, a.rec,
+  hipLaunchKernelGGL((k_fused<XY, Z, MODE, W, P>), dim3(a.nb), dim3(XY * XY * W), 0, s, a.rec,
                      a.pair_gid, a.lists, a.items, a.nitems, a.nb, sc.kind == kSchedXcd ? 1 : 0,
                      a.thr, a.field, a.acc, a.n, a.part, a.pslot, a.brick_loss);
   return hipGetLastError();
@@ -1267,15 +1342,15 @@ hipError_t run_fused(const FusedArgs& a, const Schedule& sc, hipStream_t s) {
 
 template <int XY, int Z, int W>
 hipError_t run_mode(int mode, const FusedArgs& a, const Schedule& sc, hipStream_t s) {
-  if (mode == kVjp) return run_fused<XY, Z, kVjp, W, false>(a, sc, s);
-  if (mode == kLoss) return run_fused<XY, Z, kLoss, W, false>(a, sc, s);
-  return run_fused<XY, Z, kGrad, W, false>(a, sc, s);
+  if (mode == kVjp) return run_fused<XY, Z, kVjp, W, shares_of(W)>(a, sc, s);
+  if (mode == kLoss) return run_fused<XY, Z, kLoss, W, shares_of(W)>(a, sc, s);
+  return run_fused<XY, Z, kGrad, W, shares_of(W)>(a, sc, s);
 }
 
-template <int Z, int W>
+template <int Z, int W, int P>
 hipError_t run_sliced(int mode, const FusedArgs& a, const Schedule& sc, hipStream_t s) {
-  if (mode == kLoss) return run_fused<8, Z, kLoss, W, true>(a, sc, s);
-  return run_fused<8, Z, kGrad, W, true>(a, sc, s);
+  if (mode == kLoss) return run_fused<8, Z, kLoss, W, P>(a, sc, s);
+  return run_fused<8, Z, kGrad, W, P>(a, sc, s);
 }
 
 }  // namespace
@@ -1293,7 +1368,7 @@ hipError_t launch_fused(const Record* rec, const uint32_t* pair_gid, BrickLists 
   if (bg.Bxy == 8 && bg.waves == 1 && !queue) {
     if (mode == kVjp) {
 #define GVE_VJP(Z, W, LIMIT) \
-  if (bg.Bz == Z && bg.nbricks <= (LIMIT)) return run_fused<8, Z, kVjp, W, false>(a, sc, s);
+  if (bg.Bz == Z && bg.nbricks <= (LIMIT)) return run_fused<8, Z, kVjp, W, shares_of(W)>(a, sc, s);
       GVE_VJP(8, 16, 1024) GVE_VJP(16, 16, 1024) GVE_VJP(32, 16, 1024)
       GVE_VJP(8, 8, 2048) GVE_VJP(16, 8, 2048) GVE_VJP(32, 8, 2048)
       GVE_VJP(8, 4, kSplitVjpBricks) GVE_VJP(16, 4, kSplitVjpBricks)
@@ -1301,24 +1376,25 @@ hipError_t launch_fused(const Record* rec, const uint32_t* pair_gid, BrickLists 
 #undef GVE_VJP
     } else {
 #define GVE_SLICED(Z, W, LIMIT) \
-  if (bg.Bz == Z && bg.nbricks <= (LIMIT)) return run_sliced<Z, W>(mode, a, sc, s);
+  if (bg.Bz == Z && bg.nbricks <= (LIMIT)) return run_sliced<Z, W, 1>(mode, a, sc, s);
       GVE_SLICED(8, 4, 2048)
       GVE_SLICED(16, 8, 768) GVE_SLICED(16, 4, 3072) GVE_SLICED(16, 2, kSlicedFusedBricks)
       GVE_SLICED(32, 16, 256) GVE_SLICED(32, 8, 1024) GVE_SLICED(32, 4, kSlicedFusedBricks)
 #undef GVE_SLICED
     }
   }
-  // Four waves that split a brick's pairs become 8 or 16 in small launches: 8 x 8
-  // x 8, 64 bricks 50 -> 38 -> 35 us, 512 63 -> 49 -> 52, 1,728 106 -> 102, 4,096
-  // 235 -> 236; 8 x 8 x 16, 256 82 -> 56 -> 49, 864 100 -> 86 -> 120, 2,048 182 ->
-  // 176; 8 x 8 x 32, 432 130 -> 94, 1,024 170 -> 178.
+  // Four waves asked for become 8 or 16 in small launches (the same eight partial
+  // sums), refinement iterations of cubes by 4, 8 and 16 waves: 8 x 8 x 8 bricks,
+  // 64 75, 57, 55 us; 512 110, 79, 83; 1,728 172, 138, 179; 8,000 435, 410, 690;
+  // 21,952 812, 835, 1,620.  8 x 8 x 16, 256 bricks 135, 90, 81; 864 179, 125, 152;
+  // 4,000 437, 397, 568; 10,976 733, 837, 1,350.  8 x 8 x 32, 128 bricks 164, 106,
+  // 96; 432 257, 165, 160; 1,024 355, 262, 279; 2,000 563, 452, 516; 5,488 989,
+  // 989, 1,289.
   if (bg.Bxy == 8 && bg.waves == 4 && !queue && mode != kVjp) {
-#define GVE_SPLIT(Z, W, LIMIT)                                              \
-  if (bg.Bz == Z && bg.nbricks <= (LIMIT))                                  \
-    return mode == kLoss ? run_fused<8, Z, kLoss, W, false>(a, sc, s)       \
-                         : run_fused<8, Z, kGrad, W, false>(a, sc, s);
-    GVE_SPLIT(8, 16, 128) GVE_SPLIT(16, 16, 512)
-    GVE_SPLIT(8, 8, 2048) GVE_SPLIT(16, 8, 2048) GVE_SPLIT(32, 8, 768)
+#define GVE_SPLIT(Z, W, LIMIT) \
+  if (bg.Bz == Z && bg.nbricks <= (LIMIT)) return run_sliced<Z, W, 8>(mode, a, sc, s);
+    GVE_SPLIT(8, 16, 128) GVE_SPLIT(16, 16, 512) GVE_SPLIT(32, 16, 512)
+    GVE_SPLIT(8, 8, 8192) GVE_SPLIT(16, 8, 4096) GVE_SPLIT(32, 8, 4096)
 #undef GVE_SPLIT
   }
 #define GVE_CASE(XY, Z, W) \
