@@ -1038,10 +1038,11 @@ __global__ __launch_bounds__(BXY* BXY* W) void k_fused_queue(const Record* __res
     fused_brick<BXY, BZ, MODE, W, shares_of(W)>(rec, pair_gid, lists, items, nitems, order[w], thr,
                                                 field, gacc, n, part, pslot, brick_loss, red,
                                                 steps, comb);
-    // A loss-only brick ends in a branch on thread 0, as the loop begins with
-    // one.  Without a barrier between them the compiler joins the two, and the
-    // other lanes of the wave go round the loop and its barriers without lane 0.
-    if (MODE == kLoss) __syncthreads();
+    // A brick may end in a branch on thread 0 (its loss, where no pair follows),
+    // as the loop begins with one.  Without a barrier between them the compiler
+    // may join the two, so that the other lanes of the wave go round the loop and
+    // its barriers without lane 0.
+    __syncthreads();
   }
 }
 
