@@ -452,12 +452,12 @@ struct SlicePairs {
 // kStepCap).  The record of the next pair is loaded while the current one's steps run: a
 // brick's time is its list length times the latency of a pair, and few waves
 // share a SIMD.
-template <int BZ, int SL, int STRIDE>
-__device__ inline void accumulate_slice(const Record* __restrict__ rec,
-                                        const uint32_t* __restrict__ pair_gid, uint32_t jb,
-                                        uint32_t jw, uint32_t j1, const Site& st, int slice,
-                                        float thr, float (&acc)[SL],
-                                        uint32_t* __restrict__ steps) {
+template <int BZ, int SL, int STRIDE, bool RAGGED>
+__device__ inline void accumulate_slice_of(const Record* __restrict__ rec,
+                                           const uint32_t* __restrict__ pair_gid, uint32_t jb,
+                                           uint32_t jw, uint32_t j1, const Site& st, int slice,
+                                           uint64_t cols, float thr, float (&acc)[SL],
+                                           uint32_t* __restrict__ steps) {
   if (jw >= j1) return;
   const int z0 = slice * SL;
   float zc[SL];
@@ -483,7 +483,8 @@ __device__ inline void accumulate_slice(const Record* __restrict__ rec,
     const float wa = fmaf((float)(max(s.za, z0) - BZ / 2), szv, s.wm);
     const float wb = fmaf((float)(min(s.zb, z0 + SL - 1) - BZ / 2), szv, s.wm);
     const float wn = __builtin_amdgcn_fmed3f(wa, wb, 0.0f);
-    if (__builtin_amdgcn_ballot_w64(fmaf(-wn, wn, s.qxy) > thr) != 0ull)
+    if (__builtin_amdgcn_ballot_w64(fmaf(-wn, wn, s.qxy) > thr) != 0ull &&
+        (!RAGGED || column_hit<BZ>(s, szv, cols, thr)))
       active = slice_steps<SL>(s, szv, r.c, thr, zm, zc, acc);
     if (steps && active != 0u && j - jb < kStepCap && lane == 0)
       atomicOr(&steps[j - jb], active << z0);
@@ -491,6 +492,25 @@ __device__ inline void accumulate_slice(const Record* __restrict__ rec,
     j = jn;
     r = rn;
   }
+}
+
+// A pair that reaches no column inside the volume is skipped whole, as in
+// column_hit: its steps would add c * 0 to every lane (NaN where c is not
+// finite).  A test for bricks at the volume's edge only, in a loop of their own
+// (64^3 x 2,048, decoded: 79 us, 83 with the test in every brick's loop).
+template <int BZ, int SL, int STRIDE>
+__device__ inline void accumulate_slice(const Record* __restrict__ rec,
+                                        const uint32_t* __restrict__ pair_gid, uint32_t jb,
+                                        uint32_t jw, uint32_t j1, const Site& st, int slice,
+                                        float thr, float (&acc)[SL],
+                                        uint32_t* __restrict__ steps) {
+  const uint64_t cols = __builtin_amdgcn_ballot_w64(st.col_in);
+  if (cols == ~0ull)
+    accumulate_slice_of<BZ, SL, STRIDE, false>(rec, pair_gid, jb, jw, j1, st, slice, cols, thr, acc,
+                                               steps);
+  else
+    accumulate_slice_of<BZ, SL, STRIDE, true>(rec, pair_gid, jb, jw, j1, st, slice, cols, thr, acc,
+                                              steps);
 }
 
 // Target values of the lane's column at brick offsets z0 .. z0 + NZ - 1
