@@ -122,8 +122,9 @@ __device__ inline uint32_t det_bin(uint64_t det_seed, uint64_t v, float g) {
   const float u = (float)((h >> 11) + 1ull) * 0x1.0p-53f;
   const float l = d < 0x1.0p-8f ? d * fmaf(d, fmaf(d, 0.33333333f, 0.5f), 1.0f)
                                 : -0.69314718f * __builtin_amdgcn_logf(u);
-  // a tiny g's reciprocal may overflow
-  const float a = g > 0x1.0p-100f ? l * __builtin_amdgcn_rcpf(g) : (float)((double)l / (double)g);
+  // a tiny g's reciprocal may overflow, a huge one's is subnormal (taken as 0)
+  const float a = g > 0x1.0p-100f && g < 0x1.0p100f ? l * __builtin_amdgcn_rcpf(g)
+                                                    : (float)((double)l / (double)g);
   return __float_as_uint(a) >> 20;
 }
 
