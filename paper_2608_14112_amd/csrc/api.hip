@@ -2505,10 +2505,10 @@ struct PBuckets {
   const uint32_t* start = nullptr;
 };
 
-// Bucket `batch` sets of np points (consecutive in pts): one launch when a
-// workgroup holds a set, else (batch 1) cell keys, radix sort, ranges, gather.
+// Bucket `batch` sets of np points (consecutive in pts): one launch with a
+// workgroup a set (in_lds), else (batch 1) cell keys, radix sort, ranges, gather.
 gve_status paper_bucket(gve_ctx* ctx, const float* pts, int64_t np, const gve::CellGrid& cg,
-                        int batch, PBuckets* out) {
+                        int batch, bool in_lds, PBuckets* out) {
   auto& ws = ctx->ws;
   hipStream_t s = ctx->stream;
   const int64_t ncells = (int64_t)cg.ncx * cg.ncy * cg.ncz;
@@ -2520,7 +2520,7 @@ gve_status paper_bucket(gve_ctx* ctx, const float* pts, int64_t np, const gve::C
   uint32_t* st = static_cast<uint32_t*>(ws.p_start.ptr);
   out->p4 = p4;
   out->start = st;
-  if (gve::paper_bucket_fits(np, ncells)) {
+  if (in_lds) {
     TRY_HIP(ctx, gve::paper_bucket(pts, (int)np, cg, bits_for(ncells), batch, p4, st, s));
     return GVE_OK;
   }
@@ -2540,14 +2540,23 @@ gve_status paper_bucket(gve_ctx* ctx, const float* pts, int64_t np, const gve::C
   return GVE_OK;
 }
 
+// One set of points.
+gve_status paper_bucket_one(gve_ctx* ctx, const float* pts, int64_t np, const gve::CellGrid& cg,
+                            PBuckets* out) {
+  const int64_t ncells = (int64_t)cg.ncx * cg.ncy * cg.ncz;
+  return paper_bucket(ctx, pts, np, cg, 1, gve::paper_buckets_in_lds(np, ncells, 1), out);
+}
+
 // Iterations sampled and bucketed together: their points and cell ranges stay
 // within 64 MB, and at most 32 (a batch's launches are then far cheaper than
-// its iterations).  One when a workgroup cannot hold an iteration's points.
-int paper_batch(int64_t S, const gve::CellGrid& cg, int32_t iters) {
+// its iterations).  One when they are not bucketed by a workgroup each (*in_lds).
+int paper_batch(int64_t S, const gve::CellGrid& cg, int32_t iters, bool* in_lds) {
   const int64_t ncells = (int64_t)cg.ncx * cg.ncy * cg.ncz;
-  if (!gve::paper_bucket_fits(2 * S, ncells)) return 1;
   const int64_t bytes = S * (28 + 32) + 4 * (ncells + 1);
-  return (int)std::max<int64_t>(1, std::min<int64_t>({32, iters, ((int64_t)64 << 20) / bytes}));
+  const int batch =
+      (int)std::max<int64_t>(1, std::min<int64_t>({32, iters, ((int64_t)64 << 20) / bytes}));
+  *in_lds = gve::paper_buckets_in_lds(2 * S, ncells, batch);
+  return *in_lds ? batch : 1;
 }
 
 // Zeroed accumulators (num, then den, of np points).
@@ -2778,7 +2787,7 @@ gve_status gve_paper_eval(gve_ctx* ctx, const gve_paper* p, gve_grid g, const gv
   const gve::CellGrid cg = gve::make_cells(g, o->cell);
   PBuckets bk;
   double* num = nullptr;
-  TRY(paper_bucket(ctx, d_pts, npts, cg, 1, &bk));
+  TRY(paper_bucket_one(ctx, d_pts, npts, cg, &bk));
   TRY(paper_accumulators(ctx, npts, &num));
   double* den = num + npts;
   TRY_HIP(ctx, gve::paper_forward(p->theta, p->n, cg, o->k, npts, bk.p4, bk.start, num, den,
@@ -2805,7 +2814,7 @@ gve_status gve_paper_loss_grad(gve_ctx* ctx, gve_paper* p, const float* d_field,
   PBuckets bk;
   double* acc = nullptr;
   uint32_t* hits = nullptr;
-  TRY(paper_bucket(ctx, d_pts, 2 * samples, gve::make_cells(g, o->cell), 1, &bk));
+  TRY(paper_bucket_one(ctx, d_pts, 2 * samples, gve::make_cells(g, o->cell), &bk));
   TRY(paper_accumulators(ctx, 2 * samples, &acc));
   TRY(paper_hits(ctx, p->n, &hits));
   TRY(paper_pass(ctx, p, d_field, g, *o, lam_sm, bk, d_vals, samples, acc, hits, nullptr, 0,
@@ -2843,7 +2852,8 @@ gve_status gve_paper_refine(gve_ctx* ctx, gve_paper* p, const float* d_field, gv
   TRY_HIP(ctx, gve::paper_zero(loss, (int64_t)kTerms * iters, ctx->stream));
   const gve::CellGrid cg = gve::make_cells(g, o->cell);
   const int64_t ncells = (int64_t)cg.ncx * cg.ncy * cg.ncz;
-  const int batch = paper_batch(S, cg, iters);
+  bool in_lds = false;
+  const int batch = paper_batch(S, cg, iters, &in_lds);
   float *pts = nullptr, *vals = nullptr;
   double* acc = nullptr;
   uint32_t* hits = nullptr;
@@ -2865,7 +2875,7 @@ gve_status gve_paper_refine(gve_ctx* ctx, gve_paper* p, const float* d_field, gv
       const int nb = std::min(batch, iters - i);
       TRY_HIP(ctx, gve::paper_sample(d_field, g, oh, om, (int)S, n_hi, n_mid, seed, (uint64_t)it,
                                      nb, o->v_hi, o->v_occ, pts, vals, ctx->stream));
-      TRY(paper_bucket(ctx, pts, 2 * S, cg, nb, &bk));
+      TRY(paper_bucket(ctx, pts, 2 * S, cg, nb, in_lds, &bk));
     }
     const PBuckets bj{bk.p4 + 2 * S * j, bk.start + (ncells + 1) * j};
     p->t += 1;

@@ -402,8 +402,9 @@ hipError_t paper_sample(const float* f, const gve_grid& g, const uint32_t* off_h
                         uint64_t it, int batch, float v_hi, float v_occ, float* pts, float* vals,
                         hipStream_t s);
 // Points in cell order (x, y, z, index) and the cells' ranges start [ncells + 1]
-// for `batch` iterations of np points each, if a workgroup can hold them.
-bool paper_bucket_fits(int64_t np, int64_t ncells);
+// for `batch` iterations of np points each, a workgroup an iteration: at most
+// 16,384 points, and where that is faster (paper_buckets_in_lds).
+bool paper_buckets_in_lds(int64_t np, int64_t ncells, int batch);
 hipError_t paper_bucket(const float* pts, int np, const CellGrid& cg, int bits, int batch,
                         float4* p4, uint32_t* start, hipStream_t s);
 hipError_t paper_gather(const float* pts, int64_t np, const uint32_t* sorted, float4* p4,

@@ -935,9 +935,16 @@ hipError_t paper_sample(const float* f, const gve_grid& g, const uint32_t* off_h
   return hipGetLastError();
 }
 
-// A workgroup's LDS holds 16,384 points (114 KB); the positions are 16 bits.
-bool paper_bucket_fits(int64_t np, int64_t ncells) {
-  return np <= 16 * kBucketThreads && ncells < ((int64_t)1 << 24);
+// A workgroup's LDS holds 16,384 points (114 KB); the positions are 16 bits.  One
+// workgroup also finds every cell's range of a set, about 1 ns a cell, beside
+// those of the other sets, while the radix sort and the chip-wide ranges take some
+// 45 us a set: an iteration of 3,072 samples in batches, 4,096 cells 26 us
+// (sorted: 76), 262,144 33 (94), 636,056 52 (98), 2.1 million 307 (108), 12.6
+// million 10,660 (171); one evaluation at 6,144 points, 4,096 cells 33 us (53),
+// 32,768 57 (54), 79,507 103 (68); at 16,384 points, 4,096 cells 59 (57).
+bool paper_buckets_in_lds(int64_t np, int64_t ncells, int batch) {
+  return np <= 16 * kBucketThreads &&
+         ncells <= (int64_t)32768 * (np <= 8 * kBucketThreads ? batch : batch - 1);
 }
 
 hipError_t paper_bucket(const float* pts, int np, const CellGrid& cg, int bits, int batch,
