@@ -1923,15 +1923,17 @@ gve_status gve_mlp_loss_grad(gve_ctx* ctx, const gve_mlp* m, const float* d_X, c
   if (n > kMlpRows) return fail(ctx, GVE_ERR_UNSUPPORTED, "at most 65536 rows per call");
   TRY(set_device(ctx));
   MlpBuf b;
-  TRY(mlp_buffers(ctx, n, 1, &b));
+  // without a gradient the forward pass alone, its tiles' losses behind the sum
+  const int64_t tiles = d_grad ? 0 : gve::mlp_loss_tiles(n);
+  TRY(mlp_buffers(ctx, d_grad ? n : 0, 1 + tiles, &b));
   hipStream_t s = ctx->stream;
   TRY_HIP(ctx, gve::fill_u64(reinterpret_cast<unsigned long long*>(b.acc), 1, s));
   TRY_HIP(ctx, gve::mlp_pack(m->w, b.wf, s));
-  // without d_grad the gradient goes to the (then unused) Adam-free output
-  TRY(ensure(ctx, ctx->ws.feat, sizeof(float) * GVE_MLP_NWEIGHT));
-  TRY_HIP(ctx, gve::mlp_step(d_X, d_T, nullptr, (int)n, nullptr, m->w, nullptr, nullptr, b.wf,
-                             b.work, 1.0, b.acc,
-                             d_grad ? d_grad : static_cast<float*>(ctx->ws.feat.ptr), 0.0f, 1, s));
+  if (d_grad)
+    TRY_HIP(ctx, gve::mlp_step(d_X, d_T, nullptr, (int)n, nullptr, m->w, nullptr, nullptr, b.wf,
+                               b.work, 1.0, b.acc, d_grad, 0.0f, 1, s));
+  else
+    TRY_HIP(ctx, gve::mlp_loss(d_X, d_T, (int)n, m->w, b.wf, b.acc + 1, b.acc, s));
   if (h_loss) {
     TRY_HIP(ctx, hipMemcpyAsync(ctx->ws.h_pinned, b.acc, 8, hipMemcpyDeviceToHost, s));
     TRY_HIP(ctx, hipStreamSynchronize(s));

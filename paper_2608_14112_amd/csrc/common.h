@@ -454,6 +454,11 @@ hipError_t mlp_step(const float* X, const float* T, const uint32_t* perm, int ro
                     const float* stats, float* w, float* m, float* v, unsigned short* wf,
                     void* work, double loss_scale, double* loss, float* grad_out, float lr,
                     int64_t t, hipStream_t s);
+// The loss of mlp_step alone, without standardisation: *loss += mean squared
+// error.  tile_loss: mlp_loss_tiles(rows) doubles.
+int64_t mlp_loss_tiles(int64_t rows);
+hipError_t mlp_loss(const float* X, const float* T, int rows, const float* w,
+                    const unsigned short* wf, double* tile_loss, double* loss, hipStream_t s);
 // tmp: mlp_stat_tmp_doubles() doubles.
 size_t mlp_stat_tmp_doubles();
 hipError_t mlp_colstats(const float* X, int64_t rows, int cols, float* mean, float* stdv,

@@ -233,8 +233,9 @@ __device__ inline void put_tile(unsigned short* tiles, int64_t tile, int lane, c
 // w owns hidden columns 32 w .. 32 w + 31 and keeps their z1 and z2 in
 // registers from the forward to the backward pass.  The last layer (one
 // 16-wide tile) is wave 0's.  Latency-bound: five short products with a
-// barrier between each; the weight tiles are loaded before the first.
-template <bool STD>
+// barrier between each; the weight tiles are loaded before the first.  LOSS: the
+// forward pass and o.loss alone, nothing else is stored.
+template <bool STD, bool LOSS>
 __global__ __launch_bounds__(256) void k_mlp_fb(const float* __restrict__ X,
                                                 const float* __restrict__ T,
                                                 const uint32_t* __restrict__ perm, int rows,
@@ -256,11 +257,11 @@ __global__ __launch_bounds__(256) void k_mlp_fb(const float* __restrict__ X,
   for (int u = 0; u < 2; ++u) {
     const int nt = 2 * wv + u;
     w1[u] = ld4(wf + fW1 + nt * kFrag + 4 * lane);
-    w3t[u] = ld4(wf + fW3t + nt * kFrag + 4 * lane);
+    if (!LOSS) w3t[u] = ld4(wf + fW3t + nt * kFrag + 4 * lane);
 #pragma unroll
     for (int kt = 0; kt < kHT; ++kt) {
       w2[u][kt] = ld4(wf + fW2 + (nt * kHT + kt) * kFrag + 4 * lane);
-      w2t[u][kt] = ld4(wf + fW2t + (nt * kHT + kt) * kFrag + 4 * lane);
+      if (!LOSS) w2t[u][kt] = ld4(wf + fW2t + (nt * kHT + kt) * kFrag + 4 * lane);
     }
     b1[u] = w[oB1 + 16 * nt + col];
     b2[u] = w[oB2 + 16 * nt + col];
@@ -284,7 +285,7 @@ __global__ __launch_bounds__(256) void k_mlp_fb(const float* __restrict__ X,
   bool in[4];  // rows 4 g + j of the tile belong to the batch
 #pragma unroll
   for (int j = 0; j < 4; ++j) in[j] = row0 + 4 * g + j < rows;
-  if (wv == 3) {  // x as the right operand of the first weight gradient
+  if (!LOSS && wv == 3) {  // x as the right operand of the first weight gradient
     short4v b;
 #pragma unroll
     for (int j = 0; j < 4; ++j) b[j] = (short)xs[(4 * g + j) * kRowX + col];
@@ -305,7 +306,7 @@ __global__ __launch_bounds__(256) void k_mlp_fb(const float* __restrict__ X,
       h[j] = in[j] ? a : 0.0f;
       hs[0][(4 * g + j) * kRowS + 16 * nt + col] = f2bf(h[j]);
     }
-    put_tile(o.h1, rt * kHT + nt, lane, h);
+    if (!LOSS) put_tile(o.h1, rt * kHT + nt, lane, h);
   }
   __syncthreads();
   {
@@ -327,7 +328,7 @@ __global__ __launch_bounds__(256) void k_mlp_fb(const float* __restrict__ X,
         h[j] = in[j] ? a : 0.0f;
         hs[1][(4 * g + j) * kRowS + 16 * nt + col] = f2bf(h[j]);
       }
-      put_tile(o.h2, rt * kHT + nt, lane, h);
+      if (!LOSS) put_tile(o.h2, rt * kHT + nt, lane, h);
     }
   }
   __syncthreads();
@@ -350,12 +351,15 @@ __global__ __launch_bounds__(256) void k_mlp_fb(const float* __restrict__ X,
       }
       dys[(4 * g + j) * kRowX + col] = f2bf(d[j]);
     }
-    put_tile(o.dy, rt, lane, d);
-    o.dy32[rt * 64 + lane] = float4v{d[0], d[1], d[2], d[3]};
+    if (!LOSS) {
+      put_tile(o.dy, rt, lane, d);
+      o.dy32[rt * 64 + lane] = float4v{d[0], d[1], d[2], d[3]};
+    }
 #pragma unroll
     for (int k = 32; k >= 1; k >>= 1) s += __shfl_xor(s, k, 64);
     if (lane == 0) o.loss[rt] = s;
   }
+  if constexpr (LOSS) return;
   __syncthreads();
   // backward; hs[0] (h1, last read two barriers ago) takes dz2
   const short4v da = lds_a(dys, kRowX, lane, 0);
@@ -560,6 +564,27 @@ __global__ __launch_bounds__(256) void k_mlp_wgrad(MlpTiles o, int64_t tiles, in
   }
 }
 
+// Adds the batch's loss, scaled, to *loss (one block of 256 threads).
+__device__ inline void add_loss(const double* __restrict__ tile_loss, int64_t tiles, double scale,
+                                double* __restrict__ loss) {
+  __shared__ double sh[256];
+  double s = 0.0;
+  for (int64_t k = threadIdx.x; k < tiles; k += 256) s += tile_loss[k];
+  sh[threadIdx.x] = s;
+  __syncthreads();
+  for (int k = 128; k > 0; k >>= 1) {
+    if ((int)threadIdx.x < k) sh[threadIdx.x] += sh[threadIdx.x + k];
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) *loss += sh[0] * scale;
+}
+
+__global__ __launch_bounds__(256) void k_mlp_loss(const double* __restrict__ tile_loss,
+                                                  int64_t tiles, double scale,
+                                                  double* __restrict__ loss) {
+  add_loss(tile_loss, tiles, scale, loss);
+}
+
 // Sum over the splits, in order, then the gradient to grad_out (when given) or
 // a bias-corrected Adam step on the float32 weights with their bfloat16 tiles.
 // Block 0 also adds the batch's loss, scaled, to *loss.
@@ -597,18 +622,7 @@ __global__ __launch_bounds__(256) void k_mlp_adam(const float* __restrict__ part
       store_weight_tiles(i, x, wf);
     }
   }
-  if (blockIdx.x == 0) {
-    __shared__ double sh[256];
-    double s = 0.0;
-    for (int64_t k = threadIdx.x; k < tiles; k += 256) s += tile_loss[k];
-    sh[threadIdx.x] = s;
-    __syncthreads();
-    for (int k = 128; k > 0; k >>= 1) {
-      if ((int)threadIdx.x < k) sh[threadIdx.x] += sh[threadIdx.x + k];
-      __syncthreads();
-    }
-    if (threadIdx.x == 0) *loss += sh[0] * loss_scale;
-  }
+  if (blockIdx.x == 0) add_loss(tile_loss, tiles, loss_scale, loss);
 }
 
 // Per-column mean and standard deviation (double) of a [rows][cols] matrix
@@ -1137,10 +1151,10 @@ hipError_t mlp_step(const float* X, const float* T, const uint32_t* perm, int ro
   float* part = reinterpret_cast<float*>(take((size_t)splits * GVE_MLP_NWEIGHT * 4));
   const double inv = 1.0 / ((double)rows * kOut);
   if (stats)
-    hipLaunchKernelGGL((k_mlp_fb<true>), dim3((unsigned)tiles), dim3(256), 0, s, X, T, perm, rows,
+    hipLaunchKernelGGL((k_mlp_fb<true, false>), dim3((unsigned)tiles), dim3(256), 0, s, X, T, perm, rows,
                        stats, w, wf, (float)inv, o);
   else
-    hipLaunchKernelGGL((k_mlp_fb<false>), dim3((unsigned)tiles), dim3(256), 0, s, X, T, perm, rows,
+    hipLaunchKernelGGL((k_mlp_fb<false, false>), dim3((unsigned)tiles), dim3(256), 0, s, X, T, perm, rows,
                        stats, w, wf, (float)inv, o);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
@@ -1155,6 +1169,22 @@ hipError_t mlp_step(const float* X, const float* T, const uint32_t* perm, int ro
   hipLaunchKernelGGL(k_mlp_adam, dim3((GVE_MLP_NWEIGHT + 255) / 256), dim3(256), 0, s, part, splits,
                      bias, o.loss, tiles, inv * loss_scale, loss, grad_out, w, m, v, wf, lr, b1, b2,
                      eps, ibc1, ibc2);
+  return hipGetLastError();
+}
+
+int64_t mlp_loss_tiles(int64_t rows) { return row_tiles(rows); }
+
+hipError_t mlp_loss(const float* X, const float* T, int rows, const float* w,
+                    const unsigned short* wf, double* tile_loss, double* loss, hipStream_t s) {
+  const int64_t tiles = row_tiles(rows);
+  const double inv = 1.0 / ((double)rows * kOut);
+  MlpTiles o{};
+  o.loss = tile_loss;
+  hipLaunchKernelGGL((k_mlp_fb<false, true>), dim3((unsigned)tiles), dim3(256), 0, s, X, T, nullptr,
+                     rows, nullptr, w, wf, (float)inv, o);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_mlp_loss, dim3(1), dim3(256), 0, s, tile_loss, tiles, inv, loss);
   return hipGetLastError();
 }
 
