@@ -129,11 +129,13 @@ gve_status ensure(gve_ctx* ctx, Scratch& s, size_t bytes) {
 // parameter count (u64, cumulative), [4 .. 6] work counters of the counting
 // pass, [16 ..] loss-reduction partials, then three sets of kTotalSlots
 // pair-total counters and the degenerate-quaternion counter (u64): the general
-// binning's, and two that direct binnings use in turn.  Zeroed when first
-// allocated.
+// binning's, and two that direct binnings use in turn (the allocation-free path
+// has none: its scratch is fixed and it never bins directly).  Zeroed when
+// first allocated.
 gve_status ensure_dloss(gve_ctx* ctx) {
   if (ctx->ws.dloss.ptr) return GVE_OK;
-  const size_t nd = 16 + gve::loss_reduce_tmp_doubles() + 3 * (gve::kTotalSlots + 1);
+  const size_t nd = 16 + gve::loss_reduce_tmp_doubles() +
+                    (gve::kTotalSlots + 1) * (ctx->arena_base ? 1 : 3);
   TRY(ensure(ctx, ctx->ws.dloss, sizeof(double) * nd));
   TRY_HIP(ctx, gve::fill_u64(static_cast<unsigned long long*>(ctx->ws.dloss.ptr), (int64_t)nd,
                              ctx->stream));
