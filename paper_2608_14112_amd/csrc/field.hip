@@ -1232,6 +1232,9 @@ constexpr int64_t kSlicedFusedBricks = 12288;
 // shorter, up to this many (8 x 8 x 8: 110,592 bricks 1603 -> 1521 us, 884,736
 // 8997 -> 9205; x 16: 131,072 2759 -> 2591, 442,368 7127 -> 7173).
 constexpr int64_t kSplitVjpBricks = 131072;
+// A launch has fewer than 2^32 threads: one wave from 2^24 bricks on (a single
+// image of 32,768 x 32,768).
+constexpr int64_t kMostBricks4 = (1 << 24) - 1;
 
 bool brick_shape_supported(int bxy, int bz) {
 #define GVE_CASE(XY, Z) if (bxy == XY && bz == Z) return true;
@@ -1393,7 +1396,7 @@ hipError_t launch_fused(const Record* rec, const uint32_t* pair_gid, BrickLists 
       GVE_VJP(8, 16, 1024) GVE_VJP(16, 16, 1024) GVE_VJP(32, 16, 1024)
       GVE_VJP(8, 8, 2048) GVE_VJP(16, 8, 2048) GVE_VJP(32, 8, 2048)
       GVE_VJP(8, 4, kSplitVjpBricks) GVE_VJP(16, 4, kSplitVjpBricks)
-      GVE_VJP(32, 4, bg.nbricks)
+      GVE_VJP(32, 4, kMostBricks4)
 #undef GVE_VJP
     } else {
 #define GVE_SLICED(Z, W, LIMIT) \
