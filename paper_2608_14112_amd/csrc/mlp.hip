@@ -209,7 +209,7 @@ __global__ __launch_bounds__(256) void k_mlp_infer(const float* __restrict__ X, 
 // (k_mlp_fb), the weight gradients and bias sums over the batch (k_mlp_wgrad),
 // and the sums over the batch's splits with Adam (k_mlp_adam).  Results that a
 // later kernel multiplies are stored as bfloat16 operand tiles, the bias
-// gradients' terms in float32.  At 4,096 rows a step takes 44 us (15 + 22 + 5);
+// gradients' terms in float32.  At 4,096 rows a step takes 39 us (15 + 19 + 5);
 // with a product kernel per layer and direction, separate activation, loss and
 // standardisation passes and a bias sum of one thread per column reading global
 // memory row by row (725 us each, three a step) it took 2.46 ms in 21 launches.
@@ -437,8 +437,8 @@ __device__ inline void wgrad_tiles(const unsigned short* __restrict__ a, int sa,
 }
 
 // Bias gradient of sixteen columns: the float32 terms added row by row, in row
-// order (a running sum, so its length is the kernel's: about 3 ns a row; with the reads of LDS
-// ahead of the additions 19.3 us at 4,096 rows, 21.4 without).
+// order (a running sum, whose length is the kernel's: 19.3 us at 4,096 rows, 4.7 ns
+// a row; 21.4 us before the reads of LDS were issued ahead of the additions).
 // 32 row tiles at a time are staged in LDS by all four waves, the next ones
 // while sixteen lanes of wave 0 add the current ones.
 constexpr int kBiasTiles = 32;
